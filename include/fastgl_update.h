@@ -18,7 +18,8 @@
  * (2^-28 on average) in a product of two elements - the accuracy of an fp32
  * multiply-add chain, at several times its speed.  An input element that is
  * not finite, or larger in magnitude than the largest bf16 (3.39e38), turns
- * every result it enters into NaN.  dW and db are reduced over fixed slabs of
+ * every result it enters into NaN.  With N <= 8 the products are bound by
+ * memory and are formed by plain fp32 multiply-adds instead.  dW and db are reduced over fixed slabs of
  * rows whose partial results are summed in fp64 in a fixed order, so results
  * do not depend on scheduling.
  *

@@ -24,7 +24,7 @@
 //   "col" operand   mem[contract][out]: [pair p = contracted 2p, 2p+1][out] dwords, 128 + 8 per pair
 // Lane half h (lanes 32h..32h+31) multiplies contracted indices 8h .. 8h+7 of both operands.
 #include "fastgl_update.h"
-#include "internal.h"
+#include "update_internal.h"
 
 namespace fastgl {
 namespace {
@@ -67,31 +67,11 @@ struct GemmArgs {
 // mask_quad, called when the registers are written to LDS, zeroes what does not exist or is gated
 // off.  VEC: one 16-byte load; the host selects it only when every extent is a multiple of 4, so
 // nvalid is 0 or 4.
-template <bool BF16>
-struct QuadBits;
-template <>
-struct QuadBits<false> {
-    typedef float4 type;
-    typedef float elem;
-};
-template <>
-struct QuadBits<true> {
-    typedef uint2 type;           // four bf16
-    typedef uint16_t elem;
-};
-
 template <bool GATE, bool BF16>
 struct Quad {
     typename QuadBits<BF16>::type v;
     typename QuadBits<BF16>::type g[GATE ? 1 : 0];
 };
-
-__device__ __forceinline__ float4 quad_to_f32(float4 q) { return q; }
-__device__ __forceinline__ float4 quad_to_f32(uint2 q)
-{
-    return make_float4(__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xFFFF0000u), __uint_as_float(q.y << 16),
-                       __uint_as_float(q.y & 0xFFFF0000u));
-}
 
 // `base` is uniform over the workgroup (the tile's origin), `off` a per-lane 32-bit element offset.
 template <bool VEC, bool GATE, bool BF16>
@@ -139,15 +119,6 @@ __device__ __forceinline__ float4 mask_quad(const Quad<GATE, BF16> &q, int nvali
     v.z = nvalid > 2 ? v.z : 0.f;
     v.w = nvalid > 3 ? v.w : 0.f;
     return v;
-}
-
-// fp32 -> bf16, round to nearest even (NaN stays NaN).
-__device__ __forceinline__ uint16_t f32_to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((u >> 16) | 0x0040u);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
 }
 
 __device__ __forceinline__ int clamp4(int64_t n) { return n >= 4 ? 4 : (n <= 0 ? 0 : (int)n); }
@@ -493,17 +464,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 }
 
 // out[e] = sum over slabs of part[s*stride + e], in fp64 and in a fixed order: the slabs are cut into
-// kReduceParts consecutive ranges, each summed in slab order by one thread, and the range sums are
+// PARTS consecutive ranges, each summed in slab order by one thread, and the range sums are
 // added in range order.  The first n_w elements go to dW, the remaining n_b to db (either may be NULL).
-constexpr int kReduceParts = 8, kReduceElems = 256 / kReduceParts;
+// Few elements get 64 ranges: the launch is bound by the chain of loads of a thread, and a result of a
+// narrow layer (65 elements, 562 slabs: 10.0 us with 8 ranges, 4.7 with 64) gives few threads to hide it.
+// With thousands of elements the 16-byte pieces that 64 ranges read cost more (6 464: 10 -> 24 us).
+constexpr int kReduceElemsWide = 1024;   // from this many elements on: 8 ranges
 
+template <int PARTS>
 __global__ __launch_bounds__(256) void k_update_reduce(const float *__restrict__ part, int64_t nslab, int64_t stride,
                                                        int64_t n_w, int64_t n_b, float *dW, float *db)
 {
-    __shared__ double partial[kReduceParts][kReduceElems];
-    const int el = threadIdx.x % kReduceElems, pt = threadIdx.x / kReduceElems;
-    const int64_t e = (int64_t)blockIdx.x * kReduceElems + el;
-    const int64_t per = (nslab + kReduceParts - 1) / kReduceParts;
+    constexpr int kElems = 256 / PARTS;
+    __shared__ double partial[PARTS][kElems];
+    const int el = threadIdx.x % kElems, pt = threadIdx.x / kElems;
+    const int64_t e = (int64_t)blockIdx.x * kElems + el;
+    const int64_t per = (nslab + PARTS - 1) / PARTS;
     const int64_t lo = pt * per, hi = lo + per < nslab ? lo + per : nslab;
     double s = 0.0;
     if (e < n_w + n_b) {
@@ -524,7 +500,7 @@ __global__ __launch_bounds__(256) void k_update_reduce(const float *__restrict__
     if (pt != 0 || e >= n_w + n_b) return;
     double t = partial[0][el];
 #pragma unroll
-    for (int i = 1; i < kReduceParts; ++i) t += partial[i][el];
+    for (int i = 1; i < PARTS; ++i) t += partial[i][el];
     float *dst = e < n_w ? (dW ? dW + e : nullptr) : (db ? db + (e - n_w) : nullptr);
     if (dst) *dst = (float)t;
 }
@@ -602,12 +578,18 @@ fastgl_status check_dims(int64_t M, int64_t K, int64_t N)
     return FASTGL_OK;
 }
 
+// Few result columns: plain multiply-adds instead of matrix-core tiles (update_narrow.hip).  Up to 8
+// columns the tiled kernel, which always works on 128, loses at every M and K (N = 8: 8 multiply-adds
+// per element read cost less than reading it).  K beyond the grid's second dimension stays here.
+bool narrow(int64_t K, int64_t N) { return N >= 1 && N <= kNarrowCols && K > 0 && K <= (int64_t)1 << 20; }
+
 // Rows per slab: a function of the shape alone, so results do not depend on the device or the run.
 // The height that minimises a model of the launch: the (slab, tile) workgroups run in rounds of
 // kRoundSlots, a workgroup costs its steps plus a fixed part, and every slab adds a partial result
 // that is written once and read once by the reduction.  Integer arithmetic (picoseconds).
 int64_t slab_rows(int64_t M, int64_t K, int64_t N)
 {
+    if (narrow(K, N)) return narrow_slab_rows(M);
     const int64_t tiles = (K > 0 ? ceil_div(K, kTile) : 1) * ceil_div(N, kTile);
     const int64_t partial = K * N + N;                 // floats per slab
     int64_t best = kMinSlabRows, best_cost = INT64_MAX;
@@ -654,6 +636,12 @@ fastgl_status update_fwd(bool bf16, const void *H, const void *W, const float *b
     if (misaligned_to(H, el) || misaligned_to(W, el) || misaligned_to(bias, 4) || misaligned_to(Y, el)) {
         set_error("matrices must be aligned to their element size");
         return FASTGL_ERR_INVALID_ARG;
+    }
+    if (narrow(K, N)) {
+        NarrowArgs a = {};
+        a.H = H; a.W = W; a.bias = bias; a.out = Y;
+        a.M = M; a.K = K; a.N = (int32_t)N; a.relu = relu != 0;
+        return launch_narrow_fwd(a, bf16, (hipStream_t)stream);
     }
     GemmArgs g = {};
     g.a = Operand{H, nullptr, K};
@@ -703,7 +691,13 @@ fastgl_status update_bwd(bool bf16, const void *H, const void *W, const void *Y,
     hipStream_t s = (hipStream_t)stream;
     const void *gate = relu ? Y : nullptr;
 
-    if (dH && M > 0 && K > 0) {
+    NarrowArgs na = {};
+    na.H = H; na.W = W; na.dY = dY; na.gate = gate; na.out = dH;
+    na.M = M; na.K = K; na.N = (int32_t)N;
+    if (dH && M > 0 && narrow(K, N)) {
+        st = launch_narrow_dh(na, bf16, s);
+        if (st != FASTGL_OK) return st;
+    } else if (dH && M > 0 && K > 0) {
         // dH[m][k] = sum_n dZ[m][n] W[k][n]: both operands have the contracted index contiguous.
         GemmArgs g = {};
         g.a = Operand{dY, gate, N};
@@ -718,7 +712,11 @@ fastgl_status update_bwd(bool bf16, const void *H, const void *W, const void *Y,
         const int64_t rows = slab_rows(M, K, N), nslab = ceil_div(M, rows);
         const int64_t stride = K * N + N;
         float *part = (float *)workspace;
-        if (nslab > 0) {
+        if (nslab > 0 && narrow(K, N) && dW) {
+            na.part = part; na.slab = rows;
+            st = launch_narrow_dw(na, bf16, s);
+            if (st != FASTGL_OK) return st;
+        } else if (nslab > 0) {
             GemmArgs g = {};
             g.a = Operand{H, nullptr, K};
             g.b = Operand{dY, gate, N};
@@ -730,8 +728,12 @@ fastgl_status update_bwd(bool bf16, const void *H, const void *W, const void *Y,
             if (st != FASTGL_OK) return st;
         }
         const int64_t n_w = K * N, total = n_w + N;
-        hipLaunchKernelGGL(k_update_reduce, dim3((unsigned)ceil_div(total, kReduceElems)), dim3(256), 0, s, part, nslab,
-                           stride, n_w, N, dW, db);
+        if (total >= kReduceElemsWide)
+            hipLaunchKernelGGL(k_update_reduce<8>, dim3((unsigned)ceil_div(total, 32)), dim3(256), 0, s, part, nslab, stride,
+                               n_w, N, dW, db);
+        else
+            hipLaunchKernelGGL(k_update_reduce<64>, dim3((unsigned)ceil_div(total, 4)), dim3(256), 0, s, part, nslab, stride,
+                               n_w, N, dW, db);
         FASTGL_LAUNCH_CHECK("fastgl_update_bwd (reduce)");
     }
     return FASTGL_OK;

@@ -1,0 +1,56 @@
+// Shared by the translation units of the update phase: the problem of one call, and the kernels for
+// result shapes that the tiled matrix-core kernel of update.hip does not suit.
+#pragma once
+#include "internal.h"
+
+namespace fastgl {
+
+// fp32 -> bf16, round to nearest even (NaN stays NaN).
+__device__ __forceinline__ uint16_t f32_to_bf16(float f)
+{
+    uint32_t u = __float_as_uint(f);
+    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((u >> 16) | 0x0040u);
+    u += 0x7FFFu + ((u >> 16) & 1u);
+    return (uint16_t)(u >> 16);
+}
+
+// A quad (four consecutive elements) of an fp32 or bf16 row.
+template <bool BF16>
+struct QuadBits;
+template <>
+struct QuadBits<false> {
+    typedef float4 type;
+    typedef float elem;
+};
+template <>
+struct QuadBits<true> {
+    typedef uint2 type;           // four bf16
+    typedef uint16_t elem;
+};
+
+__device__ __forceinline__ float4 quad_to_f32(float4 q) { return q; }
+__device__ __forceinline__ float4 quad_to_f32(uint2 q)
+{
+    return make_float4(__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xFFFF0000u), __uint_as_float(q.y << 16),
+                       __uint_as_float(q.y & 0xFFFF0000u));
+}
+
+// ---- update_narrow.hip: N <= kNarrowCols
+constexpr int kNarrowCols = 8;
+
+struct NarrowArgs {
+    const void *H, *W, *dY, *gate;   // gate: where it is <= 0, dY counts as 0; NULL: everywhere dY
+    const float *bias;
+    void *out;                       // Y or dH
+    float *part;                     // dW / db partials: [slab][K * N + N]
+    int64_t M, K;
+    int64_t slab;                    // rows per dW partial
+    int32_t N, relu;
+};
+
+fastgl_status launch_narrow_fwd(const NarrowArgs &a, bool bf16, hipStream_t s);
+fastgl_status launch_narrow_dh(const NarrowArgs &a, bool bf16, hipStream_t s);
+fastgl_status launch_narrow_dw(const NarrowArgs &a, bool bf16, hipStream_t s);
+int64_t narrow_slab_rows(int64_t M);
+
+}  // namespace fastgl
