@@ -583,6 +583,13 @@ fastgl_status check_dims(int64_t M, int64_t K, int64_t N)
 // per element read cost less than reading it).  K beyond the grid's second dimension stays here.
 bool narrow(int64_t K, int64_t N) { return N >= 1 && N <= kNarrowCols && K > 0 && K <= (int64_t)1 << 20; }
 
+// With more rows than this, Y with few columns comes from the tall tiles of update_rows.hip (32 columns wide) too,
+// and so does dH with 5 to 8.  For one column they are slower (M = 1.15 M, K = 64, N = 1: Y 75 us against 53), but
+// they add the same terms in the same order as for every other shape: where the sum of two such projections decides by
+// its sign (LeakyReLU of a GAT head over millions of edges), another order would turn a few of those signs.  From
+// three columns on they are faster (M = 500 K, K = 64, N = 7: Y 40 us against 63, dH 36 against 64).
+constexpr int64_t kNarrowRows = 16384;
+
 // Rows per slab: a function of the shape alone, so results do not depend on the device or the run.
 // The height that minimises a model of the launch: the (slab, tile) workgroups run in rounds of
 // kRoundSlots, a workgroup costs its steps plus a fixed part, and every slab adds a partial result
@@ -637,19 +644,19 @@ fastgl_status update_fwd(bool bf16, const void *H, const void *W, const float *b
         set_error("matrices must be aligned to their element size");
         return FASTGL_ERR_INVALID_ARG;
     }
-    if (narrow(K, N)) {
+    if (narrow(K, N) && M <= kNarrowRows) {
         NarrowArgs a = {};
         a.H = H; a.W = W; a.bias = bias; a.out = Y;
         a.M = M; a.K = K; a.N = (int32_t)N; a.relu = relu != 0;
         return launch_narrow_fwd(a, bf16, (hipStream_t)stream);
     }
-    GemmArgs g = {};
-    g.a = Operand{H, nullptr, K};
-    g.b = Operand{W, nullptr, N};
-    g.c = Y; g.ldc = N;
-    g.R = M; g.C = N; g.Kc = K; g.slab = K;
-    g.bias = bias; g.relu = relu != 0;
-    return launch_gemm<false, true, false, 0>(g, bf16, (hipStream_t)stream, "fastgl_update_fwd");
+    if (K == 0) return launch_no_terms(bf16, Y, bias, M, N, relu != 0, (hipStream_t)stream, "fastgl_update_fwd (K = 0)");
+    RowsGemm g = {};
+    g.a = H; g.lda = K;
+    g.b = W; g.ldb = N;
+    g.bias = bias; g.c = Y;
+    g.M = M; g.N = N; g.Kc = K; g.relu = relu != 0;
+    return launch_rows_gemm(g, true, bf16, (hipStream_t)stream, "fastgl_update_fwd");
 }
 
 fastgl_status update_bwd(bool bf16, const void *H, const void *W, const void *Y, const void *dY, int64_t M, int64_t K,
@@ -694,17 +701,19 @@ fastgl_status update_bwd(bool bf16, const void *H, const void *W, const void *Y,
     NarrowArgs na = {};
     na.H = H; na.W = W; na.dY = dY; na.gate = gate; na.out = dH;
     na.M = M; na.K = K; na.N = (int32_t)N;
-    if (dH && M > 0 && narrow(K, N)) {
+    if (dH && M > 0 && narrow(K, N) && (N <= 4 || M <= kNarrowRows)) {
         st = launch_narrow_dh(na, bf16, s);
         if (st != FASTGL_OK) return st;
+    } else if (dH && M > 0 && K > 0 && N > 0) {
+        RowsGemm g = {};
+        g.a = dY; g.gate = gate; g.lda = N;
+        g.b = W; g.ldb = N;
+        g.c = dH;
+        g.M = M; g.N = K; g.Kc = N;
+        st = launch_rows_gemm(g, false, bf16, s, "fastgl_update_bwd (dH)");
+        if (st != FASTGL_OK) return st;
     } else if (dH && M > 0 && K > 0) {
-        // dH[m][k] = sum_n dZ[m][n] W[k][n]: both operands have the contracted index contiguous.
-        GemmArgs g = {};
-        g.a = Operand{dY, gate, N};
-        g.b = Operand{W, nullptr, N};
-        g.c = dH; g.ldc = K;
-        g.R = M; g.C = K; g.Kc = N; g.slab = N;
-        st = launch_gemm<false, false, false, 1>(g, bf16, s, "fastgl_update_bwd (dH)");
+        st = launch_no_terms(bf16, dH, nullptr, M, K, false, s, "fastgl_update_bwd (dH, N = 0)");
         if (st != FASTGL_OK) return st;
     }
     if (want_w) {

@@ -35,6 +35,24 @@ __device__ __forceinline__ float4 quad_to_f32(uint2 q)
                        __uint_as_float(q.y & 0xFFFF0000u));
 }
 
+// ---- update_rows.hip: C[M][N] = A[M][Kc] B, A and C row-major; Kc >= 1, M >= 1, N >= 1
+struct RowsGemm {
+    const void *a, *gate;            // A; where gate (same layout) is <= 0 an element of A counts as 0; NULL: no gate
+    const void *b;
+    int64_t lda, ldb;
+    const float *bias;               // [N] or NULL
+    void *c;
+    int64_t M, N, Kc;
+    int64_t tiles_r;
+    int32_t tiles_c, relu;
+};
+// b_col: B[k][n] = b[k * ldb + n] (no gate then), else b[n * ldb + k]
+fastgl_status launch_rows_gemm(RowsGemm g, bool b_col, bool bf16, hipStream_t s, const char *what);
+
+// c[i][j] = act(bias[j]) (0 without bias): what is left of either product with nothing to contract
+fastgl_status launch_no_terms(bool bf16, void *c, const float *bias, int64_t rows, int64_t cols, bool relu, hipStream_t s,
+                              const char *what);
+
 // ---- update_narrow.hip: N <= kNarrowCols
 constexpr int kNarrowCols = 8;
 

@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("M,K,N", [(1, 1, 1), (3, 4, 2), (4, 3, 3), (5, 64, 1), (63, 255, 5), (65, 256, 8), (66, 260, 7),
-                                   (129, 1030, 4), (70001, 20, 1), (70001, 7, 6), (1025, 100, 9)])
+                                   (129, 1030, 4), (70001, 20, 1), (70001, 7, 6), (1025, 100, 9),
+                                   (20001, 64, 1), (20000, 65, 3), (20001, 3, 8), (20001, 130, 6)])
 def test_narrow_update_parity(M, K, N):
     run_case(M, K, N, relu=M % 2 == 0, bias=M % 4 != 1, seed=M + K + N, what="narrow update")
 
