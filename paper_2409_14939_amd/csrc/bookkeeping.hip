@@ -34,7 +34,8 @@
 // to fill the compute units once.
 #include <vector>
 
-#include "internal.h"
+#include "plan_device.h"
+#include "plan_once.h"
 
 namespace fastgl {
 
@@ -44,118 +45,6 @@ constexpr int kMaxSortItems = 4;                     // keys per thread and step
 constexpr int kMaxSortBlocks = 256;
 constexpr int kSplitThreads = 512;                   // workgroup of the split into buckets (bucketed transpose)
 constexpr int kMaxSplitBlocks = 512;                 // two of them per compute unit
-
-// -------------------------------------------------- block-wide primitives ----
-__device__ __forceinline__ int wave_incl_scan(int v)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int t = __shfl_up(v, o, kWave);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
-
-// Exclusive scan over all threads of the block (any multiple of 64 up to 1024);
-// *total = block sum.  `lds` needs 16 ints and is free again on return.
-__device__ __forceinline__ int block_excl_scan(int v, int *total, int *lds)
-{
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
-    int inc = wave_incl_scan(v);
-    if (lane == kWave - 1) lds[w] = inc;
-    __syncthreads();
-    int off = 0, tot = 0;
-    for (int i = 0; i < nw; ++i) {
-        int s = lds[i];
-        if (i < w) off += s;
-        tot += s;
-    }
-    __syncthreads();
-    *total = tot;
-    return off + inc - v;
-}
-
-// Block sums of two values at once.  `lds` needs 32 ints and is free again on return.
-__device__ __forceinline__ void block_sum2(int &a, int &b, int *lds)
-{
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o, kWave);
-        b += __shfl_xor(b, o, kWave);
-    }
-    if (lane == 0) {
-        lds[w] = a;
-        lds[16 + w] = b;
-    }
-    __syncthreads();
-    int sa = 0, sb = 0;
-    for (int i = 0; i < nw; ++i) {
-        sa += lds[i];
-        sb += lds[16 + i];
-    }
-    __syncthreads();
-    a = sa;
-    b = sb;
-}
-
-// ---------------------------------------- degrees + long-row buckets (roles) ----
-struct RowsArgs {
-    const int32_t *rowptr;   // [n+1]
-    int64_t n, per;          // block b owns rows [b*per, min(n,(b+1)*per))
-    int nb;
-    int32_t *len_out;        // [n] or NULL
-    float *inv, *rsq;        // [n] or NULL: 1/max(len,1), 1/sqrt(max(len,1))
-    int32_t *counts;         // [2*nb] per-block (long rows, chunks)
-    int32_t *long_rows, *chunk_ptr, *totals;
-    int32_t *edge_row;       // [nnz] or NULL: edge_row[e] = row that owns edge e
-    int32_t *split;          // [nsets+1] or NULL: first row of every equal-work row set
-    int64_t nsets;
-};
-
-// What one row contributes: its length and scale factors, the long-row counts, and the
-// equal-work row sets that start right after it.  Called by every thread of a wavefront
-// together (rows that start many sets are written by the whole wavefront); valid = the
-// thread has a row.  e0 = first edge of row r, len = its length.
-__device__ __forceinline__ void row_emit(const RowsArgs &A, int64_t r, bool valid, int e0, int len, int &nl,
-                                         int &nc)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    if (valid) {
-        if (A.len_out) A.len_out[r] = len;
-        double d = (double)(len < 1 ? 1 : len);
-        if (A.inv) A.inv[r] = (float)(1.0 / d);
-        if (A.rsq) A.rsq[r] = (float)(1.0 / sqrt(d));
-        if (len > kLongThreshold) {
-            nl += 1;
-            nc += (len + kLongChunk - 1) / kLongChunk;
-        }
-    }
-    if (A.split) {
-        // Equal-work row sets: set g starts at the first row whose work prefix
-        // W[r] = rowptr[r] + r reaches g * kWorkPerGroup.  Row r+1 is that row for
-        // every g in (W[r]/work, W[r+1]/work]; the thread of row r writes them.
-        int64_t g0 = 1, g1 = 0;   // empty
-        if (valid) {
-            g0 = ((int64_t)e0 + r) / kWorkPerGroup + 1;
-            g1 = ((int64_t)e0 + len + r + 1) / kWorkPerGroup;
-            if (r == 0) A.split[0] = 0;
-            if (r == A.n - 1 && g1 < A.nsets) A.split[A.nsets] = (int32_t)A.n;   // partial last set
-        }
-        const bool big = g1 - g0 >= kWave;
-        if (!big)
-            for (int64_t g = g0; g <= g1; ++g) A.split[g] = (int32_t)(r + 1);
-        unsigned long long m = __ballot(big);
-        while (m) {
-            const int leader = __ffsll((long long)m) - 1;
-            const int64_t lg0 = __shfl(g0, leader, kWave), lg1 = __shfl(g1, leader, kWave);
-            const int64_t lr = __shfl(r, leader, kWave);
-            for (int64_t g = lg0 + lane; g <= lg1; g += kWave) A.split[g] = (int32_t)(lr + 1);
-            m &= m - 1;
-        }
-    }
-}
 
 // Pass 1 over row pointers: row lengths, scale factors, per-block counts of long
 // rows / their chunks, and (optionally) the row id of every edge.  A thread
@@ -246,8 +135,6 @@ __device__ __forceinline__ void rows_fill(const RowsArgs &A, int b, int *lds)
 }
 
 // ------------------------------------ bucketed transpose: sizes, workgroup map ----
-constexpr int kBucketBits = 11;
-constexpr int kBucketIds = 1 << kBucketBits;
 constexpr int kMaxBuckets = 1024;                            // one thread per bucket in the histogram, two in the scatter's prologue
 constexpr int kLocalThreads = 512;
 constexpr int kLocalWaves = kLocalThreads / kWave;
@@ -329,29 +216,6 @@ struct SortArgs {
 };
 
 __device__ __forceinline__ int digit_of(const SortArgs &S, int32_t key) { return (key >> S.shift) & ((1 << S.bits) - 1); }
-
-// Lanes of the wavefront whose `bits`-bit value equals this lane's (lanes with ok == false match
-// nobody and nobody matches them).  One ballot per bit; lo / hi = the mask's halves.
-template <int BITS>
-__device__ __forceinline__ void match_lanes(int v, bool ok, unsigned &lo, unsigned &hi)
-{
-    const unsigned long long act = __ballot(ok);
-    unsigned dlo = 0, dhi = 0;   // lanes that differ from this one in some bit
-#pragma unroll
-    for (int bit = 0; bit < BITS; ++bit) {
-        const int neg = (int)((unsigned)v << (31 - bit)) >> 31;   // all ones where the bit is set
-        const unsigned long long bl = __ballot(neg < 0);
-        dlo |= (unsigned)bl ^ (unsigned)neg;
-        dhi |= (unsigned)(bl >> 32) ^ (unsigned)neg;
-    }
-    lo = ok ? (unsigned)act & ~dlo : 0u;
-    hi = ok ? (unsigned)(act >> 32) & ~dhi : 0u;
-}
-
-__device__ __forceinline__ int lanes_below(unsigned lo, unsigned hi)   // set bits of the mask below this lane
-{
-    return (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-}
 
 // Digit histogram of the block's key range.  h: 1 << bits counters.
 __device__ __forceinline__ void sort_hist(const SortArgs &S, int b, int *h)
@@ -1340,11 +1204,66 @@ static fastgl_status src_degrees(fastgl_plan *p, hipStream_t s)
     return FASTGL_OK;
 }
 
+// Plans of small blocks take one launch (plan_once.h).  A call whose blocks do not all qualify builds all of
+// them in stages: the small ones then ride along in launches that the others need anyway.
+static bool fits_once(const fastgl_plan *p, int parts, bool src_deg)
+{
+    const bool full = (parts & FASTGL_PLAN_BWD) != 0;
+    if (full || src_deg) {
+        if (p->num_edges > kOnceEdges || p->num_src > kOnceSources) return false;
+    }
+    return p->num_dst <= (full ? kOnceRows : kOnceRowsFwd);
+}
+
+static fastgl_status build_once(fastgl_plan *const *plans, const int *parts, const bool *src_deg, int n, hipStream_t s)
+{
+    static_assert(sizeof(OnceArgs) <= 4096, "kernel arguments are passed by value");
+    static bool raised = false;   // benign if two threads both do it
+    if (!raised) {
+        FASTGL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_plan_once), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)sizeof(OnceShared)));
+        raised = true;
+    }
+    for (int at = 0; at < n; at += kOnceMaxJobs) {
+        OnceArgs A;
+        A.njobs = n - at < kOnceMaxJobs ? n - at : kOnceMaxJobs;
+        int blocks = 0;
+        size_t lds = kOnceLdsDegrees;
+        for (int i = 0; i < A.njobs; ++i) {
+            fastgl_plan *p = plans[at + i];
+            const bool full = (parts[at + i] & FASTGL_PLAN_BWD) != 0, deg = !full && src_deg[at + i];
+            p->parts = full ? parts[at + i] : (parts[at + i] & ~FASTGL_PLAN_PERM) | (deg ? FASTGL_PLAN_SRC_DEG : 0);
+            OnceJob &J = A.job[i];
+            J.indptr = p->indptr; J.indices = p->indices;
+            J.num_dst = (int32_t)p->num_dst; J.num_src = (int32_t)p->num_src; J.num_edges = (int32_t)p->num_edges;
+            J.full = full ? 1 : 0;
+            J.dst = rows_args(p->indptr, p->num_dst, p->din, p->dst_inv, p->dst_rsqrt, nullptr, p->long_dst, p->chunk_ptr_dst,
+                              p->counters, nullptr, p->split_dst, p->num_edges);
+            J.src = rows_args(nullptr, p->num_src, p->dout, nullptr, p->src_rsqrt, nullptr, p->long_src, p->chunk_ptr_src,
+                              p->counters + 2, nullptr, full ? p->split_src : nullptr, p->num_edges);
+            J.indptr_T = p->indptr_T; J.indices_T = p->indices_T;
+            J.perm = full && (p->parts & FASTGL_PLAN_PERM) ? p->perm : nullptr;
+            J.buckets = full || deg ? (int)ceil_div(p->num_src > 0 ? p->num_src : (full ? 1 : 0), (int64_t)kBucketIds) : 0;
+            J.row_groups = (int)ceil_div(p->num_dst, (int64_t)kOnceThreads);
+            if (full) lds = sizeof(OnceShared);
+            A.first[i] = blocks;
+            blocks += J.buckets + (full ? 1 : 0) + 1 + J.row_groups;
+        }
+        A.first[A.njobs] = blocks;
+        hipLaunchKernelGGL(k_plan_once, dim3(blocks), dim3(kOnceThreads), lds, s, A);
+        FASTGL_LAUNCH_CHECK("k_plan_once");
+    }
+    return FASTGL_OK;
+}
+
 // Enqueue the bookkeeping of n plans; stage k of all of them shares a launch.
 // parts[i]: FASTGL_PLAN_FWD or FASTGL_PLAN_ALL; src_deg[i] asks a forward-only
 // plan for dout / src_rsqrt as well (GCN).
 fastgl_status plans_build(fastgl_plan *const *plans, const int *parts, const bool *src_deg, int n, hipStream_t s)
 {
+    bool once = true;
+    for (int i = 0; i < n; ++i) once = once && fits_once(plans[i], parts[i], src_deg[i]);
+    if (once) return build_once(plans, parts, src_deg, n, s);
     // The split of the edges runs two 512-thread workgroups per compute unit: the transposes of a
     // call share the (256) compute units, each workgroup taking about the same number of edges.
     int64_t edges = 0;

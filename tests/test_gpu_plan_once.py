@@ -1,0 +1,63 @@
+"""Plans of small blocks, which are built in one launch: bit for bit against the oracle at the edges of what that
+launch takes (and just beyond, where the staged build takes over), and small blocks built in stages together
+with a large one."""
+import numpy as np
+import pytest
+import torch
+
+import blockgen as bg
+import oracle
+from paper_2409_14939_amd import binding as B
+from gpu_util import dev_i32, read_f32, read_i32
+from test_gpu_parity import check_bookkeeping
+
+pytestmark = pytest.mark.gpu
+
+
+def exact_block(rng, num_dst, num_src, edges, hub=0):
+    """`edges` edges over the rows at random, `hub` of them in one row; sources skewed to low ids."""
+    cuts = np.sort(rng.integers(0, edges - hub + 1, num_dst - 1)) if num_dst > 1 else np.zeros(0, np.int64)
+    deg = np.diff(np.concatenate([[0], cuts, [edges - hub]]))
+    deg[rng.integers(num_dst)] += hub
+    idx = np.minimum((rng.random(edges) ** 2 * num_src).astype(np.int64), num_src - 1)
+    blk = bg.Block(np.concatenate([[0], np.cumsum(deg)]).astype(np.int32), idx.astype(np.int32), num_dst, num_src)
+    blk.check()
+    return blk
+
+
+@pytest.mark.parametrize("nd,ns,edges,hub", [(1, 1, 1, 0), (3, 2048, 64, 0), (256, 2049, 1025, 300), (24576, 40000, 65535, 0),
+                                             (24577, 40000, 65535, 0), (1000, 4097, 65536, 0), (70, 900, 65535, 60000),
+                                             (5000, 262144, 30000, 2000), (5000, 262145, 30000, 2000), (2000, 6000, 24577, 257)])
+def test_plan_of_a_small_block(nd, ns, edges, hub):
+    check_bookkeeping(exact_block(np.random.default_rng(nd + edges), nd, ns, edges, hub), "once")
+
+
+def test_small_blocks_next_to_a_large_one_and_alone():
+    rng = np.random.default_rng(5)
+    small = [exact_block(rng, 100, 3000, 2500, 400), exact_block(rng, 4000, 9000, 9000)]
+    for blocks in (small, small + [exact_block(rng, 30000, 50000, 90000, 700)]):
+        dev = [(dev_i32(b.indptr), dev_i32(b.indices), b.num_src) for b in blocks]
+        for blk, plan in zip(blocks, B.fastgl_block_plan_create_many(dev, B.PLAN_ALL | B.PLAN_PERM)):
+            v = plan.export()
+            pT, iT, perm = oracle.transpose(blk.indptr, blk.indices, blk.num_src)
+            assert np.array_equal(read_i32(plan, v.indptr_T, blk.num_src + 1), pT)
+            assert np.array_equal(read_i32(plan, v.indices_T, blk.num_edges), iT)
+            assert np.array_equal(read_i32(plan, v.perm, blk.num_edges), perm)
+
+
+@pytest.mark.parametrize("nd,ns,edges,hub", [(70, 900, 65535, 60000), (65536, 70000, 65535, 300), (65537, 70000, 3000, 0)])
+def test_forward_only_plan_with_source_degrees(nd, ns, edges, hub):
+    blk = exact_block(np.random.default_rng(nd), nd, ns, edges, hub)
+    ip, ix = dev_i32(blk.indptr), dev_i32(blk.indices)
+    plan = B.fastgl_block_plan_create(ip, ix, ns, B.PLAN_FWD | B.PLAN_SRC_DEG)
+    v = plan.export()
+    din, dout = oracle.degrees(blk.indptr, blk.indices, ns)
+    assert np.array_equal(read_i32(plan, v.din, nd), din) and np.array_equal(read_i32(plan, v.dout, ns), dout)
+    np.testing.assert_allclose(read_f32(plan, v.src_rsqrt, ns), 1.0 / np.sqrt(np.maximum(dout, 1)), rtol=1e-6)
+    rows, cptr = oracle.long_rows(blk.indptr, B.fastgl_long_row_threshold(), B.fastgl_long_row_chunk())
+    cnt = read_i32(plan, v.counters, 2)
+    assert cnt[0] == rows.shape[0] and cnt[1] == cptr[-1]
+    assert np.array_equal(read_i32(plan, v.long_dst, rows.shape[0]), rows)
+    sp = oracle.work_split(blk.indptr, B.fastgl_work_per_group())
+    assert np.array_equal(read_i32(plan, v.split_dst, sp.shape[0]), sp)
+    torch.cuda.synchronize()
