@@ -1,6 +1,13 @@
-// Device-side pieces shared by the ID map and the Match process: an open-addressing table of
-// 64-bit global IDs (linear probing, keys claimed by compare-and-swap from the empty marker -1) and
-// a workgroup-wide exclusive prefix sum.
+// Device-side pieces shared by the ID map and the Match process: open-addressing tables of 64-bit
+// global IDs (linear probing) and a workgroup-wide exclusive prefix sum.
+//
+// A slot holds 32 bits, -1 while empty: the POSITION in the input of an ID that hashed there, through which
+// the key is read from the input itself, and in the bits above it as much of the ID's hash as fits (9 bits for
+// 3 M input IDs), so that walking past other IDs reads their keys hardly ever.  What bounds the kernels around the table is the number of
+// accesses at random addresses, each a line of its own over the fabric, whatever is in it: measured on
+// tables of 7 to 72 MB, 50-65 G loads/s, 56-77 G stores/s, but 25 G read-modify-writes/s (compare-and-swap,
+// minimum or or, 4 or 8 bytes, with or without result).  So a fresh ID costs one compare-and-swap and
+// nothing else (a table of keys needs a second access for the value, and 2 to 4 times the fill).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -11,11 +18,22 @@ constexpr int kScanBlock = 1024;             // threads (= positions) per block 
 constexpr int64_t kMaxIds = (int64_t)1 << 30;
 constexpr int32_t kNoSlot = 0x7FFFFFFF;      // no table has this many slots
 
-// One table entry: the key and what is looked up through it share a 16-byte line piece.
-struct __attribute__((aligned(16))) Slot {
-    int64_t key;              // global ID, -1 while empty
-    int32_t val;              // ID map, ordered: smallest position seen; fused: local ID; Match: row
-    int32_t lid;              // ID map, ordered: local ID.  (val, lid) together: 64-bit batch mask
+constexpr int32_t kEmptySlot = -1;
+
+// Bits of a position below n in a slot; the other 31 - bits hold a piece of the hash (never the sign bit).
+inline int position_bits(int64_t n)
+{
+    int b = 1;
+    while (b < 30 && ((int64_t)1 << b) < n) ++b;
+    return b;
+}
+
+constexpr int kFillVec = 4;                  // 32-bit words per thread of a table fill; tables have room for whole ones
+
+// Entry of the overlap table for many mini-batches: a key and the 64-bit mask of the mini-batches holding it.
+struct __attribute__((aligned(16))) MaskSlot {
+    int64_t key;              // -1 while empty
+    unsigned long long mask;
 };
 
 // Capacity for n DISTINCT keys (Match, overlap counts): 2n slots (at least 1024), so the table is
@@ -46,44 +64,83 @@ __device__ __forceinline__ uint32_t hash_slot(int64_t gid, uint32_t cap)
 
 __device__ __forceinline__ uint32_t next_slot(uint32_t slot, uint32_t cap) { return slot + 1 == cap ? 0u : slot + 1; }
 
-// Slot that holds gid after the call; fresh = this thread put it there.  Keys sit STRIDE bytes apart
-// from `keys` on (16: the key of a Slot; 8: a bare array of keys).  The slot is read with a plain load
-// first and the compare-and-swap is only issued when that showed the empty marker: a key changes
-// exactly once (from -1 to an ID), so anything else that is read is final.  Ends because the table
-// always keeps empty slots.
-template <int STRIDE>
-__device__ __forceinline__ uint32_t insert_key(void *keys, uint32_t cap, int64_t gid, bool &fresh)
+// A table of positions and what a look-up needs to know of it.
+struct PositionTable {
+    int32_t *slot;            // [cap]
+    uint32_t cap;
+    int32_t bits;             // position_bits of the input
+
+    __device__ __forceinline__ int32_t position(int32_t word) const { return word & ((1 << bits) - 1); }
+    // the lower half of the hash, whose upper half chose the slot
+    __device__ __forceinline__ int32_t tag(int64_t gid) const
+    {
+        const uint32_t h = (uint32_t)((uint64_t)gid * 0x9E3779B97F4A7C15ull);
+        return (int32_t)((h >> (1 + bits)) << bits);
+    }
+    __device__ __forceinline__ bool same_tag(int32_t word, int32_t t) const { return (word ^ t) >> bits == 0; }
+};
+
+// Slot whose key is gid after the call; `holder` = the position it was seen to hold (p: this call
+// put it there).  key_at(position) = the ID at an input position.  LOOK: the slot is first read by a load that
+// may come from this XCD's L2: the KEY of a slot never changes once it has one (a smaller position of the same
+// ID may replace the one it holds), so an old reading can only show the empty marker, and the compare-and-swap
+// settles that.  Without LOOK (IDs that are not expected in the table yet) the compare-and-swap comes first.
+// Ends because the table always keeps empty slots.
+template <bool LOOK, class KeyAt>
+__device__ __forceinline__ uint32_t claim_slot(const PositionTable &t, int64_t gid, int32_t p, const KeyAt &key_at,
+                                               int32_t &holder)
 {
-    uint32_t slot = hash_slot(gid, cap);
-    fresh = false;
+    uint32_t slot = hash_slot(gid, t.cap);
+    const int32_t tag = t.tag(gid);
     for (;;) {
-        int64_t *kp = reinterpret_cast<int64_t *>(static_cast<char *>(keys) + (size_t)slot * STRIDE);
-        int64_t k = __hip_atomic_load(kp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (k == -1) {
-            k = (int64_t)atomicCAS((unsigned long long *)kp, (unsigned long long)-1ll, (unsigned long long)gid);
-            if (k == -1) {
-                fresh = true;
+        int32_t w = kEmptySlot;
+        if (LOOK) w = __hip_atomic_load(&t.slot[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (w == kEmptySlot) {
+            w = atomicCAS(&t.slot[slot], kEmptySlot, tag | p);
+            if (w == kEmptySlot) {
+                holder = p;
                 return slot;
             }
         }
-        if (k == gid) return slot;
-        slot = next_slot(slot, cap);
+        if (t.same_tag(w, tag)) {
+            holder = t.position(w);
+            if (key_at(holder) == gid) return slot;
+        }
+        slot = next_slot(slot, t.cap);
     }
 }
 
-__device__ __forceinline__ uint32_t insert_id(Slot *table, uint32_t cap, int64_t gid, bool &fresh)
+// Position that holds gid in a table that is no longer written, or kEmptySlot.  Ends at the first empty slot.
+template <class KeyAt>
+__device__ __forceinline__ int32_t find_position(const PositionTable &t, int64_t gid, const KeyAt &key_at)
 {
-    return insert_key<(int)sizeof(Slot)>(table, cap, gid, fresh);
+    uint32_t slot = hash_slot(gid, t.cap);
+    const int32_t tag = t.tag(gid);
+    for (;;) {
+        const int32_t w = t.slot[slot];
+        if (w == kEmptySlot) return kEmptySlot;
+        if (t.same_tag(w, tag) && key_at(t.position(w)) == gid) return t.position(w);
+        slot = next_slot(slot, t.cap);
+    }
 }
 
-// Slot that holds gid in a table that is no longer written, or kNoSlot.  Ends at the first empty slot.
-__device__ __forceinline__ int32_t find_id(const Slot *table, uint32_t cap, int64_t gid)
+// The four words of a fill thread; words behind `cap` belong to the table's rounded-up room.
+__device__ __forceinline__ void fill_words(const PositionTable &t, int64_t thread)
+{
+    if (thread * kFillVec < (int64_t)t.cap) reinterpret_cast<int4 *>(t.slot)[thread] = make_int4(-1, -1, -1, -1);
+}
+
+// Entry of the table of MaskSlots that holds gid after the call.
+__device__ __forceinline__ uint32_t insert_key(MaskSlot *table, uint32_t cap, int64_t gid)
 {
     uint32_t slot = hash_slot(gid, cap);
     for (;;) {
-        const int64_t k = table[slot].key;
-        if (k == gid) return (int32_t)slot;
-        if (k == -1) return kNoSlot;
+        int64_t k = __hip_atomic_load(&table[slot].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (k == -1) {
+            k = (int64_t)atomicCAS((unsigned long long *)&table[slot].key, (unsigned long long)-1ll, (unsigned long long)gid);
+            if (k == -1) return slot;
+        }
+        if (k == gid) return slot;
         slot = next_slot(slot, cap);
     }
 }
@@ -119,6 +176,30 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int base, int &out_ex
     out_excl = base + wave_sum[wv] + incl - v;
     const int total = total_s;
     __syncthreads();
+    return total;
+}
+
+// Sum of block_cnt[0 .. b) to every thread of a workgroup of kScanBlock.  Up to kSumBlocks blocks every workgroup
+// of a ranking pass adds up the counts before its own (at most 16 KB, from L2); a launch of one workgroup that
+// scans them costs 5 us, more than the kernel that counted a small hop.  Beyond that, scan_block_counts.
+constexpr int kSumBlocks = 4096;
+
+__device__ __forceinline__ int sum_before(const int32_t *block_cnt, int b)
+{
+    __shared__ int wave_sum_b[kScanBlock / 64];
+    int s = 0;
+#pragma unroll
+    for (int k = 0; k < kSumBlocks / kScanBlock; ++k) {
+        const int i = k * kScanBlock + threadIdx.x;
+        if (i < b) s += block_cnt[i];
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d);
+    if ((threadIdx.x & 63) == 0) wave_sum_b[threadIdx.x / 64] = s;
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int w = 0; w < kScanBlock / 64; ++w) total += wave_sum_b[w];
     return total;
 }
 

@@ -1,21 +1,25 @@
 // ID map of the sample phase (paper Section 2.2; Section 4.3, Algorithm 2): global IDs of one
 // sampled hop -> consecutive local IDs.  See include/fastgl_idmap.h for the contract.
 //
-// Table: open addressing with linear probing, 64-bit keys claimed by compare-and-swap from the
-// empty marker -1, capacity 1.5 x the number of input IDs (most of which repeat).  A thread reads the
-// slot with a plain load first and only issues the compare-and-swap when it saw the empty marker:
-// a key changes exactly once (from -1 to an ID), so anything else it reads is final; repeats of a
-// hub node therefore cost loads, not atomics.
+// Table: open addressing with linear probing, 32-bit slots that hold input positions (hash_table.h),
+// 1.5 slots per input ID (most of which repeat).
 //
-// FUSED mode is Algorithm 2: the claimant of a slot takes the next local ID from a counter (one
-// atomic add per workgroup, the threads that claimed a slot share it), a second kernel translates.
-// Its insertion only touches keys and its translation only local IDs, so it keeps them in two bare
-// arrays (8 + 4 bytes per slot): the array the translation reads at random is a quarter of the size
-// of a table of 16-byte entries and largely stays in L2.
-// ORDERED mode replaces the counter by "smallest position seen at this slot" (atomic min), then a
-// prefix count over the positions that are first occurrences gives every distinct ID its rank in
-// order of first appearance.  Both remember the slot of every input ID, so translation does not
-// probe again.
+// FUSED mode is Algorithm 2: destinations claim their slots first, then every neighbour entry; the claimant of
+// a slot takes the next local ID from a counter (one atomic add per workgroup, the threads that claimed a slot
+// share it), a second kernel translates.
+// ORDERED mode replaces the counter by "smallest position seen at this slot" (an atomic minimum, needed only
+// where a later position got there first), then a prefix count over the positions that are first occurrences
+// gives every distinct ID its rank in order of first appearance.
+//
+// A neighbour entry whose slot holds a destination, or that claimed the slot itself, has its local ID at
+// once; only the others are left to the translation (about half of a sampled hop's).  In FUSED mode they
+// remember the claimant's position and copy the local ID it wrote; in ORDERED mode the slot, where the ranking
+// pass has replaced the position of a first neighbour entry by its local ID (a destination's position is its
+// local ID).
+//
+// Bound by random accesses.  Products-shaped hop of 0.51 M destinations and 2.56 M neighbours, us, 16-byte
+// entries {key, smallest position, local ID} -> positions:  ordered 265 -> 166 (insert 134 -> 108, count 51 -> 20,
+// translate 43 -> 10);  fused 153 -> 124 (destinations 35 -> 23, translate 35 -> 11).
 #include "fastgl_idmap.h"
 #include "hash_table.h"
 #include "internal.h"
@@ -28,16 +32,14 @@ constexpr int32_t kFirstBit = (int32_t)0x80000000u;
 struct IdmapArgs {
     const int64_t *dst_gid, *nbr_gid;
     int64_t n_dst, n_nbr, n;
-    Slot *table;              // [cap] ORDERED: 16-byte entries
-    int64_t *keys;            // [cap] FUSED: keys ...
-    int32_t *vals;            // [cap]        ... and local IDs
-    int32_t *slot_of;         // [n] slot of every input position (kNoSlot: rejected ID); the ordered mode
-                              // sets bit 31 on positions that are first occurrences
+    PositionTable table;      // positions of input IDs; ORDERED: a first neighbour entry's local ID after ranking
+    int32_t *ref;             // ORDERED: [n] slot of every input position, bit 31 set on (candidates for) first
+                              // occurrences; FUSED: [n_nbr] neighbour entry that claimed the ID;
+                              // kNoSlot: nothing to translate
     int32_t *block_cnt;       // [blocks + 1]
     int32_t *local_nbr;
     int64_t *unique_gid;
     int32_t *result;          // [0] U, [1] violations
-    int64_t cap;              // slots of the table
     int nblocks;
     int fused;
 };
@@ -47,6 +49,11 @@ __device__ __forceinline__ int64_t id_at(const IdmapArgs &a, int64_t p)
     return p < a.n_dst ? a.dst_gid[p] : a.nbr_gid[p - a.n_dst];
 }
 
+struct IdAt {
+    const IdmapArgs &a;
+    __device__ __forceinline__ int64_t operator()(int64_t p) const { return id_at(a, p); }
+};
+
 __global__ __launch_bounds__(256) void k_idmap_fill(IdmapArgs a)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -54,16 +61,7 @@ __global__ __launch_bounds__(256) void k_idmap_fill(IdmapArgs a)
         a.result[0] = a.fused ? (int32_t)a.n_dst : 0;
         a.result[1] = 0;
     }
-    if (i >= a.cap) return;
-    if (a.fused) {
-        a.keys[i] = -1;       // a local ID is only read at a slot somebody claimed, after its claimant wrote it
-        return;
-    }
-    Slot e;
-    e.key = -1;
-    e.val = INT32_MAX;
-    e.lid = 0;
-    a.table[i] = e;
+    fill_words(a.table, i);
 }
 
 // ORDERED pass 1: claim slots, keep the smallest position per slot.
@@ -72,63 +70,77 @@ __global__ __launch_bounds__(256) void k_idmap_insert_min(IdmapArgs a)
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n) return;
     const int64_t gid = id_at(a, p);
+    int32_t ref = kNoSlot;
     if (gid < 0) {
-        a.slot_of[p] = kNoSlot;
+        if (p >= a.n_dst) a.local_nbr[p - a.n_dst] = -1;
         atomicAdd(&a.result[1], 1);
-        return;
+    } else {
+        int32_t q;
+        const uint32_t slot = claim_slot<true>(a.table, gid, (int32_t)p, IdAt{a}, q);
+        if (q > (int32_t)p) q = a.table.position(atomicMin(&a.table.slot[slot], a.table.tag(gid) | (int32_t)p));
+        if (q >= (int32_t)p)
+            ref = (int32_t)slot | kFirstBit;
+        else if (q < a.n_dst && p >= a.n_dst)
+            a.local_nbr[p - a.n_dst] = q;
+        else
+            ref = (int32_t)slot;
     }
-    bool fresh;
-    const uint32_t slot = insert_id(a.table, (uint32_t)a.cap, gid, fresh);
-    a.slot_of[p] = (int32_t)slot;
-    // the value only ever decreases, so a (possibly stale) reading that is already smaller settles it
-    if (__hip_atomic_load(&a.table[slot].val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > (int32_t)p)
-        atomicMin(&a.table[slot].val, (int32_t)p);
+    a.ref[p] = ref;
 }
 
-// ORDERED pass 2: mark the positions that are first occurrences (bit 31 of slot_of) and count them
-// per block of kScanBlock positions.
+// ORDERED pass 2: which of the positions that were the smallest of their ID when they came are still, and how
+// many per block of kScanBlock positions.
 __global__ __launch_bounds__(kScanBlock) void k_idmap_count(IdmapArgs a)
 {
     const int64_t p = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
     bool first = false;
     if (p < a.n) {
-        const int32_t slot = a.slot_of[p];
-        first = slot != kNoSlot && a.table[slot].val == (int32_t)p;
-        if (first) a.slot_of[p] = slot | kFirstBit;
+        const int32_t ref = a.ref[p];
+        if (ref < 0) {                             // bit 31
+            first = a.table.position(a.table.slot[ref & kNoSlot]) == (int32_t)p;
+            if (!first) a.ref[p] = ref & kNoSlot;
+        }
     }
     const int c = __syncthreads_count(first);
     if (threadIdx.x == 0) a.block_cnt[blockIdx.x] = c;
 }
 
-// ORDERED pass 3: block counts -> block offsets, total -> result[0].  One workgroup.
+// More than kSumBlocks blocks only: block counts -> block offsets, in place, with the total behind them.
+// One workgroup.
 __global__ __launch_bounds__(kScanBlock) void k_idmap_scan(IdmapArgs a)
 {
     const int total = scan_block_counts(a.block_cnt, a.nblocks);
     if (threadIdx.x == 0) a.result[0] = total;
 }
 
-// ORDERED pass 4: rank of every first occurrence = its local ID.
+// ORDERED pass 3: rank of every first occurrence = its local ID.  SUM: the block counts are not scanned yet.
+template <bool SUM>
 __global__ __launch_bounds__(kScanBlock) void k_idmap_rank(IdmapArgs a)
 {
     const int64_t p = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-    const int32_t so = p < a.n ? a.slot_of[p] : kNoSlot;
-    const bool first = so < 0;                     // bit 31
+    const int32_t ref = p < a.n ? a.ref[p] : kNoSlot;
+    const bool first = ref < 0;                    // bit 31
+    const int base = SUM ? sum_before(a.block_cnt, blockIdx.x) : a.block_cnt[blockIdx.x];
     int rank;
-    block_exclusive_scan(first ? 1 : 0, a.block_cnt[blockIdx.x], rank);
+    const int mine = block_exclusive_scan(first ? 1 : 0, base, rank);
+    if (SUM && threadIdx.x == 0 && (int)blockIdx.x == a.nblocks - 1) a.result[0] = base + mine;
     if (first) {
-        a.table[so & kNoSlot].lid = rank;
         a.unique_gid[rank] = id_at(a, p);
+        if (p >= a.n_dst) {
+            a.table.slot[ref & kNoSlot] = rank;
+            a.local_nbr[p - a.n_dst] = rank;
+        }
     }
     if (p < a.n_dst && (!first || rank != (int)p)) atomicAdd(&a.result[1], 1);   // repeated destination
 }
 
-// Translation (both modes): the slot of every neighbour entry is known.
+// ORDERED pass 4: the entries that neither are first occurrences nor met a destination.
 __global__ __launch_bounds__(256) void k_idmap_translate(IdmapArgs a)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= a.n_nbr) return;
-    const int32_t slot = a.slot_of[a.n_dst + e] & kNoSlot;
-    a.local_nbr[e] = slot == kNoSlot ? -1 : (a.fused ? a.vals[slot] : a.table[slot].lid);
+    const int32_t ref = a.ref[a.n_dst + e];
+    if (ref >= 0 && ref != kNoSlot) a.local_nbr[e] = a.table.position(a.table.slot[ref]);
 }
 
 // FUSED pass 1a: destination i takes local ID i.
@@ -137,15 +149,12 @@ __global__ __launch_bounds__(256) void k_idmap_fused_dst(IdmapArgs a)
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_dst) return;
     const int64_t gid = a.dst_gid[p];
-    bool fresh = false;
-    if (gid >= 0) {
-        const uint32_t slot = insert_key<8>(a.keys, (uint32_t)a.cap, gid, fresh);
-        if (fresh) {
-            a.vals[slot] = (int32_t)p;
-            a.unique_gid[p] = gid;
-        }
-    }
-    if (!fresh) atomicAdd(&a.result[1], 1);       // negative or repeated destination
+    int32_t q = kEmptySlot;
+    if (gid >= 0) claim_slot<false>(a.table, gid, (int32_t)p, IdAt{a}, q);
+    if (q == (int32_t)p)
+        a.unique_gid[p] = gid;
+    else
+        atomicAdd(&a.result[1], 1);               // negative or repeated destination
 }
 
 // FUSED pass 1b (Algorithm 2): whoever claims a slot takes the next local ID.  The claimants of a
@@ -157,11 +166,13 @@ __global__ __launch_bounds__(kScanBlock) void k_idmap_fused_nbr(IdmapArgs a)
     const int64_t e = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
     const bool active = e < a.n_nbr;
     const int64_t gid = active ? a.nbr_gid[e] : -1;
-    bool fresh = false;
-    uint32_t slot = 0;
-    if (gid >= 0) slot = insert_key<8>(a.keys, (uint32_t)a.cap, gid, fresh);
+    const int32_t p = (int32_t)(a.n_dst + e);
+    int32_t q = kEmptySlot;
+    if (gid >= 0) claim_slot<true>(a.table, gid, p, IdAt{a}, q);
+    const bool fresh = gid >= 0 && q == p;
     if (active) {
-        a.slot_of[a.n_dst + e] = gid >= 0 ? (int32_t)slot : kNoSlot;
+        a.ref[e] = q >= (int32_t)a.n_dst && !fresh ? q - (int32_t)a.n_dst : kNoSlot;
+        if (q < (int32_t)a.n_dst) a.local_nbr[e] = q;            // a destination's local ID; a rejected ID's -1
         if (gid < 0) atomicAdd(&a.result[1], 1);
     }
     int mine;
@@ -171,13 +182,23 @@ __global__ __launch_bounds__(kScanBlock) void k_idmap_fused_nbr(IdmapArgs a)
     __syncthreads();
     if (fresh) {
         const int l = range_base + mine;
-        a.vals[slot] = l;
+        a.local_nbr[e] = l;
         a.unique_gid[l] = gid;
     }
 }
 
+// FUSED pass 2: the entries whose ID another neighbour entry claimed.  A claimant's own entry is not
+// written here, so that reading it is safe.
+__global__ __launch_bounds__(256) void k_idmap_fused_translate(IdmapArgs a)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= a.n_nbr) return;
+    const int32_t ref = a.ref[e];
+    if (ref != kNoSlot) a.local_nbr[e] = a.local_nbr[ref];
+}
+
 struct Layout {
-    size_t table, slot_of, block_cnt, total;
+    size_t table, ref, block_cnt, total;
 };
 
 Layout layout(int64_t n)
@@ -185,8 +206,8 @@ Layout layout(int64_t n)
     const int64_t cap = idmap_slots(n);
     Layout L;
     size_t off = 0;
-    L.table = off; off += align_up((size_t)cap * sizeof(Slot), 256);
-    L.slot_of = off; off += align_up((size_t)(n > 0 ? n : 1) * 4, 256);
+    L.table = off; off += align_up((size_t)cap * 4, 256);
+    L.ref = off; off += align_up((size_t)(n > 0 ? n : 1) * 4, 256);
     L.block_cnt = off; off += align_up((size_t)(ceil_div(n, kScanBlock) + 1) * 4, 256);
     L.total = off;
     return L;
@@ -250,19 +271,17 @@ fastgl_status fastgl_idmap(const int64_t *dst_gid, int64_t n_dst, const int64_t 
     IdmapArgs a = {};
     a.dst_gid = dst_gid; a.nbr_gid = nbr_gid;
     a.n_dst = n_dst; a.n_nbr = n_nbr; a.n = n;
-    a.table = (Slot *)(ws + L.table);
-    a.keys = (int64_t *)(ws + L.table);                       // the fused mode's two arrays share the table's room
-    a.slot_of = (int32_t *)(ws + L.slot_of);
+    const int64_t cap = idmap_slots(n);
+    a.table = PositionTable{(int32_t *)(ws + L.table), (uint32_t)cap, position_bits(n)};
+    a.ref = (int32_t *)(ws + L.ref);
     a.block_cnt = (int32_t *)(ws + L.block_cnt);
     a.local_nbr = local_nbr; a.unique_gid = unique_gid; a.result = result;
-    a.cap = idmap_slots(n);
-    a.vals = (int32_t *)(a.keys + a.cap);
     a.nblocks = (int)ceil_div(n, kScanBlock);
     a.fused = mode == FASTGL_IDMAP_FUSED;
     hipStream_t s = (hipStream_t)stream;
     auto grid = [](int64_t items, int per) { return dim3((unsigned)(items > 0 ? ceil_div(items, per) : 1)); };
 
-    hipLaunchKernelGGL(k_idmap_fill, grid(a.cap, 256), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_idmap_fill, grid(cap, 256 * kFillVec), dim3(256), 0, s, a);
     FASTGL_LAUNCH_CHECK("fastgl_idmap (fill)");
     if (a.fused) {
         if (n_dst > 0) {
@@ -273,19 +292,28 @@ fastgl_status fastgl_idmap(const int64_t *dst_gid, int64_t n_dst, const int64_t 
             hipLaunchKernelGGL(k_idmap_fused_nbr, grid(n_nbr, kScanBlock), dim3(kScanBlock), 0, s, a);
             FASTGL_LAUNCH_CHECK("fastgl_idmap (fused map)");
         }
+        if (n_nbr > 0) {
+            hipLaunchKernelGGL(k_idmap_fused_translate, grid(n_nbr, 256), dim3(256), 0, s, a);
+            FASTGL_LAUNCH_CHECK("fastgl_idmap (translate)");
+        }
     } else if (n > 0) {
+        const dim3 blocks((unsigned)a.nblocks);
         hipLaunchKernelGGL(k_idmap_insert_min, grid(n, 256), dim3(256), 0, s, a);
         FASTGL_LAUNCH_CHECK("fastgl_idmap (insert)");
-        hipLaunchKernelGGL(k_idmap_count, dim3((unsigned)a.nblocks), dim3(kScanBlock), 0, s, a);
+        hipLaunchKernelGGL(k_idmap_count, blocks, dim3(kScanBlock), 0, s, a);
         FASTGL_LAUNCH_CHECK("fastgl_idmap (count)");
-        hipLaunchKernelGGL(k_idmap_scan, dim3(1), dim3(kScanBlock), 0, s, a);
-        FASTGL_LAUNCH_CHECK("fastgl_idmap (scan)");
-        hipLaunchKernelGGL(k_idmap_rank, dim3((unsigned)a.nblocks), dim3(kScanBlock), 0, s, a);
+        if (a.nblocks <= kSumBlocks) {
+            hipLaunchKernelGGL(k_idmap_rank<true>, blocks, dim3(kScanBlock), 0, s, a);
+        } else {
+            hipLaunchKernelGGL(k_idmap_scan, dim3(1), dim3(kScanBlock), 0, s, a);
+            FASTGL_LAUNCH_CHECK("fastgl_idmap (scan)");
+            hipLaunchKernelGGL(k_idmap_rank<false>, blocks, dim3(kScanBlock), 0, s, a);
+        }
         FASTGL_LAUNCH_CHECK("fastgl_idmap (rank)");
-    }
-    if (n_nbr > 0) {
-        hipLaunchKernelGGL(k_idmap_translate, grid(n_nbr, 256), dim3(256), 0, s, a);
-        FASTGL_LAUNCH_CHECK("fastgl_idmap (translate)");
+        if (n_nbr > 0) {
+            hipLaunchKernelGGL(k_idmap_translate, grid(n_nbr, 256), dim3(256), 0, s, a);
+            FASTGL_LAUNCH_CHECK("fastgl_idmap (translate)");
+        }
     }
     return FASTGL_OK;
 }

@@ -1,12 +1,18 @@
 // Match process and Greedy Reorder Strategy (paper Section 4.1, Algorithm 1).  See
 // include/fastgl_match.h for the contract.
 //
-// Match = set intersection through the same hash table as the ID map: the last mini-batch's IDs are
-// inserted with their row as value, the new mini-batch's IDs probe it; the misses are compacted in
-// position order (count per block, one-workgroup scan, rank) into the load lists.  The pairwise
-// overlaps of n mini-batches come from ONE table over all their IDs whose entries carry a 64-bit
-// mask of the mini-batches that hold the ID; every ID then adds its mask to its mini-batch's row of
-// the count matrix (LDS histogram per workgroup, one atomic per workgroup and column).
+// Match = set intersection through the ID map's kind of table (hash_table.h: a slot holds a position, here
+// the row of the last feature matrix): the last mini-batch's IDs are inserted, the new mini-batch's IDs probe
+// it; the misses are compacted in position order (count per block, rank) into the load lists.
+//
+// The pairwise overlaps of n mini-batches come from ONE table over all their IDs.  Up to kMarkBatches
+// mini-batches a slot has a byte per mini-batch beside it that every holder of the ID sets with a plain store
+// (twice the rate of an atomic or), and the pairs are counted by reading those marks once, in order; beyond
+// that, entries carry a 64-bit mask, and every ID adds its mask to its mini-batch's row of the count matrix
+// (LDS histogram per workgroup, one atomic per workgroup and column).
+//
+// Four mini-batches of 1.15 M nodes, us, 16-byte entries with masks -> positions and marks: overlaps 481 -> 248
+// (insert 271 -> 212, count 188 -> 24, fill 23 -> 12); Match of two of them 130 -> 107 (insert 80 -> 54).
 #include <vector>
 
 #include "fastgl_match.h"
@@ -19,8 +25,7 @@ namespace {
 struct MatchArgs {
     const int64_t *prev_gid, *new_gid;
     int64_t n_prev, n_new;
-    Slot *table;
-    int64_t cap;
+    PositionTable table;      // rows of the last mini-batch
     int32_t *block_cnt;
     int nblocks;
     int32_t *src_row, *load_pos;
@@ -28,29 +33,27 @@ struct MatchArgs {
     int32_t *result;
 };
 
-__global__ __launch_bounds__(256) void k_table_fill(Slot *table, int64_t cap, int32_t *zero, int nzero)
+struct GidAt {
+    const int64_t *gid;
+    __device__ __forceinline__ int64_t operator()(int64_t p) const { return gid[p]; }
+};
+
+__global__ __launch_bounds__(256) void k_match_fill(MatchArgs a)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nzero) zero[i] = 0;
-    if (i >= cap) return;
-    Slot e;
-    e.key = -1;
-    e.val = 0;
-    e.lid = 0;
-    table[i] = e;
+    if (i < 2) a.result[i] = 0;
+    fill_words(a.table, i);
 }
 
+// The IDs are distinct, so the compare-and-swap comes without a look at the slot.
 __global__ __launch_bounds__(256) void k_match_insert_prev(MatchArgs a)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= a.n_prev) return;
     const int64_t gid = a.prev_gid[j];
-    bool fresh = false;
-    if (gid >= 0) {
-        const uint32_t slot = insert_id(a.table, (uint32_t)a.cap, gid, fresh);
-        if (fresh) a.table[slot].val = (int32_t)j;
-    }
-    if (!fresh) atomicAdd(&a.result[1], 1);          // negative or repeated ID
+    int32_t q = kEmptySlot;
+    if (gid >= 0) claim_slot<false>(a.table, gid, (int32_t)j, GidAt{a.prev_gid}, q);
+    if (q != (int32_t)j) atomicAdd(&a.result[1], 1);          // negative or repeated ID
 }
 
 // Probe; hits get their row, misses -1 for now; misses are counted per block.
@@ -61,12 +64,10 @@ __global__ __launch_bounds__(kScanBlock) void k_match_probe(MatchArgs a)
     if (i < a.n_new) {
         const int64_t gid = a.new_gid[i];
         int32_t row = -1;
-        if (gid >= 0) {
-            const int32_t slot = find_id(a.table, (uint32_t)a.cap, gid);
-            if (slot != kNoSlot) row = a.table[slot].val;
-        } else {
+        if (gid >= 0)
+            row = find_position(a.table, gid, GidAt{a.prev_gid});
+        else
             atomicAdd(&a.result[1], 1);
-        }
         a.src_row[i] = row;
         miss = row < 0;
     }
@@ -74,18 +75,23 @@ __global__ __launch_bounds__(kScanBlock) void k_match_probe(MatchArgs a)
     if (threadIdx.x == 0) a.block_cnt[blockIdx.x] = c;
 }
 
+// More than kSumBlocks blocks only.
 __global__ __launch_bounds__(kScanBlock) void k_match_scan(MatchArgs a)
 {
     const int total = scan_block_counts(a.block_cnt, a.nblocks);
     if (threadIdx.x == 0) a.result[0] = total;
 }
 
+// SUM: the block counts are not scanned yet.
+template <bool SUM>
 __global__ __launch_bounds__(kScanBlock) void k_match_rank(MatchArgs a)
 {
     const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
     const bool miss = i < a.n_new && a.src_row[i] < 0;
+    const int base = SUM ? sum_before(a.block_cnt, blockIdx.x) : a.block_cnt[blockIdx.x];
     int k;
-    block_exclusive_scan(miss ? 1 : 0, a.block_cnt[blockIdx.x], k);
+    const int mine = block_exclusive_scan(miss ? 1 : 0, base, k);
+    if (SUM && threadIdx.x == 0 && (int)blockIdx.x == a.nblocks - 1) a.result[0] = base + mine;
     if (miss) {
         a.src_row[i] = -1 - k;
         a.load_pos[k] = (int32_t)i;
@@ -115,21 +121,120 @@ __global__ __launch_bounds__(256) void k_assemble_rows(const char *__restrict__ 
         *reinterpret_cast<uint16_t *>(dst) = *reinterpret_cast<const uint16_t *>(src + off);
 }
 
+constexpr int kMarkBatches = 8;
+constexpr int kCountBlocks = 256;            // workgroups that read the marks: one per compute unit
+
 struct OverlapArgs {
     const int64_t *gid;
     int64_t offsets[FASTGL_MAX_REORDER_BATCHES + 1];
     int n;
     int64_t total;
-    Slot *table;
     int64_t cap;
-    int32_t *slot_of;
     unsigned long long *counts;
     int32_t *violations;
+    PositionTable table;         // up to kMarkBatches
+    unsigned char *marks;        // [cap][4 or 8] 1 where the mini-batch holds the ID, unless it is the slot's holder
+    MaskSlot *masks;             // more: [cap]
+    int32_t *slot_of;            // [total]
 };
 
-__device__ __forceinline__ unsigned long long *mask_of(Slot *s)
+// Slots, and everything that is added up.  `violations` starts at the number of IDs: the count takes off every
+// (ID, mini-batch) that it finds marked, which leaves the negative and the repeated ones.
+template <typename MARK>
+__global__ __launch_bounds__(256) void k_marks_fill(OverlapArgs a)
 {
-    return reinterpret_cast<unsigned long long *>(&s->val);      // (val, lid) = 8 aligned bytes
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *a.violations = (int32_t)a.total;
+    if (i < (int64_t)a.n * a.n) a.counts[i] = 0;
+    fill_words(a.table, i);
+    if (i * kFillVec < a.cap) {
+        int4 *m = reinterpret_cast<int4 *>(a.marks) + i * (sizeof(MARK) / 4);
+#pragma unroll
+        for (int k = 0; k < (int)sizeof(MARK) / 4; ++k) m[k] = make_int4(0, 0, 0, 0);
+    }
+}
+
+// blockIdx.y = mini-batch, blockIdx.x walks its IDs.
+template <typename MARK>
+__global__ __launch_bounds__(256) void k_marks_insert(OverlapArgs a)
+{
+    const int b = blockIdx.y;
+    const int64_t p = a.offsets[b] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= a.offsets[b + 1]) return;
+    const int64_t gid = a.gid[p];
+    if (gid < 0) return;
+    int32_t q;
+    const uint32_t slot = claim_slot<true>(a.table, gid, (int32_t)p, GidAt{a.gid}, q);
+    if (q != (int32_t)p) a.marks[(size_t)slot * sizeof(MARK) + b] = 1;
+}
+
+// counts[i][j] = slots that both i and j hold: marked, or the slot's position is theirs.  A thread takes 16 bytes
+// of marks at a time, with their slots; both arrays are rounded up to whole ones, filled like the rest.
+template <typename MARK>
+__global__ __launch_bounds__(kScanBlock) void k_marks_count(OverlapArgs a)
+{
+    constexpr int NB = sizeof(MARK), PER = 16 / NB, PAIRS = NB * (NB + 1) / 2;
+    __shared__ int sum[PAIRS];
+    if (threadIdx.x < PAIRS) sum[threadIdx.x] = 0;
+    __syncthreads();
+    int c[PAIRS];
+#pragma unroll
+    for (int k = 0; k < PAIRS; ++k) c[k] = 0;
+    const int64_t pieces = (a.cap + PER - 1) / PER, step = (int64_t)gridDim.x * kScanBlock;
+    for (int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x; i < pieces; i += step) {
+        const uint4 v = reinterpret_cast<const uint4 *>(a.marks)[i];
+        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        int32_t held[PER];
+        if constexpr (PER == 4) {
+            const int4 h = reinterpret_cast<const int4 *>(a.table.slot)[i];
+            held[0] = h.x; held[1] = h.y; held[2] = h.z; held[3] = h.w;
+        } else {
+            const int2 h = reinterpret_cast<const int2 *>(a.table.slot)[i];
+            held[0] = h.x; held[1] = h.y;
+        }
+#pragma unroll
+        for (int s = 0; s < PER; ++s) {
+            if (held[s] == kEmptySlot) continue;
+            const int32_t p = a.table.position(held[s]);
+            int b = 0;
+            for (int x = 1; x < a.n; ++x) b += p >= a.offsets[x];
+#pragma unroll
+            for (int x = 0; x < NB; ++x) w[(s * NB + x) >> 2] |= b == x ? 1u << (8 * (x & 3)) : 0u;
+            int k = 0;
+#pragma unroll
+            for (int x = 0; x < NB; ++x)
+#pragma unroll
+                for (int y = x; y < NB; ++y, ++k) {
+                    const int at = s * NB;
+                    c[k] += (w[(at + x) >> 2] >> (8 * (x & 3))) & (w[(at + y) >> 2] >> (8 * (y & 3))) & 1;
+                }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < PAIRS; ++k) {
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) c[k] += __shfl_xor(c[k], d);
+        if ((threadIdx.x & 63) == 0 && c[k]) atomicAdd(&sum[k], c[k]);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < a.n * a.n) {
+        const int i = threadIdx.x / a.n, j = threadIdx.x % a.n, x = i < j ? i : j, y = i < j ? j : i;
+        const int v = sum[x * NB - x * (x - 1) / 2 + y - x];
+        if (v) atomicAdd(&a.counts[threadIdx.x], (unsigned long long)v);
+        if (v && i == j) atomicAdd(a.violations, -v);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_masks_fill(OverlapArgs a)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *a.violations = 0;
+    if (i < (int64_t)a.n * a.n) a.counts[i] = 0;
+    if (i >= a.cap) return;
+    MaskSlot e;
+    e.key = -1;
+    e.mask = 0;
+    a.masks[i] = e;
 }
 
 // blockIdx.y = mini-batch, blockIdx.x walks its IDs.
@@ -144,10 +249,9 @@ __global__ __launch_bounds__(256) void k_overlap_insert(OverlapArgs a)
         atomicAdd(a.violations, 1);
         return;
     }
-    bool fresh;
-    const uint32_t slot = insert_id(a.table, (uint32_t)a.cap, gid, fresh);
+    const uint32_t slot = insert_key(a.masks, (uint32_t)a.cap, gid);
     a.slot_of[p] = (int32_t)slot;
-    const unsigned long long old = atomicOr(mask_of(&a.table[slot]), 1ull << b);
+    const unsigned long long old = atomicOr(&a.masks[slot].mask, 1ull << b);
     if (old & (1ull << b)) atomicAdd(a.violations, 1);           // the mini-batch repeats this ID
 }
 
@@ -160,7 +264,7 @@ __global__ __launch_bounds__(256) void k_overlap_count(OverlapArgs a)
     const int64_t p = a.offsets[b] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p < a.offsets[b + 1]) {
         const int32_t slot = a.slot_of[p];
-        unsigned long long m = slot != kNoSlot ? *mask_of(&a.table[slot]) : 0ull;
+        unsigned long long m = slot != kNoSlot ? a.masks[slot].mask : 0ull;
         while (m) {
             const int j = __ffsll((long long)m) - 1;
             m &= m - 1;
@@ -172,12 +276,6 @@ __global__ __launch_bounds__(256) void k_overlap_count(OverlapArgs a)
         atomicAdd(&a.counts[(int64_t)b * a.n + threadIdx.x], (unsigned long long)hist[threadIdx.x]);
 }
 
-__global__ __launch_bounds__(256) void k_zero_u64(unsigned long long *p, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
 struct MatchLayout {
     size_t table, block_cnt, total;
 };
@@ -186,7 +284,7 @@ MatchLayout match_layout(int64_t n_prev, int64_t n_new)
 {
     MatchLayout L;
     size_t off = 0;
-    L.table = off; off += align_up((size_t)table_slots(n_prev) * sizeof(Slot), 256);
+    L.table = off; off += align_up((size_t)table_slots(n_prev) * 4, 256);
     L.block_cnt = off; off += align_up((size_t)(ceil_div(n_new, kScanBlock) + 1) * 4, 256);
     L.total = off;
     return L;
@@ -200,7 +298,7 @@ OverlapLayout overlap_layout(int64_t total_ids)
 {
     OverlapLayout L;
     size_t off = 0;
-    L.table = off; off += align_up((size_t)table_slots(total_ids) * sizeof(Slot), 256);
+    L.table = off; off += align_up((size_t)table_slots(total_ids) * sizeof(MaskSlot), 256);
     L.slot_of = off; off += align_up((size_t)(total_ids > 0 ? total_ids : 1) * 4, 256);
     L.total = off;
     return L;
@@ -260,13 +358,13 @@ fastgl_status fastgl_match(const int64_t *prev_gid, int64_t n_prev, const int64_
     if (st != FASTGL_OK) return st;
     MatchArgs a = {};
     a.prev_gid = prev_gid; a.new_gid = new_gid; a.n_prev = n_prev; a.n_new = n_new;
-    a.table = (Slot *)((char *)workspace + L.table);
-    a.cap = table_slots(n_prev);
+    const int64_t cap = table_slots(n_prev);
+    a.table = PositionTable{(int32_t *)((char *)workspace + L.table), (uint32_t)cap, position_bits(n_prev)};
     a.block_cnt = (int32_t *)((char *)workspace + L.block_cnt);
     a.nblocks = (int)ceil_div(n_new, kScanBlock);
     a.src_row = src_row; a.load_pos = load_pos; a.load_gid = load_gid; a.result = result;
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_table_fill, grid_for(a.cap, 256), dim3(256), 0, s, a.table, a.cap, result, 2);
+    hipLaunchKernelGGL(k_match_fill, grid_for(cap, 256 * kFillVec), dim3(256), 0, s, a);
     FASTGL_LAUNCH_CHECK("fastgl_match (fill)");
     if (n_prev > 0) {
         hipLaunchKernelGGL(k_match_insert_prev, grid_for(n_prev, 256), dim3(256), 0, s, a);
@@ -275,9 +373,13 @@ fastgl_status fastgl_match(const int64_t *prev_gid, int64_t n_prev, const int64_
     if (n_new > 0) {
         hipLaunchKernelGGL(k_match_probe, dim3((unsigned)a.nblocks), dim3(kScanBlock), 0, s, a);
         FASTGL_LAUNCH_CHECK("fastgl_match (probe)");
-        hipLaunchKernelGGL(k_match_scan, dim3(1), dim3(kScanBlock), 0, s, a);
-        FASTGL_LAUNCH_CHECK("fastgl_match (scan)");
-        hipLaunchKernelGGL(k_match_rank, dim3((unsigned)a.nblocks), dim3(kScanBlock), 0, s, a);
+        if (a.nblocks <= kSumBlocks) {
+            hipLaunchKernelGGL(k_match_rank<true>, dim3((unsigned)a.nblocks), dim3(kScanBlock), 0, s, a);
+        } else {
+            hipLaunchKernelGGL(k_match_scan, dim3(1), dim3(kScanBlock), 0, s, a);
+            FASTGL_LAUNCH_CHECK("fastgl_match (scan)");
+            hipLaunchKernelGGL(k_match_rank<false>, dim3((unsigned)a.nblocks), dim3(kScanBlock), 0, s, a);
+        }
         FASTGL_LAUNCH_CHECK("fastgl_match (rank)");
     }
     return FASTGL_OK;
@@ -379,23 +481,38 @@ fastgl_status fastgl_overlap_counts(const int64_t *gid, const int64_t *offsets_h
     OverlapArgs a = {};
     a.gid = gid; a.n = n; a.total = total;
     for (int b = 0; b <= n; ++b) a.offsets[b] = offsets_host[b];
-    a.table = (Slot *)((char *)workspace + L.table);
-    const int64_t cap = table_slots(total);
-    a.cap = cap;
-    a.slot_of = (int32_t *)((char *)workspace + L.slot_of);
     a.counts = (unsigned long long *)counts;
     a.violations = violations;
+    a.cap = table_slots(total);
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_table_fill, grid_for(cap, 256), dim3(256), 0, s, a.table, cap, violations, 1);
-    FASTGL_LAUNCH_CHECK("fastgl_overlap_counts (fill)");
-    if (n == 0) return FASTGL_OK;
-    hipLaunchKernelGGL(k_zero_u64, grid_for((int64_t)n * n, 256), dim3(256), 0, s, a.counts, (int64_t)n * n);
-    FASTGL_LAUNCH_CHECK("fastgl_overlap_counts (zero)");
-    if (longest == 0) return FASTGL_OK;
     const dim3 g((unsigned)ceil_div(longest, 256), (unsigned)n);
-    hipLaunchKernelGGL(k_overlap_insert, g, dim3(256), 0, s, a);
+    char *ws = (char *)workspace;
+    if (n > kMarkBatches) {
+        a.masks = (MaskSlot *)(ws + L.table);
+        a.slot_of = (int32_t *)(ws + L.slot_of);
+        hipLaunchKernelGGL(k_masks_fill, grid_for(a.cap > n * n ? a.cap : n * n, 256), dim3(256), 0, s, a);
+        FASTGL_LAUNCH_CHECK("fastgl_overlap_counts (fill)");
+        if (longest == 0) return FASTGL_OK;
+        hipLaunchKernelGGL(k_overlap_insert, g, dim3(256), 0, s, a);
+        FASTGL_LAUNCH_CHECK("fastgl_overlap_counts (insert)");
+        hipLaunchKernelGGL(k_overlap_count, g, dim3(256), 0, s, a);
+        FASTGL_LAUNCH_CHECK("fastgl_overlap_counts (count)");
+        return FASTGL_OK;
+    }
+    // the slots' positions, then their marks: at most 4 + 8 of the 16 bytes a slot has room for
+    a.table = PositionTable{(int32_t *)(ws + L.table), (uint32_t)a.cap, position_bits(total)};
+    a.marks = (unsigned char *)(ws + L.table + align_up((size_t)a.cap * 4, 256));
+    const bool four = n <= 4;
+    const dim3 gf = grid_for(a.cap, 256 * kFillVec);
+    if (four) hipLaunchKernelGGL(k_marks_fill<uint32_t>, gf, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_marks_fill<uint64_t>, gf, dim3(256), 0, s, a);
+    FASTGL_LAUNCH_CHECK("fastgl_overlap_counts (fill)");
+    if (longest == 0) return FASTGL_OK;
+    if (four) hipLaunchKernelGGL(k_marks_insert<uint32_t>, g, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_marks_insert<uint64_t>, g, dim3(256), 0, s, a);
     FASTGL_LAUNCH_CHECK("fastgl_overlap_counts (insert)");
-    hipLaunchKernelGGL(k_overlap_count, g, dim3(256), 0, s, a);
+    if (four) hipLaunchKernelGGL(k_marks_count<uint32_t>, dim3(kCountBlocks), dim3(kScanBlock), 0, s, a);
+    else hipLaunchKernelGGL(k_marks_count<uint64_t>, dim3(kCountBlocks), dim3(kScanBlock), 0, s, a);
     FASTGL_LAUNCH_CHECK("fastgl_overlap_counts (count)");
     return FASTGL_OK;
 }
