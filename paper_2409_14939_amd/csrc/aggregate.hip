@@ -77,7 +77,7 @@ __device__ __forceinline__ void pull_chunks(const PullParams &P, const GroupId &
         const int end = beg + kLongChunk < rend ? beg + kLongChunk : rend;
         const bool active = lane_off < P.row_bytes;
         const RowStore<DT, VB> unused = {nullptr, 0, 0, false};     // a chunk's sum goes to the partial-sum buffer
-        walk_run<DT, VB, HASW, true, U>(P, chunk, 0, 1, beg, end, sub, gbase, lane_off, active, unused);
+        walk_run<DT, VB, HASW, true, U>(P, chunk, 0, 1, beg, end, 0, sub, gbase, lane_off, active, unused);
     }
 }
 
@@ -101,6 +101,7 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
     const int64_t rbeg = P.split[s0], rend = P.split[s1];
     const unsigned long long gmask = P.G == kWave ? ~0ull : ((1ull << P.G) - 1ull);
     const RowStore<DT, VB> sink = {P.out, P.row_bytes, lane_off, active};
+    using acc_t = typename Slice<DT, VB>::acc_t;
     for (int64_t r0 = rbeg; r0 < rend; r0 += P.G) {
         const int nrows = rend - r0 < P.G ? (int)(rend - r0) : P.G;
         int pb = 0, pe = 0;
@@ -108,6 +109,7 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
             pb = P.rowptr[r0 + sub];
             pe = P.rowptr[r0 + sub + 1];
         }
+        const acc_t scale = row_scale<acc_t>(P.row_mode, pe - pb);
         unsigned long long lm = (__ballot(sub < nrows && pe - pb > P.long_thr) >> gbase) & gmask;
         int i = 0;
         while (i < nrows) {
@@ -117,7 +119,8 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
             }
             const unsigned long long rest = lm >> i;
             const int j = rest ? i + (__ffsll((long long)rest) - 1) : nrows;
-            walk_run<DT, VB, HASW, false, U>(P, r0, i, j, pb, pe, sub, gbase, lane_off, active, sink);
+            const int ebeg = __shfl(pb, gbase + i, kWave);
+            walk_run<DT, VB, HASW, false, U>(P, r0, i, j, ebeg, pe, scale, sub, gbase, lane_off, active, sink);
             i = j;
         }
     }

@@ -104,7 +104,8 @@ __global__ __launch_bounds__(kBlock) void k_layer_rows(const LayerParams L)
         }
         const bool active = 4 * lane < K;
         const RowToLds sink = {my_rows, L.H, row0, K, lane, active};
-        walk_run<FASTGL_F32, 16, HASW, false, kFusedUnroll>(P, row0, 0, nrows, pb, pe, lane, 0, (int64_t)lane * 16, active, sink);
+        walk_run<FASTGL_F32, 16, HASW, false, kFusedUnroll>(P, row0, 0, nrows, __shfl(pb, 0, kWave), pe,
+                                                            row_scale<double>(P.row_mode, pe - pb), lane, 0, (int64_t)lane * 16, active, sink);
     }
     __syncthreads();      // W is complete; every wavefront's rows are in LDS
 

@@ -166,19 +166,22 @@ struct RowStore {
 // ONE flat edge list, so that U row gathers are in flight whatever the row
 // lengths are (sampled blocks have rows of 1-15 edges, transposed ones of 0-3),
 // and closes a row (hand its sum and scale factor to the sink, clear the sum)
-// whenever the edge index passes the row's end.  pb / pe: lane i of the group holds
-// rowptr of its i-th row.  Column ids are fetched two chunks ahead and weights one
+// whenever the edge index passes the row's end.  ebeg: first edge of row ia; pe / scale: lane i of the group
+// holds the end and the scale factor of the group's i-th row.  The factors (a division and a square root in
+// fp64, some fifty instructions) are made by all lanes at once: made where a row is closed, they were issued
+// once per row of every group.  Column ids are fetched two chunks ahead and weights one
 // chunk ahead of use.
 // PARTIAL: the "row" is a chunk of a long row; its unscaled sum goes to slot r0 of
 // the partial-sum buffer and the sink is not called.
 template <int DT, int VB, bool HASW, bool PARTIAL, int U, class Sink>
-__device__ __forceinline__ void walk_run(const PullParams &P, int64_t r0, int ia, int ib, int pb, int pe,
-                                         int sub, int gbase, int64_t lane_off, bool active, const Sink &sink)
+__device__ __forceinline__ void walk_run(const PullParams &P, int64_t r0, int ia, int ib, int ebeg, int pe,
+                                         typename Slice<DT, VB>::acc_t scale, int sub, int gbase, int64_t lane_off,
+                                         bool active, const Sink &sink)
 {
     using S = Slice<DT, VB>;
     using acc_t = typename S::acc_t;
     const int G = P.G;
-    const int ebeg = __shfl(pb, gbase + ia, kWave), eend = __shfl(pe, gbase + ib - 1, kWave);
+    const int eend = __shfl(pe, gbase + ib - 1, kWave);
     int row = ia;
     int rend = __shfl(pe, gbase + row, kWave);
     acc_t acc[S::NE];
@@ -193,8 +196,7 @@ __device__ __forceinline__ void walk_run(const PullParams &P, int64_t r0, int ia
                 for (int i = 0; i < S::NE; ++i) dst[i] = acc[i];
             }
         } else {
-            const int len = rend - __shfl(pb, gbase + row, kWave);
-            sink(r0 + row, acc, row_scale<acc_t>(P.row_mode, len));
+            sink(r0 + row, acc, shfl_t<acc_t>(scale, gbase + row));
         }
 #pragma unroll
         for (int i = 0; i < S::NE; ++i) acc[i] = (acc_t)0;
