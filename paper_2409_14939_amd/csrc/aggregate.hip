@@ -42,12 +42,15 @@ struct GroupId {
     int64_t count;    // launched groups per tile (chunk stride)
 };
 
+template <bool WAVE>
 __device__ __forceinline__ GroupId map_group(const PullParams &P)
 {
-    const int gpb = kBlock / P.G;
+    const int gpb = kBlock / (WAVE ? kWave : P.G);
     const int64_t x = blockIdx.x % kXcds, q = blockIdx.x / kXcds;
     const int64_t lb = ((q / P.xcd_run) * kXcds + x) * P.xcd_run + q % P.xcd_run;
-    const int64_t vg = lb * gpb + threadIdx.x / P.G;
+    // a whole wavefront's group is a scalar
+    const int in_block = threadIdx.x / (WAVE ? kWave : P.G);
+    const int64_t vg = lb * gpb + (WAVE ? __builtin_amdgcn_readfirstlane(in_block) : in_block);
     const int64_t launched = P.num_blocks * gpb;
     GroupId r;
     r.tile = (int)(vg % P.ntiles);
@@ -59,12 +62,12 @@ __device__ __forceinline__ GroupId map_group(const PullParams &P)
 // Chunks of long rows.  The number of chunks lives in device memory, so the host
 // never needs to know the degrees; the groups of a column tile stride over the
 // chunks and write fp64 / fp32 partial sums of their tile to the workspace.
-template <int DT, int VB, bool HASW, int U>
+template <int DT, int VB, int W, int U, bool WAVE>
 __device__ __forceinline__ void pull_chunks(const PullParams &P, const GroupId &id, int sub, int gbase)
 {
     const int n_long = *P.n_long;
     const int64_t total = *P.n_chunks;
-    const int64_t lane_off = ((int64_t)id.tile * P.G + sub) * VB;
+    const int64_t lane_off = ((int64_t)id.tile * (WAVE ? kWave : P.G) + sub) * VB;
     for (int64_t chunk = id.g; chunk < total; chunk += id.count) {
         int lo = 0, hi = n_long;   // chunk_ptr[lo] <= chunk < chunk_ptr[hi]
         while (hi - lo > 1) {
@@ -77,7 +80,8 @@ __device__ __forceinline__ void pull_chunks(const PullParams &P, const GroupId &
         const int end = beg + kLongChunk < rend ? beg + kLongChunk : rend;
         const bool active = lane_off < P.row_bytes;
         const RowStore<DT, VB> unused = {nullptr, 0, 0, false};     // a chunk's sum goes to the partial-sum buffer
-        walk_run<DT, VB, HASW, true, U>(P, chunk, 0, 1, beg, end, 0, sub, gbase, lane_off, active, unused);
+        if constexpr (WAVE) walk_wave<DT, VB, W, true, U>(P, chunk, 0, 1, beg, end, 0, sub, lane_off, active, unused);
+        else walk_run<DT, VB, W, true, U>(P, chunk, 0, 1, beg, end, 0, sub, gbase, lane_off, active, unused);
     }
 }
 
@@ -86,24 +90,25 @@ __device__ __forceinline__ void pull_chunks(const PullParams &P, const GroupId &
 // of a few fine row sets, which the plan cut so that every set carries the same
 // work (edges + rows), whatever the degree distribution is.  Rows that are long
 // are skipped here; k_reduce_chunks finishes them.
-template <int DT, int VB, bool HASW, int U>
+template <int DT, int VB, int W, int U, bool WAVE>
 __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int sub = tid & (P.G - 1), gbase = lane & ~(P.G - 1);
-    const GroupId id = map_group(P);
-    if (P.long_rows) pull_chunks<DT, VB, HASW, U>(P, id, sub, gbase);
+    const int G = WAVE ? kWave : P.G;
+    const int sub = tid & (G - 1), gbase = lane & ~(G - 1);
+    const GroupId id = map_group<WAVE>(P);
+    if (P.long_rows) pull_chunks<DT, VB, W, U, WAVE>(P, id, sub, gbase);
     if (id.g >= P.ngroups) return;
-    const int64_t lane_off = ((int64_t)id.tile * P.G + sub) * VB;
+    const int64_t lane_off = ((int64_t)id.tile * G + sub) * VB;
     const bool active = lane_off < P.row_bytes;
     const int64_t s0 = id.g * P.sets_per_group;
     const int64_t s1 = s0 + P.sets_per_group < P.nsets ? s0 + P.sets_per_group : P.nsets;
     const int64_t rbeg = P.split[s0], rend = P.split[s1];
-    const unsigned long long gmask = P.G == kWave ? ~0ull : ((1ull << P.G) - 1ull);
+    const unsigned long long gmask = G == kWave ? ~0ull : ((1ull << G) - 1ull);
     const RowStore<DT, VB> sink = {P.out, P.row_bytes, lane_off, active};
     using acc_t = typename Slice<DT, VB>::acc_t;
-    for (int64_t r0 = rbeg; r0 < rend; r0 += P.G) {
-        const int nrows = rend - r0 < P.G ? (int)(rend - r0) : P.G;
+    for (int64_t r0 = rbeg; r0 < rend; r0 += G) {
+        const int nrows = rend - r0 < G ? (int)(rend - r0) : G;
         int pb = 0, pe = 0;
         if (sub < nrows) {
             pb = P.rowptr[r0 + sub];
@@ -119,8 +124,12 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
             }
             const unsigned long long rest = lm >> i;
             const int j = rest ? i + (__ffsll((long long)rest) - 1) : nrows;
-            const int ebeg = __shfl(pb, gbase + i, kWave);
-            walk_run<DT, VB, HASW, false, U>(P, r0, i, j, ebeg, pe, scale, sub, gbase, lane_off, active, sink);
+            if constexpr (WAVE) {
+                walk_wave<DT, VB, W, false, U>(P, r0, i, j, lane_value(pb, i), pe, scale, sub, lane_off, active, sink);
+            } else {
+                const int ebeg = __shfl(pb, gbase + i, kWave);
+                walk_run<DT, VB, W, false, U>(P, r0, i, j, ebeg, pe, scale, sub, gbase, lane_off, active, sink);
+            }
             i = j;
         }
     }
@@ -206,16 +215,22 @@ static void group_shape(int64_t row_bytes, int vb, int *G, int *ntiles)
     *ntiles = (int)ceil_div(slices, g);
 }
 
-template <int DT, int VB>
-static fastgl_status launch_typed(const PullParams &P, bool hasw, bool with_long, int64_t nblocks, hipStream_t s)
+template <int DT, int VB, int W>
+static void launch_rows(const PullParams &P, hipStream_t s)
 {
-    if (nblocks > 0) {
-        dim3 grid((unsigned)P.num_blocks);
-        const bool narrow = P.G <= 16;
-        if (hasw && narrow) hipLaunchKernelGGL((k_pull_rows<DT, VB, true, kUnrollNarrow>), grid, dim3(kBlock), 0, s, P);
-        else if (hasw) hipLaunchKernelGGL((k_pull_rows<DT, VB, true, kUnroll>), grid, dim3(kBlock), 0, s, P);
-        else if (narrow) hipLaunchKernelGGL((k_pull_rows<DT, VB, false, kUnrollNarrow>), grid, dim3(kBlock), 0, s, P);
-        else hipLaunchKernelGGL((k_pull_rows<DT, VB, false, kUnroll>), grid, dim3(kBlock), 0, s, P);
+    const dim3 grid((unsigned)P.num_blocks);
+    if (P.G == kWave) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollWave, true>), grid, dim3(kBlock), 0, s, P);
+    else if (P.G > 16) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnroll, false>), grid, dim3(kBlock), 0, s, P);
+    else hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollNarrow, false>), grid, dim3(kBlock), 0, s, P);
+}
+
+template <int DT, int VB>
+static fastgl_status launch_typed(const PullParams &P, bool with_long, hipStream_t s)
+{
+    if (P.num_blocks > 0) {
+        if (P.edge_w && P.col_scale) launch_rows<DT, VB, kTwoWeights>(P, s);
+        else if (P.edge_w || P.col_scale) launch_rows<DT, VB, kOneWeight>(P, s);
+        else launch_rows<DT, VB, kNoWeight>(P, s);
         FASTGL_LAUNCH_CHECK("k_pull_rows");
     }
     if (with_long) {
@@ -239,6 +254,11 @@ fastgl_status launch_pull(const PullDesc &d, hipStream_t s)
     const int vb = pick_slice_bytes(P.row_bytes, d.in, d.out, elem);
     int G, ntiles;
     group_shape(P.row_bytes, vb, &G, &ntiles);
+    // walk_run counts slices in 32 bits; beyond that (more than 2^27 rows of 32 slices) a whole wavefront takes a row
+    if (d.num_cols * (P.row_bytes / vb) > (int64_t)UINT32_MAX) {
+        G = kWave;
+        ntiles = (int)ceil_div(P.row_bytes / vb, (int64_t)G);
+    }
     P.G = G; P.ntiles = ntiles;
     P.num_rows = d.num_rows;
     P.split = d.split;
@@ -256,13 +276,11 @@ fastgl_status launch_pull(const PullDesc &d, hipStream_t s)
     const int gpb = kBlock / G;
     P.xcd_run = kXcdRun;
     P.num_blocks = ceil_div(ceil_div(P.ngroups * ntiles, gpb), (int64_t)kXcds * P.xcd_run) * P.xcd_run * kXcds;
-    const int64_t nblocks = P.num_blocks;
     if (P.num_blocks > 0x7FFFFFFFLL) {
-        set_error("block too large for one launch (%lld workgroups)", (long long)nblocks);
+        set_error("block too large for one launch (%lld workgroups)", (long long)P.num_blocks);
         return FASTGL_ERR_UNSUPPORTED;
     }
-    const bool hasw = d.edge_w != nullptr || d.col_scale != nullptr;
-#define FASTGL_CASE(DT, VB) return launch_typed<DT, VB>(P, hasw, with_long, nblocks, s)
+#define FASTGL_CASE(DT, VB) return launch_typed<DT, VB>(P, with_long, s)
     if (d.dtype == FASTGL_F32) {
         switch (vb) {
             case 16: FASTGL_CASE(FASTGL_F32, 16);

@@ -62,7 +62,7 @@ struct RowToLds {
     }
 };
 
-template <bool HASW>
+template <int WEIGHTS>
 __global__ __launch_bounds__(kBlock) void k_layer_rows(const LayerParams L)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kBlock) void k_layer_rows(const LayerParams L)
     const int K = L.K, N = L.N;
     float *w_lds = lds;                                   // [K][kFusedCols]
     float *h_lds = lds + (size_t)K * kFusedCols;          // [kRowsPerBlock][K]
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 
     // 1. W -> LDS, columns beyond N read as zero.  W is walked as the contiguous array it is, 16
     //    independent loads per lane at a time (a load that waits for the previous one's LDS write
@@ -104,8 +104,9 @@ __global__ __launch_bounds__(kBlock) void k_layer_rows(const LayerParams L)
         }
         const bool active = 4 * lane < K;
         const RowToLds sink = {my_rows, L.H, row0, K, lane, active};
-        walk_run<FASTGL_F32, 16, HASW, false, kFusedUnroll>(P, row0, 0, nrows, __shfl(pb, 0, kWave), pe,
-                                                            row_scale<double>(P.row_mode, pe - pb), lane, 0, (int64_t)lane * 16, active, sink);
+        walk_wave<FASTGL_F32, 16, WEIGHTS, false, kFusedUnroll>(P, row0, 0, nrows, lane_value(pb, 0), pe,
+                                                                row_scale<double>(P.row_mode, pe - pb), lane,
+                                                                (int64_t)lane * 16, active, sink);
     }
     __syncthreads();      // W is complete; every wavefront's rows are in LDS
 
@@ -149,17 +150,25 @@ bool fuses(int64_t K, int64_t N, fastgl_dtype dtype, const void *X, const void *
 
 // The fused kernel's LDS (W and 16 rows of H: up to 80 KB) is beyond the default limit of a launch;
 // the limit of each variant is raised once, to what the largest fused shape needs.
-template <bool HASW>
+template <int WEIGHTS>
 fastgl_status raise_lds_limit()
 {
     static bool done = false;       // benign if two threads both do it
     if (!done) {
         const int most = (kMaxFusedK * kFusedCols + kRowsPerBlock * kMaxFusedK) * (int)sizeof(float);
-        FASTGL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_layer_rows<HASW>),
+        FASTGL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_layer_rows<WEIGHTS>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, most));
         done = true;
     }
     return FASTGL_OK;
+}
+
+template <int WEIGHTS>
+fastgl_status launch_layer(const LayerParams &L, unsigned blocks, size_t lds_bytes, hipStream_t s)
+{
+    const fastgl_status st = raise_lds_limit<WEIGHTS>();
+    if (st == FASTGL_OK) hipLaunchKernelGGL(k_layer_rows<WEIGHTS>, dim3(blocks), dim3(kBlock), lds_bytes, s, L);
+    return st;
 }
 
 }  // namespace
@@ -246,12 +255,11 @@ fastgl_status fastgl_layer_fwd(const int32_t *indptr, const int32_t *indices, co
     L.rows = num_dst; L.K = (int32_t)K; L.N = (int32_t)N; L.relu = relu != 0;
     const size_t lds_bytes = ((size_t)K * kFusedCols + (size_t)kRowsPerBlock * K) * sizeof(float);
     const unsigned blocks = (unsigned)ceil_div(num_dst, kRowsPerBlock);
-    const bool hasw = d.edge_w != nullptr || d.col_scale != nullptr;
     hipStream_t s = (hipStream_t)stream;
-    st = hasw ? raise_lds_limit<true>() : raise_lds_limit<false>();
+    if (d.edge_w && d.col_scale) st = launch_layer<kTwoWeights>(L, blocks, lds_bytes, s);
+    else if (d.edge_w || d.col_scale) st = launch_layer<kOneWeight>(L, blocks, lds_bytes, s);
+    else st = launch_layer<kNoWeight>(L, blocks, lds_bytes, s);
     if (st != FASTGL_OK) return st;
-    if (hasw) hipLaunchKernelGGL(k_layer_rows<true>, dim3(blocks), dim3(kBlock), lds_bytes, s, L);
-    else hipLaunchKernelGGL(k_layer_rows<false>, dim3(blocks), dim3(kBlock), lds_bytes, s, L);
     FASTGL_LAUNCH_CHECK("fastgl_layer_fwd");
     return FASTGL_OK;
 }

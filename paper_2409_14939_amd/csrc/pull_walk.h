@@ -10,6 +10,7 @@ namespace fastgl {
 
 constexpr int kUnroll = 6;        // row gathers in flight per lane (wide groups)
 constexpr int kUnrollNarrow = 4;  // groups of <= 16 lanes fetch <= 16 column ids at a time: 4 divides that
+constexpr int kUnrollWave = 8;    // groups of a whole wavefront: divides the 64 column ids of a chunk
 
 template <int DT> struct AccT { using type = double; };
 template <> struct AccT<FASTGL_BF16> { using type = float; };
@@ -129,20 +130,37 @@ template <typename T> __device__ __forceinline__ T shfl_t(T v, int src);
 template <> __device__ __forceinline__ float shfl_t<float>(float v, int src) { return __shfl(v, src, kWave); }
 template <> __device__ __forceinline__ double shfl_t<double>(double v, int src) { return __shfl(v, src, kWave); }
 
+// The value of one lane (the same for all: a scalar).
+__device__ __forceinline__ int lane_value(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ float lane_value(float v, int lane)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Weights of the edges.  kOneWeight: edge_w or col_scale, a float; kTwoWeights: their product, in the type of
+// the sums (fp64 holds it exactly, so one float fewer is handed round for a single weight).
+enum { kNoWeight = 0, kOneWeight = 1, kTwoWeights = 2 };
+template <int W, typename acc_t> struct WeightT { using type = float; };
+template <typename acc_t> struct WeightT<kTwoWeights, acc_t> { using type = acc_t; };
+
 // Column ids and weights of up to G consecutive edges, one per lane of a group.
-template <bool HASW, typename acc_t>
-__device__ __forceinline__ int load_cols(const PullParams &P, int k, int kend)
+__device__ __forceinline__ int load_col(const PullParams &P, int k, int kend)
 {
     return k < kend ? P.col[k] : 0;
 }
 
-template <bool HASW, typename acc_t>
-__device__ __forceinline__ acc_t load_weight(const PullParams &P, int k, int kend, int c)
+template <int W, typename acc_t>
+__device__ __forceinline__ typename WeightT<W, acc_t>::type load_weight(const PullParams &P, int k, int kend, int c)
 {
-    acc_t w = (acc_t)1;
-    if (HASW && k < kend) {
-        if (P.edge_w) w = (acc_t)P.edge_w[P.eid ? P.eid[k] : k];
-        if (P.col_scale) w *= (acc_t)P.col_scale[c];
+    typename WeightT<W, acc_t>::type w = 1;
+    if (W != kNoWeight && k < kend) {
+        if (P.edge_w) w = P.edge_w[P.eid ? P.eid[k] : k];
+        if (W == kTwoWeights) w *= P.col_scale[c];
+        else if (P.col_scale) w = P.col_scale[c];
     }
     return w;
 }
@@ -162,6 +180,18 @@ struct RowStore {
     }
 };
 
+// The unscaled sum of a chunk of a long row.
+template <int DT, int VB>
+__device__ __forceinline__ void put_partial(const PullParams &P, int64_t chunk, int64_t lane_off, bool active,
+                                            const typename Slice<DT, VB>::acc_t (&acc)[Slice<DT, VB>::NE])
+{
+    using S = Slice<DT, VB>;
+    if (!active) return;
+    typename S::acc_t *dst = reinterpret_cast<typename S::acc_t *>(P.partials) + chunk * P.feat + lane_off / VB * S::NE;
+#pragma unroll
+    for (int i = 0; i < S::NE; ++i) dst[i] = acc[i];
+}
+
 // A group walks the edges of a run of consecutive rows [ia, ib) of its row set as
 // ONE flat edge list, so that U row gathers are in flight whatever the row
 // lengths are (sampled blocks have rows of 1-15 edges, transposed ones of 0-3),
@@ -173,15 +203,21 @@ struct RowStore {
 // chunk ahead of use.
 // PARTIAL: the "row" is a chunk of a long row; its unscaled sum goes to slot r0 of
 // the partial-sum buffer and the sink is not called.
-template <int DT, int VB, bool HASW, bool PARTIAL, int U, class Sink>
+//
+// Instructions per edge count next to the gathers.  Column ids are turned into positions in units of VB bytes
+// by the lane that loads them (32 bits: the host sees to that), and lanes beyond the row's end gather its
+// first slice instead of being masked out.
+template <int DT, int VB, int W, bool PARTIAL, int U, class Sink>
 __device__ __forceinline__ void walk_run(const PullParams &P, int64_t r0, int ia, int ib, int ebeg, int pe,
                                          typename Slice<DT, VB>::acc_t scale, int sub, int gbase, int64_t lane_off,
                                          bool active, const Sink &sink)
 {
     using S = Slice<DT, VB>;
     using acc_t = typename S::acc_t;
+    using w_t = typename WeightT<W, acc_t>::type;
     const int G = P.G;
     const int eend = __shfl(pe, gbase + ib - 1, kWave);
+    const uint32_t row_slices = (uint32_t)(P.row_bytes / VB), my_slice = active ? (uint32_t)(lane_off / VB) : 0u;
     int row = ia;
     int rend = __shfl(pe, gbase + row, kWave);
     acc_t acc[S::NE];
@@ -189,48 +225,102 @@ __device__ __forceinline__ void walk_run(const PullParams &P, int64_t r0, int ia
     for (int i = 0; i < S::NE; ++i) acc[i] = (acc_t)0;
 
     auto close_row = [&]() {
-        if constexpr (PARTIAL) {
-            if (active) {
-                acc_t *dst = reinterpret_cast<acc_t *>(P.partials) + r0 * P.feat + lane_off / VB * S::NE;
-#pragma unroll
-                for (int i = 0; i < S::NE; ++i) dst[i] = acc[i];
-            }
-        } else {
-            sink(r0 + row, acc, shfl_t<acc_t>(scale, gbase + row));
-        }
+        if constexpr (PARTIAL) put_partial<DT, VB>(P, r0, lane_off, active, acc);
+        else sink(r0 + row, acc, shfl_t<acc_t>(scale, gbase + row));
 #pragma unroll
         for (int i = 0; i < S::NE; ++i) acc[i] = (acc_t)0;
         ++row;
         rend = __shfl(pe, gbase + (row < ib ? row : ib - 1), kWave);
     };
 
-    int cur_c = load_cols<HASW, acc_t>(P, ebeg + sub, eend);
-    int nxt_c = load_cols<HASW, acc_t>(P, ebeg + G + sub, eend);
-    acc_t cur_w = load_weight<HASW, acc_t>(P, ebeg + sub, eend, cur_c);
+    const int c0 = load_col(P, ebeg + sub, eend);
+    int nxt_c = load_col(P, ebeg + G + sub, eend);
+    w_t cur_w = load_weight<W, acc_t>(P, ebeg + sub, eend, c0);
+    uint32_t cur_at = (uint32_t)c0 * row_slices;
     for (int k0 = ebeg; k0 < eend; k0 += G) {
         const int n = eend - k0 < G ? eend - k0 : G;
-        const int nn_c = load_cols<HASW, acc_t>(P, k0 + 2 * G + sub, eend);
-        const acc_t nxt_w = load_weight<HASW, acc_t>(P, k0 + G + sub, eend, nxt_c);
+        const int nn_c = load_col(P, k0 + 2 * G + sub, eend);
+        const w_t nxt_w = load_weight<W, acc_t>(P, k0 + G + sub, eend, nxt_c);
         for (int j0 = 0; j0 < n; j0 += U) {
             uint32_t raw[U][S::NW];
 #pragma unroll
             for (int t = 0; t < U; ++t) {
                 const int j = j0 + t;
-                const int c = __shfl(cur_c, gbase + (j & (G - 1)), kWave);
-                if (j < n && active) S::load(P.in + (int64_t)c * P.row_bytes + lane_off, raw[t]);
+                const uint32_t at = (uint32_t)__shfl((int)cur_at, gbase + (j & (G - 1)), kWave) + my_slice;
+                if (j < n) S::load(P.in + (uint64_t)at * VB, raw[t]);
             }
 #pragma unroll
             for (int t = 0; t < U; ++t) {
                 const int j = j0 + t;
                 acc_t w = (acc_t)1;
-                if (HASW) w = shfl_t<acc_t>(cur_w, gbase + (j & (G - 1)));
+                if (W != kNoWeight) w = (acc_t)shfl_t<w_t>(cur_w, gbase + (j & (G - 1)));
                 if (j < n) {
                     const int e = k0 + j;
                     while (e >= rend) close_row();
-                    if (active) S::template fma<HASW>(acc, raw[t], w);
+                    S::template fma<W != kNoWeight>(acc, raw[t], w);
                 }
             }
         }
+        cur_at = (uint32_t)nxt_c * row_slices;
+        cur_w = nxt_w;
+        nxt_c = nn_c;
+    }
+    while (row < ib) close_row();
+}
+
+// The same for a group that is a whole wavefront (rows of more than 32 slices): what the lanes of a group
+// share - the edge, its column, its weight, the row's end - is a scalar, so that an edge costs a few scalar
+// instructions, the load, and the conversions and multiply-adds of the slice.  r0, ia, ib and ebeg must be
+// scalars already (readfirstlane).
+template <int DT, int VB, int W, bool PARTIAL, int U, class Sink>
+__device__ __forceinline__ void walk_wave(const PullParams &P, int64_t r0, int ia, int ib, int ebeg, int pe,
+                                          typename Slice<DT, VB>::acc_t scale, int lane, int64_t lane_off, bool active,
+                                          const Sink &sink)
+{
+    using S = Slice<DT, VB>;
+    using acc_t = typename S::acc_t;
+    using w_t = typename WeightT<W, acc_t>::type;
+    const int eend = lane_value(pe, ib - 1);
+    const uint32_t my_off = active ? (uint32_t)lane_off : 0u;
+    int row = ia;
+    int rend = lane_value(pe, row);
+    acc_t acc[S::NE];
+#pragma unroll
+    for (int i = 0; i < S::NE; ++i) acc[i] = (acc_t)0;
+
+    auto close_row = [&]() {
+        if constexpr (PARTIAL) put_partial<DT, VB>(P, r0, lane_off, active, acc);
+        else sink(r0 + row, acc, lane_value(scale, row));
+#pragma unroll
+        for (int i = 0; i < S::NE; ++i) acc[i] = (acc_t)0;
+        ++row;
+        rend = lane_value(pe, row < ib ? row : ib - 1);
+    };
+
+    int cur_c = load_col(P, ebeg + lane, eend);
+    int nxt_c = load_col(P, ebeg + kWave + lane, eend);
+    w_t cur_w = load_weight<W, acc_t>(P, ebeg + lane, eend, cur_c);
+    for (int k0 = ebeg; k0 < eend; k0 += kWave) {
+        const int n = eend - k0 < kWave ? eend - k0 : kWave;
+        const int nn_c = load_col(P, k0 + 2 * kWave + lane, eend);
+        const w_t nxt_w = load_weight<W, acc_t>(P, k0 + kWave + lane, eend, nxt_c);
+        auto batch = [&](int j0, int m) {               // m <= U edges
+            uint32_t raw[U][S::NW];
+#pragma unroll
+            for (int t = 0; t < U; ++t)
+                if (t < m) S::load(P.in + (int64_t)lane_value(cur_c, j0 + t) * P.row_bytes + my_off, raw[t]);
+#pragma unroll
+            for (int t = 0; t < U; ++t)
+                if (t < m) {
+                    acc_t w = (acc_t)1;
+                    if (W != kNoWeight) w = (acc_t)lane_value(cur_w, j0 + t);
+                    while (k0 + j0 + t >= rend) close_row();
+                    S::template fma<W != kNoWeight>(acc, raw[t], w);
+                }
+        };
+        int j0 = 0;
+        for (; j0 + U <= n; j0 += U) batch(j0, U);
+        if (j0 < n) batch(j0, n - j0);
         cur_c = nxt_c;
         cur_w = nxt_w;
         nxt_c = nn_c;
