@@ -27,6 +27,7 @@
 namespace fastgl {
 
 constexpr int kXcdRun = 16;
+constexpr int kReduceBlocks = 1024;   // workgroups for the long rows, whose number the host does not know
 
 // Which (row set, column tile) a lane group works on.
 //
@@ -135,39 +136,54 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
     }
 }
 
+// Long rows: the partial sums of a row's chunks, scaled and stored.  A workgroup takes a (row, column tile); its
+// 256 / G groups sum consecutive ranges of the chunks, each in chunk order with 8 loads in flight, and the ranges
+// are added in order.  Bound by latency: a row of 25 000 edges has 200 chunks, a chain of 25 loads for one group.
+// Both directions of the all-neighbours block (65 536 and 1 M rows, up to 25 000 edges), us, one group per row -> now:
+// 32 -> 21 with 32 columns, 52 -> 43 with 256.
 template <int DT, int VB>
 __global__ __launch_bounds__(kBlock) void k_reduce_chunks(PullParams P)
 {
     using S = Slice<DT, VB>;
     using acc_t = typename S::acc_t;
-    const int tid = threadIdx.x;
-    const int sub = tid & (P.G - 1);
+    __shared__ acc_t range_sum[S::NE][kBlock];
+    const int tid = threadIdx.x, sub = tid & (P.G - 1), part = tid / P.G, parts = kBlock / P.G;
     const int64_t total = (int64_t)(*P.n_long) * P.ntiles;
-    const int64_t stride = (int64_t)gridDim.x * kBlock / P.G;
-    for (int64_t unit = ((int64_t)blockIdx.x * kBlock + tid) / P.G; unit < total; unit += stride) {
+    for (int64_t unit = blockIdx.x; unit < total; unit += gridDim.x) {
         const int li = (int)(unit / P.ntiles);
         const int tile = (int)(unit - (int64_t)li * P.ntiles);
         const int64_t lane_off = ((int64_t)tile * P.G + sub) * VB;
-        if (lane_off >= P.row_bytes) continue;
+        const bool active = lane_off < P.row_bytes;
         const int row = P.long_rows[li];
+        const int first = P.chunk_ptr[li], last = P.chunk_ptr[li + 1];
+        const int per = (last - first + parts - 1) / parts;
+        const int lo = first + part * per, hi = lo + per < last ? lo + per : last;
         acc_t acc[S::NE];
 #pragma unroll
         for (int i = 0; i < S::NE; ++i) acc[i] = (acc_t)0;
         const acc_t *src = reinterpret_cast<const acc_t *>(P.partials) + ((int64_t)tile * P.G + sub) * S::NE;
-        // partial sums are added in chunk order (fixed result); 8 are fetched at a time
-        const int c1 = P.chunk_ptr[li + 1];
-        for (int c0 = P.chunk_ptr[li]; c0 < c1; c0 += 8) {
-            acc_t part[8][S::NE];
+        if (active) {
+            for (int c0 = lo; c0 < hi; c0 += 8) {
+                acc_t load[8][S::NE];
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
+                for (int k = 0; k < 8; ++k)
 #pragma unroll
-                for (int i = 0; i < S::NE; ++i)
-                    part[k][i] = c0 + k < c1 ? src[(int64_t)(c0 + k) * P.feat + i] : (acc_t)0;
+                    for (int i = 0; i < S::NE; ++i)
+                        load[k][i] = c0 + k < hi ? src[(int64_t)(c0 + k) * P.feat + i] : (acc_t)0;
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
+                for (int k = 0; k < 8; ++k)
 #pragma unroll
-                for (int i = 0; i < S::NE; ++i) acc[i] += part[k][i];
+                    for (int i = 0; i < S::NE; ++i) acc[i] += load[k][i];
+            }
         }
+        __syncthreads();                       // the previous unit's sums have been read
+#pragma unroll
+        for (int i = 0; i < S::NE; ++i) range_sum[i][tid] = acc[i];
+        __syncthreads();
+        if (part != 0 || !active) continue;    // the barriers of the next unit are reached by all
+        for (int q = 1; q < parts && q * per < last - first; ++q)
+#pragma unroll
+            for (int i = 0; i < S::NE; ++i) acc[i] += range_sum[i][q * P.G + sub];
         const int len = P.rowptr[row + 1] - P.rowptr[row];
         S::store(P.out + (int64_t)row * P.row_bytes + lane_off, acc, row_scale<acc_t>(P.row_mode, len));
     }
@@ -234,7 +250,7 @@ static fastgl_status launch_typed(const PullParams &P, bool with_long, hipStream
         FASTGL_LAUNCH_CHECK("k_pull_rows");
     }
     if (with_long) {
-        hipLaunchKernelGGL((k_reduce_chunks<DT, VB>), dim3(512), dim3(kBlock), 0, s, P);
+        hipLaunchKernelGGL((k_reduce_chunks<DT, VB>), dim3(kReduceBlocks), dim3(kBlock), 0, s, P);
         FASTGL_LAUNCH_CHECK("k_reduce_chunks");
     }
     return FASTGL_OK;
