@@ -8,15 +8,19 @@
 // the vector ALUs, and the kernel is bound by its row gathers like the aggregation kernel is, so
 // the product is done with plain fp32 multiply-adds rather than on the matrix cores.
 //
-//   workgroup = 4 wavefronts; a wavefront owns kRowsPerWave consecutive target rows
-//   1. W (K x N, zero-padded to 64 columns) is copied to LDS once per workgroup
+//   workgroup = 4 wavefronts; a wavefront owns RPW consecutive target rows and a quarter of the K terms
+//   1. lane n loads its column of the wavefront's quarter of W (K x N) into registers, all loads in flight
+//      together, behind the row pointers'
 //   2. each wavefront walks the edges of its rows as one flat list (the aggregation kernel's
-//      walk: 64 lanes x 16 bytes cover a row of up to 256 floats, 12 row gathers in flight, fp64
+//      walk: 64 lanes x 16 bytes cover a row of up to 256 floats, 8 row gathers in flight, fp64
 //      sums), scales and rounds each finished row to fp32 exactly as the aggregation kernel does,
 //      and keeps it in LDS
-//   3. lane n of the wavefront forms y[r][n] = b[n] + sum_k H[r][k] W[k][n] for its rows, k
-//      ascending, one fp32 multiply-add per term: W[k][n] is read once for all rows of the
-//      wavefront, H[r][k..k+3] as one broadcast 16-byte read
+//   3. lane n forms the sum of its quarter's terms for ALL rows of the workgroup, k ascending, one fp32
+//      multiply-add per term (H[r][k..k+3] is one broadcast 16-byte read); the four sums go through LDS and
+//      y[r][n] = ((s0 + s1) + (s2 + s3)) + b[n]
+// Bound by latency where there are few rows: the rows' gathers and W come in together, and the chain of
+// multiply-adds is a quarter of K long.  K = 256, N = 47, us,
+// W through LDS and K terms per wavefront -> now: 16 rows of 15 edges 21.6 -> 8.5, 8 000 rows 42 -> 37.
 //
 // Every other shape takes the two kernels of the separate calls, back to back on the stream.
 #include "fastgl_update.h"
@@ -25,12 +29,13 @@
 namespace fastgl {
 namespace {
 
-constexpr int kRowsPerWave = 4;
 constexpr int kWavesPerBlock = kBlock / kWave;
-constexpr int kRowsPerBlock = kRowsPerWave * kWavesPerBlock;
 constexpr int kMaxFusedK = 256;     // 64 lanes x 4 floats
 constexpr int kFusedCols = 64;      // one lane per output column
-constexpr int kFusedUnroll = 12;    // row gathers in flight per lane: LDS limits a CU to 8 wavefronts of this kernel, registers are plentiful
+constexpr int kQuarter = kMaxFusedK / kWavesPerBlock;   // most terms of a wavefront
+// Rows of a wavefront: one while that gives at most two workgroups per compute unit, else four (every workgroup
+// reads W once).
+constexpr int64_t kFewRows = 2048;
 
 struct LayerParams {
     PullParams pull;                // rowptr, col, eid, edge_w, col_scale, in, G = 64, row_mode, row_bytes, feat
@@ -43,7 +48,7 @@ struct LayerParams {
 // A finished row: scaled and rounded to fp32 once (the value the aggregation kernel would store),
 // kept in LDS for the product and, if asked for, streamed to H.
 struct RowToLds {
-    float *lds_rows;                // this wavefront's rows, [kRowsPerWave][K]
+    float *lds_rows;                // this wavefront's rows, [rows][K]
     float *H;
     int64_t row0;                   // first row of the wavefront
     int32_t K, sub;
@@ -62,113 +67,90 @@ struct RowToLds {
     }
 };
 
-template <int WEIGHTS>
+template <int WEIGHTS, int RPW>
 __global__ __launch_bounds__(kBlock) void k_layer_rows(const LayerParams L)
 {
-    extern __shared__ __attribute__((aligned(16))) float lds[];
+    constexpr int ROWS = RPW * kWavesPerBlock;
+    __shared__ __attribute__((aligned(16))) float h_lds[ROWS * kMaxFusedK];     // [ROWS][K]
+    __shared__ float part[kWavesPerBlock][ROWS][kFusedCols];
     const PullParams &P = L.pull;
     const int K = L.K, N = L.N;
-    float *w_lds = lds;                                   // [K][kFusedCols]
-    float *h_lds = lds + (size_t)K * kFusedCols;          // [kRowsPerBlock][K]
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-
-    // 1. W -> LDS, columns beyond N read as zero.  W is walked as the contiguous array it is, 16
-    //    independent loads per lane at a time (a load that waits for the previous one's LDS write
-    //    would make this loop the longest phase of the kernel).
-    for (int i = tid; i < K * (kFusedCols - N); i += kBlock)
-        w_lds[(i / (kFusedCols - N)) * kFusedCols + N + i % (kFusedCols - N)] = 0.f;
-    const int total_w = K * N;
-    for (int base = 0; base < total_w; base += 16 * kBlock) {
-        float t[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int i = base + j * kBlock + tid;
-            t[j] = i < total_w ? L.W[i] : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int i = base + j * kBlock + tid;
-            if (i < total_w) w_lds[(i / N) * kFusedCols + i % N] = t[j];
-        }
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS + wave * RPW;
+    const int nrows = L.rows - row0 < RPW ? (int)(L.rows - row0) : RPW;         // may be <= 0
+    int pb = 0, pe = 0;
+    if (lane < nrows) {
+        pb = P.rowptr[row0 + lane];
+        pe = P.rowptr[row0 + lane + 1];
     }
+
+    // 1. this wavefront's terms of W: k_first .. + terms, K and both of them multiples of 4
+    const int per = 4 * ((K + 4 * kWavesPerBlock - 1) / (4 * kWavesPerBlock)), k_first = wave * per;
+    const int terms = K - k_first < per ? K - k_first : per;                    // may be <= 0
+    float w[kQuarter];
+    const float *w_col = L.W + (lane < N ? lane : N - 1);
+#pragma unroll
+    for (int i = 0; i < kQuarter; ++i) {
+        const int k = k_first + i;
+        w[i] = w_col[(int64_t)(k < K ? k : K - 1) * N];
+    }
+    __builtin_amdgcn_sched_barrier(0);
 
     // 2. aggregate this wavefront's rows into LDS
-    const int64_t row0 = (int64_t)blockIdx.x * kRowsPerBlock + wave * kRowsPerWave;
-    const int nrows = L.rows - row0 < kRowsPerWave ? (int)(L.rows - row0) : kRowsPerWave;   // may be <= 0
-    float *my_rows = h_lds + wave * kRowsPerWave * K;
     if (nrows > 0) {
-        int pb = 0, pe = 0;
-        if (lane < nrows) {
-            pb = P.rowptr[row0 + lane];
-            pe = P.rowptr[row0 + lane + 1];
-        }
         const bool active = 4 * lane < K;
-        const RowToLds sink = {my_rows, L.H, row0, K, lane, active};
-        walk_wave<FASTGL_F32, 16, WEIGHTS, false, kFusedUnroll>(P, row0, 0, nrows, lane_value(pb, 0), pe,
-                                                                row_scale<double>(P.row_mode, pe - pb), lane,
-                                                                (int64_t)lane * 16, active, sink);
+        const RowToLds sink = {h_lds + wave * RPW * K, L.H, row0, K, lane, active};
+        walk_wave<FASTGL_F32, 16, WEIGHTS, false, kUnrollWave>(P, row0, 0, nrows, lane_value(pb, 0), pe,
+                                                               row_scale<double>(P.row_mode, pe - pb), lane,
+                                                               (int64_t)lane * 16, active, sink);
     }
-    __syncthreads();      // W is complete; every wavefront's rows are in LDS
+    __syncthreads();
 
-    // 3. the product: lane = output column
-    if (nrows <= 0) return;
-    float acc[kRowsPerWave];
-    const float b = (L.bias && lane < N) ? L.bias[lane] : 0.f;
+    // 3. lane = output column; rows that do not exist hold whatever LDS held: computed, never stored
+    float acc[ROWS];
 #pragma unroll
-    for (int r = 0; r < kRowsPerWave; ++r) acc[r] = b;
-    for (int k = 0; k < K; k += 4) {
-        float w[4];
+    for (int r = 0; r < ROWS; ++r) acc[r] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = w_lds[(k + i) * kFusedCols + lane];
+    for (int i = 0; i < kQuarter; i += 4) {
+        if (i < terms) {                                                        // the same for the wavefront
 #pragma unroll
-        for (int r = 0; r < kRowsPerWave; ++r) {
-            // rows beyond nrows hold whatever LDS held: computed, never stored
-            const float4 h = *reinterpret_cast<const float4 *>(my_rows + r * K + k);
-            acc[r] = __builtin_fmaf(h.x, w[0], acc[r]);
-            acc[r] = __builtin_fmaf(h.y, w[1], acc[r]);
-            acc[r] = __builtin_fmaf(h.z, w[2], acc[r]);
-            acc[r] = __builtin_fmaf(h.w, w[3], acc[r]);
+            for (int r = 0; r < ROWS; ++r) {
+                const float4 h = *reinterpret_cast<const float4 *>(h_lds + r * K + k_first + i);
+                acc[r] = __builtin_fmaf(h.x, w[i], acc[r]);
+                acc[r] = __builtin_fmaf(h.y, w[i + 1], acc[r]);
+                acc[r] = __builtin_fmaf(h.z, w[i + 2], acc[r]);
+                acc[r] = __builtin_fmaf(h.w, w[i + 3], acc[r]);
+            }
         }
     }
-    if (lane < N) {
 #pragma unroll
-        for (int r = 0; r < kRowsPerWave; ++r) {
-            if (r >= nrows) break;
-            float v = acc[r];
-            if (L.relu) v = v > 0.f ? v : 0.f;
-            L.Y[(row0 + r) * N + lane] = v;
-        }
+    for (int r = 0; r < ROWS; ++r) part[wave][r][lane] = acc[r];
+    __syncthreads();
+    if (lane >= N) return;
+    const float b = L.bias ? L.bias[lane] : 0.f;
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+        if (i >= nrows) break;
+        const int r = wave * RPW + i;
+        float v = ((part[0][r][lane] + part[1][r][lane]) + (part[2][r][lane] + part[3][r][lane])) + b;
+        if (L.relu) v = v > 0.f ? v : 0.f;
+        L.Y[(row0 + i) * N + lane] = v;
     }
 }
 
-// X rows are read and H rows written 16 bytes per lane.
 bool fuses(int64_t K, int64_t N, fastgl_dtype dtype, const void *X, const void *H)
 {
     return dtype == FASTGL_F32 && K > 0 && K % 4 == 0 && K <= kMaxFusedK && N > 0 && N <= kFusedCols &&
            (((uintptr_t)X | (uintptr_t)H) & 15) == 0;
 }
 
-// The fused kernel's LDS (W and 16 rows of H: up to 80 KB) is beyond the default limit of a launch;
-// the limit of each variant is raised once, to what the largest fused shape needs.
 template <int WEIGHTS>
-fastgl_status raise_lds_limit()
+void launch_layer(const LayerParams &L, hipStream_t s)
 {
-    static bool done = false;       // benign if two threads both do it
-    if (!done) {
-        const int most = (kMaxFusedK * kFusedCols + kRowsPerBlock * kMaxFusedK) * (int)sizeof(float);
-        FASTGL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_layer_rows<WEIGHTS>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, most));
-        done = true;
-    }
-    return FASTGL_OK;
-}
-
-template <int WEIGHTS>
-fastgl_status launch_layer(const LayerParams &L, unsigned blocks, size_t lds_bytes, hipStream_t s)
-{
-    const fastgl_status st = raise_lds_limit<WEIGHTS>();
-    if (st == FASTGL_OK) hipLaunchKernelGGL(k_layer_rows<WEIGHTS>, dim3(blocks), dim3(kBlock), lds_bytes, s, L);
-    return st;
+    if (L.rows <= kFewRows)
+        hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 1>), dim3((unsigned)ceil_div(L.rows, kWavesPerBlock)), dim3(kBlock), 0, s, L);
+    else
+        hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 4>), dim3((unsigned)ceil_div(L.rows, 4 * kWavesPerBlock)), dim3(kBlock), 0, s, L);
 }
 
 }  // namespace
@@ -253,13 +235,10 @@ fastgl_status fastgl_layer_fwd(const int32_t *indptr, const int32_t *indices, co
     L.W = (const float *)W; L.bias = bias;
     L.H = (float *)H; L.Y = (float *)Y;
     L.rows = num_dst; L.K = (int32_t)K; L.N = (int32_t)N; L.relu = relu != 0;
-    const size_t lds_bytes = ((size_t)K * kFusedCols + (size_t)kRowsPerBlock * K) * sizeof(float);
-    const unsigned blocks = (unsigned)ceil_div(num_dst, kRowsPerBlock);
     hipStream_t s = (hipStream_t)stream;
-    if (d.edge_w && d.col_scale) st = launch_layer<kTwoWeights>(L, blocks, lds_bytes, s);
-    else if (d.edge_w || d.col_scale) st = launch_layer<kOneWeight>(L, blocks, lds_bytes, s);
-    else st = launch_layer<kNoWeight>(L, blocks, lds_bytes, s);
-    if (st != FASTGL_OK) return st;
+    if (d.edge_w && d.col_scale) launch_layer<kTwoWeights>(L, s);
+    else if (d.edge_w || d.col_scale) launch_layer<kOneWeight>(L, s);
+    else launch_layer<kNoWeight>(L, s);
     FASTGL_LAUNCH_CHECK("fastgl_layer_fwd");
     return FASTGL_OK;
 }

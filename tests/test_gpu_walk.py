@@ -1,0 +1,30 @@
+"""Row walks at the widths where their kind changes (32 and 33 slices: lane groups or whole wavefronts; 64 and 65: one or
+two column tiles), with no, one and two weights per edge, long rows whose chunks fill one or several ranges of the
+reduction; and the one-kernel layer around the number of rows where a wavefront takes four of them (2 048).
+Against the oracle, with the tolerances of the parity tests and of the layer's tests."""
+import numpy as np
+import pytest
+
+import blockgen as bg
+from test_gpu_layer import check_layer
+from test_gpu_parity import check_block
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode,weighted", [("sum", False), ("mean", True), ("gcn", False), ("gcn", True)])
+@pytest.mark.parametrize("feat,dtype", [(8, "f32"), (128, "f32"), (129, "f32"), (132, "f32"), (260, "f32"), (66, "f32"),
+                                        (256, "bf16"), (264, "bf16"), (130, "bf16"), (33, "bf16"), (520, "bf16")])
+def test_widths(feat, dtype, mode, weighted):
+    rng = np.random.default_rng(feat)
+    for hub in (129, 257, 128 * 9 + 1, 128 * 70):
+        blk = bg.random_block(rng, 301, 517, 5.0, empty_frac=0.2, hub_rows=2, hub_deg=hub)
+        check_block(blk, mode, dtype, feat, weighted, True, feat + hub, f"hub {hub}")
+
+
+@pytest.mark.parametrize("rows", [1, 3, 4, 5, 2047, 2048, 2049, 2065])
+@pytest.mark.parametrize("mode,K,N,weighted", [("gcn", 256, 47, False), ("gcn", 60, 64, True), ("sum", 4, 1, False)])
+def test_layer_rows(rows, mode, K, N, weighted):
+    rng = np.random.default_rng(rows + K)
+    blk = bg.random_block(rng, rows, 2 * rows + 40, 9.0, empty_frac=0.1)
+    check_layer(blk, mode, K, N, True, weighted, True, True, rows + K, "rows")
