@@ -44,27 +44,33 @@ constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kMaxSortItems = 4;                     // keys per thread and step: 1, 2 or 4
 constexpr int kMaxSortBlocks = 256;
 constexpr int kSplitThreads = 512;                   // workgroup of the split into buckets (bucketed transpose)
+constexpr int64_t kExpandEdges = 16384;              // edges of a block of the row pass that writes a row per edge
 constexpr int kMaxSplitBlocks = 512;                 // two of them per compute unit
 
 // Pass 1 over row pointers: row lengths, scale factors, per-block counts of long
 // rows / their chunks, and (optionally) the row id of every edge.  A thread
-// expands its own short rows; rows longer than a wavefront are expanded by the
-// whole wavefront, one after the other.
+// expands its own short rows; longer ones are expanded by the whole wavefront, one
+// after the other.  A block of fewer rows than threads (rows_args: rows of many edges)
+// deals them to all its wavefronts; they are mostly long then.
 __device__ __forceinline__ void rows_count(const RowsArgs &A, int b, int *lds)
 {
     int64_t beg = b * A.per, end = beg + A.per < A.n ? beg + A.per : A.n;
-    const int lane = threadIdx.x & (kWave - 1);
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    const int64_t share = (A.per + nw - 1) / nw;
+    const int rows = share < kWave ? (int)share : kWave;       // of a wavefront, per turn
+    const int most = rows < kWave ? kWave / 4 : kWave;          // edges of a row that its thread expands
     int nl = 0, nc = 0;
-    for (int64_t base = beg; base < end; base += blockDim.x) {
-        const int64_t r = base + threadIdx.x;
+    for (int64_t base = beg; base < end; base += (int64_t)nw * rows) {
+        const int64_t r = base + w * rows + lane;
+        const bool have = lane < rows && r < end;
         int e0 = 0, len = 0;
-        if (r < end) {
+        if (have) {
             e0 = A.rowptr[r];
             len = A.rowptr[r + 1] - e0;
         }
-        row_emit(A, r, r < end, e0, len, nl, nc);
+        row_emit(A, r, have, e0, len, nl, nc);
         if (A.edge_row) {
-            const bool big = len > kWave;
+            const bool big = len > most;
             if (!big)
                 for (int k = 0; k < len; ++k) A.edge_row[e0 + k] = (int32_t)r;
             unsigned long long m = __ballot(big);
@@ -889,6 +895,9 @@ static RowsArgs rows_args(const int32_t *rowptr, int64_t n, int32_t *len_out, fl
 {
     RowsArgs A;
     int64_t b = ceil_div(n, (int64_t)kSortThreads * 2);   // two rows per thread while that gives at most kMaxScanBlocks blocks
+    // Rows of many edges: at most about kExpandEdges of them per block.  65 536 rows of 100 edges were 32 blocks,
+    // the longest part of their launch (49 us, now 30; the three blocks of the headline mini-batch 31 -> 24).
+    if (edge_row && b < ceil_div(nnz, kExpandEdges)) b = ceil_div(nnz, kExpandEdges) < n ? ceil_div(nnz, kExpandEdges) : n;
     if (b < 1) b = 1;
     if (b > kMaxScanBlocks) b = kMaxScanBlocks;
     A.rowptr = rowptr; A.n = n; A.nb = (int)b;
