@@ -9,8 +9,10 @@
 // with cross-lane reads.  The destination of every edge comes from a small expansion pass.
 //
 // Softmax: a group of 8, 32 or 64 lanes (by the block's mean row length) walks one destination row
-// three times (maximum, sum of exponentials, write); rows longer than kLongRow are queued and taken by whole workgroups afterwards.  exp and
-// the sums are fp64, so the result is the correctly rounded quotient up to one unit in the last place.
+// three times (maximum, sum of exponentials, write); rows longer than kLongRow are taken by their whole workgroup
+// afterwards, one after the other.  exp and the sums are fp64, so the result is the correctly rounded quotient up to
+// one unit in the last place.  One launch: with a queue of long rows for a launch of its own (and one that clears
+// its length) a call cost three, 9.5 us more than now where no row is long.
 #include <type_traits>
 
 #include "fastgl_edge.h"
@@ -19,8 +21,7 @@
 namespace fastgl {
 namespace {
 
-constexpr int kLongRow = 1024;       // softmax rows longer than this go to the workgroup-per-row pass
-constexpr int kLongGrid = 256;       // workgroups of that pass
+constexpr int kLongRow = 1024;       // softmax rows longer than this are taken by a whole workgroup
 constexpr int kEdgeUnroll = 4;       // edges in flight per lane group in k_edge_dot (reduce4 assumes 4)
 constexpr int kEdgeSteps = 8;        // batches of that many edges per lane group
 
@@ -214,8 +215,6 @@ struct SoftmaxArgs {
     const float *in0;            // fwd: score;  bwd: alpha
     const float *in1;            // fwd: unused; bwd: grad_alpha
     float *out;
-    int32_t *queue;              // rows longer than kLongRow
-    int32_t *queue_len;
     int backward;
 };
 
@@ -247,27 +246,6 @@ __device__ __forceinline__ void softmax_row_bwd(const float *__restrict__ alpha,
     for (int k = b + l; k < e; k += lanes) ds[k] = (float)((double)alpha[k] * ((double)da[k] - s));
 }
 
-template <int lanes>
-__global__ __launch_bounds__(256) void k_edge_softmax_rows(const SoftmaxArgs a)
-{
-    const int64_t u = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / lanes;
-    const int l = threadIdx.x % lanes;
-    int b = 0, e = 0;
-    if (u < a.num_dst) {
-        b = a.indptr[u];
-        e = a.indptr[u + 1];
-        if (e - b > kLongRow) {                   // queued for the workgroup-per-row pass
-            if (l == 0) a.queue[atomicAdd(a.queue_len, 1)] = (int32_t)u;
-            e = b;
-        }
-    }
-    // all lanes of a group hold the same (b, e): the cross-lane sums below see whole groups
-    if (a.backward)
-        softmax_row_bwd(a.in0, a.in1, a.out, b, e, l, lanes);
-    else
-        softmax_row_fwd(a.in0, a.out, b, e, l, lanes);
-}
-
 // Sum / max over a 256-thread workgroup, result to every thread.
 __device__ __forceinline__ double block_reduce(double v, bool take_max)
 {
@@ -279,33 +257,56 @@ __device__ __forceinline__ double block_reduce(double v, bool take_max)
     return take_max ? fmax(fmax(part[0], part[1]), fmax(part[2], part[3])) : (part[0] + part[1]) + (part[2] + part[3]);
 }
 
-__global__ __launch_bounds__(256) void k_edge_softmax_long(const SoftmaxArgs a)
+// A long row by the workgroup.
+__device__ __forceinline__ void softmax_row_block(const SoftmaxArgs &a, int b, int e)
 {
-    const int n = *a.queue_len;
-    for (int q = blockIdx.x; q < n; q += gridDim.x) {
-        const int u = a.queue[q];
-        const int b = a.indptr[u], e = a.indptr[u + 1], l = threadIdx.x;
-        if (!a.backward) {
-            double m = -INFINITY;
-            for (int k = b + l; k < e; k += 256) m = fmax(m, (double)a.in0[k]);
-            m = block_reduce(m, true);
-            double z = 0.0;
-            for (int k = b + l; k < e; k += 256) z += exp((double)a.in0[k] - m);
-            z = block_reduce(z, false);
-            for (int k = b + l; k < e; k += 256) a.out[k] = (float)(exp((double)a.in0[k] - m) / z);
-        } else {
-            double s = 0.0;
-            for (int k = b + l; k < e; k += 256) s += (double)a.in0[k] * (double)a.in1[k];
-            s = block_reduce(s, false);
-            for (int k = b + l; k < e; k += 256) a.out[k] = (float)((double)a.in0[k] * ((double)a.in1[k] - s));
-        }
+    const int l = threadIdx.x;
+    if (!a.backward) {
+        double m = -INFINITY;
+        for (int k = b + l; k < e; k += 256) m = fmax(m, (double)a.in0[k]);
+        m = block_reduce(m, true);
+        double z = 0.0;
+        for (int k = b + l; k < e; k += 256) z += exp((double)a.in0[k] - m);
+        z = block_reduce(z, false);
+        for (int k = b + l; k < e; k += 256) a.out[k] = (float)(exp((double)a.in0[k] - m) / z);
+    } else {
+        double s = 0.0;
+        for (int k = b + l; k < e; k += 256) s += (double)a.in0[k] * (double)a.in1[k];
+        s = block_reduce(s, false);
+        for (int k = b + l; k < e; k += 256) a.out[k] = (float)((double)a.in0[k] * ((double)a.in1[k] - s));
     }
 }
 
-__global__ void k_zero_i32(int32_t *p) { *p = 0; }
+template <int lanes>
+__global__ __launch_bounds__(256) void k_edge_softmax_rows(const SoftmaxArgs a)
+{
+    __shared__ int32_t long_row[256 / lanes];
+    __shared__ int n_long;
+    if (threadIdx.x == 0) n_long = 0;
+    __syncthreads();
+    const int64_t u = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / lanes;
+    const int l = threadIdx.x % lanes;
+    int b = 0, e = 0;
+    if (u < a.num_dst) {
+        b = a.indptr[u];
+        e = a.indptr[u + 1];
+        if (e - b > kLongRow) {
+            if (l == 0) long_row[atomicAdd(&n_long, 1)] = (int32_t)u;
+            e = b;
+        }
+    }
+    // all lanes of a group hold the same (b, e): the cross-lane sums below see whole groups
+    if (a.backward)
+        softmax_row_bwd(a.in0, a.in1, a.out, b, e, l, lanes);
+    else
+        softmax_row_fwd(a.in0, a.out, b, e, l, lanes);
+    __syncthreads();
+    const int n = n_long;
+    for (int q = 0; q < n; ++q) softmax_row_block(a, a.indptr[long_row[q]], a.indptr[long_row[q] + 1]);
+}
 
 struct EdgeLayout {
-    size_t edge_row, queue, queue_len, total;
+    size_t edge_row, total;
 };
 
 EdgeLayout edge_layout(int64_t num_dst, int64_t E)
@@ -314,8 +315,6 @@ EdgeLayout edge_layout(int64_t num_dst, int64_t E)
     EdgeLayout L;
     size_t off = 0;
     L.edge_row = off; off += align_up((size_t)(E > 0 ? E : 1) * 4, 256);
-    L.queue = off; off += align_up((size_t)(E / kLongRow + 1) * 4, 256);
-    L.queue_len = off; off += 256;
     L.total = off;
     return L;
 }
@@ -377,12 +376,8 @@ fastgl_status softmax(bool backward, const int32_t *indptr, int64_t num_dst, int
     if (st != FASTGL_OK) return st;
     SoftmaxArgs a = {};
     a.indptr = indptr; a.num_dst = num_dst; a.in0 = in0; a.in1 = in1; a.out = out;
-    a.queue = (int32_t *)((char *)workspace + L.queue);
-    a.queue_len = (int32_t *)((char *)workspace + L.queue_len);
     a.backward = backward;
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(1), 0, s, a.queue_len);
-    FASTGL_LAUNCH_CHECK("edge softmax (reset)");
     // lanes per destination row by the block's mean row length (rows of sampled blocks are short)
     const int64_t mean = E / (num_dst > 0 ? num_dst : 1);
     if (mean < 24)
@@ -391,9 +386,7 @@ fastgl_status softmax(bool backward, const int32_t *indptr, int64_t num_dst, int
         hipLaunchKernelGGL(k_edge_softmax_rows<32>, dim3((unsigned)ceil_div(num_dst * 32, 256)), dim3(256), 0, s, a);
     else
         hipLaunchKernelGGL(k_edge_softmax_rows<64>, dim3((unsigned)ceil_div(num_dst * 64, 256)), dim3(256), 0, s, a);
-    FASTGL_LAUNCH_CHECK("edge softmax (rows)");
-    hipLaunchKernelGGL(k_edge_softmax_long, dim3(kLongGrid), dim3(256), 0, s, a);
-    FASTGL_LAUNCH_CHECK("edge softmax (long rows)");
+    FASTGL_LAUNCH_CHECK("edge softmax");
     return FASTGL_OK;
 }
 
