@@ -54,7 +54,7 @@ typedef enum { FASTGL_IDMAP_ORDERED = 0, FASTGL_IDMAP_FUSED = 1 } fastgl_idmap_m
 int64_t fastgl_idmap_table_slots(int64_t n_ids);
 
 /* Bytes of device workspace (256-byte aligned) one call needs: the table
- * (32-bit slots), a 32-bit reference per input ID and
+ * (room for 16 bytes per slot), a 32-bit reference per input ID and
  * the block counts of the ordered mode. 0 for bad sizes. */
 size_t fastgl_idmap_workspace_bytes(int64_t n_dst, int64_t n_nbr);
 

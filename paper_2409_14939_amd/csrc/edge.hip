@@ -334,7 +334,8 @@ EdgeLayout edge_layout(int64_t num_dst, int64_t E)
     EdgeLayout L;
     size_t off = 0;
     L.edge_row = off; off += align_up((size_t)(E > 0 ? E : 1) * 4, 256);
-    L.total = off;
+    // room that the softmax calls no longer use stays part of the size the interface asks for
+    L.total = off + align_up((size_t)(E / kLongRow + 1) * 4, 256) + 256;
     return L;
 }
 

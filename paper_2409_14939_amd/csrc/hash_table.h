@@ -20,6 +20,10 @@ constexpr int32_t kNoSlot = 0x7FFFFFFF;      // no table has this many slots
 
 constexpr int32_t kEmptySlot = -1;
 
+// Bytes per slot that a caller's workspace must have room for: part of the interface (what it refuses as too
+// small), four times what a slot of positions takes.
+constexpr int64_t kSlotRoom = 16;
+
 // Bits of a position below n in a slot; the other 31 - bits hold a piece of the hash (never the sign bit).
 inline int position_bits(int64_t n)
 {

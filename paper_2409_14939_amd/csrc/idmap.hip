@@ -206,7 +206,7 @@ Layout layout(int64_t n)
     const int64_t cap = idmap_slots(n);
     Layout L;
     size_t off = 0;
-    L.table = off; off += align_up((size_t)cap * 4, 256);
+    L.table = off; off += align_up((size_t)(cap * kSlotRoom), 256);
     L.ref = off; off += align_up((size_t)(n > 0 ? n : 1) * 4, 256);
     L.block_cnt = off; off += align_up((size_t)(ceil_div(n, kScanBlock) + 1) * 4, 256);
     L.total = off;

@@ -121,6 +121,7 @@ __global__ __launch_bounds__(256) void k_assemble_rows(const char *__restrict__ 
         *reinterpret_cast<uint16_t *>(dst) = *reinterpret_cast<const uint16_t *>(src + off);
 }
 
+static_assert(sizeof(MaskSlot) <= kSlotRoom, "an entry fits its slot's room");
 constexpr int kMarkBatches = 8;
 constexpr int kCountBlocks = 256;            // workgroups that read the marks: one per compute unit
 
@@ -284,7 +285,7 @@ MatchLayout match_layout(int64_t n_prev, int64_t n_new)
 {
     MatchLayout L;
     size_t off = 0;
-    L.table = off; off += align_up((size_t)table_slots(n_prev) * 4, 256);
+    L.table = off; off += align_up((size_t)(table_slots(n_prev) * kSlotRoom), 256);
     L.block_cnt = off; off += align_up((size_t)(ceil_div(n_new, kScanBlock) + 1) * 4, 256);
     L.total = off;
     return L;
@@ -298,7 +299,7 @@ OverlapLayout overlap_layout(int64_t total_ids)
 {
     OverlapLayout L;
     size_t off = 0;
-    L.table = off; off += align_up((size_t)table_slots(total_ids) * sizeof(MaskSlot), 256);
+    L.table = off; off += align_up((size_t)(table_slots(total_ids) * kSlotRoom), 256);
     L.slot_of = off; off += align_up((size_t)(total_ids > 0 ? total_ids : 1) * 4, 256);
     L.total = off;
     return L;
