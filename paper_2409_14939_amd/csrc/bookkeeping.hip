@@ -1219,7 +1219,7 @@ static bool fits_once(const fastgl_plan *p, int parts, bool src_deg)
 {
     const bool full = (parts & FASTGL_PLAN_BWD) != 0;
     if (full || src_deg) {
-        if (p->num_edges > kOnceEdges || p->num_src > kOnceSources) return false;
+        if (p->num_edges > (full ? kOnceFullEdges : kOnceEdges) || p->num_src > kOnceSources) return false;
     }
     return p->num_dst <= (full ? kOnceRows : kOnceRowsFwd);
 }

@@ -4,7 +4,7 @@
 // before: for a block of a few thousand edges that is 20 us of launch latency around 2 us of work.  Here
 // nobody waits for anybody: every workgroup recomputes from the block's own arrays what it needs from the
 // others.  That costs reads (every bucket's workgroup scans all source ids, at most 256 KB out of L2) and is
-// why it stops at 65 535 edges: up to there an edge id and a row pointer fit 16 bits of LDS.
+// why it stops at 65 535 edges (up to there an edge id and a row pointer fit 16 bits of LDS), full plans at 16 384.
 //
 //   bucket      2 048 consecutive source ids: counts the edges per source of its bucket and the edges of the
 //               buckets before it, writes the bucket's rows of indptr_T, out-degrees, scale factors and row
@@ -16,7 +16,7 @@
 //   destination rows  1 024 rows per workgroup: degrees, scale factors, row sets
 //   long destinations one workgroup: ordered list of the long destination rows
 //
-// 256 seeds, fan-out 5 (1 276 edges): 5 launches, 22 us -> 1 launch, see kOnceEdges for the other end.
+// 256 seeds, fan-out 5 (1 276 edges): 5 launches, 22 us -> 1 launch, see kOnceFullEdges for the other end.
 #pragma once
 #include "plan_device.h"
 
@@ -27,7 +27,10 @@ constexpr int kBucketIds = 1 << kBucketBits;
 
 constexpr int kOnceThreads = 1024;
 constexpr int kOnceWaves = kOnceThreads / kWave;
-constexpr int kOnceEdges = 65535;          // 16-bit edge ids and row pointers
+constexpr int kOnceEdges = 65535;          // 16-bit edge ids and row pointers; forward-only plans with source degrees
+// Full plans: two chunks of a bucket at most. One bucket's workgroup places its edges chunk by chunk, so a block whose
+// sources fall into few buckets is a chain: 44 080 edges over 10 359 sources 76 us here, 43 us in stages.
+constexpr int kOnceFullEdges = 16384;
 constexpr int kOnceRows = 24576;           // row pointers in LDS (backward plans)
 constexpr int kOnceRowsFwd = 65536;        // forward-only plans: what one workgroup scans for long rows
 constexpr int kOnceSources = 1 << 18;      // 128 buckets

@@ -61,3 +61,8 @@ def test_forward_only_plan_with_source_degrees(nd, ns, edges, hub):
     sp = oracle.work_split(blk.indptr, B.fastgl_work_per_group())
     assert np.array_equal(read_i32(plan, v.split_dst, sp.shape[0]), sp)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("edges", [16384, 16385])
+def test_full_plan_around_the_edge_limit(edges):
+    check_bookkeeping(exact_block(np.random.default_rng(edges), 3000, 4097, edges, 9000), "once")
