@@ -12,7 +12,8 @@ import torch
 import blockgen as bg
 import oracle
 from paper_2409_14939_amd import binding as B
-from gpu_util import assert_close, dev_feat, dev_i32, host_feat, make_inputs, read_i32
+from gpu_util import as_f64, assert_close, dev_feat, dev_i32, host_feat, make_inputs, read_i32
+from test_gpu_update import close_bf16
 
 pytestmark = pytest.mark.gpu
 GUARD_ROWS = 3
@@ -114,6 +115,24 @@ def test_update_outputs_between_guard_bands(M, K, N):
     dHr, dWr, dbr = oracle.update_bwd(H, W, Yref, dY, True)
     for got, ref, what in ((Y.t, Yref, "Y"), (dH.t, dHr, "dH"), (dW.t, dWr, "dW"), (db.t.view(N), dbr, "db")):
         np.testing.assert_allclose(got.cpu().numpy(), ref, rtol=2e-4, atol=2e-4 * max(1.0, float(np.abs(ref).max())), err_msg=what)
+
+
+def test_tall_bf16_update_outputs_between_guard_bands():
+    """Odd numbers of rows and columns in bf16 on tall tiles of each width: the result ends in the middle of a dword."""
+    for M, K, N in [(17001, 9, 31), (17001, 101, 47), (9003, 61, 101), (31001, 33, 127), (31001, 255, 21), (31001, 17, 255)]:
+        rng = np.random.default_rng(M + K + N)
+        bits = lambda *s: bg.to_bf16_bits(rng.standard_normal(s).astype(np.float32))
+        H, W, dY = bits(M, K), bits(K, N), bits(M, N)
+        Y, dH = Guarded(M, N, torch.bfloat16), Guarded(M, K, torch.bfloat16)
+        print(f"guard bands: tall bf16 update M={M} K={K} N={N}", flush=True)
+        B.fastgl_update_fwd(dev_feat(H, "bf16"), dev_feat(W, "bf16"), None, False, Y.t)
+        Y.check("update Y")
+        B.fastgl_update_bwd(dev_feat(H, "bf16"), dev_feat(W, "bf16"), None, dev_feat(dY, "bf16"), False, want=("dH",), dH=dH.t)
+        dH.check("update dH")
+        aH, aW = np.abs(as_f64(H, "bf16")), np.abs(as_f64(W, "bf16"))
+        close_bf16(host_feat(Y.t, "bf16"), oracle.update_fwd_bf16(H, W, None, False), aH @ aW, K, "Y")
+        dHr, _, _ = oracle.update_bwd_bf16(H, W, None, dY, False, want=("dH",))
+        close_bf16(host_feat(dH.t, "bf16"), dHr, np.abs(as_f64(dY, "bf16")) @ aW.T, N, "dH")
 
 
 @pytest.mark.parametrize("K,N", [(256, 47), (100, 64), (64, 1), (602, 47)])

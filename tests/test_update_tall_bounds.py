@@ -1,0 +1,62 @@
+"""Host-side model of what the tall tiles of the update phase (csrc/update_rows.hip, k_update_tall) store through
+their result buffer: a tile's rows past the last one are not masked, they are dropped because their offset is at or
+past the buffer's size.  No element outside the result may survive that, for any remainder of rows and columns and
+either element size.  The model mirrors the kernel's index arithmetic; it has to be changed with it."""
+import random
+
+import numpy as np
+
+TALL_ROWS, FULL = 128, 240
+
+
+def tall_tiles(M, N, b_col):
+    rows = -(-M // TALL_ROWS)
+    if b_col and N <= 32:
+        return 1
+    best, best_cost = 2, -(-N // 64) * 64 * 20
+    for nt in (4, 8):
+        tiles = -(-N // (32 * nt))
+        cost = tiles * 32 * nt * (17 if nt == 4 else 16)
+        if rows * tiles >= FULL and cost <= best_cost:
+            best, best_cost = nt, cost
+    return best
+
+
+def exact(nbytes):
+    return nbytes
+
+
+def whole_dwords(nbytes):
+    return (nbytes + 3) & ~3
+
+
+def stores_in_bounds(M, N, eb, b_col, size=exact):
+    nt = 32 * tall_tiles(M, N, b_col)
+    r0 = (M - 1) // TALL_ROWS * TALL_ROWS                     # the last row tile: the others hold whole rows
+    row, col = np.meshgrid(np.arange(TALL_ROWS), np.arange(nt), indexing="ij")
+    for c0 in {0, (N - 1) // nt * nt}:
+        off = (row * N + col) * eb
+        kept = (c0 + col < N) & (off < size(((M - r0) * N - c0) * eb))
+        if not np.array_equal(kept, (r0 + row < M) & (c0 + col < N)):
+            return False
+    return True
+
+
+def shapes():
+    rng = random.Random(5)
+    yield from [(17001, 61), (9003, 101), (31001, 255), (17000, 47), (16385, 1), (31000, 256)]
+    for _ in range(200):
+        yield rng.randint(16385, 40000), rng.randint(1, 300)
+
+
+def test_tall_tiles_store_their_result_and_nothing_else():
+    for M, N in shapes():
+        for eb in (2, 4):
+            for b_col in (False, True):
+                assert stores_in_bounds(M, N, eb, b_col), (M, N, eb, b_col)
+
+
+def test_the_model_sees_a_size_rounded_up():
+    """The mistake the model exists for: a size rounded up to a dword lets the bf16 element behind the result through."""
+    assert not stores_in_bounds(17001, 61, 2, True, whole_dwords)
+    assert not stores_in_bounds(9003, 101, 2, False, whole_dwords)
