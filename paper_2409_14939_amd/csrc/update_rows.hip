@@ -245,15 +245,21 @@ constexpr uint32_t kNowhere = 0x80000000u;     // beyond every buffer made here
 constexpr int kStream = 2;                     // non-temporal
 constexpr int64_t kMaxTallLd = (int64_t)1 << 21;   // row length up to which every offset inside a tile stays below 2^31 bytes
 
-// Exactly `bytes` bytes: the element behind a matrix belongs to somebody else (stores are dropped there by this size
-// alone: the rows of a tile past the last one are not masked).
+// Exactly `bytes` bytes: the element behind a matrix belongs to somebody else.  Stores are dropped there by this size
+// alone (the rows of a tile past the last one are not masked), and the rows of a column operand past the last one
+// are 0 by it: whatever lies there would meet A's zeros in the matrix instructions, and 0 times NaN is NaN.
 __device__ __forceinline__ Rsrc buffer_from(const void *p, int64_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)(bytes < 0x7FFFFFFF ? bytes : 0x7FFFFFFF), kRsrcFormat);
 }
 
-// Operands: a dword that holds the last bf16 element counts as inside.
-__device__ __forceinline__ int64_t whole_dwords(int64_t bytes) { return (bytes + 3) & ~(int64_t)3; }
+// Size of an operand loaded by rows.  Rows of odd length are loaded in aligned dwords: the one that holds the last
+// element counts as inside, its other half (of a row that does not exist) goes no further than funnel and settle.
+template <int V>
+__device__ __forceinline__ int64_t loadable(int64_t bytes)
+{
+    return V == kOdd ? (bytes + 3) & ~(int64_t)3 : bytes;
+}
 
 // Elements k .. k+7 of the row of K elements that starts at byte offset `row`.
 template <int V>
@@ -357,11 +363,11 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES == 4 && GATE && !BF16) 
     const int Kc = (int)g.Kc;
 
     // A from the tile's first row on; B from its first element (row operand: the tile's first row) on
-    const int64_t abytes = whole_dwords((g.M - r0) * g.lda * EB);
+    const int64_t abytes = loadable<VA>((g.M - r0) * g.lda * EB);
     const Rsrc ra = buffer_from((const char *)g.a + r0 * g.lda * EB, abytes);
     const Rsrc rg = buffer_from(GATE ? (const char *)g.gate + r0 * g.lda * EB : nullptr, GATE ? abytes : 0);
-    const Rsrc rb = BCOL ? buffer_from(g.b, whole_dwords(g.Kc * g.ldb * EB))
-                         : buffer_from((const char *)g.b + c0 * g.ldb * EB, whole_dwords((g.N - c0) * g.ldb * EB));
+    const Rsrc rb = BCOL ? buffer_from(g.b, g.Kc * g.ldb * EB)
+                         : buffer_from((const char *)g.b + c0 * g.ldb * EB, loadable<VB>((g.N - c0) * g.ldb * EB));
     const uint32_t arow = (uint32_t)(wave * kWaveRows + l32) * (uint32_t)g.lda * EB;
     const uint32_t ldb = (uint32_t)g.ldb * EB;
 

@@ -23,10 +23,10 @@ SENTINEL = {torch.float32: 0x7FC5A5A5, torch.bfloat16: 0x7FC5}      # NaN patter
 class Guarded:
     """rows x cols matrix of `dtype` in the middle of a larger allocation filled with a sentinel."""
 
-    def __init__(self, rows, cols, dtype):
+    def __init__(self, rows, cols, dtype, align=1):                 # align: of the matrix, in elements
         self.rows, self.cols, self.dtype = rows, cols, dtype
         self.it = torch.int32 if dtype == torch.float32 else torch.int16
-        self.band = max(GUARD_ROWS * cols, 64)                      # elements before and after
+        self.band = -(-max(GUARD_ROWS * cols, 64) // align) * align # elements before and after
         self.raw = torch.full((2 * self.band + rows * cols,), SENTINEL[dtype], dtype=self.it, device="cuda")
         self.t = self.raw[self.band:self.band + rows * cols].view(dtype).view(rows, cols)
         assert self.t.is_contiguous()
@@ -133,6 +133,31 @@ def test_tall_bf16_update_outputs_between_guard_bands():
         close_bf16(host_feat(Y.t, "bf16"), oracle.update_fwd_bf16(H, W, None, False), aH @ aW, K, "Y")
         dHr, _, _ = oracle.update_bwd_bf16(H, W, None, dY, False, want=("dH",))
         close_bf16(host_feat(dH.t, "bf16"), dHr, np.abs(as_f64(dY, "bf16")) @ aW.T, N, "dH")
+
+
+@pytest.mark.parametrize("align", [1, 8])
+def test_tall_bf16_update_operands_between_nan_bands(align):
+    """Every operand packed between NaN: odd sizes in bf16 end in the middle of a dword, and neither the other half of it
+    nor the elements of rows that do not exist may reach a result (tall tiles of each width; rows of odd length at
+    odd addresses, loaded element by element, and at aligned ones, loaded in dwords)."""
+    for M, K, N in [(17001, 101, 31), (17001, 101, 47), (9003, 61, 101), (31001, 33, 127), (31001, 17, 255), (17001, 5, 33)]:
+        rng = np.random.default_rng(M + K + N)
+        bits = lambda *s: bg.to_bf16_bits(rng.standard_normal(s).astype(np.float32))
+
+        def banded(a):
+            g = Guarded(*a.shape, torch.bfloat16, align)
+            g.t.copy_(dev_feat(a, "bf16"))
+            return g.t
+
+        H, W, dY = bits(M, K), bits(K, N), bits(M, N)
+        print(f"NaN bands: tall bf16 update M={M} K={K} N={N} align={align}", flush=True)
+        Y = B.fastgl_update_fwd(banded(H), banded(W), None, True)
+        Yref = oracle.update_fwd_bf16(H, W, None, True)
+        aH, aW = np.abs(as_f64(H, "bf16")), np.abs(as_f64(W, "bf16"))
+        close_bf16(host_feat(Y, "bf16"), Yref, aH @ aW, K, "Y")
+        dH, _, _ = B.fastgl_update_bwd(banded(H), banded(W), banded(Yref), banded(dY), True, want=("dH",))
+        dHr, _, _ = oracle.update_bwd_bf16(H, W, Yref, dY, True, want=("dH",))
+        close_bf16(host_feat(dH, "bf16"), dHr, (np.abs(as_f64(dY, "bf16")) * (as_f64(Yref, "bf16") > 0)) @ aW.T, N, "dH")
 
 
 @pytest.mark.parametrize("K,N", [(256, 47), (100, 64), (64, 1), (602, 47)])

@@ -1,7 +1,8 @@
-"""Host-side model of what the tall tiles of the update phase (csrc/update_rows.hip, k_update_tall) store through
-their result buffer: a tile's rows past the last one are not masked, they are dropped because their offset is at or
-past the buffer's size.  No element outside the result may survive that, for any remainder of rows and columns and
-either element size.  The model mirrors the kernel's index arithmetic; it has to be changed with it."""
+"""Host-side model of what the tall tiles of the update phase (csrc/update_rows.hip, k_update_tall) move through
+buffers: an access whose offset is at or past the buffer's size is dropped (a store) or gives 0 (a load).
+Results: a tile's rows past the last one are not masked, only dropped that way; no element outside the result may
+survive, for any remainder of rows and columns and either element size.  Column operand (W of the forward pass): rows
+past the last one are not masked either; every one of their elements must come back as 0.  The model mirrors the kernel's index arithmetic; it has to be changed with it."""
 import random
 
 import numpy as np
@@ -42,6 +43,12 @@ def stores_in_bounds(M, N, eb, b_col, size=exact):
     return True
 
 
+def column_operand_ends(K, N, eb, size=exact):
+    """Elements of the rows K, K + 1, ... that a stage of 64 contracted indices and the one ahead of it may ask for."""
+    row, col = np.meshgrid(np.arange(K, K + 128), np.arange(256), indexing="ij")
+    return not ((row * N + col) * eb < size(K * N * eb)).any()
+
+
 def shapes():
     rng = random.Random(5)
     yield from [(17001, 61), (9003, 101), (31001, 255), (17000, 47), (16385, 1), (31000, 256)]
@@ -60,3 +67,10 @@ def test_the_model_sees_a_size_rounded_up():
     """The mistake the model exists for: a size rounded up to a dword lets the bf16 element behind the result through."""
     assert not stores_in_bounds(17001, 61, 2, True, whole_dwords)
     assert not stores_in_bounds(9003, 101, 2, False, whole_dwords)
+
+
+def test_rows_of_a_column_operand_past_the_last_one_are_zero():
+    for K, N in [(101, 47), (33, 9), (17, 255), (100, 256), (1, 1)]:
+        for eb in (2, 4):
+            assert column_operand_ends(K, N, eb), (K, N, eb)
+    assert not column_operand_ends(101, 47, 2, whole_dwords)
