@@ -14,8 +14,11 @@
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <exception>
+#include <new>
 #include <vector>
 
 #include "fastgl_agg.h"
@@ -195,7 +198,8 @@ PyObject *tuple(std::initializer_list<at::Tensor> ts)
     return r;
 }
 
-// Every function: METH_FASTCALL with a fixed number of arguments, exceptions turned into Python's.
+// Every function: METH_FASTCALL with a fixed number of arguments, exceptions turned into the ones torch raises for
+// them (torch.OutOfMemoryError for an allocation that does not fit: programs catch it and go on with less).
 typedef PyObject *(*Body)(PyObject *const *);
 template <Body BODY, int NARGS>
 PyObject *entry(PyObject *, PyObject *const *a, Py_ssize_t n)
@@ -208,8 +212,10 @@ PyObject *entry(PyObject *, PyObject *const *a, Py_ssize_t n)
         return BODY(a);
     } catch (const Raised &) {
         return nullptr;
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (const std::bad_alloc &) {
+        return PyErr_NoMemory();
+    } catch (const std::exception &) {
+        torch::translate_exception_to_python(std::current_exception());
         return nullptr;
     }
 }
