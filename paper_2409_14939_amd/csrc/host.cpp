@@ -281,13 +281,18 @@ PyObject *aggregate_static(PyObject *const *a)
     return wrap(out);
 }
 
-// (blocks: sequence of (indptr, indices, num_src), parts, plan_mems: sequence or None) -> [(handle, memory)]
+// (blocks: sequence of (indptr, indices, num_src), parts, plan_mems: indexed by block, or None) -> [(handle, memory)]
 PyObject *plan_create_many(PyObject *const *a)
 {
     const int parts = (int)integer(a[1]);
-    struct Seq {
+    struct Seq {                             // no iterators: binding.py goes through the blocks once more
         PyObject *s;
-        explicit Seq(PyObject *o) : s(PySequence_Fast(o, "a sequence is expected")) { if (!s) throw Raised{}; }
+        explicit Seq(PyObject *o) : s(nullptr)
+        {
+            if (!PySequence_Check(o)) fail(PyExc_TypeError, "blocks must be a sequence of (indptr, indices, num_src)");
+            s = PySequence_Fast(o, "a sequence is expected");
+            if (!s) throw Raised{};
+        }
         ~Seq() { Py_DECREF(s); }
         Py_ssize_t n() const { return PySequence_Fast_GET_SIZE(s); }
         PyObject *at(Py_ssize_t i) const { return PySequence_Fast_GET_ITEM(s, i); }
@@ -297,19 +302,16 @@ PyObject *plan_create_many(PyObject *const *a)
     std::vector<fastgl_block_desc> desc((size_t)n);
     std::vector<at::Tensor> mem((size_t)n);
     std::vector<fastgl_plan *> out((size_t)n, nullptr);
-    PyObject *mems = nullptr;
-    struct Drop { PyObject *&o; ~Drop() { Py_XDECREF(o); } } drop{mems};
-    if (!none(a[2])) {
-        mems = PySequence_Fast(a[2], "plan memory must be a sequence");
-        if (!mems) throw Raised{};
-        if (PySequence_Fast_GET_SIZE(mems) < n) fail(PyExc_IndexError, "fewer plan buffers than blocks");
-    }
+    struct Ref { PyObject *o; ~Ref() { Py_XDECREF(o); } };
     for (Py_ssize_t i = 0; i < n; ++i) {
         const Seq item(blocks.at(i));
         if (item.n() != 3) fail(PyExc_ValueError, "a block is (indptr, indices, num_src)");
         const Block b(item.at(0), item.at(1), item.at(2));
-        if (mems) mem[i] = tensor(PySequence_Fast_GET_ITEM(mems, i), "plan memory");
-        else
+        if (!none(a[2])) {
+            const Ref index{PyLong_FromSsize_t(i)}, m{index.o ? PyObject_GetItem(a[2], index.o) : nullptr};
+            if (!m.o) throw Raised{};
+            mem[i] = tensor(m.o, "plan memory");
+        } else
             mem[i] = at::empty({(int64_t)fastgl_block_plan_bytes(b.num_dst, b.num_src, b.num_edges)},
                                b.indptr.options().dtype(at::kByte));
         fastgl_block_desc &d = desc[(size_t)i];

@@ -1,7 +1,10 @@
 """What the Python calls accept, refuse and raise (argument marshalling, not results)."""
+import numpy as np
 import pytest
 import torch
 
+import blockgen as bg
+from gpu_util import dev_i32
 from paper_2409_14939_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -18,3 +21,37 @@ def test_an_allocation_that_does_not_fit_raises_torchs_error():
         assert B.fastgl_gather_rows(table, ids[:8]).shape == (8, 1 << 14)
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
+
+
+def small_blocks():
+    rng = np.random.default_rng(4)
+    out = []
+    for nd, ns in ((20, 50), (7, 30)):
+        b = bg.random_block(rng, nd, ns, 4.0)
+        out.append((dev_i32(b.indptr), dev_i32(b.indices), b.num_src))
+    return out
+
+
+def test_blocks_are_a_sequence():
+    """A generator cannot be gone through twice: refused before anything is built, like sets and dicts."""
+    blocks = small_blocks()
+    for bad in ((b for b in blocks), iter(blocks), set(blocks), dict.fromkeys(blocks), 3, [(x for x in blocks[0])]):
+        with pytest.raises(TypeError):
+            B.fastgl_block_plan_create_many(bad)
+    with pytest.raises(ValueError):
+        B.fastgl_block_plan_create_many([blocks[0][:2]])
+    assert B.fastgl_block_plan_create_many([]) == []
+    for good in (blocks, tuple(blocks), [list(b) for b in blocks]):
+        assert [p.num_src for p in B.fastgl_block_plan_create_many(good)] == [50, 30]
+
+
+def test_plan_memory_is_anything_indexed_by_block():
+    blocks = small_blocks()
+    need = max(B.fastgl_block_plan_bytes(ip.numel() - 1, ns, ix.numel()) for ip, ix, ns in blocks)
+    need = -(-need // 256) * 256
+    rows = torch.empty((2, need), dtype=torch.uint8, device="cuda")
+    for mems in ([rows[0], rows[1]], {0: rows[0], 1: rows[1]}, rows, [rows[0], rows[1], None]):
+        made = B.fastgl_block_plan_create_many(blocks, plan_mems=mems)
+        assert [p.mem.data_ptr() for p in made] == [rows[0].data_ptr(), rows[1].data_ptr()]
+    with pytest.raises(IndexError):
+        B.fastgl_block_plan_create_many(blocks, plan_mems=[rows[0]])
