@@ -92,26 +92,36 @@ const at::Tensor &features(PyObject *o, const char *name)
     return x;
 }
 
+// A size or an enumerator: an int and nothing that int() would round or parse.
 int64_t integer(PyObject *o)
 {
-    const long long v = PyLong_AsLongLong(o);
-    if (v == -1 && PyErr_Occurred()) {
-        if (!PyErr_ExceptionMatches(PyExc_TypeError)) throw Raised{};
-        PyErr_Clear();
-        PyObject *i = PyNumber_Long(o);          // what int() accepts: numpy scalars, one-element tensors
-        if (!i) throw Raised{};
-        const long long w = PyLong_AsLongLong(i);
-        Py_DECREF(i);
-        if (w == -1 && PyErr_Occurred()) throw Raised{};
-        return w;
+    if (!PyLong_Check(o)) {
+        PyErr_Format(PyExc_TypeError, "an int is expected, not %s", Py_TYPE(o)->tp_name);
+        throw Raised{};
     }
+    const long long v = PyLong_AsLongLong(o);
+    if (v == -1 && PyErr_Occurred()) throw Raised{};
     return v;
 }
 
-float real(PyObject *o)
+// What int() makes of it.
+int64_t to_integer(PyObject *o)
 {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Raised{};
+    PyObject *i = PyNumber_Long(o);
+    if (!i) throw Raised{};
+    const long long v = PyLong_AsLongLong(i);
+    Py_DECREF(i);
+    if (v == -1 && PyErr_Occurred()) throw Raised{};
+    return v;
+}
+
+// What float() makes of it.
+float to_real(PyObject *o)
+{
+    PyObject *f = PyNumber_Float(o);
+    if (!f) throw Raised{};
+    const double v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
     return (float)v;
 }
 
@@ -495,7 +505,7 @@ PyObject *overlap_counts(PyObject *const *a)
     if (!seq) throw Raised{};
     struct Drop { PyObject *o; ~Drop() { Py_DECREF(o); } } drop{seq};
     std::vector<int64_t> off;
-    for (Py_ssize_t i = 0; i < PySequence_Fast_GET_SIZE(seq); ++i) off.push_back(integer(PySequence_Fast_GET_ITEM(seq, i)));
+    for (Py_ssize_t i = 0; i < PySequence_Fast_GET_SIZE(seq); ++i) off.push_back(to_integer(PySequence_Fast_GET_ITEM(seq, i)));
     if (off.empty()) fail(PyExc_ValueError, "offsets must hold at least one entry");
     const int n = (int)off.size() - 1;
     const at::Tensor counts = at::empty({n, n}, gid.options()), viol = at::empty({1}, gid.options().dtype(at::kInt));
@@ -565,7 +575,7 @@ PyObject *edge_score_fwd(PyObject *const *a)
     const at::Tensor &el = dev(a[2], at::kFloat, "el"), &er = dev(a[3], at::kFloat, "er");
     const int64_t nd = ip.numel() - 1, E = ix.numel();
     if (el.numel() != nd) fail(PyExc_ValueError, "el must have one entry per destination node");
-    const float slope = real(a[4]);
+    const float slope = to_real(a[4]);
     const Out score(a[5], at::kFloat, {E}, el, "score");
     if (score.t.numel() != E) fail(PyExc_ValueError, "score must have one entry per edge");
     run([&](void *s) {
@@ -581,7 +591,7 @@ PyObject *edge_score_bwd(PyObject *const *a)
 {
     const at::Tensor &ip = dev(a[0], at::kInt, "indptr"), &ix = dev(a[1], at::kInt, "indices");
     const at::Tensor &el = dev(a[2], at::kFloat, "el"), &er = dev(a[3], at::kFloat, "er");
-    const float slope = real(a[4]);
+    const float slope = to_real(a[4]);
     const at::Tensor &g = dev(a[5], at::kFloat, "grad_score");
     const int64_t nd = ip.numel() - 1, E = ix.numel();
     if (el.numel() != nd || g.numel() != E)

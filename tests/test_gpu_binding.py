@@ -55,3 +55,30 @@ def test_plan_memory_is_anything_indexed_by_block():
         assert [p.mem.data_ptr() for p in made] == [rows[0].data_ptr(), rows[1].data_ptr()]
     with pytest.raises(IndexError):
         B.fastgl_block_plan_create_many(blocks, plan_mems=[rows[0]])
+
+
+@pytest.mark.parametrize("bad", [2.0, 2.7, "2", None, np.int64(2), np.float32(2)])
+def test_sizes_are_ints(bad):
+    """What the C types refuse is refused: nothing is truncated or parsed on the way."""
+    ip, ix, ns = small_blocks()[0]
+    X = torch.ones((ns, 4), device="cuda")
+    rows = torch.zeros(2, dtype=torch.int32, device="cuda")
+    for call in (lambda: B.fastgl_block_plan_create(ip, ix, bad), lambda: B.fastgl_block_plan_create(ip, ix, ns, bad),
+                 lambda: B.fastgl_block_aggregate_fwd(ip, ix, None, bad, "sum", X),
+                 lambda: B.fastgl_edge_weight_grad(ip, ix, bad, "sum", X, X[:20]),
+                 lambda: B.fastgl_assemble_rows(X, X, rows, bad)):
+        with pytest.raises(TypeError):
+            call()
+    assert B.fastgl_assemble_rows(X, X, rows, 2).shape == (2, 4)
+
+
+def test_numbers_that_are_converted():
+    """Offsets go through int(), the slope through float(): whatever those take."""
+    gid = torch.arange(6, dtype=torch.int64, device="cuda")
+    ref = B.fastgl_overlap_counts(gid, [0, 3, 6])[0]
+    for offsets in (np.array([0, 3, 6]), [0, "3", 6.0], torch.tensor([0, 3, 6])):
+        assert torch.equal(B.fastgl_overlap_counts(gid, offsets)[0], ref)
+    ip, ix, ns = small_blocks()[0]
+    el, er = torch.ones(20, device="cuda") * -1, torch.zeros(ns, device="cuda")
+    for slope in ("0.25", np.float64(0.25), torch.tensor(0.25)):
+        assert torch.equal(B.fastgl_edge_score_fwd(ip, ix, el, er, slope), B.fastgl_edge_score_fwd(ip, ix, el, er, 0.25))
