@@ -186,15 +186,9 @@ def fastgl_block_workspace_bytes(num_dst: int, num_src: int, num_edges: int, fea
 class Plan:
     """Owner of one fastgl_plan handle and of the device buffer behind it."""
 
-    __slots__ = ("_handle", "mem", "indptr", "indices", "num_src", "__weakref__")
-
     def __init__(self, handle, mem, indptr, indices, num_src):
-        self._handle, self.mem = handle, mem                  # the handle: an address, None once destroyed
+        self.handle, self.mem = handle, mem                   # the handle: c_void_p (or an address), None once destroyed
         self.indptr, self.indices, self.num_src = indptr, indices, num_src
-
-    @property
-    def handle(self):
-        return None if self._handle is None else ctypes.c_void_p(self._handle)
 
     def export(self) -> PlanView:
         v = PlanView()
@@ -202,9 +196,9 @@ class Plan:
         return v
 
     def destroy(self) -> None:
-        if self._handle is not None and _host is not None:    # _host is gone while the interpreter shuts down
-            _host.plan_destroy(self._handle)
-        self._handle = None
+        if self.handle is not None and _lib is not None:      # _lib is gone while the interpreter shuts down
+            _lib.fastgl_block_plan_destroy(self.handle)
+        self.handle = None
 
     def __del__(self):
         self.destroy()
@@ -219,7 +213,7 @@ def fastgl_block_plan_create(indptr: torch.Tensor, indices: torch.Tensor, num_sr
 def fastgl_block_plan_create_many(blocks, parts: int = PLAN_ALL, plan_mems=None):
     """blocks: list of (indptr, indices, num_src); returns one Plan per block, built together."""
     made = _native().plan_create_many(blocks, parts, plan_mems)
-    return [Plan(h, mem, *b) for (h, mem), b in zip(made, blocks)]
+    return [Plan(ctypes.c_void_p(h), mem, *b) for (h, mem), b in zip(made, blocks)]
 
 
 def fastgl_block_aggregate_fwd(indptr, indices, edge_w, num_src: int, mode: str, X: torch.Tensor,

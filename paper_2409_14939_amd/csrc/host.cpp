@@ -30,7 +30,8 @@
 namespace {
 
 PyObject *g_error_class = nullptr;   // binding.FastglError
-PyObject *g_handle_name = nullptr;   // interned name of Plan's handle attribute
+PyObject *g_handle_name = nullptr;   // interned names: of Plan's handle attribute
+PyObject *g_value_name = nullptr;    // and of c_void_p's value
 
 struct Raised {};                    // a Python exception is set
 
@@ -163,10 +164,16 @@ struct Scratch {
     size_t n() const { return (size_t)t.numel(); }
 };
 
+// The handle of anything with the attribute of that name: None, an address, or a c_void_p around either.
 const fastgl_plan *plan_of(PyObject *o)
 {
     if (none(o)) return nullptr;
     PyObject *h = PyObject_GetAttr(o, g_handle_name);
+    if (h && !none(h) && !PyLong_Check(h)) {
+        PyObject *v = PyObject_GetAttr(h, g_value_name);
+        Py_DECREF(h);
+        h = v;
+    }
     if (!h) throw Raised{};
     const void *p = none(h) ? nullptr : PyLong_AsVoidPtr(h);
     Py_DECREF(h);
@@ -338,12 +345,6 @@ PyObject *plan_create_many(PyObject *const *a)
         PyList_SET_ITEM(r, i, t);
     }
     return r;
-}
-
-PyObject *plan_destroy(PyObject *const *a)
-{
-    fastgl_block_plan_destroy(static_cast<fastgl_plan *>(PyLong_AsVoidPtr(a[0])));
-    Py_RETURN_NONE;
 }
 
 // (table, ids, out) -> out
@@ -621,7 +622,7 @@ PyObject *set_error_class(PyObject *const *a)
 
 #define FN(name, nargs) {#name, (PyCFunction)(void (*)(void))entry<name, nargs>, METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {
-    FN(aggregate, 10), FN(aggregate_static, 7), FN(plan_create_many, 3), FN(plan_destroy, 1), FN(gather_rows, 3),
+    FN(aggregate, 10), FN(aggregate_static, 7), FN(plan_create_many, 3), FN(gather_rows, 3),
     FN(update_fwd, 5), FN(layer_fwd, 14), FN(update_bwd, 12), FN(idmap, 7), FN(match, 7), FN(assemble_rows, 5),
     FN(overlap_counts, 3), FN(edge_weight_grad, 9), FN(edge_softmax_fwd, 4), FN(edge_softmax_bwd, 5),
     FN(edge_score_fwd, 6), FN(edge_score_bwd, 11), FN(set_error_class, 1), {nullptr, nullptr, 0, nullptr}};
@@ -634,6 +635,7 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_host", "Native marshalling of t
 
 PyMODINIT_FUNC PyInit__host(void)
 {
-    g_handle_name = PyUnicode_InternFromString("_handle");
-    return g_handle_name ? PyModule_Create(&g_module) : nullptr;
+    g_handle_name = PyUnicode_InternFromString("handle");
+    g_value_name = PyUnicode_InternFromString("value");
+    return g_handle_name && g_value_name ? PyModule_Create(&g_module) : nullptr;
 }

@@ -1,4 +1,7 @@
 """What the Python calls accept, refuse and raise (argument marshalling, not results)."""
+import ctypes
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -82,3 +85,22 @@ def test_numbers_that_are_converted():
     el, er = torch.ones(20, device="cuda") * -1, torch.zeros(ns, device="cuda")
     for slope in ("0.25", np.float64(0.25), torch.tensor(0.25)):
         assert torch.equal(B.fastgl_edge_score_fwd(ip, ix, el, er, slope), B.fastgl_edge_score_fwd(ip, ix, el, er, 0.25))
+
+
+def test_plan_is_an_ordinary_object():
+    """Attributes may be added and the handle handed on: to another Plan, or to any object that carries it."""
+    ip, ix, ns = small_blocks()[0]
+    X = torch.randn((ns, 4), device="cuda")
+    plan = B.fastgl_block_plan_create(ip, ix, ns)
+    assert isinstance(plan.handle, ctypes.c_void_p)
+    plan.epoch = 3
+    ref = B.fastgl_block_aggregate_fwd(ip, ix, None, ns, "gcn", X, plan=plan)
+    owner = B.Plan(plan.handle, plan.mem, ip, ix, ns)
+    plan.handle = None
+    plan.destroy()                                            # nothing left to destroy
+    for p in (owner, SimpleNamespace(handle=owner.handle), SimpleNamespace(handle=owner.handle.value)):
+        assert torch.equal(B.fastgl_block_aggregate_fwd(ip, ix, None, ns, "gcn", X, plan=p), ref)
+    assert owner.export().din
+    owner.destroy()
+    assert owner.handle is None
+    assert torch.equal(B.fastgl_block_aggregate_fwd(ip, ix, None, ns, "gcn", X, plan=owner), ref)   # as without a plan
