@@ -285,7 +285,8 @@ def fastgl_update_bwd(H: torch.Tensor, W: torch.Tensor, Y: Optional[torch.Tensor
                       workspace: Optional[torch.Tensor] = None):
     """Returns (dH, dW, db); parts not named in `want` (and not passed in) are None.  H, W, Y, dY, dH
     float32, or all bfloat16; dW and db are float32 either way."""
-    return _native().update_bwd(H, W, Y, dY, relu, "dH" in want, "dW" in want, "db" in want, dH, dW, db, workspace)
+    return _native().update_bwd(H, W, Y, dY, relu, dH is None and "dH" in want, dW is None and "dW" in want,
+                                db is None and "db" in want, dH, dW, db, workspace)
 
 
 def fastgl_idmap_table_slots(n_ids: int) -> int:
@@ -379,5 +380,5 @@ def fastgl_edge_score_bwd(indptr, indices, el: torch.Tensor, er: torch.Tensor, s
                           grad_er: Optional[torch.Tensor] = None):
     """(grad_el, grad_er); `want` selects which are computed when no array is passed in (the other is
     None).  grad_er needs a plan built with PLAN_BWD | PLAN_PERM."""
-    return _native().edge_score_bwd(indptr, indices, el, er, slope, grad_score, plan, "el" in want, "er" in want, grad_el,
-                                    grad_er)
+    return _native().edge_score_bwd(indptr, indices, el, er, slope, grad_score, plan, grad_el is None and "el" in want,
+                                    grad_er is None and "er" in want, grad_el, grad_er)

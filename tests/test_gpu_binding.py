@@ -104,3 +104,17 @@ def test_plan_is_an_ordinary_object():
     owner.destroy()
     assert owner.handle is None
     assert torch.equal(B.fastgl_block_aggregate_fwd(ip, ix, None, ns, "gcn", X, plan=owner), ref)   # as without a plan
+
+
+def test_want_is_not_asked_for_results_that_are_passed_in():
+    H, W, dY = (torch.randn(s, device="cuda") for s in ((5, 3), (3, 2), (5, 2)))
+    ref = B.fastgl_update_bwd(H, W, None, dY, False)
+    out = [torch.empty_like(t) for t in ref]
+    got = B.fastgl_update_bwd(H, W, None, dY, False, None, *out)
+    assert all(torch.equal(a, b) and a is c for a, b, c in zip(got, ref, out))
+    ip, ix, ns = small_blocks()[0]
+    plan = B.fastgl_block_plan_create(ip, ix, ns, B.PLAN_ALL | B.PLAN_PERM)
+    el, er, g = torch.randn(20, device="cuda"), torch.randn(ns, device="cuda"), torch.randn(ix.numel(), device="cuda")
+    ref = B.fastgl_edge_score_bwd(ip, ix, el, er, 0.2, g, plan)
+    got = B.fastgl_edge_score_bwd(ip, ix, el, er, 0.2, g, plan, None, torch.empty_like(el), torch.empty_like(er))
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
