@@ -80,13 +80,16 @@ fastgl_dtype feat_dtype(const at::Tensor &x)
     fail(PyExc_TypeError, "features must be float32 or bfloat16");
 }
 
-// Feature matrix: contiguous, on the device, float32 or bfloat16, two dimensions.
+// Two dimensions, or more of which the others are 1.
+bool matrix(const at::Tensor &x) { return x.dim() >= 2 && (x.dim() == 2 || x.numel() == x.size(0) * x.size(1)); }
+
+// Feature matrix: contiguous, on the device, float32 or bfloat16.
 const at::Tensor &features(PyObject *o, const char *name)
 {
     const at::Tensor &x = tensor(o, name);
     feat_dtype(x);
     dev(o, x.scalar_type(), name);
-    if (x.dim() != 2) {
+    if (!matrix(x)) {
         PyErr_Format(PyExc_ValueError, "%s must have two dimensions", name);
         throw Raised{};
     }
@@ -366,7 +369,7 @@ PyObject *update_fwd(PyObject *const *a)
 {
     const at::Tensor &H = features(a[0], "H"), &W = dev(a[1], H.scalar_type(), "W");
     const int64_t M = H.size(0), K = H.size(1);
-    if (W.dim() != 2 || W.size(0) != K) fail(PyExc_ValueError, "W must be [K,N] and bias [N]");
+    if (H.dim() != 2 || !matrix(W) || W.size(0) != K) fail(PyExc_ValueError, "W must be [K,N] and bias [N]");
     const int64_t N = W.size(1);
     const int relu = truth(a[3]);
     if (!none(a[2]) && !shape1(tensor(a[2], "bias"), N)) fail(PyExc_ValueError, "W must be [K,N] and bias [N]");
@@ -391,7 +394,7 @@ PyObject *layer_fwd(PyObject *const *a)
     const auto mode = (fastgl_agg_mode)integer(a[4]);
     const at::Tensor &X = features(a[5], "X"), &W = dev(a[6], X.scalar_type(), "W");
     const int64_t K = X.size(1);
-    if (X.size(0) != b.num_src || W.dim() != 2 || W.size(0) != K ||
+    if (X.size(0) != b.num_src || !matrix(W) || W.size(0) != K ||
         (!none(a[7]) && !shape1(tensor(a[7], "bias"), W.size(1))))
         fail(PyExc_ValueError, "X must be [num_src,K], W [K,N], bias [N]");
     const int64_t N = W.size(1);
@@ -416,7 +419,7 @@ PyObject *update_bwd(PyObject *const *a)
     const at::Tensor &H = features(a[0], "H"), &W = dev(a[1], H.scalar_type(), "W"), &dY = dev(a[3], H.scalar_type(), "dY");
     const void *Y = none(a[2]) ? nullptr : dev(a[2], H.scalar_type(), "Y").data_ptr();
     const int64_t M = H.size(0), K = H.size(1);
-    const bool fits = W.dim() == 2 && W.size(0) == K && shape2(dY, M, W.size(1)) &&
+    const bool fits = H.dim() == 2 && matrix(W) && W.size(0) == K && shape2(dY, M, W.size(1)) &&
                       (none(a[2]) || shape2(tensor(a[2], "Y"), M, W.size(1)));
     if (!fits) fail(PyExc_ValueError, "shapes must be H [M,K], W [K,N], Y and dY [M,N]");
     const int64_t N = W.size(1);
@@ -487,7 +490,7 @@ PyObject *assemble_rows(PyObject *const *a)
     const at::Tensor &prev = features(a[0], "X_prev"), &load = dev(a[1], prev.scalar_type(), "X_load");
     const at::Tensor &row = dev(a[2], at::kInt, "src_row");
     const int64_t feat = prev.size(1), n = row.numel(), n_load = integer(a[3]);
-    if (load.dim() != 2 || load.size(1) != feat || load.size(0) < n_load)
+    if (!matrix(load) || load.size(1) != feat || load.size(0) < n_load)
         fail(PyExc_ValueError, "X_load must be [>= n_load, feat]");
     const Out out(a[4], prev.scalar_type(), {n, feat}, prev, "out");
     if (!shape2(out.t, n, feat)) fail(PyExc_ValueError, "out must be [n_new, feat]");

@@ -118,3 +118,17 @@ def test_want_is_not_asked_for_results_that_are_passed_in():
     ref = B.fastgl_edge_score_bwd(ip, ix, el, er, 0.2, g, plan)
     got = B.fastgl_edge_score_bwd(ip, ix, el, er, 0.2, g, plan, None, torch.empty_like(el), torch.empty_like(er))
     assert all(torch.equal(a, b) for a, b in zip(got, ref))
+
+
+def test_feature_matrices_with_further_dimensions_of_one():
+    ip, ix, ns = small_blocks()[0]
+    X, W = torch.randn((ns, 4), device="cuda"), torch.randn((4, 3), device="cuda")
+    ids = torch.arange(5, device="cuda")
+    ref = B.fastgl_block_aggregate_fwd(ip, ix, None, ns, "gcn", X)
+    assert torch.equal(B.fastgl_block_aggregate_fwd(ip, ix, None, ns, "gcn", X[..., None]), ref)
+    assert torch.equal(B.fastgl_gather_rows(X[..., None, None], ids), X[:5])
+    assert torch.equal(B.fastgl_update_fwd(ref, W[..., None], None, False), B.fastgl_update_fwd(ref, W, None, False))
+    for call in (lambda: B.fastgl_block_aggregate_fwd(ip, ix, None, ns, "gcn", X.view(ns, 2, 2)),
+                 lambda: B.fastgl_gather_rows(X.view(-1), ids), lambda: B.fastgl_update_fwd(ref[..., None], W, None, False)):
+        with pytest.raises(ValueError):
+            call()
