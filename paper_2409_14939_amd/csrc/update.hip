@@ -825,8 +825,9 @@ fastgl_status update_bwd(bool bf16, const void *H, const void *W, const void *Y,
         const int64_t rows = slab_rows(M, K, N), nslab = ceil_div(M, rows);
         const int64_t stride = K * N + N;
         float *part = (float *)workspace;
-        if (nslab > 0 && narrow(K, N) && dW) {
+        if (nslab > 0 && narrow(K, N)) {         // also for db alone: its bits do not depend on what else is asked for
             na.part = part; na.slab = rows;
+            if (!dW) na.H = nullptr;
             st = launch_narrow_dw(na, bf16, s);
             if (st != FASTGL_OK) return st;
         } else if (nslab > 0) {

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void k_narrow_dh(const NarrowArgs a, int G)
 
 // Partials of dW and db over one slab of rows (blockIdx.x) for 4 G columns of H (blockIdx.y): every
 // lane keeps the sums of its quad over the rows of its row lane, the 256 / G row lanes are added in LDS
-// in a fixed order.
+// in a fixed order.  H may be NULL: db alone.
 template <int NMAX, bool VEC, bool BF16>
 __global__ __launch_bounds__(256) void k_narrow_dw(const NarrowArgs a, int G)
 {
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void k_narrow_dw(const NarrowArgs a, int G)
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i][n] = 0.f;
     }
-    const bool mine = k < a.K;
+    const bool mine = a.H && k < a.K;
     for (int64_t m = beg + t / G; m < end; m += (int64_t)kRows * lanes) {
         float4 h[kRows];
         float z[kRows][NMAX];

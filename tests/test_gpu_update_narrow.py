@@ -2,7 +2,9 @@
 their lane groups: K around the lanes of a group and beyond one column block of dW, rows around the rows in
 flight and beyond one slab, quads and single elements, both data types."""
 import pytest
+import torch
 
+from paper_2409_14939_amd import binding as B
 from test_gpu_update import run_case, test_update_parity_bf16 as bf16_case
 
 pytestmark = pytest.mark.gpu
@@ -18,3 +20,14 @@ def test_narrow_update_parity(M, K, N):
 @pytest.mark.parametrize("M,K,N", [(1500, 64, 1), (300, 18, 7), (257, 260, 8)])
 def test_narrow_update_parity_bf16(M, K, N):
     bf16_case(M, K, N, M % 2 == 0)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("M,K,N", [(5000, 64, 1), (5001, 30, 3), (3001, 300, 8), (3000, 64, 9), (3000, 64, 47), (2000, 100, 256)])
+def test_results_do_not_depend_on_what_else_is_asked_for(M, K, N, dtype):
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    H, W, dY = (torch.randn(s, generator=g, device="cuda").to(dtype) for s in ((M, K), (K, N), (M, N)))
+    Y = B.fastgl_update_fwd(H, W, None, True)
+    full = B.fastgl_update_bwd(H, W, Y, dY, True)
+    for i, name in enumerate(("dH", "dW", "db")):
+        assert torch.equal(B.fastgl_update_bwd(H, W, Y, dY, True, want=(name,))[i], full[i]), name
