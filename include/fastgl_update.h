@@ -53,7 +53,7 @@ size_t fastgl_update_bwd_workspace_bytes(int64_t M, int64_t K, int64_t N);
 
 /* Eq. 2 backward.  Y is the forward OUTPUT and is read only when relu != 0
  * (it may be NULL otherwise).  Any of dH, dW, db may be NULL to skip that
- * result; dW and db need `workspace` (256-byte aligned, at least
+ * result (H is read for dW alone, W for dH alone); dW and db need `workspace` (256-byte aligned, at least
  * fastgl_update_bwd_workspace_bytes(M,K,N) bytes), dH alone does not. */
 fastgl_status fastgl_update_bwd(const float *H, const float *W, const float *Y, const float *dY,
                                 int64_t M, int64_t K, int64_t N, int relu,

@@ -836,6 +836,10 @@ fastgl_status update_bwd(bool bf16, const void *H, const void *W, const void *Y,
             g.b = Operand{dY, gate, N};
             g.c = part; g.ldc = N; g.c_slab = stride;
             g.R = K; g.C = N; g.Kc = M; g.slab = rows;
+            if (!H) {                            // db alone: column sums without a product
+                g.a = Operand{dY, nullptr, 0};
+                g.R = 0;
+            }
             g.split = 1; g.n_outer = nslab;
             g.colsum = part + K * N; g.colsum_slab = stride;
             st = launch_gemm<true, true, true, 2>(g, bf16, s, "fastgl_update_bwd (dW)");

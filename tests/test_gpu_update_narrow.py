@@ -31,3 +31,16 @@ def test_results_do_not_depend_on_what_else_is_asked_for(M, K, N, dtype):
     full = B.fastgl_update_bwd(H, W, Y, dY, True)
     for i, name in enumerate(("dH", "dW", "db")):
         assert torch.equal(B.fastgl_update_bwd(H, W, Y, dY, True, want=(name,))[i], full[i]), name
+
+
+@pytest.mark.parametrize("M,K,N", [(5001, 30, 3), (3000, 64, 9), (3001, 300, 130), (2000, 100, 256)])
+def test_db_alone_needs_neither_h_nor_w(M, K, N):
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    H, W, dY = (torch.randn(s, generator=g, device="cuda") for s in ((M, K), (K, N), (M, N)))
+    Y = B.fastgl_update_fwd(H, W, None, True)
+    ref = B.fastgl_update_bwd(H, W, Y, dY, True, want=("db",))[2]
+    db = torch.empty_like(ref)
+    ws = torch.empty(B.fastgl_update_bwd_workspace_bytes(M, K, N), dtype=torch.uint8, device="cuda")
+    B._check(B.lib().fastgl_update_bwd(None, None, B._ptr(Y), B._ptr(dY), M, K, N, 1, None, None, B._ptr(db), B._ptr(ws),
+                                       ws.numel(), B._stream()))
+    assert torch.equal(db, ref)
