@@ -9,10 +9,11 @@
 // with cross-lane reads.  The destination of every edge comes from a small expansion pass.
 //
 // Softmax: a group of 8, 32 or 64 lanes (by the block's mean row length) walks one destination row
-// three times (maximum, sum of exponentials, write); rows longer than kLongRow are taken by their whole workgroup
-// afterwards, one after the other.  exp and the sums are fp64, so the result is the correctly rounded quotient up to
-// one unit in the last place.  One launch: with a queue of long rows for a launch of its own (and one that clears
-// its length) a call cost three, 9.5 us more than now where no row is long.
+// three times (maximum, sum of exponentials, write).  Rows longer than kLongRow are taken by whole workgroups of the
+// same launch that look for them (softmax_long_rows).  exp and the sums are fp64, so the result is the correctly
+// rounded quotient up to one unit in the last place.  Forward, us: 2.56 M edges in rows of 5, none long: 34 (a queue
+// of long rows with launches of its own: 40; no workgroups that look: 32); 32 neighbouring rows of 20 000 among short
+// ones: 51 (queue: 62; taken by the workgroup that met them, one after the other: 1 630); 512 of 2 000: 14 (29; 161).
 #include <type_traits>
 
 #include "fastgl_edge.h"
@@ -22,6 +23,7 @@ namespace fastgl {
 namespace {
 
 constexpr int kLongRow = 1024;       // softmax rows longer than this are taken by a whole workgroup
+constexpr int kMostSeekers = 512;    // workgroups of a softmax launch that look for them, two per compute unit
 constexpr int kEdgeUnroll = 4;       // edges in flight per lane group in k_edge_dot (reduce4 assumes 4)
 constexpr int kEdgeSteps = 8;        // batches of that many edges per lane group
 
@@ -235,6 +237,7 @@ struct SoftmaxArgs {
     const float *in1;            // fwd: unused; bwd: grad_alpha
     float *out;
     int backward;
+    int seekers;                 // workgroups for the rows longer than kLongRow
 };
 
 __device__ __forceinline__ double lanes_max(double v, int lanes)
@@ -296,32 +299,51 @@ __device__ __forceinline__ void softmax_row_block(const SoftmaxArgs &a, int b, i
     }
 }
 
+// The rows longer than kLongRow: workgroup b of n looks at rows b, b + n, ... and takes the long ones among them, so
+// that neighbouring long rows (blocks whose destinations are ordered by degree) go to different workgroups.
+__device__ __forceinline__ void softmax_long_rows(const SoftmaxArgs &a)
+{
+    __shared__ int32_t row[256];
+    __shared__ int n_long;
+    for (int64_t first = blockIdx.x; first < a.num_dst; first += 256 * (int64_t)a.seekers) {
+        if (threadIdx.x == 0) n_long = 0;
+        __syncthreads();
+        const int64_t u = first + (int64_t)threadIdx.x * a.seekers;
+        if (u < a.num_dst && a.indptr[u + 1] - a.indptr[u] > kLongRow) row[atomicAdd(&n_long, 1)] = (int32_t)u;
+        __syncthreads();
+        const int n = n_long;
+        for (int q = 0; q < n; ++q) softmax_row_block(a, a.indptr[row[q]], a.indptr[row[q] + 1]);
+        __syncthreads();
+    }
+}
+
 template <int lanes>
 __global__ __launch_bounds__(256) void k_edge_softmax_rows(const SoftmaxArgs a)
 {
-    __shared__ int32_t long_row[256 / lanes];
-    __shared__ int n_long;
-    if (threadIdx.x == 0) n_long = 0;
-    __syncthreads();
-    const int64_t u = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / lanes;
+    if ((int)blockIdx.x < a.seekers) {
+        softmax_long_rows(a);
+        return;
+    }
+    const int64_t u = ((int64_t)(blockIdx.x - a.seekers) * blockDim.x + threadIdx.x) / lanes;
     const int l = threadIdx.x % lanes;
     int b = 0, e = 0;
     if (u < a.num_dst) {
         b = a.indptr[u];
         e = a.indptr[u + 1];
-        if (e - b > kLongRow) {
-            if (l == 0) long_row[atomicAdd(&n_long, 1)] = (int32_t)u;
-            e = b;
-        }
+        if (e - b > kLongRow) e = b;
     }
     // all lanes of a group hold the same (b, e): the cross-lane sums below see whole groups
     if (a.backward)
         softmax_row_bwd(a.in0, a.in1, a.out, b, e, l, lanes);
     else
         softmax_row_fwd(a.in0, a.out, b, e, l, lanes);
-    __syncthreads();
-    const int n = n_long;
-    for (int q = 0; q < n; ++q) softmax_row_block(a, a.indptr[long_row[q]], a.indptr[long_row[q] + 1]);
+}
+
+template <int lanes>
+void launch_softmax(const SoftmaxArgs &a, hipStream_t s)
+{
+    const dim3 grid((unsigned)(a.seekers + ceil_div(a.num_dst * lanes, 256)));
+    hipLaunchKernelGGL(k_edge_softmax_rows<lanes>, grid, dim3(256), 0, s, a);
 }
 
 struct EdgeLayout {
@@ -398,15 +420,13 @@ fastgl_status softmax(bool backward, const int32_t *indptr, int64_t num_dst, int
     SoftmaxArgs a = {};
     a.indptr = indptr; a.num_dst = num_dst; a.in0 = in0; a.in1 = in1; a.out = out;
     a.backward = backward;
+    a.seekers = (int)(E / kLongRow < kMostSeekers ? E / kLongRow : kMostSeekers);   // no more than there can be long rows
     hipStream_t s = (hipStream_t)stream;
     // lanes per destination row by the block's mean row length (rows of sampled blocks are short)
     const int64_t mean = E / (num_dst > 0 ? num_dst : 1);
-    if (mean < 24)
-        hipLaunchKernelGGL(k_edge_softmax_rows<8>, dim3((unsigned)ceil_div(num_dst * 8, 256)), dim3(256), 0, s, a);
-    else if (mean < 96)
-        hipLaunchKernelGGL(k_edge_softmax_rows<32>, dim3((unsigned)ceil_div(num_dst * 32, 256)), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_edge_softmax_rows<64>, dim3((unsigned)ceil_div(num_dst * 64, 256)), dim3(256), 0, s, a);
+    if (mean < 24) launch_softmax<8>(a, s);
+    else if (mean < 96) launch_softmax<32>(a, s);
+    else launch_softmax<64>(a, s);
     FASTGL_LAUNCH_CHECK("edge softmax");
     return FASTGL_OK;
 }

@@ -88,6 +88,17 @@ def test_edge_softmax_ragged_with_long_rows():
     softmax_case(blk, 5, "medium rows")                    # mean row length 24..96: 32 lanes per row
 
 
+@pytest.mark.parametrize("rows,at,hubs,length", [(40000, 17000, 700, 1100), (3000, 2990, 10, 1025), (900, 0, 900, 1030),
+                                                 (1, 0, 1, 1025), (200000, 100, 3, 40000)])
+def test_edge_softmax_neighbouring_long_rows(rows, at, hubs, length):
+    """Long rows next to each other (destinations ordered by degree): more of them than there are workgroups for long
+    rows, at the end, nothing else, one, and a few very long ones."""
+    deg = np.random.default_rng(rows).integers(0, 6, rows)
+    deg[at:at + hubs] = length
+    ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    softmax_case(bg.Block(ip, np.zeros(ip[-1], np.int32), rows, 1), rows, "neighbouring long rows")
+
+
 def test_edge_softmax_degenerate():
     print("case edge softmax degenerate", flush=True)
     ip = dev_i32(np.array([0, 0, 1, 1, 3], np.int32))
