@@ -1217,11 +1217,9 @@ static fastgl_status src_degrees(fastgl_plan *p, hipStream_t s)
 // them in stages: the small ones then ride along in launches that the others need anyway.
 static bool fits_once(const fastgl_plan *p, int parts, bool src_deg)
 {
-    const bool full = (parts & FASTGL_PLAN_BWD) != 0;
-    if (full || src_deg) {
-        if (p->num_edges > (full ? kOnceFullEdges : kOnceEdges) || p->num_src > kOnceSources) return false;
-    }
-    return p->num_dst <= (full ? kOnceRows : kOnceRowsFwd);
+    if (parts & FASTGL_PLAN_BWD) return p->num_edges <= kOnceFullEdges && p->num_src <= kOnceSourcesFull && p->num_dst <= kOnceRows;
+    if (src_deg) return p->num_edges <= kOnceEdges && p->num_src <= kOnceSources && p->num_dst <= kOnceRows;
+    return p->num_dst <= kOnceRowsFwd;
 }
 
 static fastgl_status build_once(fastgl_plan *const *plans, const int *parts, const bool *src_deg, int n, hipStream_t s)

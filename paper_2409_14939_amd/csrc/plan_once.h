@@ -3,8 +3,9 @@
 // A plan built in stages is a chain of 2 (forward only) to 9 launches, each of which waits for the one
 // before: for a block of a few thousand edges that is 20 us of launch latency around 2 us of work.  Here
 // nobody waits for anybody: every workgroup recomputes from the block's own arrays what it needs from the
-// others.  That costs reads (every bucket's workgroup scans all source ids, at most 256 KB out of L2) and is
-// why it stops at 65 535 edges (up to there an edge id and a row pointer fit 16 bits of LDS), full plans at 16 384.
+// others.  That costs reads (every bucket's workgroup scans all source ids, at most 256 KB out of L2) and chains of
+// steps in the workgroups that there is one of (the lists of long rows, a bucket's chunks): the limits below are where
+// those chains, growing with the block, take as long as the launches they save.
 //
 //   bucket      2 048 consecutive source ids: counts the edges per source of its bucket and the edges of the
 //               buckets before it, writes the bucket's rows of indptr_T, out-degrees, scale factors and row
@@ -12,11 +13,11 @@
 //               (counts per wavefront and source, column scan, lane match - as k_plan_buckets does); the
 //               destination row of an edge comes from a binary search in row pointers held in LDS
 //   source degrees  the first half of that, for a forward-only plan of a GCN-normalised pass
-//   long sources    one workgroup: degrees of all sources (32 768 at a time), ordered list of the long ones
+//   long sources    one workgroup: degrees of all sources, ordered list of the long ones
 //   destination rows  1 024 rows per workgroup: degrees, scale factors, row sets
 //   long destinations one workgroup: ordered list of the long destination rows
 //
-// 256 seeds, fan-out 5 (1 276 edges): 5 launches, 22 us -> 1 launch, see kOnceFullEdges for the other end.
+// 256 seeds, fan-out 5 (1 276 edges, 1 276 sources), us a plan: 24 in stages (9 launches), 11 here.
 #pragma once
 #include "plan_device.h"
 
@@ -27,16 +28,24 @@ constexpr int kBucketIds = 1 << kBucketBits;
 
 constexpr int kOnceThreads = 1024;
 constexpr int kOnceWaves = kOnceThreads / kWave;
-constexpr int kOnceEdges = 65535;          // 16-bit edge ids and row pointers; forward-only plans with source degrees
-// Full plans: two chunks of a bucket at most. One bucket's workgroup places its edges chunk by chunk, so a block whose
-// sources fall into few buckets is a chain: 44 080 edges over 10 359 sources 76 us here, 43 us in stages.
+// Limits, us a plan in one launch / in stages (calls one after the other; a call that is waited for adds 3 to both).
+// Edges of a forward-only plan with source degrees: 16-bit row pointers and edge ids; 65 535 edges: 14 / 19.
+constexpr int kOnceEdges = 65535;
+// Edges of a full plan: two chunks of a bucket at most. One bucket's workgroup places its edges chunk by chunk, so a
+// block whose sources fall into few buckets is a chain: 44 080 edges over 10 359 sources 76 / 43; 16 384: 20 / 35.
 constexpr int kOnceFullEdges = 16384;
-constexpr int kOnceRows = 24576;           // row pointers in LDS (backward plans)
-constexpr int kOnceRowsFwd = 65536;        // forward-only plans: what one workgroup scans for long rows
-constexpr int kOnceSources = 1 << 18;      // 128 buckets
+// Destination rows: one workgroup scans all of them for long ones, 1 024 a step.  Forward-only: 8 192 rows 6.7 / 8.4,
+// 16 384 rows 11 / 8.7, 65 536 rows 38 / 8.8, for any number of edges.  With source degrees (more launches to save)
+// and full plans (row pointers in LDS): 24 576 rows 16 / 18 and 22 / 29.
+constexpr int kOnceRowsFwd = 8192;
+constexpr int kOnceRows = 24576;
+// Sources of a full plan: one workgroup counts their degrees in LDS and scans them for long ones: 5 000 edges over
+// 32 768 sources 18 / 25, over 65 536 (two windows of counters) 33 / 25, over 262 144 127 / 25.  Source degrees alone
+// need no list: 128 buckets, 262 144 sources, 14 / 19.
+constexpr int kOnceSourcesFull = 32768;
+constexpr int kOnceSources = 1 << 18;
 constexpr int kOnceChunk = 8192;           // edges of a bucket placed at a time
 constexpr int kOnceRounds = kOnceChunk / kOnceThreads;   // 64-edge rounds per wavefront
-constexpr int kDegreeWindow = 32768;       // sources whose degrees the long-source workgroup holds at a time
 constexpr int kOnceMaxJobs = 8;
 static_assert(kBucketIds == 2 * kOnceThreads, "two sources per thread");
 
@@ -63,7 +72,7 @@ struct OnceShared {
             uint32_t list[kOnceChunk];                  // collected edges: id | source within the bucket << 16
             uint16_t rows[kOnceRows + 2];               // indptr
         };
-        unsigned degree[kDegreeWindow / 2];             // 16-bit counters, two to a word
+        unsigned degree[kOnceSourcesFull / 2];          // 16-bit counters, two to a word
     };
 };
 constexpr size_t kOnceLdsDegrees = sizeof(int) * kBucketIds;   // a forward-only plan needs no more than this
@@ -100,11 +109,12 @@ struct KeyRun {
     }
 };
 
-// Ordered list of the rows (of a window that starts at row `first`) longer than the threshold; nl, nc: how many
-// rows and chunks precede them.  len(i): length of the window's row i.
+// Ordered list of the rows longer than the threshold, their chunks, and how many there are of both.  len(i): length
+// of row i; n = 0: none can be long.
 template <class LEN>
-__device__ __forceinline__ void once_long_rows(const RowsArgs &A, int64_t first, int n, int &nl, int &nc, int *lds, LEN len)
+__device__ __forceinline__ void once_long_rows(const RowsArgs &A, int n, int *lds, LEN len)
 {
+    int nl = 0, nc = 0;
     for (int base = 0; base < n; base += kOnceThreads) {
         const int i = base + threadIdx.x;
         const int l = i < n ? len(i) : 0;
@@ -114,16 +124,12 @@ __device__ __forceinline__ void once_long_rows(const RowsArgs &A, int64_t first,
         int tl, tc;
         const int el = block_excl_scan(isl, &tl, lds), ec = block_excl_scan(nch, &tc, lds);
         if (isl) {
-            A.long_rows[nl + el] = (int32_t)(first + i);
+            A.long_rows[nl + el] = (int32_t)i;
             A.chunk_ptr[nl + el] = nc + ec;
         }
         nl += tl;
         nc += tc;
     }
-}
-
-__device__ __forceinline__ void once_totals(const RowsArgs &A, int nl, int nc)
-{
     if (threadIdx.x != 0) return;
     A.chunk_ptr[nl] = nc;
     A.totals[0] = nl;
@@ -248,21 +254,16 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, OnceShared 
 
 __device__ __forceinline__ void once_long_sources(const OnceJob &J, OnceShared &M, int *lds)
 {
-    const KeyRun run(J.indices, J.num_edges);
-    int nl = 0, nc = 0;
-    for (int64_t first = 0; first < J.num_src && J.num_edges > kLongThreshold; first += kDegreeWindow) {
-        for (int i = threadIdx.x; i < kDegreeWindow / 2; i += kOnceThreads) M.degree[i] = 0;
+    const int n = J.num_edges > kLongThreshold ? J.num_src : 0;
+    if (n > 0) {
+        for (int i = threadIdx.x; i < kOnceSourcesFull / 2; i += kOnceThreads) M.degree[i] = 0;
         __syncthreads();
-        run.each([&](int, int32_t key, bool ok) {
-            const int64_t k = key - first;
-            if (ok && k >= 0 && k < kDegreeWindow) atomicAdd(&M.degree[k >> 1], 1u << ((k & 1) * 16));
+        KeyRun(J.indices, J.num_edges).each([&](int, int32_t k, bool ok) {
+            if (ok && (uint32_t)k < (uint32_t)kOnceSourcesFull) atomicAdd(&M.degree[k >> 1], 1u << ((k & 1) * 16));
         });
         __syncthreads();
-        const int n = J.num_src - first < kDegreeWindow ? (int)(J.num_src - first) : kDegreeWindow;
-        once_long_rows(J.src, first, n, nl, nc, lds, [&](int i) { return (int)((M.degree[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu); });
-        __syncthreads();
     }
-    once_totals(J.src, nl, nc);
+    once_long_rows(J.src, n, lds, [&](int i) { return (int)((M.degree[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu); });
 }
 
 // Workgroups of a job, in this order: buckets, long sources (with the transpose), long destinations, row groups.
@@ -286,11 +287,8 @@ __global__ __launch_bounds__(kOnceThreads) void k_plan_once(OnceArgs A)
     }
     b -= J.full ? 1 : 0;
     if (b == 0) {
-        int nl = 0, nc = 0;
         const int32_t *p = J.indptr;
-        if (J.num_edges > kLongThreshold)
-            once_long_rows(J.dst, 0, J.num_dst, nl, nc, lds, [&](int i) { return p[i + 1] - p[i]; });
-        once_totals(J.dst, nl, nc);
+        once_long_rows(J.dst, J.num_edges > kLongThreshold ? J.num_dst : 0, lds, [&](int i) { return p[i + 1] - p[i]; });
         return;
     }
     const int64_t r = (int64_t)(b - 1) * kOnceThreads + threadIdx.x;

@@ -66,3 +66,28 @@ def test_forward_only_plan_with_source_degrees(nd, ns, edges, hub):
 @pytest.mark.parametrize("edges", [16384, 16385])
 def test_full_plan_around_the_edge_limit(edges):
     check_bookkeeping(exact_block(np.random.default_rng(edges), 3000, 4097, edges, 9000), "once")
+
+
+@pytest.mark.parametrize("nd,ns,edges,hub", [(3000, 32768, 16384, 300), (3000, 32769, 16384, 300), (24576, 32768, 16384, 300),
+                                             (24577, 32768, 16384, 300), (100, 32768, 16384, 0)])
+def test_full_plan_around_the_limits_of_rows_and_sources(nd, ns, edges, hub):
+    blk = exact_block(np.random.default_rng(nd + ns), nd, ns, edges, hub)
+    blk.indices[-900:] = ns - 1                                # the last source is a long row of the transpose
+    check_bookkeeping(blk, "once")
+
+
+@pytest.mark.parametrize("nd", [8192, 8193, 24576, 24577])
+@pytest.mark.parametrize("parts", [B.PLAN_FWD, B.PLAN_FWD | B.PLAN_SRC_DEG])
+def test_forward_only_plan_around_the_row_limits(nd, parts):
+    ns, edges = 30000, 50000
+    blk = exact_block(np.random.default_rng(nd), nd, ns, edges, 5000)
+    plan = B.fastgl_block_plan_create(dev_i32(blk.indptr), dev_i32(blk.indices), ns, parts)
+    v = plan.export()
+    din, dout = oracle.degrees(blk.indptr, blk.indices, ns)
+    assert np.array_equal(read_i32(plan, v.din, nd), din)
+    if parts & B.PLAN_SRC_DEG:
+        assert np.array_equal(read_i32(plan, v.dout, ns), dout)
+    rows, cptr = oracle.long_rows(blk.indptr, B.fastgl_long_row_threshold(), B.fastgl_long_row_chunk())
+    cnt = read_i32(plan, v.counters, 2)
+    assert cnt[0] == rows.shape[0] and cnt[1] == cptr[-1]
+    assert np.array_equal(read_i32(plan, v.long_dst, rows.shape[0]), rows)
