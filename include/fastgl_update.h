@@ -16,12 +16,17 @@
  * into three bf16 pieces whose sum is the element exactly, and six of the nine
  * piece products are added up, which leaves a relative error of at most 2^-23
  * (2^-28 on average) in a product of two elements - the accuracy of an fp32
- * multiply-add chain, at several times its speed.  An input element that is
- * not finite, or larger in magnitude than the largest bf16 (3.39e38), turns
- * every result it enters into NaN.  With N <= 8 the products are bound by
- * memory and are formed by plain fp32 multiply-adds instead.  dW and db are reduced over fixed slabs of
- * rows whose partial results are summed in fp64 in a fixed order, so results
- * do not depend on scheduling.
+ * multiply-add chain, at several times its speed.  With N <= 8 the products
+ * are bound by memory and may be formed by plain fp32 multiply-adds instead,
+ * whichever is the faster for the shape.
+ * Elements that are not finite: every result that such an element enters is not
+ * finite, and no other result changes (a ReLU turns NaN into 0, and what it
+ * closes in the backward pass does not enter).  From bf16 pieces it is NaN, also
+ * for finite elements larger in magnitude than the largest bf16 (3.39e38), whose
+ * first piece is infinite; from multiply-adds, from bf16 storage and in db it is
+ * what IEEE arithmetic gives, infinity or NaN.
+ * dW and db are reduced over fixed slabs of rows whose partial results are
+ * summed in fp64 in a fixed order, so results do not depend on scheduling.
  *
  * Conventions are those of fastgl_agg.h: every array is DEVICE memory owned by
  * the caller, the library allocates nothing, work is enqueued on `stream`
