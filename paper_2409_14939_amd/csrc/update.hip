@@ -682,16 +682,21 @@ fastgl_status check_dims(int64_t M, int64_t K, int64_t N)
     return FASTGL_OK;
 }
 
-// Few result columns: plain multiply-adds instead of matrix-core tiles (update_narrow.hip).  Up to 8
-// columns the tiled kernel, which always works on 128, loses at every M and K (N = 8: 8 multiply-adds
-// per element read cost less than reading it).  K beyond the grid's second dimension stays here.
+// Few result columns: plain multiply-adds instead of matrix-core tiles (update_narrow.hip).  dW with the reduction, us
+// with cold caches, K = 64, tiles of 128 columns -> multiply-adds: N = 1: 20 000 rows 38 -> 11, 1.15 M 358 -> 114;
+// N = 8: 27 -> 14, 235 -> 143.  Y and dH: see kNarrowRows.  K beyond the grid's second dimension stays here.
 bool narrow(int64_t K, int64_t N) { return N >= 1 && N <= kNarrowCols && K > 0 && K <= (int64_t)1 << 20; }
 
 // With more rows than this, Y with few columns comes from the tall tiles of update_rows.hip (32 columns wide) too,
-// and so does dH with 5 to 8.  For one column they are slower (M = 1.15 M, K = 64, N = 1: Y 75 us against 53), but
-// they add the same terms in the same order as for every other shape: where the sum of two such projections decides by
-// its sign (LeakyReLU of a GAT head over millions of edges), another order would turn a few of those signs.  From
-// three columns on they are faster (M = 500 K, K = 64, N = 7: Y 40 us against 63, dH 36 against 64).
+// and so does dH with 5 to 8.  us a call with cold caches, multiply-adds / tall tiles, K = 64:
+//   Y   N = 1: 20 000 rows 7.6 / 9.2, 512 K 49 / 53, 1.15 M 98 / 103;   N = 2: 9.7 / 9.4, 56 / 54, 106 / 104;
+//       N = 4: 13 / 9, 89 / 55, 189 / 104;   N = 8: 20 / 9, 183 / 56, 398 / 108
+//   dH  N = 1: 6.4 / 9.7, 29 / 51, 59 / 104;   N = 3: 6.9 / 10.5, 42 / 71, 91 / 145;   N = 4: 9.1 / 8.9, 68 / 47,
+//       143 / 101;   N = 8: 13 / 9, 127 / 47, 274 / 98
+// So beyond the line Y is faster on tall tiles from two columns on, dH from four (the rule sends it there from five).
+// Y with one column is not (in the step of an attention head, part of H still in the Infinity Cache, 1.15 M rows took
+// 53 / 82): it stays with them because another order of terms would turn a few of millions of LeakyReLU signs from
+// what earlier versions of the library gave.  Below the line the order is the multiply-adds'.
 constexpr int64_t kNarrowRows = 16384;
 
 // Rows per slab: a function of the shape alone, so results do not depend on the device or the run.

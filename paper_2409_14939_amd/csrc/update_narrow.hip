@@ -7,7 +7,9 @@
 // per step.  Here a group of G lanes (a power of two, quads of four elements per lane) covers a row, as
 // in the aggregation kernel, and several rows are in flight per lane; products are plain fp32
 // multiply-adds (one rounding per term, sums of four lanes' chains added pairwise).
-// M = 1 150 398, K = 64, N = 1, fp32: Y 235 -> 53 us, dH 148 -> 53 us, dW 239 -> 45 us (6.5 TB/s).
+// M = 1 150 398, K = 64, N = 1, fp32, us in the step of an attention head (part of H still in the Infinity Cache):
+// dH 148 -> 55, dW 239 -> 47 (6.3 TB/s); a call with cold caches, the reduction included: 152 -> 59, 358 -> 114.
+// Y comes from here for up to kNarrowRows rows (update.hip): 20 000 rows 18.7 -> 7.6.
 #include "update_internal.h"
 
 namespace fastgl {

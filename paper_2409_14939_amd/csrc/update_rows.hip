@@ -16,13 +16,17 @@
 //     operands up front (no staging, no barrier before the end) and the four partial tiles are added in
 //     LDS.
 //
-// fp32, us before (128 x 128 tiles, both operands through LDS) -> now:  M = 1.15 M, 100 -> 64: 331 -> 194;  512 K,
-// 100 -> 256: 257 -> 215 (730 MB at 3.4 TB/s);  91 K, 256 -> 256: 95 -> 80 (900 TFLOP/s of plane products; a large bf16
-// product reaches 1 135 here);  1 000, 256 -> 256: 26 -> 7;  16, 256 -> 47: 22 -> 6.  bf16: 221 -> 64, 169 -> 106,
-// 54 -> 34, 22 -> 5, 18 -> 4.
+// us a call with cold caches, before (128 x 128 tiles, both operands through LDS) -> now, fp32 (bf16):
+//   Y   M = 1.15 M, 100 -> 64: 381 -> 225 (251 -> 131);  512 K, 100 -> 256: 257 -> 253, 730 MB at 2.9 TB/s (185 -> 138);
+//       91 K, 256 -> 256: 97 -> 86, 835 TFLOP/s of plane products where a large bf16 product reaches 1 135 (62 -> 43);
+//       1 000, 256 -> 256: 34 -> 10 (29 -> 8);  16, 256 -> 47: 30 -> 9 (27 -> 7)
+//   dH  M = 1.15 M, 64 -> 100: 290 -> 232, gated 347 -> 280;  91 K, 256 -> 256: 91 -> 94, gated 109 -> 122 (a second set
+//       of octets per step: the one shape that lost)
 //
-// A step of 16 contracted indices goes into one matrix instruction per plane product (lane half h: indices 8 h .. + 7)
-// and the steps are added in ascending order, whatever the tile: results do not depend on the tile's width.
+// A step of 16 contracted indices goes into one matrix instruction per plane product (lane half h: indices 8 h .. + 7).
+// Tall tiles add the steps in ascending order, so results do not depend on a tile's width; small tiles add four
+// partial sums of consecutive steps.  The tall loop runs whole turns of 32 indices (64 with 64 columns or fewer): K = 100
+// costs eight steps.
 #include <type_traits>
 
 #include "update_internal.h"

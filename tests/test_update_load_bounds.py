@@ -1,8 +1,9 @@
-"""Host-side model of every global load address of the update kernel (csrc/update.hip: PlaneMover
-init / nvalid / fetch and run_steps), checked against the extents of the operands: no lane of any
-workgroup may read outside [0, numel) of the matrix it loads from, including the masked lanes (which
-load the first element of the tile's first step) and the look-ahead fetch of the step after the
-last one.  The model mirrors the kernel's index arithmetic line by line; it has to be changed with
+"""Host-side model of every global load address of the tiled update kernel (csrc/update.hip: PlaneMover
+and HalfMover init / nvalid / fetch and run_steps), checked against the extents of the operands: no
+lane of any workgroup may read outside [0, numel) of the matrix it loads from, including the masked
+lanes (which load the first element of the tile's first step) and the look-ahead fetch of the step
+after the last one.  The kernel forms dW and db (two "col" operands); the model also covers its tiles
+on "row" operands.  The row products' own kernels: test_update_tall_bounds.py.  The model mirrors the kernel's index arithmetic line by line; it has to be changed with
 it."""
 import random
 
@@ -90,6 +91,36 @@ def test_every_load_of_the_update_kernel_stays_inside_its_operand():
     shapes = SHAPES + [(rng.randint(1, 700), rng.randint(1, 300), rng.randint(1, 300)) for _ in range(200)]
     for M, K, N in shapes:
         assert all_products_in_bounds(M, K, N), (M, K, N)
+
+
+def half_tile_in_bounds(M, N, vec, slab, first_row_of_missing_step=0):
+    """dY as the operand of 64 columns (N <= 64): two columns of two contracted rows per lane."""
+    t = np.arange(256)
+    for kbeg, kend in {(0, min(slab, M)), ((M - 1) // slab * slab, M)}:
+        nstep = max((kend - kbeg + K_STEP - 1) // K_STEP, 1)
+        n_plain = max(0, min((kend - kbeg) // K_STEP - 1 if vec and N == 64 else 0, nstep - 1))
+        for k, mask in [(kbeg, True)] + [(kbeg + K_STEP * (i + 1), i >= n_plain) for i in range(nstep)]:
+            origin = (k if k < kend else first_row_of_missing_step) * N
+            for s in range(2):
+                off = (2 * (t >> 5) + s) * N + 2 * (t & 31)
+                n = np.clip(N - 2 * (t & 31), 0, 2)
+                n = np.where(k + 2 * (t >> 5) + s < kend, n, 0) if mask else np.full(256, 2)
+                if vec:
+                    last = origin + np.where(n == 2, off, 0) + 1
+                else:
+                    last = origin + np.maximum(np.where(n > 0, off, 0), np.where(n > 1, off + 1, 0))
+                if last.max() >= M * N:
+                    return False
+    return True
+
+
+def test_every_load_of_the_narrow_tile_stays_inside_its_operand():
+    rng = random.Random(2)
+    shapes = [(1150398, 64), (8000, 47), (1, 9), (31, 10), (33, 32), (1001, 64), (16, 64), (17, 12)]
+    for M, N in shapes + [(rng.randint(1, 700), rng.randint(9, 64)) for _ in range(200)]:
+        for vec in ((True, False) if N % 4 == 0 else (False,)):
+            assert half_tile_in_bounds(M, N, vec, slab_rows(M, 100, N)), (M, N, vec)
+    assert not half_tile_in_bounds(1001, 64, True, slab_rows(1001, 100, 64), 1001)
 
 
 def test_the_model_sees_a_fetch_past_the_last_step():

@@ -2,7 +2,9 @@
 buffers: an access whose offset is at or past the buffer's size is dropped (a store) or gives 0 (a load).
 Results: a tile's rows past the last one are not masked, only dropped that way; no element outside the result may
 survive, for any remainder of rows and columns and either element size.  Column operand (W of the forward pass): rows
-past the last one are not masked either; every one of their elements must come back as 0.  The model mirrors the kernel's index arithmetic; it has to be changed with it."""
+past the last one are not masked either; every one of their elements must come back as 0.  Rows loaded eight elements
+at a time (load_at, load_oct, buffer_oct; the small tiles have no buffer around them): every load lies inside its row,
+or, for rows of odd length in bf16, in the aligned dword that holds the row's last element.  The model mirrors the kernel's index arithmetic; it has to be changed with it."""
 import random
 
 import numpy as np
@@ -74,3 +76,38 @@ def test_rows_of_a_column_operand_past_the_last_one_are_zero():
         for eb in (2, 4):
             assert column_operand_ends(K, N, eb), (K, N, eb)
     assert not column_operand_ends(101, 47, 2, whole_dwords)
+
+
+def row_load_bytes(V, k, K, row):
+    """[first, last] byte of the loads of elements k .. k + 7 of a row of K elements that starts at byte `row`."""
+    if V == 4:                                                # fp32: two quads
+        at = [min(k + 4 * i, K - 4) for i in range(2)]
+        return row + 4 * min(at), row + 4 * max(at) + 15
+    if V == 8:                                                # bf16, rows of whole dwords
+        at = row + 2 * min(k, K - 8)
+        return at, at + 15
+    if V == 9:                                                # bf16, odd rows: the five dwords around eight elements
+        at = row + 2 * min(k, K - 8)
+        base = at & ~3
+        return base, base + (16 if at & 2 else 12) + 3
+    eb = 4 if V == 1 else 2                                   # element by element
+    at = [k + i if k + i < K else 0 for i in range(8)]
+    return row + eb * min(at), row + eb * max(at) + eb - 1
+
+
+def test_row_loads_stay_inside_their_rows():
+    for V, eb, lengths in ((4, 4, range(4, 70)), (8, 2, range(8, 70, 2)), (9, 2, range(9, 70, 2)), (1, 4, range(1, 20)), (2, 2, range(1, 70))):
+        for K in lengths:
+            for r in range(3):                                # the third row is the matrix's last
+                row, end = r * K * eb, 3 * K * eb
+                for k in range(0, K + 128, 8):
+                    first, last = row_load_bytes(V, k, K, row)
+                    if V == 9:
+                        assert first >= 0 and last < whole_dwords(row + K * eb) <= whole_dwords(end), (V, K, r, k)
+                    else:
+                        assert row <= first and last < row + K * eb, (V, K, r, k)
+
+
+def test_offsets_inside_a_tile_fit_32_bits():
+    """Rows of up to 2^21 elements: the last element that a tile of 256 rows may ask for lies below 2^31 bytes."""
+    assert 255 * (1 << 21) * 4 + (1 << 21) * 4 - 1 < 1 << 31
