@@ -3,25 +3,34 @@
 //
 //   out[r,:] = rowscale(len_r) * sum_{k in row r} a_k * colscale[col_k] * in[col_k,:]
 //
-// Mapping to the machine.  A feature row is cut into slices of VB bytes (16 when
-// the row size allows, so one lane moves one dwordx4) and a "group" of G lanes
-// (a power of two, <= 64) covers G consecutive slices.  One group owns a set of
+// Mapping to the machine.  A feature row is cut into slices of 16 bytes (rows of
+// any length: the last slice ends with the row) and a "group" of G lanes (a power
+// of two, 4 to 64) covers G consecutive slices.  A wavefront owns a set of
 // consecutive rows (x one column tile) from start to end, so each output element
 // has a single writer and the summation order is fixed: results do not depend on
 // scheduling.  The row sets come from the plan and carry equal work (edges +
-// rows), so skewed degree distributions do not overload a group.
+// rows), and the groups of a wavefront share its edges equally (walk_flat), so
+// skewed degree distributions overload neither a wavefront nor a group.
 // The partial sum lives in registers (the paper keeps it in shared memory on its
 // GPU; with one lane per slice registers serve the same purpose at no traffic).
 // The lanes of a group fetch column ids and weights with one coalesced load and
-// hand them round with cross-lane reads, then issue up to 6 independent row
+// hand them round with cross-lane reads, then issue up to 8 independent row
 // gathers before the first use.  Output rows leave with streaming stores.
+//
+// Bound by the fabric (random rows: 7.1 TB/s from the Infinity Cache, 5.5-6 from HBM) where a block is large, by the
+// chain of dependent loads (row sets, row pointers, column ids, weights, rows) and the fetch of the code where it is
+// small.  Measured, us, rows walked by one group each / shared by the groups of a wavefront:
+//   all neighbours of 65 536 nodes (rows of up to 256 edges and chunks of longer ones), 32 columns: forward 149 / 96,
+//   backward 123 / 84;  of 5 313 nodes, 8 columns bf16, both directions: 391 / 20 (a group was a single lane)
+//   reddit-shaped layer, 602 columns (8-byte slices, five column tiles / 16-byte slices, three): 83 / 81, 100 / 92
+//   256 rows, 64 columns: 4.6 / 4.0, backward 8.2 / 5.4
+//   rows of 404 and 256 bytes, 2.56 M edges: 217 / 218, 105 / 108 - nothing to share out there
 //
 // f32 rows accumulate in fp64, bf16 rows in fp32; one rounding at the store.
 //
-// Rows longer than kLongThreshold edges are not walked by one group: they are
-// cut into chunks of kLongChunk edges that any group can take (in the same
-// launch); the partial sums go to the workspace and are added in chunk order by
-// a second, small kernel, so the result is still deterministic.
+// Rows longer than kLongThreshold edges are cut into chunks of kLongChunk edges that any
+// wavefront can take (in the same launch); the partial sums go to the workspace and are
+// added in chunk order by a second, small kernel, so the result is still deterministic.
 #include "pull_walk.h"
 
 namespace fastgl {
@@ -29,47 +38,39 @@ namespace fastgl {
 constexpr int kXcdRun = 16;
 constexpr int kReduceBlocks = 1024;   // workgroups for the long rows, whose number the host does not know
 
-// Which (row set, column tile) a lane group works on.
+// Which (row sets, column tile) a wavefront works on.
 //
 // Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2.
-// Consecutive logical workgroups are handed to an XCD in runs of P.xcd_run, so
+// Consecutive logical workgroups are handed to an XCD in runs of kXcdRun, so
 // that neighbouring rows (which share output cache lines and first-touch source
 // rows) share an L2, while every XCD still samples the whole row range: blocks
 // whose hubs all sit at low ids stay balanced.  The column tiles of a row set
-// (rows wider than 64 slices) sit in neighbouring groups.
-struct GroupId {
-    int64_t g;        // index of the group's first fine row set / P.sets_per_group
+// (rows wider than 64 slices) sit in neighbouring wavefronts.
+struct WaveId {
+    int64_t w;        // index of the wavefront's first fine row set / P.sets_per_wave
     int tile;         // column tile
-    int64_t count;    // launched groups per tile (chunk stride)
 };
 
-template <bool WAVE>
-__device__ __forceinline__ GroupId map_group(const PullParams &P)
+__device__ __forceinline__ WaveId map_wave(const PullParams &P)
 {
-    const int gpb = kBlock / (WAVE ? kWave : P.G);
-    const int64_t x = blockIdx.x % kXcds, q = blockIdx.x / kXcds;
-    const int64_t lb = ((q / P.xcd_run) * kXcds + x) * P.xcd_run + q % P.xcd_run;
-    // a whole wavefront's group is a scalar
-    const int in_block = threadIdx.x / (WAVE ? kWave : P.G);
-    const int64_t vg = lb * gpb + (WAVE ? __builtin_amdgcn_readfirstlane(in_block) : in_block);
-    const int64_t launched = P.num_blocks * gpb;
-    GroupId r;
-    r.tile = (int)(vg % P.ntiles);
-    r.g = vg / P.ntiles;
-    r.count = (launched - r.tile + P.ntiles - 1) / P.ntiles;
+    const uint32_t x = blockIdx.x % kXcds, q = blockIdx.x / kXcds;
+    const uint64_t lb = ((uint64_t)(q / kXcdRun) * kXcds + x) * kXcdRun + q % kXcdRun;
+    const uint64_t v = lb * (kBlock / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    WaveId r;
+    r.w = P.ntiles > 1 ? (int64_t)__umul64hi(v, P.tile_inv) : (int64_t)v;     // v < 2^34, ntiles < 2^20: exact
+    r.tile = (int)(v - (uint64_t)r.w * (uint32_t)P.ntiles);
     return r;
 }
 
 // Chunks of long rows.  The number of chunks lives in device memory, so the host
-// never needs to know the degrees; the groups of a column tile stride over the
+// never needs to know the degrees; the wavefronts of a column tile stride over the
 // chunks and write fp64 / fp32 partial sums of their tile to the workspace.
-template <int DT, int VB, int W, int U, bool WAVE>
-__device__ __forceinline__ void pull_chunks(const PullParams &P, const GroupId &id, int sub, int gbase)
+template <int DT, int VB, int W, int U, bool WAVE, bool BATCH>
+__device__ __forceinline__ void pull_chunks(const PullParams &P, Window<DT, VB> &win, int n_long,
+                                            int64_t total, const WaveId &id, int lane, int64_t lane_off, bool active)
 {
-    const int n_long = *P.n_long;
-    const int64_t total = *P.n_chunks;
-    const int64_t lane_off = ((int64_t)id.tile * (WAVE ? kWave : P.G) + sub) * VB;
-    for (int64_t chunk = id.g; chunk < total; chunk += id.count) {
+    if (id.w >= P.chunk_waves) return;
+    for (int64_t chunk = id.w; chunk < total; chunk += P.chunk_waves) {
         int lo = 0, hi = n_long;   // chunk_ptr[lo] <= chunk < chunk_ptr[hi]
         while (hi - lo > 1) {
             int mid = lo + ((hi - lo) >> 1);
@@ -79,44 +80,50 @@ __device__ __forceinline__ void pull_chunks(const PullParams &P, const GroupId &
         const int rbeg = P.rowptr[row], rend = P.rowptr[row + 1];
         const int beg = rbeg + ((int)chunk - P.chunk_ptr[lo]) * kLongChunk;
         const int end = beg + kLongChunk < rend ? beg + kLongChunk : rend;
-        const bool active = lane_off < P.row_bytes;
         const RowStore<DT, VB> unused = {nullptr, 0, 0, false};     // a chunk's sum goes to the partial-sum buffer
-        if constexpr (WAVE) walk_wave<DT, VB, W, true, U>(P, chunk, 0, 1, beg, end, 0, sub, lane_off, active, unused);
-        else walk_run<DT, VB, W, true, U>(P, chunk, 0, 1, beg, end, 0, sub, gbase, lane_off, active, unused);
+        if constexpr (WAVE) walk_wave<DT, VB, W, true, U>(P, chunk, 0, 1, beg, end, 0, lane, lane_off, active, unused);
+        else walk_flat<DT, VB, W, true, U, BATCH>(P, win, chunk, 0, 1, beg, end, lane, lane_off, active, unused);
     }
 }
 
-// One launch covers every row.  Each group first takes its share of the long-row
-// chunks (usually none), then its own row set: the consecutive rows
+// One launch covers every row.  Each wavefront first takes its share of the long-row
+// chunks (usually none), then its own rows: the consecutive rows
 // of a few fine row sets, which the plan cut so that every set carries the same
 // work (edges + rows), whatever the degree distribution is.  Rows that are long
 // are skipped here; k_reduce_chunks finishes them.
-template <int DT, int VB, int W, int U, bool WAVE>
+template <int DT, int VB, int W, int U, bool WAVE, bool BATCH>
 __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
 {
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int G = WAVE ? kWave : P.G;
-    const int sub = tid & (G - 1), gbase = lane & ~(G - 1);
-    const GroupId id = map_group<WAVE>(P);
-    if (P.long_rows) pull_chunks<DT, VB, W, U, WAVE>(P, id, sub, gbase);
-    if (id.g >= P.ngroups) return;
-    const int64_t lane_off = ((int64_t)id.tile * G + sub) * VB;
-    const bool active = lane_off < P.row_bytes;
-    const int64_t s0 = id.g * P.sets_per_group;
-    const int64_t s1 = s0 + P.sets_per_group < P.nsets ? s0 + P.sets_per_group : P.nsets;
-    const int64_t rbeg = P.split[s0], rend = P.split[s1];
-    const unsigned long long gmask = G == kWave ? ~0ull : ((1ull << G) - 1ull);
-    const RowStore<DT, VB> sink = {P.out, P.row_bytes, lane_off, active};
     using acc_t = typename Slice<DT, VB>::acc_t;
-    for (int64_t r0 = rbeg; r0 < rend; r0 += G) {
-        const int nrows = rend - r0 < G ? (int)(rend - r0) : G;
+    __shared__ Window<DT, VB> windows[WAVE ? 1 : kBlock / kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    Window<DT, VB> &win = windows[WAVE ? 0 : threadIdx.x / kWave];
+    const WaveId id = map_wave(P);
+    const int64_t slice = WAVE ? (int64_t)id.tile * kWave + lane : lane & (P.G - 1);
+    const int64_t lane_off = slice_offset<VB>(P, slice);
+    const bool active = slice * VB < P.row_bytes;
+    // all that the wavefront needs to know first, loaded together
+    const int64_t s0 = id.w * P.sets_per_wave, s1 = s0 + P.sets_per_wave;
+    const int n_long = P.long_rows ? *P.n_long : 0, n_chunks = P.long_rows ? *P.n_chunks : 0;
+    const int64_t rbeg = P.split[s0 < P.nsets ? s0 : P.nsets], rend = P.split[s1 < P.nsets ? s1 : P.nsets];
+    if (n_chunks > 0) pull_chunks<DT, VB, W, U, WAVE, BATCH>(P, win, n_long, n_chunks, id, lane, lane_off, active);
+    const RowStore<DT, VB> sink = {P.out, P.row_bytes, lane_off, active};
+    for (int64_t r0 = rbeg; r0 < rend; r0 += kWave) {
+        const int nrows = rend - r0 < kWave ? (int)(rend - r0) : kWave;
         int pb = 0, pe = 0;
-        if (sub < nrows) {
-            pb = P.rowptr[r0 + sub];
-            pe = P.rowptr[r0 + sub + 1];
+        if (lane < nrows) {
+            pb = P.rowptr[r0 + lane];
+            pe = P.rowptr[r0 + lane + 1];
         }
         const acc_t scale = row_scale<acc_t>(P.row_mode, pe - pb);
-        unsigned long long lm = (__ballot(sub < nrows && pe - pb > P.long_thr) >> gbase) & gmask;
+        if constexpr (!WAVE) {
+            // the window is this wavefront's alone: its LDS accesses are carried out in order
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            win.end[lane] = pe;
+            win.scale[lane] = scale;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        const unsigned long long lm = __ballot(lane < nrows && pe - pb > P.long_thr);
         int i = 0;
         while (i < nrows) {
             if ((lm >> i) & 1ull) {   // a long row: its chunks were handled above
@@ -125,12 +132,8 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
             }
             const unsigned long long rest = lm >> i;
             const int j = rest ? i + (__ffsll((long long)rest) - 1) : nrows;
-            if constexpr (WAVE) {
-                walk_wave<DT, VB, W, false, U>(P, r0, i, j, lane_value(pb, i), pe, scale, sub, lane_off, active, sink);
-            } else {
-                const int ebeg = __shfl(pb, gbase + i, kWave);
-                walk_run<DT, VB, W, false, U>(P, r0, i, j, ebeg, pe, scale, sub, gbase, lane_off, active, sink);
-            }
+            if constexpr (WAVE) walk_wave<DT, VB, W, false, U>(P, r0, i, j, lane_value(pb, i), pe, scale, lane, lane_off, active, sink);
+            else walk_flat<DT, VB, W, false, U, BATCH>(P, win, r0, i, j, lane_value(pb, i), pe, lane, lane_off, active, sink);
             i = j;
         }
     }
@@ -152,8 +155,8 @@ __global__ __launch_bounds__(kBlock) void k_reduce_chunks(PullParams P)
     for (int64_t unit = blockIdx.x; unit < total; unit += gridDim.x) {
         const int li = (int)(unit / P.ntiles);
         const int tile = (int)(unit - (int64_t)li * P.ntiles);
-        const int64_t lane_off = ((int64_t)tile * P.G + sub) * VB;
-        const bool active = lane_off < P.row_bytes;
+        const int64_t slice = (int64_t)tile * P.G + sub, lane_off = slice_offset<VB>(P, slice);
+        const bool active = slice * VB < P.row_bytes;
         const int row = P.long_rows[li];
         const int first = P.chunk_ptr[li], last = P.chunk_ptr[li + 1];
         const int per = (last - first + parts - 1) / parts;
@@ -161,7 +164,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_chunks(PullParams P)
         acc_t acc[S::NE];
 #pragma unroll
         for (int i = 0; i < S::NE; ++i) acc[i] = (acc_t)0;
-        const acc_t *src = reinterpret_cast<const acc_t *>(P.partials) + ((int64_t)tile * P.G + sub) * S::NE;
+        const acc_t *src = reinterpret_cast<const acc_t *>(P.partials) + lane_off / S::ES;
         if (active) {
             for (int c0 = lo; c0 < hi; c0 += 8) {
                 acc_t load[8][S::NE];
@@ -189,43 +192,47 @@ __global__ __launch_bounds__(kBlock) void k_reduce_chunks(PullParams P)
     }
 }
 
-template <int VB>
+// A row's last slice ends with the row (slice_offset): rows of any length move 16 bytes per lane.
+template <int DT, int VB>
 __global__ __launch_bounds__(kBlock) void k_gather_rows(const char *__restrict__ table,
                                                         const int64_t *__restrict__ ids, int64_t num_units,
-                                                        int32_t ntiles, int32_t G, int64_t row_bytes,
+                                                        int32_t ntiles, uint64_t tile_inv, int32_t lg_G, int64_t row_bytes,
                                                         char *__restrict__ out)
 {
+    using S = Slice<DT, VB>;
     const int tid = threadIdx.x;
-    const int sub = tid & (G - 1);
-    const int64_t unit = ((int64_t)blockIdx.x * kBlock + tid) / G;
+    const int sub = tid & ((1 << lg_G) - 1);
+    const int64_t unit = ((int64_t)blockIdx.x * kBlock + tid) >> lg_G;
     if (unit >= num_units) return;
-    const int64_t row = unit / ntiles;
+    const int64_t row = ntiles > 1 ? (int64_t)__umul64hi((uint64_t)unit, tile_inv) : unit;   // unit * ntiles < 2^64
     const int tile = (int)(unit - row * ntiles);
-    const int64_t lane_off = ((int64_t)tile * G + sub) * VB;
-    if (lane_off >= row_bytes) return;
-    uint32_t r[Slice<FASTGL_BF16, VB>::NW];
-    Slice<FASTGL_BF16, VB>::load(table + ids[row] * row_bytes + lane_off, r);
+    const int64_t at = (((int64_t)tile << lg_G) + sub) * VB, lane_off = at < row_bytes - VB ? at : row_bytes - VB;
+    if (at >= row_bytes) return;
+    uint32_t r[S::NW];
+    S::load(table + ids[row] * row_bytes + lane_off, r);
     char *p = out + row * row_bytes + lane_off;
-    if constexpr (VB == 16) *reinterpret_cast<uint4 *>(p) = make_uint4(r[0], r[1], r[2], r[3]);
-    else if constexpr (VB == 8) *reinterpret_cast<uint2 *>(p) = make_uint2(r[0], r[1]);
-    else if constexpr (VB == 4) *reinterpret_cast<uint32_t *>(p) = r[0];
+    if constexpr (VB == 16) *reinterpret_cast<typename S::u32x4 *>(p) = typename S::u32x4{r[0], r[1], r[2], r[3]};
+    else if constexpr (VB == 8) *reinterpret_cast<typename S::u32x2 *>(p) = typename S::u32x2{r[0], r[1]};
+    else if constexpr (VB == 4) *reinterpret_cast<typename S::u32x1 *>(p) = r[0];
     else *reinterpret_cast<uint16_t *>(p) = (uint16_t)r[0];
 }
 
 // ------------------------------------------------------------- host side ----
-// Largest slice width (bytes) that divides the row size and the buffer alignment.
-static int pick_slice_bytes(int64_t row_bytes, const void *a, const void *b, int elem)
+// Width of a slice: 16 bytes, or as much of that as fits a row.  Rows need not be whole slices (slice_offset).
+static int slice_bytes(int64_t row_bytes)
 {
-    uintptr_t bits = (uintptr_t)a | (uintptr_t)b | (uintptr_t)row_bytes;
-    for (int vb = 16; vb > elem; vb >>= 1)
-        if ((bits & (uintptr_t)(vb - 1)) == 0) return vb;
-    return elem;
+    int vb = 16;
+    while (vb > row_bytes) vb >>= 1;
+    return vb;
 }
 
-static void group_shape(int64_t row_bytes, int vb, int *G, int *ntiles)
+// ceil(2^64 / n): the upper half of its product with x is x / n while x * n < 2^64.  0 for n = 1.
+static uint64_t tile_inverse(int n) { return n > 1 ? UINT64_MAX / (uint64_t)n + 1 : 0; }
+
+static void group_shape(int64_t row_bytes, int vb, int smallest, int *G, int *ntiles)
 {
-    int64_t slices = row_bytes / vb;
-    int g = 1;
+    const int64_t slices = ceil_div(row_bytes, (int64_t)vb);
+    int g = smallest;
     while (g < kWave && g < slices) g <<= 1;
     *G = g;
     *ntiles = (int)ceil_div(slices, g);
@@ -235,22 +242,24 @@ template <int DT, int VB, int W>
 static void launch_rows(const PullParams &P, hipStream_t s)
 {
     const dim3 grid((unsigned)P.num_blocks);
-    if (P.G == kWave) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollWave, true>), grid, dim3(kBlock), 0, s, P);
-    else if (P.G > 16) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnroll, false>), grid, dim3(kBlock), 0, s, P);
-    else hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollNarrow, false>), grid, dim3(kBlock), 0, s, P);
+    if (P.G == kWave) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollWave, true, false>), grid, dim3(kBlock), 0, s, P);
+    else if (P.G <= kBatchLanes) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollNarrow, false, true>), grid, dim3(kBlock), 0, s, P);
+    else hipLaunchKernelGGL((k_pull_rows<DT, 16, W, kUnroll, false, false>), grid, dim3(kBlock), 0, s, P);
 }
 
 template <int DT, int VB>
-static fastgl_status launch_typed(const PullParams &P, bool with_long, hipStream_t s)
+static fastgl_status launch_typed(const PullParams &P, unsigned reduce_blocks, hipStream_t s)
 {
     if (P.num_blocks > 0) {
         if (P.edge_w && P.col_scale) launch_rows<DT, VB, kTwoWeights>(P, s);
-        else if (P.edge_w || P.col_scale) launch_rows<DT, VB, kOneWeight>(P, s);
+        else if (P.edge_w && P.eid) launch_rows<DT, VB, kPermWeight>(P, s);
+        else if (P.edge_w) launch_rows<DT, VB, kEdgeWeight>(P, s);
+        else if (P.col_scale) launch_rows<DT, VB, kColWeight>(P, s);
         else launch_rows<DT, VB, kNoWeight>(P, s);
         FASTGL_LAUNCH_CHECK("k_pull_rows");
     }
-    if (with_long) {
-        hipLaunchKernelGGL((k_reduce_chunks<DT, VB>), dim3(kReduceBlocks), dim3(kBlock), 0, s, P);
+    if (reduce_blocks) {
+        hipLaunchKernelGGL((k_reduce_chunks<DT, VB>), dim3(reduce_blocks), dim3(kBlock), 0, s, P);
         FASTGL_LAUNCH_CHECK("k_reduce_chunks");
     }
     return FASTGL_OK;
@@ -267,36 +276,49 @@ fastgl_status launch_pull(const PullDesc &d, hipStream_t s)
     P.row_bytes = d.feat * elem;
     P.feat = d.feat;
     P.row_mode = d.row_mode;
-    const int vb = pick_slice_bytes(P.row_bytes, d.in, d.out, elem);
+    const int vb = slice_bytes(P.row_bytes);
     int G, ntiles;
-    group_shape(P.row_bytes, vb, &G, &ntiles);
-    // walk_run counts slices in 32 bits; beyond that (more than 2^27 rows of 32 slices) a whole wavefront takes a row
-    if (d.num_cols * (P.row_bytes / vb) > (int64_t)UINT32_MAX) {
+    group_shape(P.row_bytes, vb, kUnrollNarrow, &G, &ntiles);   // a group loads as many column ids at a time as it has lanes
+    P.unit_shift = 1;
+    while ((1 << P.unit_shift) < vb && P.row_bytes % (2 << P.unit_shift) == 0) ++P.unit_shift;
+    // walk_flat counts units in 32 bits; beyond that (more than 2^27 rows of 32 slices) a whole wavefront takes a row
+    if (d.num_cols * (P.row_bytes >> P.unit_shift) > (int64_t)UINT32_MAX) {
         G = kWave;
-        ntiles = (int)ceil_div(P.row_bytes / vb, (int64_t)G);
+        ntiles = (int)ceil_div(ceil_div(P.row_bytes, (int64_t)vb), (int64_t)G);
     }
     P.G = G; P.ntiles = ntiles;
+    P.lg_G = __builtin_ctz((unsigned)G);
+    P.tile_inv = tile_inverse(ntiles);
     P.num_rows = d.num_rows;
     P.split = d.split;
     P.nsets = d.nsets;
-    // several fine sets per group when there are plenty: amortises the row-pointer /
-    // column-id latency over more gathers while keeping >= ~16K groups in flight
-    int spg = 1;
-    while (spg < 8 && (d.nsets / (spg * 2)) * G * ntiles / kWave >= 16384) spg *= 2;
-    P.sets_per_group = spg;
-    P.ngroups = ceil_div(d.nsets, P.sets_per_group);
-    const bool with_long = d.long_rows != nullptr;
+    // Fine sets per wavefront: as few as leave every compute unit four wavefronts, until a group has kUnrollNarrow edges
+    // to gather (512 rows of 16 floats with 430 edges: 4 sets 11.6 us, 1 set 5.2); up to a set (16 edges and rows) per group
+    // while that gives at least the 4 096 wavefronts that the device holds at once; more when there are plenty: that amortises
+    // the row-pointer / column-id latency over more gathers while keeping >= 16 K wavefronts (at least 8 K: all neighbours,
+    // width 32, forward 98 -> 106 us, 2.56 M edges of 64 floats 113 -> 118; at least 32 K: 104 and 117).
+    const int groups = kWave / G;
+    int spw = 1;
+    while (spw < groups / kUnrollNarrow && d.nsets / (spw * 2) * ntiles >= 1024) spw *= 2;
+    while (spw < groups && d.nsets / (spw * 2) * ntiles >= 4096) spw *= 2;
+    while (spw >= groups && spw < 8 * groups && d.nsets / (spw * 2) * ntiles >= 16384) spw *= 2;
+    P.sets_per_wave = spw;
+    P.nwaves = ceil_div(d.nsets, (int64_t)spw);
+    const bool with_long = d.long_rows != nullptr && d.nnz > kLongThreshold;
     P.long_thr = with_long ? kLongThreshold : INT32_MAX;
-    P.long_rows = d.long_rows; P.chunk_ptr = d.chunk_ptr; P.n_long = d.n_long; P.n_chunks = d.n_chunks;
+    P.long_rows = with_long ? d.long_rows : nullptr;
+    P.chunk_ptr = d.chunk_ptr; P.n_long = d.n_long; P.n_chunks = d.n_chunks;
     P.partials = (char *)d.partials;
-    const int gpb = kBlock / G;
-    P.xcd_run = kXcdRun;
-    P.num_blocks = ceil_div(ceil_div(P.ngroups * ntiles, gpb), (int64_t)kXcds * P.xcd_run) * P.xcd_run * kXcds;
+    P.num_blocks = ceil_div(ceil_div(P.nwaves * ntiles, (int64_t)(kBlock / kWave)), (int64_t)kXcds * kXcdRun) * kXcdRun * kXcds;
+    P.chunk_waves = P.num_blocks * (kBlock / kWave) / ntiles;
     if (P.num_blocks > 0x7FFFFFFFLL) {
         set_error("block too large for one launch (%lld workgroups)", (long long)P.num_blocks);
         return FASTGL_ERR_UNSUPPORTED;
     }
-#define FASTGL_CASE(DT, VB) return launch_typed<DT, VB>(P, with_long, s)
+    // workgroups for the long rows: no more than there can be
+    const int64_t most_long = cap_long_rows(d.nnz) * ntiles;
+    const unsigned reduce_blocks = !with_long ? 0u : (unsigned)(most_long < kReduceBlocks ? most_long : kReduceBlocks);
+#define FASTGL_CASE(DT, VB) return launch_typed<DT, VB>(P, reduce_blocks, s)
     if (d.dtype == FASTGL_F32) {
         switch (vb) {
             case 16: FASTGL_CASE(FASTGL_F32, 16);
@@ -320,9 +342,9 @@ fastgl_status launch_gather_rows(const void *table, const int64_t *ids, int64_t 
     if (n == 0) return FASTGL_OK;
     const int elem = dtype == FASTGL_F32 ? 4 : 2;
     const int64_t row_bytes = feat * elem;
-    const int vb = pick_slice_bytes(row_bytes, table, out, elem);
+    const int vb = slice_bytes(row_bytes);
     int G, ntiles;
-    group_shape(row_bytes, vb, &G, &ntiles);
+    group_shape(row_bytes, vb, 1, &G, &ntiles);
     const int64_t units = n * ntiles;
     const int64_t nblocks = ceil_div(units * G, kBlock);
     if (nblocks > 0x7FFFFFFFLL) {
@@ -330,13 +352,23 @@ fastgl_status launch_gather_rows(const void *table, const int64_t *ids, int64_t 
         return FASTGL_ERR_UNSUPPORTED;
     }
     dim3 grid((unsigned)nblocks);
+    const int lg_G = __builtin_ctz((unsigned)G);
     const char *t = (const char *)table;
     char *o = (char *)out;
-    switch (vb) {
-        case 16: hipLaunchKernelGGL(k_gather_rows<16>, grid, dim3(kBlock), 0, s, t, ids, units, ntiles, G, row_bytes, o); break;
-        case 8: hipLaunchKernelGGL(k_gather_rows<8>, grid, dim3(kBlock), 0, s, t, ids, units, ntiles, G, row_bytes, o); break;
-        case 4: hipLaunchKernelGGL(k_gather_rows<4>, grid, dim3(kBlock), 0, s, t, ids, units, ntiles, G, row_bytes, o); break;
-        default: hipLaunchKernelGGL(k_gather_rows<2>, grid, dim3(kBlock), 0, s, t, ids, units, ntiles, G, row_bytes, o); break;
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, s, t, ids, units, ntiles, tile_inverse(ntiles), lg_G, row_bytes, o); };
+    if (dtype == FASTGL_F32) {
+        switch (vb) {
+            case 16: go(k_gather_rows<FASTGL_F32, 16>); break;
+            case 8: go(k_gather_rows<FASTGL_F32, 8>); break;
+            default: go(k_gather_rows<FASTGL_F32, 4>); break;
+        }
+    } else {
+        switch (vb) {
+            case 16: go(k_gather_rows<FASTGL_BF16, 16>); break;
+            case 8: go(k_gather_rows<FASTGL_BF16, 8>); break;
+            case 4: go(k_gather_rows<FASTGL_BF16, 4>); break;
+            default: go(k_gather_rows<FASTGL_BF16, 2>); break;
+        }
     }
     FASTGL_LAUNCH_CHECK("k_gather_rows");
     return FASTGL_OK;

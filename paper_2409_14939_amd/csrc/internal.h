@@ -34,6 +34,19 @@ fastgl_status hip_fail(hipError_t e, const char *what);
         if (e__ != hipSuccess) return ::fastgl::hip_fail(e__, name);        \
     } while (0)
 
+// Words in memory that are aligned to an element of ES bytes: global loads and stores of up to 16 bytes may start at any
+// address.
+template <int ES> struct Words {
+    typedef uint32_t x4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint32_t x2 __attribute__((ext_vector_type(2), aligned(4)));
+    typedef uint32_t x1 __attribute__((aligned(4)));
+};
+template <> struct Words<2> {
+    typedef uint32_t x4 __attribute__((ext_vector_type(4), aligned(2)));
+    typedef uint32_t x2 __attribute__((ext_vector_type(2), aligned(2)));
+    typedef uint32_t x1 __attribute__((aligned(2)));
+};
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

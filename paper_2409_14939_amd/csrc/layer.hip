@@ -237,7 +237,8 @@ fastgl_status fastgl_layer_fwd(const int32_t *indptr, const int32_t *indices, co
     L.rows = num_dst; L.K = (int32_t)K; L.N = (int32_t)N; L.relu = relu != 0;
     hipStream_t s = (hipStream_t)stream;
     if (d.edge_w && d.col_scale) launch_layer<kTwoWeights>(L, s);
-    else if (d.edge_w || d.col_scale) launch_layer<kOneWeight>(L, s);
+    else if (d.edge_w) launch_layer<kEdgeWeight>(L, s);
+    else if (d.col_scale) launch_layer<kColWeight>(L, s);
     else launch_layer<kNoWeight>(L, s);
     FASTGL_LAUNCH_CHECK("fastgl_layer_fwd");
     return FASTGL_OK;

@@ -1,0 +1,110 @@
+"""Feature rows of any length and alignment (the last 16-byte piece of a row ends with it and starts inside the piece
+before) and rows shared by the lane groups of a wavefront: aggregation both ways, table gather, assembly and edge weight
+gradient.  Against the oracle with the tolerances of the parity tests; copies byte for byte, with a guard around them."""
+import numpy as np
+import pytest
+import torch
+
+import blockgen as bg
+import oracle
+from paper_2409_14939_amd import binding as B
+from gpu_util import assert_close, dev_feat, dev_i32, host_feat, make_inputs
+from test_gpu_parity import check_block
+
+pytestmark = pytest.mark.gpu
+FEATS = {"f32": [1, 2, 3, 4, 5, 7, 13, 17, 31, 63, 65, 101, 131, 255, 257, 602],
+         "bf16": [1, 2, 3, 5, 7, 8, 9, 15, 17, 62, 99, 127, 129, 255, 257, 513, 530]}
+
+
+def block_of(lengths, num_src, seed):
+    rng = np.random.default_rng(seed)
+    indptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    return bg.Block(indptr, rng.integers(0, num_src, indptr[-1]).astype(np.int32), len(lengths), num_src)
+
+
+@pytest.mark.parametrize("dtype,feat", [(d, f) for d in FEATS for f in FEATS[d]])
+def test_widths(dtype, feat):
+    blk = bg.random_block(np.random.default_rng(feat), 150, 333, 5.0, empty_frac=0.2, hub_rows=3, hub_deg=300)
+    check_block(blk, "gcn", dtype, feat, feat % 2 == 0, True, feat, "odd width")
+
+
+# runs of edges that end inside, at and between rows; rows over several groups; windows of more than 64 rows; none at all
+SHAPES = {"one row": [200], "one edge": [1], "two edges": [0, 2, 0], "ends alone": [90] + [0] * 200 + [90],
+          "empty among full": [0, 17] * 80, "256 each": [256] * 9, "one long in the middle": [1] * 70 + [257] + [1] * 70,
+          "growing": list(range(120)), "mixed": [3, 0, 0, 250, 1, 1, 1, 0, 64, 63, 65, 0] * 7, "ones": [1] * 1000}
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("dtype,feat", [("f32", 4), ("f32", 30), ("f32", 64), ("f32", 128), ("f32", 256), ("bf16", 8),
+                                        ("bf16", 100), ("bf16", 256)])
+def test_row_shapes(shape, dtype, feat):
+    blk = block_of(SHAPES[shape], 97, len(shape))
+    check_block(blk, "mean", dtype, feat, False, True, feat, shape)
+    check_block(blk, "gcn", dtype, feat, True, True, feat, shape + ", weighted")
+
+
+def shifted(a, dtype, by):
+    """`a` on the device at an address `by` elements past an aligned one."""
+    t = dev_feat(a, dtype)
+    room = torch.empty(t.numel() + by, dtype=t.dtype, device="cuda")
+    room[by:] = t.reshape(-1)
+    return room[by:].reshape(t.shape)
+
+
+@pytest.mark.parametrize("dtype,feat,by", [("f32", 8, 1), ("f32", 129, 3), ("bf16", 64, 1), ("bf16", 33, 5)])
+def test_any_alignment(dtype, feat, by):
+    blk = bg.random_block(np.random.default_rng(by), 200, 411, 6.0, hub_rows=2, hub_deg=400)
+    rng = np.random.default_rng(feat)
+    X, G = make_inputs(rng, blk.num_src, feat, dtype), make_inputs(rng, blk.num_dst, feat, dtype)
+    ip, ix, src = dev_i32(blk.indptr), dev_i32(blk.indices), blk.num_src
+    Xd, Gd = shifted(X, dtype, by), shifted(G, dtype, by)
+    out, dX = shifted(G, dtype, by), shifted(X, dtype, by)
+    B.fastgl_block_aggregate_fwd(ip, ix, None, src, "sum", Xd, out=out)
+    B.fastgl_block_aggregate_bwd(ip, ix, None, src, "sum", Gd, grad_X=dX)
+    assert_close(host_feat(out, dtype), oracle.aggregate_fwd(blk.indptr, blk.indices, None, src, "sum", dtype, X), dtype)
+    assert_close(host_feat(dX, dtype), oracle.aggregate_bwd(blk.indptr, blk.indices, None, src, "sum", dtype, G), dtype)
+    dw = B.fastgl_edge_weight_grad(ip, ix, src, "sum", Xd, Gd)
+    same = B.fastgl_edge_weight_grad(ip, ix, src, "sum", Xd.clone(), Gd.clone())
+    assert torch.equal(dw, same)
+
+
+@pytest.mark.parametrize("dtype,feat", [(d, f) for d in FEATS for f in FEATS[d]])
+@pytest.mark.parametrize("by", [0, 1])
+def test_copies(dtype, feat, by):
+    rng = np.random.default_rng(feat)
+    table = shifted(make_inputs(rng, 300, feat, dtype), dtype, by)
+    load = shifted(make_inputs(rng, 50, feat, dtype), dtype, by)
+    ids = torch.from_numpy(rng.integers(0, 300, 77)).cuda()
+    bits = torch.int32 if dtype == "f32" else torch.int16
+
+    def guarded():
+        room = torch.full((77 * feat + 2 * 64 + by,), 7, dtype=bits, device="cuda")
+        return room, room[64 + by:64 + by + 77 * feat].view(table.dtype).reshape(77, feat)
+
+    room, out = guarded()
+    B.fastgl_gather_rows(table, ids, out=out)
+    assert torch.equal(out.view(bits), table.view(bits)[ids])
+    assert (room[:64 + by] == 7).all() and (room[-64:] == 7).all()
+    src = torch.from_numpy(rng.integers(-50, 300, 77).astype(np.int32)).cuda()
+    room, out = guarded()
+    B.fastgl_assemble_rows(table, load, src, 50, out=out)
+    want = torch.where((src >= 0)[:, None], table.view(bits)[src.clamp(min=0).long()], load.view(bits)[(-1 - src).clamp(min=0).long()])
+    assert torch.equal(out.view(bits), want)
+    assert (room[:64 + by] == 7).all() and (room[-64:] == 7).all()
+
+
+@pytest.mark.parametrize("dtype,feat", [(d, f) for d in FEATS for f in FEATS[d]])
+@pytest.mark.parametrize("edges_per_row", [2.0, 300.0])
+def test_edge_weight_grad(dtype, feat, edges_per_row):
+    blk = bg.random_block(np.random.default_rng(feat), 140, 300, edges_per_row, empty_frac=0.2)
+    rng = np.random.default_rng(feat)
+    X, G = make_inputs(rng, blk.num_src, feat, dtype), make_inputs(rng, blk.num_dst, feat, dtype)
+    x, g = (a.astype(np.float64) if dtype == "f32" else bg.bf16_bits_to_f32(a).astype(np.float64) for a in (X, G))
+    got = B.fastgl_edge_weight_grad(dev_i32(blk.indptr), dev_i32(blk.indices), blk.num_src, "sum", dev_feat(X, dtype),
+                                    dev_feat(G, dtype)).cpu().numpy()
+    rows = np.repeat(np.arange(blk.num_dst), np.diff(blk.indptr))
+    terms = np.abs(g[rows] * x[blk.indices]).sum(1)
+    want = (g[rows] * x[blk.indices]).sum(1)
+    # fp64 sums rounded once; bf16: products exact, a chain of at most feat fp32 additions
+    bound = 2.0 ** -24 * np.abs(want) + (feat + 2) * (2.0 ** -52 if dtype == "f32" else 2.0 ** -24) * terms
+    assert (np.abs(got - want) <= bound).all()
