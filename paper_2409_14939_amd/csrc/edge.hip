@@ -80,50 +80,33 @@ __device__ __forceinline__ ACC reduce4(const ACC (&v)[4], int l, int lanes, int 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// Dot product of one piece (PIECE bytes at byte offset `off` of both rows).
-template <bool BF16, int PIECE, typename ACC>
-__device__ __forceinline__ ACC piece_dot(const char *__restrict__ x, const char *__restrict__ g, int64_t off)
+// Dot product of one piece (PIECE bytes at byte offset `off` of both rows; 16 bytes or one element), which needs no more
+// alignment than an element.  RAGGED: without its first `skip` elements.
+template <bool BF16, int PIECE, bool RAGGED, typename ACC>
+__device__ __forceinline__ ACC piece_dot(const char *__restrict__ x, const char *__restrict__ g, int64_t off, int skip)
 {
     ACC s = 0;
-    if constexpr (!BF16) {
-        if constexpr (PIECE == 16) {
-            const float4 a = *reinterpret_cast<const float4 *>(x + off), b = *reinterpret_cast<const float4 *>(g + off);
-            s += (ACC)a.x * (ACC)b.x;
-            s += (ACC)a.y * (ACC)b.y;
-            s += (ACC)a.z * (ACC)b.z;
-            s += (ACC)a.w * (ACC)b.w;
-        } else if constexpr (PIECE == 8) {
-            const float2 a = *reinterpret_cast<const float2 *>(x + off), b = *reinterpret_cast<const float2 *>(g + off);
-            s += (ACC)a.x * (ACC)b.x;
-            s += (ACC)a.y * (ACC)b.y;
-        } else {
-            s += (ACC)(*reinterpret_cast<const float *>(x + off)) * (ACC)(*reinterpret_cast<const float *>(g + off));
-        }
-    } else {
-        if constexpr (PIECE == 2) {
-            const uint32_t wa = *reinterpret_cast<const uint16_t *>(x + off), wb = *reinterpret_cast<const uint16_t *>(g + off);
-            s += (ACC)bf16_lo(wa) * (ACC)bf16_lo(wb);
-        } else {
-            constexpr int W = PIECE / 4;
-            uint32_t a[W], b[W];
-            if constexpr (W == 4) {
-                const uint4 va = *reinterpret_cast<const uint4 *>(x + off), vb = *reinterpret_cast<const uint4 *>(g + off);
-                a[0] = va.x; a[1] = va.y; a[2] = va.z; a[3] = va.w;
-                b[0] = vb.x; b[1] = vb.y; b[2] = vb.z; b[3] = vb.w;
-            } else if constexpr (W == 2) {
-                const uint2 va = *reinterpret_cast<const uint2 *>(x + off), vb = *reinterpret_cast<const uint2 *>(g + off);
-                a[0] = va.x; a[1] = va.y;
-                b[0] = vb.x; b[1] = vb.y;
-            } else {
-                a[0] = *reinterpret_cast<const uint32_t *>(x + off);
-                b[0] = *reinterpret_cast<const uint32_t *>(g + off);
-            }
+    if constexpr (PIECE == 16) {
+        using u32x4 = typename Words<BF16 ? 2 : 4>::x4;
+        const u32x4 a = *reinterpret_cast<const u32x4 *>(x + off), b = *reinterpret_cast<const u32x4 *>(g + off);
+        auto add = [&](int e, float u, float v) {
+            const ACC t = (ACC)u * (ACC)v;
+            s += !RAGGED || e >= skip ? t : (ACC)0;
+        };
 #pragma unroll
-            for (int i = 0; i < W; ++i) {
-                s += (ACC)bf16_lo(a[i]) * (ACC)bf16_lo(b[i]);
-                s += (ACC)bf16_hi(a[i]) * (ACC)bf16_hi(b[i]);
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (BF16) {
+                add(2 * i, bf16_lo(a[i]), bf16_lo(b[i]));
+                add(2 * i + 1, bf16_hi(a[i]), bf16_hi(b[i]));
+            } else {
+                add(i, __uint_as_float(a[i]), __uint_as_float(b[i]));
             }
         }
+    } else if constexpr (BF16) {
+        const uint32_t a = *reinterpret_cast<const uint16_t *>(x + off), b = *reinterpret_cast<const uint16_t *>(g + off);
+        s = (ACC)bf16_lo(a) * (ACC)bf16_lo(b);
+    } else {
+        s = (ACC)(*reinterpret_cast<const float *>(x + off)) * (ACC)(*reinterpret_cast<const float *>(g + off));
     }
     return s;
 }
@@ -134,8 +117,10 @@ struct DotArgs {
     const float *src_scale;      // [num_src] or NULL
     float *grad_w;
     int64_t E, row_bytes;
-    int pieces;                  // row_bytes / PIECE
+    int pieces;                  // ceil(row_bytes / PIECE); the last one ends with the row
+    int skip;                    // elements of the last piece that the one before it has
     int lanes;                   // lanes per edge group: power of two <= 64
+    int steps;                   // batches of kEdgeUnroll edges per group, at most kEdgeSteps
     int mode;                    // 0 none, 1: 1/len, 2: 1/sqrt(len) of the destination row
 };
 
@@ -157,9 +142,9 @@ __device__ __forceinline__ double edge_scale(const DotArgs &a, int32_t u, int32_
 // group - half of all loads (2.56 M edges of 64 floats: 143 -> 129 us).  Narrower rows leave a workgroup more edges
 // than LDS should hold.
 constexpr int kStagedLanes = 8;
-constexpr int kGroupEdges = kEdgeUnroll * kEdgeSteps;
+constexpr int kGroupEdges = kEdgeUnroll * kEdgeSteps;    // at most
 
-template <bool BF16, int PIECE, bool STAGED>
+template <bool BF16, int PIECE, bool RAGGED, bool STAGED>
 __global__ __launch_bounds__(256) void k_edge_dot(const DotArgs a)
 {
     using ACC = typename std::conditional<BF16, float, double>::type;
@@ -168,25 +153,26 @@ __global__ __launch_bounds__(256) void k_edge_dot(const DotArgs a)
     const int lanes = a.lanes;
     const int groups_per_block = 256 / lanes;
     const int grp = threadIdx.x / lanes, l = threadIdx.x % lanes;
-    const int64_t block_first = (int64_t)blockIdx.x * groups_per_block * kGroupEdges;
+    const int group_edges = kEdgeUnroll * a.steps;
+    const int64_t block_first = (int64_t)blockIdx.x * groups_per_block * group_edges;
     if constexpr (STAGED) {
-        for (int i = threadIdx.x; i < groups_per_block * kGroupEdges; i += 256) {
+        for (int i = threadIdx.x; i < groups_per_block * group_edges; i += 256) {
             const int64_t e = block_first + i < a.E ? block_first + i : a.E - 1;   // a clamped edge is computed and dropped
             row_s[i] = a.edge_row[e];
             col_s[i] = a.indices[e];
         }
         __syncthreads();
     }
-    // a group takes kEdgeSteps batches of kEdgeUnroll consecutive edges; without staging the row and column of the
+    // a group takes a.steps batches of kEdgeUnroll consecutive edges; without staging the row and column of the
     // next batch's edges are fetched while the current batch's rows are in flight
-    const int64_t first = block_first + grp * kGroupEdges;
+    const int64_t first = block_first + grp * group_edges;
     int32_t u[kEdgeUnroll], v[kEdgeUnroll], un[kEdgeUnroll], vn[kEdgeUnroll];
     auto numbers = [&](int step) {
 #pragma unroll
         for (int k = 0; k < kEdgeUnroll; ++k) {
             if constexpr (STAGED) {
-                un[k] = row_s[grp * kGroupEdges + step * kEdgeUnroll + k];
-                vn[k] = col_s[grp * kGroupEdges + step * kEdgeUnroll + k];
+                un[k] = row_s[grp * group_edges + step * kEdgeUnroll + k];
+                vn[k] = col_s[grp * group_edges + step * kEdgeUnroll + k];
             } else {
                 const int64_t at = first + step * kEdgeUnroll + k, e = at < a.E ? at : a.E - 1;
                 un[k] = a.edge_row[e];
@@ -195,7 +181,7 @@ __global__ __launch_bounds__(256) void k_edge_dot(const DotArgs a)
         }
     };
     numbers(0);
-    for (int step = 0; step < kEdgeSteps; ++step) {
+    for (int step = 0; step < a.steps; ++step) {
         const int64_t e0 = first + (int64_t)step * kEdgeUnroll;
         if (e0 >= a.E) break;                                        // uniform over the group
 #pragma unroll
@@ -203,16 +189,17 @@ __global__ __launch_bounds__(256) void k_edge_dot(const DotArgs a)
             u[k] = un[k];
             v[k] = vn[k];
         }
-        if (step + 1 < kEdgeSteps) numbers(step + 1);
+        if (step + 1 < a.steps) numbers(step + 1);
         ACC acc[kEdgeUnroll];
 #pragma unroll
         for (int k = 0; k < kEdgeUnroll; ++k) acc[k] = 0;
         for (int p = l; p < a.pieces; p += lanes) {
-            const int64_t off = (int64_t)p * PIECE;
+            const bool last = RAGGED && p == a.pieces - 1;
+            const int64_t off = last ? a.row_bytes - PIECE : (int64_t)p * PIECE;
 #pragma unroll
             for (int k = 0; k < kEdgeUnroll; ++k)
-                acc[k] += piece_dot<BF16, PIECE, ACC>(a.X + (int64_t)v[k] * a.row_bytes,
-                                                      a.G + (int64_t)u[k] * a.row_bytes, off);
+                acc[k] += piece_dot<BF16, PIECE, RAGGED, ACC>(a.X + (int64_t)v[k] * a.row_bytes,
+                                                              a.G + (int64_t)u[k] * a.row_bytes, off, last ? a.skip : 0);
         }
         if (lanes >= 4) {
             int k;
@@ -395,13 +382,13 @@ fastgl_status check_workspace(void *workspace, size_t have, size_t need)
     return FASTGL_OK;
 }
 
-template <bool BF16, int PIECE>
+template <bool BF16, int PIECE, bool RAGGED>
 void launch_dot(const DotArgs &a, hipStream_t s)
 {
     const int groups_per_block = 256 / a.lanes;
-    const dim3 grid((unsigned)ceil_div(a.E, (int64_t)groups_per_block * kGroupEdges));
-    if (a.lanes >= kStagedLanes) hipLaunchKernelGGL((k_edge_dot<BF16, PIECE, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_edge_dot<BF16, PIECE, false>), grid, dim3(256), 0, s, a);
+    const dim3 grid((unsigned)ceil_div(a.E, (int64_t)groups_per_block * kEdgeUnroll * a.steps));
+    if (a.lanes >= kStagedLanes) hipLaunchKernelGGL((k_edge_dot<BF16, PIECE, RAGGED, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_edge_dot<BF16, PIECE, RAGGED, false>), grid, dim3(256), 0, s, a);
 }
 
 fastgl_status softmax(bool backward, const int32_t *indptr, int64_t num_dst, int64_t E, const float *in0,
@@ -569,27 +556,23 @@ fastgl_status fastgl_edge_weight_grad(const int32_t *indptr, const int32_t *indi
     a.src_scale = src_scale; a.grad_w = grad_w;
     a.E = num_edges; a.row_bytes = feat * elem;
     a.mode = mode == FASTGL_AGG_MEAN ? 1 : (mode == FASTGL_AGG_GCN ? 2 : 0);
-    const uintptr_t both = (uintptr_t)X | (uintptr_t)grad_out;
-    int piece = (int)elem;
-    for (int cand = 16; cand > elem; cand >>= 1)
-        if (a.row_bytes % cand == 0 && (both & (uintptr_t)(cand - 1)) == 0) {
-            piece = cand;
-            break;
-        }
-    a.pieces = (int)(a.row_bytes / piece);
+    const int piece = a.row_bytes >= 16 ? 16 : (int)elem;      // of rows of any length and alignment (piece_dot)
+    a.pieces = (int)ceil_div(a.row_bytes, (int64_t)piece);
+    a.skip = (int)((a.pieces * (int64_t)piece - a.row_bytes) / elem);
     a.lanes = 1;
     while (a.lanes < 64 && a.lanes < a.pieces) a.lanes *= 2;
+    // fewer edges per group where there are few: four workgroups per compute unit (10 302 edges of 56 floats, 21
+    // workgroups of 8 batches each 18.4 us; 161 of one batch 4.5)
+    a.steps = kEdgeSteps;
+    while (a.steps > 1 && ceil_div(num_edges, (int64_t)(256 / a.lanes) * kEdgeUnroll * a.steps) < 1024) a.steps /= 2;
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(k_edge_rows, dim3((unsigned)ceil_div(num_dst * 8, 256)), dim3(256), 0, s, indptr, num_dst,
                        num_edges, (int32_t *)a.edge_row);
     FASTGL_LAUNCH_CHECK("fastgl_edge_weight_grad (edge rows)");
     const bool bf = dtype == FASTGL_BF16;
-    switch (piece) {
-    case 16: bf ? launch_dot<true, 16>(a, s) : launch_dot<false, 16>(a, s); break;
-    case 8: bf ? launch_dot<true, 8>(a, s) : launch_dot<false, 8>(a, s); break;
-    case 4: bf ? launch_dot<true, 4>(a, s) : launch_dot<false, 4>(a, s); break;
-    default: launch_dot<true, 2>(a, s); break;
-    }
+    if (piece == 16 && a.skip) bf ? launch_dot<true, 16, true>(a, s) : launch_dot<false, 16, true>(a, s);
+    else if (piece == 16) bf ? launch_dot<true, 16, false>(a, s) : launch_dot<false, 16, false>(a, s);
+    else bf ? launch_dot<true, 2, false>(a, s) : launch_dot<false, 4, false>(a, s);
     FASTGL_LAUNCH_CHECK("fastgl_edge_weight_grad");
     return FASTGL_OK;
 }

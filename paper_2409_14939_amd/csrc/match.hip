@@ -99,22 +99,23 @@ __global__ __launch_bounds__(kScanBlock) void k_match_rank(MatchArgs a)
     }
 }
 
-// Row copy: one thread moves one VEC-byte piece; consecutive threads take consecutive pieces of a row.
-template <int VEC>
+// Row copy: one thread moves one VEC-byte piece; consecutive threads take consecutive pieces of a row.  The last piece of a
+// row ends with it, so that rows of any length and alignment move 16 bytes per thread.
+template <int ELEM, int VEC>
 __global__ __launch_bounds__(256) void k_assemble_rows(const char *__restrict__ X_prev, const char *__restrict__ X_load,
                                                        const int32_t *__restrict__ src_row, int64_t n_new,
-                                                       int64_t row_bytes, int pieces, char *__restrict__ X_new)
+                                                       int64_t row_bytes, int pieces, uint64_t pieces_inv, char *__restrict__ X_new)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = t / pieces;
+    const int64_t i = pieces > 1 ? (int64_t)__umul64hi((uint64_t)t, pieces_inv) : t;     // t / pieces: t * pieces < 2^64
     if (i >= n_new) return;
-    const int64_t off = (t - i * pieces) * VEC;
+    const int64_t at = (t - i * pieces) * VEC, off = at < row_bytes - VEC ? at : row_bytes - VEC;
     const int32_t r = src_row[i];
     const char *src = r >= 0 ? X_prev + (int64_t)r * row_bytes : X_load + (int64_t)(-1 - r) * row_bytes;
     char *dst = X_new + i * row_bytes + off;
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    using u32x4 = typename Words<ELEM>::x4;
     if (VEC == 16)
-        __builtin_nontemporal_store(*reinterpret_cast<const f32x4 *>(src + off), reinterpret_cast<f32x4 *>(dst));
+        __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(src + off), reinterpret_cast<u32x4 *>(dst));
     else if (VEC == 4)
         *reinterpret_cast<uint32_t *>(dst) = *reinterpret_cast<const uint32_t *>(src + off);
     else
@@ -414,9 +415,8 @@ fastgl_status fastgl_assemble_rows(const void *X_prev, int64_t n_prev, const voi
         return FASTGL_ERR_UNSUPPORTED;
     }
     const int64_t row_bytes = feat * elem;
-    const bool v16 = row_bytes % 16 == 0 && ((((uintptr_t)X_prev | (uintptr_t)X_load | (uintptr_t)X_new) & 15) == 0);
-    const int vec = v16 ? 16 : (int)elem;
-    const int64_t pieces = row_bytes / vec;
+    const int vec = row_bytes >= 16 ? 16 : (int)elem;
+    const int64_t pieces = ceil_div(row_bytes, (int64_t)vec);
     const int64_t threads = n_new * pieces;
     if (ceil_div(threads, 256) >= INT32_MAX) {
         set_error("assemble too large");
@@ -425,15 +425,12 @@ fastgl_status fastgl_assemble_rows(const void *X_prev, int64_t n_prev, const voi
     const dim3 g = grid_for(threads, 256);
     hipStream_t s = (hipStream_t)stream;
     const char *xp = (const char *)X_prev, *xl = (const char *)X_load;
-    if (vec == 16)
-        hipLaunchKernelGGL(k_assemble_rows<16>, g, dim3(256), 0, s, xp, xl, src_row, n_new, row_bytes, (int)pieces,
-                           (char *)X_new);
-    else if (vec == 4)
-        hipLaunchKernelGGL(k_assemble_rows<4>, g, dim3(256), 0, s, xp, xl, src_row, n_new, row_bytes, (int)pieces,
-                           (char *)X_new);
-    else
-        hipLaunchKernelGGL(k_assemble_rows<2>, g, dim3(256), 0, s, xp, xl, src_row, n_new, row_bytes, (int)pieces,
-                           (char *)X_new);
+    const uint64_t inv = pieces > 1 ? UINT64_MAX / (uint64_t)pieces + 1 : 0;       // ceil(2^64 / pieces)
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, g, dim3(256), 0, s, xp, xl, src_row, n_new, row_bytes, (int)pieces, inv, (char *)X_new);
+    };
+    if (dtype == FASTGL_F32) vec == 16 ? go(k_assemble_rows<4, 16>) : go(k_assemble_rows<4, 4>);
+    else vec == 16 ? go(k_assemble_rows<2, 16>) : go(k_assemble_rows<2, 2>);
     FASTGL_LAUNCH_CHECK("fastgl_assemble_rows");
     return FASTGL_OK;
 }
