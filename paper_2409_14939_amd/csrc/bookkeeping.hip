@@ -1217,7 +1217,10 @@ static fastgl_status src_degrees(fastgl_plan *p, hipStream_t s)
 // them in stages: the small ones then ride along in launches that the others need anyway.
 static bool fits_once(const fastgl_plan *p, int parts, bool src_deg)
 {
-    if (parts & FASTGL_PLAN_BWD) return p->num_edges <= kOnceFullEdges && p->num_src <= kOnceSourcesFull && p->num_dst <= kOnceRows;
+    if (parts & FASTGL_PLAN_BWD) {
+        const int64_t most = p->num_edges <= 4 * p->num_src ? kOnceSparseEdges : kOnceFullEdges;
+        return p->num_edges <= most && p->num_src <= kOnceSourcesFull && p->num_dst <= kOnceRows;
+    }
     if (src_deg) return p->num_edges <= kOnceEdges && p->num_src <= kOnceSources && p->num_dst <= kOnceRows;
     return p->num_dst <= kOnceRowsFwd;
 }
@@ -1250,7 +1253,7 @@ static fastgl_status build_once(fastgl_plan *const *plans, const int *parts, con
                               p->counters + 2, nullptr, full ? p->split_src : nullptr, p->num_edges);
             J.indptr_T = p->indptr_T; J.indices_T = p->indices_T;
             J.perm = full && (p->parts & FASTGL_PLAN_PERM) ? p->perm : nullptr;
-            J.buckets = full || deg ? (int)ceil_div(p->num_src > 0 ? p->num_src : (full ? 1 : 0), (int64_t)kBucketIds) : 0;
+            J.buckets = full || deg ? (int)ceil_div(p->num_src > 0 ? p->num_src : (full ? 1 : 0), (int64_t)(full ? kOnceIds : kBucketIds)) : 0;
             J.row_groups = (int)ceil_div(p->num_dst, (int64_t)kOnceThreads);
             if (full) lds = sizeof(OnceShared);
             A.first[i] = blocks;

@@ -7,17 +7,19 @@
 // steps in the workgroups that there is one of (the lists of long rows, a bucket's chunks): the limits below are where
 // those chains, growing with the block, take as long as the launches they save.
 //
-//   bucket      2 048 consecutive source ids: counts the edges per source of its bucket and the edges of the
+//   bucket      512 consecutive source ids: counts the edges per source of its bucket and the edges of the
 //               buckets before it, writes the bucket's rows of indptr_T, out-degrees, scale factors and row
 //               sets, collects the bucket's edges in order (8 192 at a time) and places them stably
 //               (counts per wavefront and source, column scan, lane match - as k_plan_buckets does); the
-//               destination row of an edge comes from a binary search in row pointers held in LDS
-//   source degrees  the first half of that, for a forward-only plan of a GCN-normalised pass
+//               destination row of an edge comes from a binary search in row pointers held in LDS.  Every workgroup
+//               looks at all source ids, so small buckets cost reads, but the chain from there on is as long as the
+//               edges of a bucket (15 369 edges over 6 597 sources, two layers: 25 us with 2 048 ids, 13 now)
+//   source degrees  the first half of that for 2 048 ids, for a forward-only plan of a GCN-normalised pass
 //   long sources    one workgroup: degrees of all sources, ordered list of the long ones
 //   destination rows  1 024 rows per workgroup: degrees, scale factors, row sets
 //   long destinations one workgroup: ordered list of the long destination rows
 //
-// 256 seeds, fan-out 5 (1 276 edges, 1 276 sources), us a plan: 24 in stages (9 launches), 11 here.
+// 256 seeds, fan-out 5 (1 276 edges, 1 276 sources), us a plan: 24 in stages (9 launches), 9 here.
 #pragma once
 #include "plan_device.h"
 
@@ -31,9 +33,12 @@ constexpr int kOnceWaves = kOnceThreads / kWave;
 // Limits, us a plan in one launch / in stages (calls one after the other; a call that is waited for adds 3 to both).
 // Edges of a forward-only plan with source degrees: 16-bit row pointers and edge ids; 65 535 edges: 14 / 19.
 constexpr int kOnceEdges = 65535;
-// Edges of a full plan: two chunks of a bucket at most. One bucket's workgroup places its edges chunk by chunk, so a
-// block whose sources fall into few buckets is a chain: 44 080 edges over 10 359 sources 76 / 43; 16 384: 20 / 35.
-constexpr int kOnceFullEdges = 16384;
+// Edges of a full plan.  One bucket's workgroup places its edges chunk by chunk, so a block whose edges fall into few
+// buckets is a chain: 16 000 edges over 1 333 sources, 9 862 in one bucket, 27 / 40; 24 000 over 2 000, 16 932 in one,
+// 49 / 43.  With at most four edges per source on average the buckets stay small: 32 000 over 19 200 26 / 36 (5 199 in
+// one), 48 000 over 28 800 35 / 37 (6 356), evenly spread 24 / 32; 64 000 40 / 40.
+constexpr int kOnceFullEdges = 20480;
+constexpr int kOnceSparseEdges = 49152;
 // Destination rows: one workgroup scans all of them for long ones, 1 024 a step.  Forward-only: 8 192 rows 6.7 / 8.4,
 // 16 384 rows 11 / 8.7, 65 536 rows 38 / 8.8, for any number of edges.  With source degrees (more launches to save)
 // and full plans (row pointers in LDS): 24 576 rows 16 / 18 and 22 / 29.
@@ -45,9 +50,10 @@ constexpr int kOnceRows = 24576;
 constexpr int kOnceSourcesFull = 32768;
 constexpr int kOnceSources = 1 << 18;
 constexpr int kOnceChunk = 8192;           // edges of a bucket placed at a time
-constexpr int kOnceRounds = kOnceChunk / kOnceThreads;   // 64-edge rounds per wavefront
 constexpr int kOnceMaxJobs = 8;
-static_assert(kBucketIds == 2 * kOnceThreads, "two sources per thread");
+constexpr int kOnceBits = 9;               // source ids of a bucket of a full plan
+constexpr int kOnceIds = 1 << kOnceBits;
+static_assert(kOnceIds <= kOnceThreads && kBucketIds == 2 * kOnceThreads, "one or two sources per thread");
 
 struct OnceJob {
     const int32_t *indptr, *indices;
@@ -68,7 +74,7 @@ struct OnceShared {
     union {
         struct {
             int start[kBucketIds];                      // edges per source, then where its next edges go (within the bucket)
-            unsigned tab[kOnceWaves][kBucketIds / 2];   // per wavefront and source: count, then offset (16 bits each)
+            unsigned tab[kOnceWaves][kOnceIds / 2];     // per wavefront and source: count, then offset (16 bits each)
             uint32_t list[kOnceChunk];                  // collected edges: id | source within the bucket << 16
             uint16_t rows[kOnceRows + 2];               // indptr
         };
@@ -136,23 +142,25 @@ __device__ __forceinline__ void once_long_rows(const RowsArgs &A, int n, int *ld
     A.totals[1] = nc;
 }
 
+// BITS: 1 << BITS source ids; FULL: with the transpose.
+template <int BITS, bool FULL>
 __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, OnceShared &M, int *lds)
 {
+    constexpr int kIds = 1 << BITS, kPer = kIds > kOnceThreads ? kIds / kOnceThreads : 1;   // sources per thread
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
     const KeyRun run(J.indices, J.num_edges);
-    M.start[t] = 0;
-    M.start[t + kOnceThreads] = 0;
-    if (J.full)
+    for (int i = t; i < kIds; i += kOnceThreads) M.start[i] = 0;
+    if (FULL)
         for (int i = t; i <= J.num_dst; i += kOnceThreads) M.rows[i] = (uint16_t)J.indptr[i];
     __syncthreads();
     // edges of the bucket (per source too) and of the buckets before it
     int mine = 0, before = 0;
     run.each([&](int, int32_t key, bool ok) {
-        const int b = key >> kBucketBits;
+        const int b = key >> BITS;
         const bool in = ok && b == d;
         mine += __popcll(__ballot(in));
         before += __popcll(__ballot(ok && b < d));
-        if (in) atomicAdd(&M.start[key & (kBucketIds - 1)], 1);
+        if (in) atomicAdd(&M.start[key & (kIds - 1)], 1);
     });
     if (lane == 0) {
         lds[32 + w] = mine;
@@ -166,89 +174,102 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, OnceShared 
         total += lds[32 + k];
         B0 += lds[48 + k];
     }
-    const int c0 = M.start[2 * t], c1 = M.start[2 * t + 1];
+    const bool holds = kPer * t < kIds;      // this thread has sources: the same for a wavefront
+    int c[kPer], sum_c = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        c[k] = holds ? M.start[kPer * t + k] : 0;
+        sum_c += c[k];
+    }
     int all;
-    const int e0 = block_excl_scan(c0 + c1, &all, lds);
-    M.start[2 * t] = e0;
-    M.start[2 * t + 1] = e0 + c0;
+    int at = block_excl_scan(sum_c, &all, lds);
     int nl = 0, nc = 0;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {            // the bucket's rows
-        const int64_t r = (int64_t)d * kBucketIds + 2 * t + k;
-        const bool valid = r < J.num_src;
-        const int at = B0 + e0 + (k ? c0 : 0), len = k ? c1 : c0;
-        if (valid && J.full) J.indptr_T[r] = at;
-        row_emit(J.src, r, valid, at, len, nl, nc);
+    for (int k = 0; k < kPer; ++k) {         // the bucket's rows
+        const int64_t r = (int64_t)d * kIds + kPer * t + k;
+        const bool valid = holds && r < J.num_src;
+        if (holds) M.start[kPer * t + k] = at;
+        if (FULL && valid) J.indptr_T[r] = B0 + at;
+        row_emit(J.src, r, valid, B0 + at, c[k], nl, nc);
+        at += c[k];
     }
-    if (!J.full) return;
-    if (d == J.buckets - 1 && t == 0) J.indptr_T[J.num_src] = J.num_edges;
-
-    for (int f0 = 0; f0 < total; f0 += kOnceChunk) {
-        const int n = total - f0 < kOnceChunk ? total - f0 : kOnceChunk;
-        uint4 *z = reinterpret_cast<uint4 *>(&M.tab[0][0]);
-#pragma unroll
-        for (int k = 0; k < (int)(sizeof(M.tab) / sizeof(uint4)) / kOnceThreads; ++k) z[k * kOnceThreads + t] = make_uint4(0u, 0u, 0u, 0u);
-        int at = listed - f0;                // place in this chunk's list of the next edge of this wavefront
-        run.each([&](int e, int32_t key, bool ok) {
-            const bool in = ok && (key >> kBucketBits) == d;
-            const unsigned long long m = __ballot(in);
-            const int p = at + lanes_below((unsigned)m, (unsigned)(m >> 32));
-            if (in && p >= 0 && p < n) M.list[p] = (uint32_t)e | ((uint32_t)(key & (kBucketIds - 1)) << 16);
-            at += __popcll(m);
-        });
-        __syncthreads();
-        // this wavefront's run of the list: seg entries, a multiple of 64
-        const int seg = ((n + kOnceThreads - 1) / kOnceThreads) * kWave;
-        const int s0 = w * seg < n ? w * seg : n, s1 = s0 + seg < n ? s0 + seg : n;
-        int kk[kOnceRounds], ee[kOnceRounds], row[kOnceRounds];
-#pragma unroll
-        for (int u = 0; u < kOnceRounds; ++u) {
-            const int i = s0 + u * kWave + lane;
-            const uint32_t v = i < s1 ? M.list[i] : 0u;
-            kk[u] = i < s1 ? (int)(v >> 16) : -1;
-            ee[u] = (int)(v & 0xFFFFu);
-            row[u] = 0;
-            if (kk[u] >= 0) atomicAdd(&M.tab[w][kk[u] >> 1], 1u << ((kk[u] & 1) * 16));
-        }
-        // destination rows: the last row that starts at or before the edge; the rounds' searches side by side
+    if constexpr (FULL) {
+        if (d == J.buckets - 1 && t == 0) J.indptr_T[J.num_src] = J.num_edges;
         int span = 1;
         while (span < J.num_dst) span <<= 1;
-        for (int step = span >> 1; step > 0; step >>= 1) {
+        for (int f0 = 0; f0 < total; f0 += kOnceChunk) {
+            const int n = total - f0 < kOnceChunk ? total - f0 : kOnceChunk;
+            uint4 *z = reinterpret_cast<uint4 *>(&M.tab[0][0]);
+            for (int k = t; k < (int)(sizeof(M.tab) / sizeof(uint4)); k += kOnceThreads) z[k] = make_uint4(0u, 0u, 0u, 0u);
+            int to = listed - f0;            // place in this chunk's list of the next edge of this wavefront
+            run.each([&](int e, int32_t key, bool ok) {
+                const bool in = ok && (key >> BITS) == d;
+                const unsigned long long m = __ballot(in);
+                const int p = to + lanes_below((unsigned)m, (unsigned)(m >> 32));
+                if (in && p >= 0 && p < n) M.list[p] = (uint32_t)e | ((uint32_t)(key & (kIds - 1)) << 16);
+                to += __popcll(m);
+            });
+            __syncthreads();
+            // this wavefront's run of the list: seg entries, a multiple of 64
+            const int seg = ((n + kOnceThreads - 1) / kOnceThreads) * kWave;
+            const int s0 = w * seg < n ? w * seg : n, s1 = s0 + seg < n ? s0 + seg : n;
+            for (int i = s0 + lane; i < s1; i += kWave) {
+                const int k = (int)(M.list[i] >> 16);
+                atomicAdd(&M.tab[w][k >> 1], 1u << ((k & 1) * 16));
+            }
+            __syncthreads();
+            unsigned sum = 0;                // column scan over the wavefronts, two sources to a word
+            if (t < kIds / 2) {
 #pragma unroll
-            for (int u = 0; u < kOnceRounds; ++u) {
-                const int q = row[u] + step;
-                if (s0 + u * kWave < s1 && q < J.num_dst && (int)M.rows[q] <= ee[u]) row[u] = q;
+                for (int k = 0; k < kOnceWaves; ++k) {
+                    const unsigned v = M.tab[k][t];
+                    M.tab[k][t] = sum;
+                    sum += v;
+                }
+            }
+            __syncthreads();
+            constexpr int kSide = 2;         // rounds of 64 edges side by side
+            for (int i0 = s0; i0 < s1; i0 += kSide * kWave) {
+                int kk[kSide], ee[kSide], row[kSide];
+#pragma unroll
+                for (int u = 0; u < kSide; ++u) {
+                    const int i = i0 + u * kWave + lane;
+                    const uint32_t v = i < s1 ? M.list[i] : 0u;
+                    kk[u] = i < s1 ? (int)(v >> 16) : -1;
+                    ee[u] = (int)(v & 0xFFFFu);
+                    row[u] = 0;
+                }
+                // destination rows: the last row that starts at or before the edge
+                for (int step = span >> 1; step > 0; step >>= 1) {
+#pragma unroll
+                    for (int u = 0; u < kSide; ++u) {
+                        const int q = row[u] + step;
+                        row[u] = q < J.num_dst && (int)M.rows[q < J.num_dst ? q : 0] <= ee[u] ? q : row[u];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kSide; ++u) {
+                    const bool ok = kk[u] >= 0;
+                    const int k = ok ? kk[u] : 0, sh = (k & 1) * 16;
+                    unsigned mlo, mhi;
+                    match_lanes<BITS>(k, ok, mlo, mhi);
+                    const int lower = lanes_below(mlo, mhi);
+                    const int prior = (int)((M.tab[w][k >> 1] >> sh) & 0xFFFFu);
+                    // the LDS read above is issued before this update by the same wavefront
+                    if (ok && lower == 0) atomicAdd(&M.tab[w][k >> 1], (unsigned)(__popc(mlo) + __popc(mhi)) << sh);
+                    const int pos = B0 + M.start[k] + prior + lower;
+                    if (ok && pos < J.num_edges) {
+                        J.indices_T[pos] = row[u];
+                        if (J.perm) J.perm[pos] = ee[u];
+                    }
+                }
+            }
+            __syncthreads();
+            if (t < kIds / 2) {
+                M.start[2 * t] += (int)(sum & 0xFFFFu);
+                M.start[2 * t + 1] += (int)(sum >> 16);
             }
         }
-        __syncthreads();
-        unsigned sum = 0;                    // column scan over the wavefronts, two sources to a word
-#pragma unroll
-        for (int k = 0; k < kOnceWaves; ++k) {
-            const unsigned v = M.tab[k][t];
-            M.tab[k][t] = sum;
-            sum += v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < kOnceRounds; ++u) {
-            if (s0 + u * kWave >= s1) break;                 // the same for the whole wavefront
-            const bool ok = kk[u] >= 0;
-            const int k = ok ? kk[u] : 0, sh = (k & 1) * 16;
-            unsigned mlo, mhi;
-            match_lanes<kBucketBits>(k, ok, mlo, mhi);
-            const int lower = lanes_below(mlo, mhi);
-            const int prior = (int)((M.tab[w][k >> 1] >> sh) & 0xFFFFu);
-            // the LDS read above is issued before this update by the same wavefront
-            if (ok && lower == 0) atomicAdd(&M.tab[w][k >> 1], (unsigned)(__popc(mlo) + __popc(mhi)) << sh);
-            const int pos = B0 + M.start[k] + prior + lower;
-            if (ok && pos < J.num_edges) {
-                J.indices_T[pos] = row[u];
-                if (J.perm) J.perm[pos] = ee[u];
-            }
-        }
-        __syncthreads();
-        M.start[2 * t] += (int)(sum & 0xFFFFu);
-        M.start[2 * t + 1] += (int)(sum >> 16);
     }
 }
 
@@ -277,7 +298,8 @@ __global__ __launch_bounds__(kOnceThreads) void k_plan_once(OnceArgs A)
     const OnceJob &J = A.job[j];
     int b = blockIdx.x - A.first[j];
     if (b < J.buckets) {
-        once_bucket(J, b, M, lds);
+        if (J.full) once_bucket<kOnceBits, true>(J, b, M, lds);
+        else once_bucket<kBucketBits, false>(J, b, M, lds);
         return;
     }
     b -= J.buckets;

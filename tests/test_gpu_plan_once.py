@@ -63,9 +63,17 @@ def test_forward_only_plan_with_source_degrees(nd, ns, edges, hub):
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("edges", [16384, 16385])
+@pytest.mark.parametrize("edges", [16384, 16385, 20480, 20481])
 def test_full_plan_around_the_edge_limit(edges):
     check_bookkeeping(exact_block(np.random.default_rng(edges), 3000, 4097, edges, 9000), "once")
+
+
+# the limit of sparse blocks (at most four edges per source), buckets of 512 sources, several chunks of one bucket
+@pytest.mark.parametrize("nd,ns,edges", [(300, 5119, 20480), (300, 5119, 20481), (300, 5120, 20480), (300, 5121, 20484), (9000, 12288, 49152),
+                                         (9000, 12289, 49152), (9000, 12289, 49153), (9000, 12287, 49152), (700, 511, 20000),
+                                         (700, 512, 20000), (700, 513, 20000), (700, 1024, 8192), (700, 1025, 8193)])
+def test_full_plan_around_the_limit_of_sparse_blocks(nd, ns, edges):
+    check_bookkeeping(exact_block(np.random.default_rng(ns + edges), nd, ns, edges, 500), "once")
 
 
 @pytest.mark.parametrize("nd,ns,edges,hub", [(3000, 32768, 16384, 300), (3000, 32769, 16384, 300), (24576, 32768, 16384, 300),
