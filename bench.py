@@ -83,8 +83,8 @@ def idmap_leg(args, w, B, bg, torch, np, with_cpu):
         h["uniq"] = torch.empty(n, dtype=torch.int64, device=dev)
         h["res"] = torch.empty(2, dtype=torch.int32, device=dev)
         # table fill + one entry touched per ID + IDs in + slot array out and in + indices out + source list out
-        # (slots of 4 bytes in both modes)
-        h["bytes"] = {mode: per * B.fastgl_idmap_table_slots(n) + per * n + 8 * n + 8 * n + 4 * nbr.size + 8 * blk.num_src
+        # (four slots of 4 bytes per ID in both modes)
+        h["bytes"] = {mode: per * max(4 * n, B.fastgl_idmap_table_slots(n)) + per * n + 8 * n + 8 * n + 4 * nbr.size + 8 * blk.num_src
                       for mode, per in (("ordered", 4), ("fused", 4))}
         hops.append(h)
     n_ids = sum(h["dst"].numel() + h["nbr"].numel() for h in hops)

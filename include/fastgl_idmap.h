@@ -47,14 +47,15 @@ extern "C" {
 
 typedef enum { FASTGL_IDMAP_ORDERED = 0, FASTGL_IDMAP_FUSED = 1 } fastgl_idmap_mode;
 
-/* Slots of the hash table used for n_ids = n_dst + n_nbr global IDs: 1.5 per
- * input ID (at least 1024).  At most n_ids keys ever enter it, so it keeps empty
- * slots and linear probing always ends; a sampled hop, whose IDs mostly repeat,
- * fills a quarter of it. 0 if n_ids is negative or too large. */
+/* Entries of 16 bytes that a workspace for n_ids = n_dst + n_nbr global IDs has
+ * room for: 1.5 per input ID (at least 1024).  The table has at least as many
+ * slots (32 bits each, four per input ID).  At most n_ids keys ever enter it, so
+ * it keeps empty slots and linear probing always ends. 0 if n_ids is negative
+ * or too large. */
 int64_t fastgl_idmap_table_slots(int64_t n_ids);
 
 /* Bytes of device workspace (256-byte aligned) one call needs: the table
- * (room for 16 bytes per slot), a 32-bit reference per input ID and
+ * (16 bytes per entry), a 32-bit reference per input ID and
  * the block counts of the ordered mode. 0 for bad sizes. */
 size_t fastgl_idmap_workspace_bytes(int64_t n_dst, int64_t n_nbr);
 

@@ -40,22 +40,32 @@ struct __attribute__((aligned(16))) MaskSlot {
     unsigned long long mask;
 };
 
-// Capacity for n DISTINCT keys (Match, overlap counts): 2n slots (at least 1024), so the table is
-// never more than half full and a probe sequence always ends at an empty slot.
+// Entries that the workspace has room for, for n DISTINCT keys (Match, overlap counts): 2n (at least 1024), so a table
+// of that many is never more than half full and a probe sequence always ends at an empty slot.
 inline int64_t table_slots(int64_t n)
 {
     const int64_t cap = 2 * n;
     return cap < 1024 ? 1024 : cap;
 }
 
-// Capacity for the n input IDs of the ID map, most of which repeat (a sampled hop holds every hub
-// many times): 1.5 n slots.  The table can never fill up (there are at most n keys), a hop whose IDs
-// are all distinct loads it to two thirds, a typical one (a third to a half distinct) to a quarter.
-// Sized by the distinct IDs it would be smaller still, but their number is only known afterwards.
+// The same for the n input IDs of the ID map, most of which repeat (a sampled hop holds every hub many times): 1.5 n.
 inline int64_t idmap_slots(int64_t n)
 {
     const int64_t cap = n + n / 2;
     return cap < 1024 ? 1024 : cap;
+}
+
+// Slots of a table of positions of n IDs whose workspace has room for `room` entries of kSlotRoom bytes: four per ID,
+// which is at most what the room holds in 32-bit slots, so that a look nearly always ends at its first slot.  An ID's
+// chain of dependent accesses (slot, key, next slot) is what a small table's launches wait for, a wavefront for the
+// longest of 64: us with 1.5 / 3 / 4 / 6 slots per ID, ordered maps of three hops of 34 seeds 137 / 108 / 105 / 104, of
+// two hops of 5 017 seeds 124 / 113 / 113 / 114, of the headline's three hops 339 / 334 / 334 / 337; with 2 / 3 / 4 / 8,
+// windows of mini-batches of 34 seeds 133 / 126 / 121 / 120, of 8 000 1 580 / 1 550 / 1 545 / 1 554.
+inline int64_t position_slots(int64_t n, int64_t room)
+{
+    static_assert(4 * (int64_t)sizeof(int32_t) <= kSlotRoom, "four slots to an entry's room");
+    const int64_t cap = n <= kMaxIds / 4 ? 4 * n : 0;        // slot numbers stay below 2^30
+    return cap > room ? cap : room;
 }
 
 // Slot of an ID in a table of `cap` slots (any size below 2^31, not only powers of two): the upper

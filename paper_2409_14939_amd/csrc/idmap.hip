@@ -2,7 +2,7 @@
 // sampled hop -> consecutive local IDs.  See include/fastgl_idmap.h for the contract.
 //
 // Table: open addressing with linear probing, 32-bit slots that hold input positions (hash_table.h),
-// 1.5 slots per input ID (most of which repeat).
+// four slots per input ID (most of which repeat).
 //
 // FUSED mode is Algorithm 2: destinations claim their slots first, then every neighbour entry; the claimant of
 // a slot takes the next local ID from a counter (one atomic add per workgroup, the threads that claimed a slot
@@ -271,7 +271,7 @@ fastgl_status fastgl_idmap(const int64_t *dst_gid, int64_t n_dst, const int64_t 
     IdmapArgs a = {};
     a.dst_gid = dst_gid; a.nbr_gid = nbr_gid;
     a.n_dst = n_dst; a.n_nbr = n_nbr; a.n = n;
-    const int64_t cap = idmap_slots(n);
+    const int64_t cap = position_slots(n, idmap_slots(n));
     a.table = PositionTable{(int32_t *)(ws + L.table), (uint32_t)cap, position_bits(n)};
     a.ref = (int32_t *)(ws + L.ref);
     a.block_cnt = (int32_t *)(ws + L.block_cnt);

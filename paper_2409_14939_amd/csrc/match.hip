@@ -360,7 +360,7 @@ fastgl_status fastgl_match(const int64_t *prev_gid, int64_t n_prev, const int64_
     if (st != FASTGL_OK) return st;
     MatchArgs a = {};
     a.prev_gid = prev_gid; a.new_gid = new_gid; a.n_prev = n_prev; a.n_new = n_new;
-    const int64_t cap = table_slots(n_prev);
+    const int64_t cap = position_slots(n_prev, table_slots(n_prev));
     a.table = PositionTable{(int32_t *)((char *)workspace + L.table), (uint32_t)cap, position_bits(n_prev)};
     a.block_cnt = (int32_t *)((char *)workspace + L.block_cnt);
     a.nblocks = (int)ceil_div(n_new, kScanBlock);
