@@ -4,8 +4,8 @@
 //
 // The tiled kernel here forms dW and db (Y and dH: update_rows.hip; up to 8 columns: update_narrow.hip).
 // A workgroup of 4 wavefronts owns a 128 x 128 tile of the result (each wavefront a 64 x 64 quarter =
-// 2 x 2 accumulators of v_mfma_f32_32x32x16_bf16), or a 128 x 64 tile (a wavefront 32 x 64), and walks the contracted dimension in steps of 16, staged through two LDS buffers; three
-// workgroups share a compute unit.
+// 2 x 2 accumulators of v_mfma_f32_32x32x16_bf16), or a 128 x 64 tile (a wavefront 32 x 64), and walks the
+// contracted dimension in steps of 16, staged through two LDS buffers; three workgroups share a compute unit.
 //
 // The bf16 instruction runs at 16 times the rate of the fp32 one, so fp32 operands are not
 // multiplied as fp32: an element x is cut into three bf16 planes, x = x1 + x2 + x3 exactly
@@ -16,13 +16,21 @@
 // 2^-28 |a||b| on average.  bf16 storage needs one plane and one product.  An element that is not
 // finite, or beyond the largest bf16 (3.39e38), turns the results it enters into NaN.
 //
-// Each operand is copied to LDS from the layout it has in memory, so both kinds of operand get
-// coalesced global loads.  One plane of an operand tile (128 out x 16 contracted) in LDS:
-//   "row" operand   mem[out][contract]: 32 bytes per out index; the two 16-byte halves (contracted
-//                   0..7, 8..15) swap places where bit 2 ^ bit 3 of the out index is set
-//                   (conflict-free 16-byte reads)
-//   "col" operand   mem[contract][out]: [pair p = contracted 2p, 2p+1][out] dwords, 128 + 8 per pair
-// Lane half h (lanes 32h..32h+31) multiplies contracted indices 8h .. 8h+7 of both operands.
+// Both operands have the contracted index outside (mem[contract][out]: H and dZ) and are copied to LDS as they lie in
+// memory, four neighbouring columns per lane and load.  One plane of an operand tile (16 contracted x 128 out) in LDS:
+// [pair p = contracted 2p, 2p+1][out] dwords, 128 + 8 per pair.  Lane half h (lanes 32h..32h+31) multiplies contracted
+// indices 8h .. 8h+7 of both operands.
+//
+// Rows of any length and alignment: the four columns of a lane start early enough to end with the row, and move to
+// their places in registers.  Columns that do not exist are not masked: what they hold stays in columns of the result
+// that are not stored.  Only contracted indices past the end have to be zeros.
+// Bound by the matrix cores and the memory for fp32 (1.25 GB of operands at 4.3 TB/s for 512 K rows), by the
+// partial results' traffic for bf16 (as much as the operands for 87 000 rows; loads two steps ahead, and two steps to a
+// barrier, change nothing).
+// us with cold caches, gated, with the reduction; single-element loads for rows that are no whole quads, masks in tiles
+// at the matrix' edge, and 4 loads in flight in the reduction -> now:
+//   fp32  40 000 rows, 131 x 99: 87 -> 37;  300 000, 57 x 33: 95 -> 67;  100 000, 40 x 10: 35 -> 27;  512 K, 100 x 256: 307 -> 289
+//   bf16  200 000, 99 x 128: 110 -> 68;  300 000, 128 x 64: 72 -> 69;  87 000, 128 x 256: 62 -> 61;  50 000, 256 x 256: 51 -> 51
 #include <type_traits>
 
 #include "fastgl_update.h"
@@ -41,140 +49,74 @@ constexpr int kRoundSlots = 768;        // workgroups the device this is tuned f
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 struct Operand {
-    const void *p;        // element (out o, contracted k) at p[o*ld + k] ("row") or p[k*ld + o] ("col")
+    const void *p;        // element (contracted k, out o) at p[k*ld + o]
     const void *gate;     // same layout, or NULL; where gate <= 0 the element reads as 0 (ReLU derivative)
-    int64_t ld;           // fp32 or bf16 elements (the kernel's BF16 argument says which)
+    int64_t ld;           // out indices: fp32 or bf16 elements (the kernel's BF16 argument says which)
 };
 
 struct GemmArgs {
     Operand a, b;
-    void *c;                    // [R][C] result (of slab s: c + s*c_slab): fp32, or bf16 for Y / dH of a bf16 call
+    float *c;                   // [slab][c_slab]: [R][C] partial of every slab
     int64_t ldc, c_slab;
     int64_t R, C, Kc;           // result rows, result columns, contracted length
-    int64_t slab;               // contracted indices per slab (>= Kc when not split)
-    int64_t n_outer;            // slabs (split) or row tiles (not split)
+    int64_t slab, n_slabs;      // contracted indices per slab
     int tiles_r, tiles_c;
-    int split;                  // 1: outer index = slab, inner = (row tile, column tile)
-    const float *bias;          // [C] or NULL, added before the activation
-    int relu;
-    float *colsum;              // [slab][colsum_slab]: sums of operand b over the slab, or NULL
+    float *colsum;              // [slab][colsum_slab]: sums of operand b over the slab
     int64_t colsum_slab;
 };
 
-// A quad = four consecutive elements p[off..off+3] of which the first `nvalid` exist; the rest must
-// read as 0.  Loading and masking are split so that the loads of the next stage stay in flight
-// during the MFMAs of the current one: load_quad only issues loads (no control flow around them - a
-// load behind a branch is waited for at the join - and no arithmetic on the result); an element
-// that does not exist is loaded from offset 0, which the host guarantees to be readable.
-// mask_quad, called when the registers are written to LDS, zeroes what does not exist or is gated
-// off.  VEC: one 16-byte load; the host selects it only when every extent is a multiple of 4, so
-// nvalid is 0 or 4.
+// A quad = four consecutive elements.  Loading and everything after are split so that the loads of the next steps stay
+// in flight during the MFMAs of the current one: loads have no control flow around them (a load behind a branch is
+// waited for at the join) and no arithmetic on their result.
 template <bool GATE, bool BF16>
 struct Quad {
     typename QuadBits<BF16>::type v;
     typename QuadBits<BF16>::type g[GATE ? 1 : 0];
 };
 
-// `base` is uniform over the workgroup (the tile's origin), `off` a per-lane 32-bit element offset.
-template <bool VEC, bool GATE, bool BF16>
-__device__ __forceinline__ void load_quad(const void *__restrict__ base_, const void *__restrict__ gate_,
-                                          uint32_t off, int nvalid, Quad<GATE, BF16> &q)
+// Four elements from p on, which need no more alignment than an element has.
+__device__ __forceinline__ float4 load_four(const float *p)
 {
-    typedef typename QuadBits<BF16>::type Q;
-    typedef typename QuadBits<BF16>::elem E;
-    const E *base = static_cast<const E *>(base_), *gate = static_cast<const E *>(gate_);
-    if (VEC) {
-        const uint32_t o = nvalid >= 4 ? off : 0u;
-        q.v = *reinterpret_cast<const Q *>(base + o);
-        if (GATE) q.g[0] = *reinterpret_cast<const Q *>(gate + o);
-    } else {
-        E e[4], f[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t o = i < nvalid ? off + i : 0u;
-            e[i] = base[o];
-            if (GATE) f[i] = gate[o];
-        }
-        if constexpr (BF16) {
-            q.v = make_uint2((uint32_t)e[0] | ((uint32_t)e[1] << 16), (uint32_t)e[2] | ((uint32_t)e[3] << 16));
-            if (GATE) q.g[0] = make_uint2((uint32_t)f[0] | ((uint32_t)f[1] << 16), (uint32_t)f[2] | ((uint32_t)f[3] << 16));
-        } else {
-            q.v = make_float4(e[0], e[1], e[2], e[3]);
-            if (GATE) q.g[0] = make_float4(f[0], f[1], f[2], f[3]);
-        }
-    }
+    const Words<4>::x4 w = *reinterpret_cast<const Words<4>::x4 *>(p);
+    return make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3]));
 }
-
-template <bool GATE, bool BF16>
-__device__ __forceinline__ float4 mask_quad(const Quad<GATE, BF16> &q, int nvalid)
+__device__ __forceinline__ uint2 load_four(const uint16_t *p)
 {
-    float4 v = quad_to_f32(q.v);
-    if (GATE) {
-        const float4 g = quad_to_f32(q.g[0]);
-        v.x = g.x > 0.f ? v.x : 0.f;
-        v.y = g.y > 0.f ? v.y : 0.f;
-        v.z = g.z > 0.f ? v.z : 0.f;
-        v.w = g.w > 0.f ? v.w : 0.f;
-    }
-    v.x = nvalid > 0 ? v.x : 0.f;
-    v.y = nvalid > 1 ? v.y : 0.f;
-    v.z = nvalid > 2 ? v.z : 0.f;
-    v.w = nvalid > 3 ? v.w : 0.f;
-    return v;
+    const Words<2>::x2 w = *reinterpret_cast<const Words<2>::x2 *>(p);
+    return make_uint2(w[0], w[1]);
+}
+// The same one by one, where a row has fewer: element i < n, the others the first one again.
+template <class E>
+__device__ __forceinline__ typename QuadBits<sizeof(E) == 2>::type load_few(const E *p, uint32_t off, int n)
+{
+    E e[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[i] = p[i < n ? off + i : 0u];
+    if constexpr (sizeof(E) == 2) return make_uint2((uint32_t)e[0] | ((uint32_t)e[1] << 16), (uint32_t)e[2] | ((uint32_t)e[3] << 16));
+    else return make_float4(e[0], e[1], e[2], e[3]);
 }
 
 __device__ __forceinline__ int clamp4(int64_t n) { return n >= 4 ? 4 : (n <= 0 ? 0 : (int)n); }
 
-// Writes a wavefront's 32 FA x 64 part of the result tile at (r0, c0): bias, activation, rounding.
+// Writes a wavefront's 32 FA x 64 part of the result tile at (r0, c0).
 // Accumulator element e of lane (h, l32) is row 8*(e/4) + 4*h + e%4, column l32 of its 32 x 32 tile.
-// Y and dH of a bf16 call are bf16; slab partials are always fp32.  Y and dH leave with streaming
-// stores (STREAM); slab partials are re-read at once.
-template <bool OUT_BF16, bool STREAM, int FA>
+template <int FA>
 __device__ __forceinline__ void write_tile(const GemmArgs &g, const f32x16 (&acc)[FA][2], int64_t r0, int64_t c0,
                                            int64_t slab_id, int wr, int wc, int h, int l32)
 {
     const int64_t row0 = r0 + wr * 32 * FA + 4 * h, col0 = c0 + wc * 64 + l32;
-    typedef typename QuadBits<OUT_BF16>::elem OutT;
-    OutT *cb = static_cast<OutT *>(g.c) + slab_id * g.c_slab + row0 * g.ldc + col0;
-    const bool relu = g.relu != 0;
-    auto put = [](OutT *dst, float v, bool stream) {
-        if constexpr (OUT_BF16) {
-            const uint16_t w = f32_to_bf16(v);
-            if (stream) __builtin_nontemporal_store(w, dst); else *dst = w;
-        } else {
-            if (stream) __builtin_nontemporal_store(v, dst); else *dst = v;
-        }
-    };
-    if (r0 + kTile <= g.R && c0 + 64 * FA <= g.C) {
+    float *cb = g.c + slab_id * g.c_slab + row0 * g.ldc + col0;
+    const bool whole = r0 + kTile <= g.R && c0 + 64 * FA <= g.C;       // uniform
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const float bj = g.bias ? g.bias[col0 + 32 * j] : 0.f;
+    for (int j = 0; j < 2; ++j) {
+        if (!whole && col0 + 32 * j >= g.C) continue;
 #pragma unroll
-            for (int i = 0; i < FA; ++i)
+        for (int i = 0; i < FA; ++i)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    float v = acc[i][j][e] + bj;
-                    if (relu) v = v > 0.f ? v : 0.f;
-                    put(&cb[(int64_t)(32 * i + 8 * (e >> 2) + (e & 3)) * g.ldc + 32 * j], v, STREAM);
-                }
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t col = col0 + 32 * j;
-            if (col >= g.C) continue;
-            const float bj = g.bias ? g.bias[col] : 0.f;
-#pragma unroll
-            for (int i = 0; i < FA; ++i)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int dr = 32 * i + 8 * (e >> 2) + (e & 3);
-                    if (row0 + dr >= g.R) continue;
-                    float v = acc[i][j][e] + bj;
-                    if (relu) v = v > 0.f ? v : 0.f;
-                    put(&cb[(int64_t)dr * g.ldc + 32 * j], v, false);
-                }
-        }
+            for (int e = 0; e < 16; ++e) {
+                const int dr = 32 * i + 8 * (e >> 2) + (e & 3);
+                if (whole || row0 + dr < g.R) cb[(int64_t)dr * g.ldc + 32 * j] = acc[i][j][e];
+            }
     }
 }
 
@@ -182,11 +124,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kPairStride = kTile + 8;                        // dwords between pairs of a "col" plane
-constexpr int kPlaneBytes = (kStep / 2) * kPairStride * 4;    // >= kTile * 32, the "row" plane
-static_assert(kPlaneBytes >= kTile * 32 && kStep == 16, "plane size");
-
-__device__ __forceinline__ int row_swizzle(int o) { return ((o >> 2) ^ (o >> 3)) & 1; }
+constexpr int kPairStride = kTile + 8;                        // dwords between pairs of a plane
+constexpr int kPlaneBytes = (kStep / 2) * kPairStride * 4;
 
 // Planes of the pair (x0, x1), packed as two bf16 per dword (x0 in the low half).
 template <int PLANES>
@@ -203,142 +142,149 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t (&w)[PLA
     }
 }
 
-// One 128 (out) x 16 (contracted) operand tile: global -> registers (fetch), registers -> bf16
-// planes in LDS (stage).  "row": lane t holds contracted 4(t%4)..+3 of out indices t/4 and t/4 + 64;
-// "col": lane t holds out indices 4(t%32)..+3 of contracted 2(t/32) and 2(t/32) + 1.  SUM keeps a
-// running sum per held out index of everything staged ("col" only).  MASK = false is for whole steps
-// of tiles that lie inside the matrices: no lane masks at all.
-template <bool COL, bool VEC, bool GATE, bool BF16, int PLANES, bool SUM>
+// One operand tile of 16 contracted x 128 out indices: global -> registers (fetch), registers -> bf16 planes in LDS
+// (stage).  Lane t has out indices 4(t%32)..+3 of contracted 2(t/32) and 2(t/32) + 1.  SUM keeps a running sum per held
+// out index of everything staged.  MASK = false is for steps that lie inside the contracted range.
+// QUADS: rows of at least four elements; else element by element.
+template <bool QUADS, bool GATE, bool BF16, int PLANES, bool SUM>
 struct PlaneMover {
     typedef typename QuadBits<BF16>::elem E;
     Quad<GATE, BF16> r[2];      // [slot]
-    uint32_t off[2];
-    int nv_out;             // row: bit s set if slot s is an existing out index; col: quad elements in range
-    int64_t ld, o0;
+    uint32_t off[2];            // of the slot's quad from the step's first row on
+    uint32_t first;             // the same in the first row: an element that exists
+    int moved;                  // columns that the quad starts early
+    int n_out;                  // !QUADS: columns that exist
+    bool any_moved;             // the same for the workgroup
+    int64_t ld;
     const E *p, *gate;
     float sum[SUM ? 4 : 1];
 
-    __device__ __forceinline__ void init(const Operand &op, int64_t o0_, int64_t omax)
+    __device__ __forceinline__ void init(const Operand &op, int64_t o0, int64_t omax)
     {
-        static_assert(!SUM || COL, "running sums are kept for col operands");
         const int t = threadIdx.x;
-        ld = op.ld; o0 = o0_; p = static_cast<const E *>(op.p); gate = static_cast<const E *>(op.gate);
-        nv_out = 0;
+        ld = op.ld; p = static_cast<const E *>(op.p); gate = static_cast<const E *>(op.gate);
+        const int64_t o = o0 + 4 * (t & 31), last = omax - 4, at = QUADS && o > last ? last : o;
+        first = QUADS ? (uint32_t)at : 0u;
+        moved = (int)(o - at < 3 ? o - at : 3);          // more: none of the quad's columns exists
+        any_moved = QUADS && (omax & 3) && o0 + kTile > omax;
+        n_out = clamp4(omax - o);
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (!COL) {
-                const int dr = t / 4 + 64 * s;
-                off[s] = (uint32_t)dr * (uint32_t)ld + 4u * (t % 4);
-                if (o0 + dr < omax) nv_out |= 1 << s;
-            } else {
-                off[s] = (uint32_t)(2 * (t >> 5) + s) * (uint32_t)ld + 4u * (t & 31);
-            }
-        }
-        if (COL) nv_out = clamp4(omax - (o0 + 4 * (t & 31)));
+        for (int s = 0; s < 2; ++s) off[s] = (uint32_t)(2 * (t >> 5) + s) * (uint32_t)ld + (uint32_t)at;
 #pragma unroll
         for (int j = 0; j < (SUM ? 4 : 1); ++j) sum[j] = 0.f;
     }
 
-    template <bool MASK>
-    __device__ __forceinline__ int nvalid(int s, int64_t k0, int64_t kend) const
+    __device__ __forceinline__ static bool in_range(int s, int64_t k0, int64_t kend)
     {
-        if (!MASK) return 4;
-        const int t = threadIdx.x;
-        if (!COL) return (nv_out >> s) & 1 ? clamp4(kend - (k0 + 4 * (t % 4))) : 0;
-        return k0 + 2 * (t >> 5) + s < kend ? nv_out : 0;
+        return k0 + 2 * (int)(threadIdx.x >> 5) + s < kend;
     }
 
+    // A row beyond kend (of a step that is, of row 0) is loaded from the step's first row, all masked.
     template <bool MASK>
     __device__ __forceinline__ void fetch(int64_t k0, int64_t kend)
     {
-        // A step beyond kend has no element; its (all masked) loads go to contracted index 0 of the
-        // tile's first out index, an element that exists whenever the operand has any (the host
-        // substitutes a readable pointer when it has none).
-        const int64_t kf = k0 < kend ? k0 : 0;                         // uniform
-        const int64_t origin = COL ? kf * ld + o0 : o0 * ld + kf;      // uniform
+        const int64_t origin = (k0 < kend ? k0 : 0) * ld;              // uniform
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
-            load_quad<VEC, GATE, BF16>(p + origin, GATE ? gate + origin : nullptr, off[s],
-                                       nvalid<MASK>(s, k0, kend), r[s]);
+        for (int s = 0; s < 2; ++s) {
+            const bool ok = !MASK || in_range(s, k0, kend);
+            if constexpr (QUADS) {
+                const uint32_t o = ok ? off[s] : first;
+                r[s].v = load_four(p + origin + o);
+                if constexpr (GATE) r[s].g[0] = load_four(gate + origin + o);
+            } else {
+                r[s].v = load_few(p + origin, off[s], ok ? n_out : 0);
+                if constexpr (GATE) r[s].g[0] = load_few(gate + origin, off[s], ok ? n_out : 0);
+            }
+        }
     }
 
-    // (k0, kend) must be those of the fetch that filled the register set.
+    // (k0, kend) must be those of the fetch that filled the registers.
     template <bool MASK>
     __device__ __forceinline__ void stage(char *lds, int64_t k0, int64_t kend)
     {
         const int t = threadIdx.x;
-        const float4 v0 = mask_quad<GATE, BF16>(r[0], nvalid<MASK>(0, k0, kend));
-        const float4 v1 = mask_quad<GATE, BF16>(r[1], nvalid<MASK>(1, k0, kend));
-        if (!COL) {
+        float4 v[2];
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const float4 v = s == 0 ? v0 : v1;
-                const int o = t / 4 + 64 * s, kq = t % 4;
-                uint32_t lo[PLANES], hi[PLANES];
-                split_pair<PLANES>(v.x, v.y, lo);
-                split_pair<PLANES>(v.z, v.w, hi);
-                char *dst = lds + o * 32 + 16 * ((kq >> 1) ^ row_swizzle(o)) + 8 * (kq & 1);
-#pragma unroll
-                for (int pl = 0; pl < PLANES; ++pl)
-                    *reinterpret_cast<uint2 *>(dst + pl * kPlaneBytes) = make_uint2(lo[pl], hi[pl]);
+        for (int s = 0; s < 2; ++s) {
+            v[s] = quad_to_f32(r[s].v);
+            if constexpr (GATE) {
+                const float4 g = quad_to_f32(r[s].g[0]);
+                v[s].x = g.x > 0.f ? v[s].x : 0.f;
+                v[s].y = g.y > 0.f ? v[s].y : 0.f;
+                v[s].z = g.z > 0.f ? v[s].z : 0.f;
+                v[s].w = g.w > 0.f ? v[s].w : 0.f;
             }
-        } else {
-            uint32_t w[4][PLANES];
-            split_pair<PLANES>(v0.x, v1.x, w[0]);
-            split_pair<PLANES>(v0.y, v1.y, w[1]);
-            split_pair<PLANES>(v0.z, v1.z, w[2]);
-            split_pair<PLANES>(v0.w, v1.w, w[3]);
-            char *dst = lds + ((t >> 5) * kPairStride + 4 * (t & 31)) * 4;
-#pragma unroll
-            for (int pl = 0; pl < PLANES; ++pl)
-                *reinterpret_cast<uint4 *>(dst + pl * kPlaneBytes) = make_uint4(w[0][pl], w[1][pl], w[2][pl], w[3][pl]);
-            if (SUM) {
-                sum[0] += v0.x + v1.x;
-                sum[1] += v0.y + v1.y;
-                sum[2] += v0.z + v1.z;
-                sum[3] += v0.w + v1.w;
+            if (any_moved) {             // what moves up from behind the quad is a column that does not exist
+                if (moved & 1) v[s] = make_float4(v[s].y, v[s].z, v[s].w, v[s].w);
+                if (moved & 2) v[s] = make_float4(v[s].z, v[s].w, v[s].w, v[s].w);
             }
+            if (MASK && !in_range(s, k0, kend)) v[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        uint32_t w[4][PLANES];
+        split_pair<PLANES>(v[0].x, v[1].x, w[0]);
+        split_pair<PLANES>(v[0].y, v[1].y, w[1]);
+        split_pair<PLANES>(v[0].z, v[1].z, w[2]);
+        split_pair<PLANES>(v[0].w, v[1].w, w[3]);
+        char *dst = lds + ((t >> 5) * kPairStride + 4 * (t & 31)) * 4;
+#pragma unroll
+        for (int pl = 0; pl < PLANES; ++pl)
+            *reinterpret_cast<uint4 *>(dst + pl * kPlaneBytes) = make_uint4(w[0][pl], w[1][pl], w[2][pl], w[3][pl]);
+        if (SUM) {
+            sum[0] += v[0].x + v[1].x;
+            sum[1] += v[0].y + v[1].y;
+            sum[2] += v[0].z + v[1].z;
+            sum[3] += v[0].w + v[1].w;
         }
     }
 };
 
-// A "col" operand tile of 64 out indices: lane t holds out indices 2(t%32), +1 of contracted 2(t/32) and
-// 2(t/32) + 1, so that all lanes have the same share; LDS as above, the first 64 dwords of every pair.
-template <bool VEC, bool GATE, bool BF16, int PLANES, bool SUM>
+// A tile of 64 out indices: lane t has out indices 2(t%32), +1 of contracted 2(t/32) and 2(t/32) + 1, so that all lanes
+// have the same share; LDS as above, the first 64 dwords of every pair.
+template <bool QUADS, bool GATE, bool BF16, int PLANES, bool SUM>
 struct HalfMover {
     typedef typename QuadBits<BF16>::elem E;
     typedef typename std::conditional<BF16, uint32_t, float2>::type Duo;
-    Duo v[2], g[GATE ? 2 : 1];  // [slot]
-    uint32_t off[2];
-    int nv_out;                 // out indices in range, 0 .. 2
-    int64_t ld, o0;
+    Duo v[2], g[GATE ? 2 : 1];           // [slot]
+    uint32_t off[2], first;
+    int n_out;                           // !QUADS: columns that exist, 0 .. 2
+    bool moved, any_moved;
+    int64_t ld;
     const E *p, *gate;
     float sum[2];
 
-    __device__ __forceinline__ void init(const Operand &op, int64_t o0_, int64_t omax)
+    __device__ __forceinline__ void init(const Operand &op, int64_t o0, int64_t omax)
     {
         const int t = threadIdx.x;
-        ld = op.ld; o0 = o0_; p = static_cast<const E *>(op.p); gate = static_cast<const E *>(op.gate);
+        ld = op.ld; p = static_cast<const E *>(op.p); gate = static_cast<const E *>(op.gate);
+        const int64_t o = o0 + 2 * (t & 31), last = omax - 2, at = QUADS && o > last ? last : o;
+        first = QUADS ? (uint32_t)at : 0u;
+        moved = o > at;
+        any_moved = QUADS && (omax & 1) && o0 + kTile / 2 > omax;
+        const int n = clamp4(omax - o);
+        n_out = n < 2 ? n : 2;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) off[s] = (uint32_t)(2 * (t >> 5) + s) * (uint32_t)ld + 2u * (t & 31);
-        const int n = clamp4(omax - (o0 + 2 * (t & 31)));
-        nv_out = n < 2 ? n : 2;
+        for (int s = 0; s < 2; ++s) off[s] = (uint32_t)(2 * (t >> 5) + s) * (uint32_t)ld + (uint32_t)at;
         sum[0] = sum[1] = 0.f;
     }
 
-    template <bool MASK>
-    __device__ __forceinline__ int nvalid(int s, int64_t k0, int64_t kend) const
+    __device__ __forceinline__ static bool in_range(int s, int64_t k0, int64_t kend)
     {
-        if (!MASK) return 2;
-        return k0 + 2 * (int)(threadIdx.x >> 5) + s < kend ? nv_out : 0;
+        return k0 + 2 * (int)(threadIdx.x >> 5) + s < kend;
     }
 
-    __device__ __forceinline__ static Duo load(const E *base, uint32_t o, int n)
+    __device__ __forceinline__ Duo load(const E *base, int s, bool ok) const
     {
-        if constexpr (VEC) {
-            return *reinterpret_cast<const Duo *>(base + (n == 2 ? o : 0u));
+        if constexpr (QUADS) {
+            const E *q = base + (ok ? off[s] : first);
+            if constexpr (BF16) {
+                return *reinterpret_cast<const Words<2>::x1 *>(q);
+            } else {
+                const Words<4>::x2 w = *reinterpret_cast<const Words<4>::x2 *>(q);
+                return make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
+            }
         } else {
-            const E x = base[n > 0 ? o : 0u], y = base[n > 1 ? o + 1 : 0u];
+            const int n = ok ? n_out : 0;
+            const E x = base[n > 0 ? off[s] : 0u], y = base[n > 1 ? off[s] + 1 : 0u];
             if constexpr (BF16) return (uint32_t)x | ((uint32_t)y << 16);
             else return make_float2(x, y);
         }
@@ -349,16 +295,15 @@ struct HalfMover {
         return make_float2(__uint_as_float(d << 16), __uint_as_float(d & 0xFFFF0000u));
     }
 
-    // A step beyond kend loads, all masked, from contracted index 0, as PlaneMover does.
     template <bool MASK>
     __device__ __forceinline__ void fetch(int64_t k0, int64_t kend)
     {
-        const int64_t origin = (k0 < kend ? k0 : 0) * ld + o0;         // uniform
+        const int64_t origin = (k0 < kend ? k0 : 0) * ld;              // uniform
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const int n = nvalid<MASK>(s, k0, kend);
-            v[s] = load(p + origin, off[s], n);
-            if constexpr (GATE) g[s] = load(gate + origin, off[s], n);
+            const bool ok = !MASK || in_range(s, k0, kend);
+            v[s] = load(p + origin, s, ok);
+            if constexpr (GATE) g[s] = load(gate + origin, s, ok);
         }
     }
 
@@ -369,15 +314,14 @@ struct HalfMover {
         float2 x[2];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            const int n = nvalid<MASK>(s, k0, kend);
             x[s] = to_f32(v[s]);
             if constexpr (GATE) {
                 const float2 open = to_f32(g[s]);
                 x[s].x = open.x > 0.f ? x[s].x : 0.f;
                 x[s].y = open.y > 0.f ? x[s].y : 0.f;
             }
-            x[s].x = n > 0 ? x[s].x : 0.f;
-            x[s].y = n > 1 ? x[s].y : 0.f;
+            if (any_moved && moved) x[s].x = x[s].y;
+            if (MASK && !in_range(s, k0, kend)) x[s] = make_float2(0.f, 0.f);
         }
         uint32_t w[2][PLANES];
         split_pair<PLANES>(x[0].x, x[1].x, w[0]);
@@ -393,10 +337,8 @@ struct HalfMover {
 };
 
 // The eight values (contracted indices 8h .. 8h+7) of out index o in one plane.
-template <bool COL>
 __device__ __forceinline__ uint4 read_plane(const char *plane, int o, int h)
 {
-    if (!COL) return *reinterpret_cast<const uint4 *>(plane + o * 32 + 16 * (h ^ row_swizzle(o)));
     const uint32_t *q = reinterpret_cast<const uint32_t *>(plane) + 4 * h * kPairStride + o;
     return make_uint4(q[0], q[kPairStride], q[2 * kPairStride], q[3 * kPairStride]);
 }
@@ -407,7 +349,7 @@ struct Frags {
     uint4 a[FA][PLANES], b[2][PLANES];
 };
 
-template <bool A_COL, bool B_COL, int PLANES, int FA>
+template <int PLANES, int FA>
 __device__ __forceinline__ void read_frags(const char *la, const char *lb, int wr, int wc, int l32, int h,
                                            Frags<PLANES, FA> &f)
 {
@@ -415,8 +357,8 @@ __device__ __forceinline__ void read_frags(const char *la, const char *lb, int w
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int pl = 0; pl < PLANES; ++pl) {
-            if (i < FA) f.a[i][pl] = read_plane<A_COL>(la + pl * kPlaneBytes, wr * 32 * FA + i * 32 + l32, h);
-            f.b[i][pl] = read_plane<B_COL>(lb + pl * kPlaneBytes, wc * 64 + i * 32 + l32, h);
+            if (i < FA) f.a[i][pl] = read_plane(la + pl * kPlaneBytes, wr * 32 * FA + i * 32 + l32, h);
+            f.b[i][pl] = read_plane(lb + pl * kPlaneBytes, wc * 64 + i * 32 + l32, h);
         }
 }
 
@@ -440,37 +382,34 @@ __device__ __forceinline__ void mma_frags(const Frags<PLANES, FA> &f, f32x16 (&a
 
 // One step of the contracted range: the loads of the next step are issued, this step is multiplied
 // out of LDS buffer `cur`, and the next one is split into the other buffer.  No branch inside.
-template <bool MASK, bool A_COL, bool B_COL, int PLANES, int FA, class MoverA, class MoverB>
-__device__ __forceinline__ void one_step(MoverA &ma, MoverB &mb, char *la, char *lb, int cur, int operand_bytes,
-                                         int64_t k0, int64_t kend, int wr, int wc, int l32, int h,
-                                         f32x16 (&acc)[FA][2])
+template <bool MASK, int PLANES, int FA, class MoverA, class MoverB>
+__device__ __forceinline__ void one_step(MoverA &ma, MoverB &mb, char *la, char *lb, int cur, int64_t k0, int64_t kend,
+                                         int wr, int wc, int l32, int h, f32x16 (&acc)[FA][2])
 {
+    constexpr int kBytes = PLANES * kPlaneBytes;
     ma.template fetch<MASK>(k0 + kStep, kend);
     mb.template fetch<MASK>(k0 + kStep, kend);
     __builtin_amdgcn_sched_barrier(0);       // the loads stay ahead of the step's other work
     Frags<PLANES, FA> f;
-    read_frags<A_COL, B_COL, PLANES, FA>(la + cur * operand_bytes, lb + cur * operand_bytes, wr, wc, l32, h, f);
+    read_frags<PLANES, FA>(la + cur * kBytes, lb + cur * kBytes, wr, wc, l32, h, f);
     mma_frags<PLANES, FA>(f, acc);
-    ma.template stage<MASK>(la + (cur ^ 1) * operand_bytes, k0 + kStep, kend);
-    mb.template stage<MASK>(lb + (cur ^ 1) * operand_bytes, k0 + kStep, kend);
+    ma.template stage<MASK>(la + (cur ^ 1) * kBytes, k0 + kStep, kend);
+    mb.template stage<MASK>(lb + (cur ^ 1) * kBytes, k0 + kStep, kend);
     __syncthreads();
 }
 
-// The contracted range [kbeg, kend) of one result tile.  The first n_plain steps touch nothing but
-// whole steps of a tile that lies inside both operands (a step also loads and converts the one after
-// it) and run without lane masks; the others, at least one, mask what does not exist - a step beyond
-// kend is a step of zeros.  The MFMAs are not behind any condition other than the two loop counts:
-// accumulators that can reach the end by a path without MFMAs are given a second set of registers
-// by the compiler.
-template <bool A_COL, bool B_COL, int PLANES, int FA, class MoverA, class MoverB>
-__device__ __forceinline__ void run_steps(MoverA &ma, MoverB &mb, char *la, char *lb, int operand_bytes, int64_t kbeg,
-                                          int64_t kend, bool inside, int wr, int wc, int l32, int h,
-                                          f32x16 (&acc)[FA][2])
+// The contracted range [kbeg, kend) of one result tile.  The first steps touch nothing but whole steps (a step also loads
+// and converts the one after it) and run without masks; the others, at least one, mask what does not exist - a
+// step beyond kend is a step of zeros.  The MFMAs are not behind any condition other than the two loop counts:
+// accumulators that can reach the end by a path without MFMAs are given a second set of registers by the compiler.
+template <int PLANES, int FA, class MoverA, class MoverB>
+__device__ __forceinline__ void run_steps(MoverA &ma, MoverB &mb, char *la, char *lb, int64_t kbeg, int64_t kend, bool quads,
+                                          int wr, int wc, int l32, int h, f32x16 (&acc)[FA][2])
 {
     const int64_t len = kend > kbeg ? kend - kbeg : 0;
     const int64_t nstep = len > 0 ? (len + kStep - 1) / kStep : 1;
-    int64_t n_plain = inside ? len / kStep - 1 : 0;
-    n_plain = n_plain < 0 ? 0 : (n_plain > nstep - 1 ? nstep - 1 : n_plain);
+    int64_t plain = quads ? len / kStep - 1 : 0;
+    plain = plain < 0 ? 0 : plain;                         // < nstep
     ma.template fetch<true>(kbeg, kend);
     mb.template fetch<true>(kbeg, kend);
     ma.template stage<true>(la, kbeg, kend);
@@ -478,18 +417,18 @@ __device__ __forceinline__ void run_steps(MoverA &ma, MoverB &mb, char *la, char
     __syncthreads();
     int64_t k0 = kbeg;
     int cur = 0;
-    for (int64_t i = 0; i < n_plain; ++i, k0 += kStep, cur ^= 1)
-        one_step<false, A_COL, B_COL, PLANES, FA>(ma, mb, la, lb, cur, operand_bytes, k0, kend, wr, wc, l32, h, acc);
-    int64_t i = n_plain;
+    for (int64_t i = 0; i < plain; ++i, k0 += kStep, cur ^= 1)
+        one_step<false, PLANES, FA>(ma, mb, la, lb, cur, k0, kend, wr, wc, l32, h, acc);
+    int64_t i = plain;
     do {
-        one_step<true, A_COL, B_COL, PLANES, FA>(ma, mb, la, lb, cur, operand_bytes, k0, kend, wr, wc, l32, h, acc);
+        one_step<true, PLANES, FA>(ma, mb, la, lb, cur, k0, kend, wr, wc, l32, h, acc);
         k0 += kStep;
         cur ^= 1;
     } while (++i < nstep);
 }
 
 // FA: a wavefront's 32-row fragments.  2: the tile is 128 x 128.  1: it is 128 x 64, a wavefront has 32 rows of it.
-template <bool A_COL, bool B_COL, bool COLSUM, bool VEC, bool GATE_A, bool GATE_B, bool BF16, int FA>
+template <bool QUADS, bool GATE, bool BF16, int FA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_update_gemm(const GemmArgs g)
 {
     constexpr int PLANES = BF16 ? 1 : 3;
@@ -500,25 +439,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int64_t bid = blockIdx.x;
     const int xcd = (int)(bid % kXcds);
     const int64_t q = bid / kXcds;
-    const int n_inner = g.split ? g.tiles_r * g.tiles_c : g.tiles_c;
+    const int n_inner = g.tiles_r * g.tiles_c;
     const int inner = (int)(q % n_inner);
-    const int64_t outer = (q / n_inner) * kXcds + xcd;
-    if (outer >= g.n_outer) return;
-    int64_t tile_r, kbeg, kend, slab_id;
-    int tile_c;
-    if (g.split) {
-        slab_id = outer;
-        tile_r = inner / g.tiles_c;
-        tile_c = inner % g.tiles_c;
-        kbeg = slab_id * g.slab;
-        kend = kbeg + g.slab < g.Kc ? kbeg + g.slab : g.Kc;
-    } else {
-        slab_id = 0;
-        tile_r = outer;
-        tile_c = inner;
-        kbeg = 0;
-        kend = g.Kc;
-    }
+    const int64_t slab_id = (q / n_inner) * kXcds + xcd;
+    if (slab_id >= g.n_slabs) return;
+    const int64_t tile_r = inner / g.tiles_c;
+    const int tile_c = inner % g.tiles_c;
+    const int64_t kbeg = slab_id * g.slab, kend = kbeg + g.slab < g.Kc ? kbeg + g.slab : g.Kc;
     constexpr int kCols = 64 * FA;
     const int64_t r0 = tile_r * kTile, c0 = (int64_t)tile_c * kCols;
 
@@ -526,7 +453,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int wr = FA == 2 ? wave >> 1 : wave, wc = FA == 2 ? wave & 1 : 0;      // 2 x 2 or 4 x 1 wavefronts
     const int h = lane >> 5, l32 = lane & 31;
 
-    const bool inside = VEC && r0 + kTile <= g.R && c0 + kCols <= g.C;   // uniform
     f32x16 acc[FA][2];
 #pragma unroll
     for (int i = 0; i < FA; ++i)
@@ -534,15 +460,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    PlaneMover<A_COL, VEC, GATE_A, BF16, PLANES, false> ma;
-    static_assert(FA == 2 || B_COL, "tiles of 64 columns are for col operands");
-    typename std::conditional<FA == 2, PlaneMover<B_COL, VEC, GATE_B, BF16, PLANES, COLSUM>,
-                              HalfMover<VEC, GATE_B, BF16, PLANES, COLSUM>>::type mb;
+    PlaneMover<QUADS, false, BF16, PLANES, false> ma;
+    typename std::conditional<FA == 2, PlaneMover<QUADS, GATE, BF16, PLANES, true>,
+                              HalfMover<QUADS, GATE, BF16, PLANES, true>>::type mb;
     ma.init(g.a, r0, g.R);
     mb.init(g.b, c0, g.C);
-    run_steps<A_COL, B_COL, PLANES, FA>(ma, mb, lds_a[0], lds_b[0], kOperandBytes, kbeg, kend, inside, wr, wc, l32, h, acc);
-    write_tile<BF16 && !COLSUM, !COLSUM, FA>(g, acc, r0, c0, slab_id, wr, wc, h, l32);
-    if (COLSUM && tile_r == 0) {
+    run_steps<PLANES, FA>(ma, mb, lds_a[0], lds_b[0], kbeg, kend, QUADS, wr, wc, l32, h, acc);
+    write_tile<FA>(g, acc, r0, c0, slab_id, wr, wc, h, l32);
+    if (tile_r == 0) {
         // Every barrier above has been passed by all lanes, so the LDS is free: add up the eight
         // running sums of each column in a fixed order.
         float *red = reinterpret_cast<float *>(lds_b[0]);
@@ -581,15 +506,21 @@ __global__ __launch_bounds__(256) void k_update_reduce(const float *__restrict__
     if (e < n_w + n_b) {
         const float *q = part + e;
         int64_t k = lo;
-        for (; k + 4 <= hi; k += 4) {
-            const float v0 = q[k * stride], v1 = q[(k + 1) * stride], v2 = q[(k + 2) * stride],
-                        v3 = q[(k + 3) * stride];
-            s += (double)v0;
-            s += (double)v1;
-            s += (double)v2;
-            s += (double)v3;
+        constexpr int kAhead = 16;           // loads in flight: a range's chain is what the launch waits for
+        for (; k + kAhead <= hi; k += kAhead) {
+            float v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) v[u] = q[(k + u) * stride];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) s += (double)v[u];
         }
-        for (; k < hi; ++k) s += (double)q[k * stride];
+        if (k < hi) {
+            float v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) v[u] = q[(k + u < hi ? k + u : hi - 1) * stride];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) s += k + u < hi ? (double)v[u] : 0.0;
+        }
     }
     partial[pt][el] = s;
     __syncthreads();
@@ -601,70 +532,45 @@ __global__ __launch_bounds__(256) void k_update_reduce(const float *__restrict__
     if (dst) *dst = (float)t;
 }
 
-// Quad loads (16 bytes of fp32, 8 bytes of bf16) need every row of the operand to start aligned to a
-// quad and to hold whole quads.
-bool quad_ok(const Operand &op, bool bf16)
-{
-    const uintptr_t m = bf16 ? 7 : 15;
-    return op.p && op.ld % 4 == 0 && (((uintptr_t)op.p | (uintptr_t)op.gate) & m) == 0;
-}
-
-// WHICH names the operand that may carry a gate: 0 none, 1 a, 2 b.
-template <bool A_COL, bool B_COL, bool COLSUM, int WHICH, bool VEC, bool BF16, int FA>
-void launch_gates(const GemmArgs &g, unsigned blocks, hipStream_t s)
-{
-    if (WHICH == 1 && g.a.gate)
-        hipLaunchKernelGGL((k_update_gemm<A_COL, B_COL, COLSUM, VEC, WHICH == 1, false, BF16, FA>), dim3(blocks), dim3(256),
-                           0, s, g);
-    else if (WHICH == 2 && g.b.gate)
-        hipLaunchKernelGGL((k_update_gemm<A_COL, B_COL, COLSUM, VEC, false, WHICH == 2, BF16, FA>), dim3(blocks), dim3(256),
-                           0, s, g);
-    else
-        hipLaunchKernelGGL((k_update_gemm<A_COL, B_COL, COLSUM, VEC, false, false, BF16, FA>), dim3(blocks), dim3(256), 0, s,
-                           g);
-}
-
-template <bool A_COL, bool B_COL, bool COLSUM, int WHICH>
 fastgl_status launch_gemm(GemmArgs &g, bool bf16, hipStream_t s, const char *what)
 {
+    // Up to 64 result columns: no matrix instructions and no conversions for columns that do not exist.
+    // us, tiles of 128 columns -> 64:  fp32 M = 1.15 M, 100 x 64: 262 -> 212;  8 000, 256 x 47: 29 -> 16 (bf16,
+    // 1 000 rows: 15 -> 10).
+    const bool half = g.C <= kTile / 2;
     g.tiles_r = (int)ceil_div(g.R, kTile);
     g.tiles_c = (int)ceil_div(g.C, kTile);
-    if (g.split && g.tiles_r == 0) g.tiles_r = 1;          // column sums are still owed when R == 0
-    const int64_t n_inner = g.split ? (int64_t)g.tiles_r * g.tiles_c : g.tiles_c;
-    if (!g.split) g.n_outer = g.tiles_r;
-    const int64_t blocks = ceil_div(g.n_outer, kXcds) * kXcds * n_inner;
+    if (g.tiles_r == 0) g.tiles_r = 1;                     // column sums are still owed when R == 0
+    const int64_t blocks = ceil_div(g.n_slabs, kXcds) * kXcds * g.tiles_r * g.tiles_c;
     if (blocks == 0) return FASTGL_OK;
     if (blocks >= INT32_MAX) {
         set_error("%s: too many tiles (%lld)", what, (long long)blocks);
         return FASTGL_ERR_UNSUPPORTED;
     }
-    bool vec = quad_ok(g.a, bf16) && quad_ok(g.b, bf16);
+    bool quads = g.a.ld >= 4 && g.b.ld >= 4;
     if (g.R == 0) {            // operand a has no elements: give its (all masked) loads a readable address
         g.a.p = g.b.p;
         g.a.gate = nullptr;
-        vec = false;
+        quads = false;
     }
-    if (g.Kc == 0) {           // nothing to contract: the same for both operands (the result exists)
-        g.a.p = g.b.p = g.c;
-        g.a.gate = g.b.gate = nullptr;
-        vec = false;
-    }
-    const unsigned nb = (unsigned)blocks;
-    auto go = [&](auto fa) {
+    const dim3 grid((unsigned)blocks);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, g); };
+    auto gated = [&](auto q, auto type, auto fa) {
+        constexpr bool Q = decltype(q)::value, T = decltype(type)::value;
         constexpr int FA = decltype(fa)::value;
-        if (bf16) {
-            if (vec) launch_gates<A_COL, B_COL, COLSUM, WHICH, true, true, FA>(g, nb, s);
-            else launch_gates<A_COL, B_COL, COLSUM, WHICH, false, true, FA>(g, nb, s);
-        } else {
-            if (vec) launch_gates<A_COL, B_COL, COLSUM, WHICH, true, false, FA>(g, nb, s);
-            else launch_gates<A_COL, B_COL, COLSUM, WHICH, false, false, FA>(g, nb, s);
-        }
+        if (g.b.gate) go(k_update_gemm<Q, true, T, FA>);
+        else go(k_update_gemm<Q, false, T, FA>);
     };
-    // Up to 64 result columns: no matrix instructions and no conversions for columns that do not exist.
-    // us, tiles of 128 columns -> 64:  fp32 M = 1.15 M, 100 x 64: 262 -> 212;  8 000, 256 x 47: 29 -> 16 (bf16,
-    // 1 000 rows: 15 -> 10).
-    if (B_COL && g.C <= 64) go(std::integral_constant<int, 1>());
-    else go(std::integral_constant<int, 2>());
+    auto typed = [&](auto q, auto fa) {
+        if (bf16) gated(q, std::true_type(), fa);
+        else gated(q, std::false_type(), fa);
+    };
+    auto wide = [&](auto fa) {
+        if (quads) typed(std::true_type(), fa);
+        else typed(std::false_type(), fa);
+    };
+    if (half) wide(std::integral_constant<int, 1>());
+    else wide(std::integral_constant<int, 2>());
     FASTGL_LAUNCH_CHECK(what);
     return FASTGL_OK;
 }
@@ -845,9 +751,9 @@ fastgl_status update_bwd(bool bf16, const void *H, const void *W, const void *Y,
                 g.a = Operand{dY, nullptr, 0};
                 g.R = 0;
             }
-            g.split = 1; g.n_outer = nslab;
+            g.n_slabs = nslab;
             g.colsum = part + K * N; g.colsum_slab = stride;
-            st = launch_gemm<true, true, true, 2>(g, bf16, s, "fastgl_update_bwd (dW)");
+            st = launch_gemm(g, bf16, s, "fastgl_update_bwd (dW)");
             if (st != FASTGL_OK) return st;
         }
         const int64_t n_w = K * N, total = n_w + N;
