@@ -7,8 +7,8 @@
 //
 //   k_update_tall   bound by HBM for narrow layers, by the matrix cores for wide ones.  A wavefront owns
 //     32 rows and NTILES x 32 columns.  Nobody else needs its rows, so A never passes through LDS: a lane
-//     loads 64 contiguous bytes of its row per 32 contracted indices, one such chunk ahead, and cuts them
-//     into planes in registers.  B goes through LDS (all wavefronts of the workgroup read it), cut into
+//     loads 64 contiguous bytes of its row per 32 contracted indices, two such chunks ahead where registers allow,
+//     and cuts them into planes in registers.  B goes through LDS (all wavefronts of the workgroup read it), cut into
 //     planes when it is written there, double buffered.  With NTILES = 8 a row is read and cut once for
 //     256 columns.
 //   k_update_small  bound by latency: too few rows to fill the chip with such tiles.  A workgroup owns
@@ -16,17 +16,20 @@
 //     operands up front (no staging, no barrier before the end) and the four partial tiles are added in
 //     LDS.
 //
-// us a call with cold caches, before (128 x 128 tiles, both operands through LDS) -> now, fp32 (bf16):
-//   Y   M = 1.15 M, 100 -> 64: 381 -> 225 (251 -> 131);  512 K, 100 -> 256: 257 -> 253, 730 MB at 2.9 TB/s (185 -> 138);
-//       91 K, 256 -> 256: 97 -> 86, 835 TFLOP/s of plane products where a large bf16 product reaches 1 135 (62 -> 43);
-//       1 000, 256 -> 256: 34 -> 10 (29 -> 8);  16, 256 -> 47: 30 -> 9 (27 -> 7)
-//   dH  M = 1.15 M, 64 -> 100: 290 -> 232, gated 347 -> 280;  91 K, 256 -> 256: 91 -> 94, gated 109 -> 122 (a second set
-//       of octets per step: the one shape that lost)
+// us a call with cold caches, first version (128 x 128 tiles, both operands through LDS) -> whole turns of 32 or 64
+// indices, one chunk ahead -> now, fp32:
+//   Y   M = 1.15 M, 100 -> 64: 381 -> 225 -> 218;  512 K, 100 -> 256: 257 -> 250 -> 220, 730 MB at 3.3 TB/s;
+//       91 K, 256 -> 256: 97 -> 87 -> 84, 855 TFLOP/s of plane products where a large bf16 product reaches 1 135
+//   dH, gated  M = 1.15 M, 64 -> 100: 347 -> 284 -> 272;  512 K, 256 -> 100: 316 -> 310;  91 K, 256 -> 256: 109 -> 121 -> 110
+// bf16: Y 300 K, 128 -> 256: 79 -> 78, gated dH 256 -> 128: 141 -> 128;  87 K, 128 -> 256: 26.8 -> 27.0 (1 % lost).
+// What is left of the 512 K product: 178 us without the matrix instructions, 190 without the stores, 143 to move its bytes
+// at 5.1 TB/s; priorities that let one of a unit's two workgroups run ahead of the other changed nothing.
+// k_update_small: 1 000, 256 -> 256: 34 -> 10 (bf16 29 -> 8);  16, 256 -> 47: 30 -> 9 (27 -> 7)
 //
 // A step of 16 contracted indices goes into one matrix instruction per plane product (lane half h: indices 8 h .. + 7).
 // Tall tiles add the steps in ascending order, so results do not depend on a tile's width; small tiles add four
-// partial sums of consecutive steps.  The tall loop runs whole turns of 32 indices (64 with 64 columns or fewer): K = 100
-// costs eight steps.
+// partial sums of consecutive steps.  The tall loop ends with the last step that holds a term (K = 100: seven, which is
+// where most of 250 -> 220 came from: with whole turns eight were multiplied).
 #include <type_traits>
 
 #include "update_internal.h"
@@ -351,10 +354,13 @@ __device__ __forceinline__ Oct<true> column(const ColPair<true> &c, int which)
 
 // LDS stage of B: [plane][octet slot][column] x 16 bytes (a lane's eight elements of one plane).
 template <int NTILES, bool BCOL, bool GATE, int VA, int VB, bool BF16>
-__global__ __launch_bounds__(256, NTILES == 8 || (NTILES == 4 && GATE && !BF16) ? 2 : 3) void k_update_tall(const RowsGemm g)
+__global__ __launch_bounds__(256, NTILES == 8 || (NTILES <= 4 && GATE && !BF16) ? 2 : 3) void k_update_tall(const RowsGemm g)
 {
     constexpr int NT = NTILES * 32, KS = NT < 64 ? 64 : kStageElems / NT, SLOTS = KS / 8, PL = Planes<BF16>::N;
-    constexpr int SUP = KS < 32 ? 32 : KS;                    // contracted indices per turn of the loop
+    // Chunks of 32 contracted indices of A under way: two where the registers of the second cost neither a wavefront nor
+    // spills (Y M = 512 K, 100 -> 256: 226 us with one, 220 with two; gated dH M = 1.15 M, 64 -> 100: 270 and 257).  Fp32
+    // with a gate and 64 columns takes two wavefronts a SIMD for it (M = 40 K, 99 -> 131: 39 us with three and spills, 36).
+    constexpr int AHEAD = !BF16 && (NTILES == 4 || (GATE && NTILES == 8)) ? 1 : 2;
     constexpr uint32_t EB = BF16 ? 2 : 4;
     __shared__ uint4 lds[2][PL][SLOTS][NT];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, h = lane >> 5, l32 = lane & 31;
@@ -381,16 +387,18 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES == 4 && GATE && !BF16) 
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
 
-    Oct<BF16> ar[2], gr[GATE ? 2 : 1];
-    auto load_a = [&](int k0) {                               // this lane's octets of the chunk: indices k0 + 16 s + 8 h .. + 7
+    // Contracted indices per turn of the loop: no more than chunks and stages need (gated dH M = 512 K, 256 -> 100: 310 us
+    // with 32, 323 with 64).
+    constexpr int TURN = AHEAD == 1 && KS <= 32 ? 32 : 64;
+    Oct<BF16> ar[AHEAD][2], gr[AHEAD][GATE ? 2 : 1];
+    auto load_a = [&](int to, int k0) {                       // this lane's octets of the chunk: indices k0 + 16 s + 8 h .. + 7
+        const uint32_t row = arow + (k0 < Kc ? 0u : kNowhere);        // chunks past the end touch no memory
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            buffer_oct<VA>(ra, arow, k0 + 16 * s + 8 * h, Kc, ar[s]);
-            if constexpr (GATE) buffer_oct<VA>(rg, arow, k0 + 16 * s + 8 * h, Kc, gr[s]);
+            buffer_oct<VA>(ra, row, k0 + 16 * s + 8 * h, Kc, ar[to][s]);
+            if constexpr (GATE) buffer_oct<VA>(rg, row, k0 + 16 * s + 8 * h, Kc, gr[to][s]);
         }
     };
-    // first contracted index of octet slot i of the stage that starts at (k0, step s)
-    auto slot_k = [&](int k0, int s, int i) { return k0 + 8 * i + (KS == 16 ? 16 * s : 0); };
     // which two octets of a stage a thread brings: BCOL two columns of one slot, else one column's two slots
     const int bc = BCOL ? 2 * (t % (NT / 2)) : t % NT;
     const int bs = BCOL ? t / (NT / 2) : 2 * (t / NT);
@@ -400,17 +408,17 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES == 4 && GATE && !BF16) 
     ColPair<BF16> bcols;
     Oct<BF16> brow[BCOL ? 1 : 2];
     const bool brings = NT >= 64 || bs < SLOTS;               // 32 columns: half of the threads
-    auto load_b = [&](int k0, int s) {
+    auto load_b = [&](int k0) {                               // the stage of KS contracted indices from k0 on
         if (!brings) return;                                  // the same for a whole wavefront
         if constexpr (BCOL) {
-            buffer_cols<VB>(rb, (uint32_t)slot_k(k0, s, bs) * ldb + bcol, ldb, bcols);
+            buffer_cols<VB>(rb, (uint32_t)(k0 + 8 * bs) * ldb + bcol, ldb, bcols);
         } else {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
-                buffer_oct<VB>(rb, (uint32_t)bc * ldb, slot_k(k0, s, bs + i), Kc, brow[i]);
+                buffer_oct<VB>(rb, (uint32_t)bc * ldb, k0 + 8 * (bs + i), Kc, brow[i]);
         }
     };
-    auto stage_b = [&](int buf, int k0, int s) {
+    auto stage_b = [&](int buf, int k0) {
         if (!brings) return;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -425,7 +433,7 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES == 4 && GATE && !BF16) 
                 }
             } else {
                 o = brow[i];
-                if (k0 + SUP > Kc) settle<VB>(o, slot_k(k0, s, slot), Kc);
+                if (k0 + KS > Kc) settle<VB>(o, k0 + 8 * slot, Kc);
             }
             Planes<BF16> f;
             to_planes(o, f);
@@ -434,18 +442,10 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES == 4 && GATE && !BF16) 
         }
     };
 
-    // the stage after the one at (k0, s)
-    auto next_stage = [](int &k0, int &s) {
-        if (KS == 16 && s == 0) {
-            s = 1;
-        } else {
-            k0 += SUP;
-            s = 0;
-        }
-    };
-    load_b(0, 0);
+    load_b(0);
     __builtin_amdgcn_sched_barrier(0);
-    load_a(0);
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) load_a(i, 32 * i);
     float bias[NTILES];
 #pragma unroll
     for (int j = 0; j < NTILES; ++j) bias[j] = 0.f;
@@ -456,61 +456,59 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES == 4 && GATE && !BF16) 
             bias[j] = g.bias[col < g.N ? col : 0];
         }
     }
-    stage_b(0, 0, 0);
-    int lk = 0, ls = 0;                                       // the stage whose loads are under way
-    next_stage(lk, ls);
-    load_b(lk, ls);
+    stage_b(0, 0);
+    int lk = KS;                                              // the stage whose loads are under way
+    load_b(lk);
     __syncthreads();
     int cur = 0;
-    // Order of a step: the next stage, whose loads were issued a step ago, goes to the other LDS buffer; the
-    // loads of the stage after it are issued; then this stage is multiplied.  Loads of B and A are issued in
-    // the order in which they are waited for.
-    for (int k0 = 0; k0 < Kc; k0 += SUP) {
+    // Order of a stage: the next one, whose loads were issued a stage ago, goes to the other LDS buffer; the
+    // loads of the one after it are issued; then this one is multiplied.  Loads of B and A are issued in the
+    // order in which they are waited for.
+    Planes<BF16> fa[2];
+    for (int k0 = 0; k0 < Kc; k0 += TURN) {
 #pragma unroll
-        for (int cc = 0; cc < SUP / 32; ++cc) {
-            const int kc = k0 + 32 * cc;
-            Planes<BF16> fa[2];
-            if constexpr (GATE)
+        for (int step = 0; step < TURN / 16; ++step) {        // 16 contracted indices
+            const int cc = step >> 1, s = step & 1, kc = k0 + 32 * cc, from = cc % AHEAD;
+            if (step > 0 && k0 + 16 * step >= Kc) break;
+            if (s == 0) {
+                if constexpr (GATE)
 #pragma unroll
-                for (int s = 0; s < 2; ++s) gate_oct(ar[s], gr[s]);
-            if (kc + 32 > Kc)
+                    for (int i = 0; i < 2; ++i) gate_oct(ar[from][i], gr[from][i]);
+                if (kc + 32 > Kc)
 #pragma unroll
-                for (int s = 0; s < 2; ++s) settle<VA>(ar[s], kc + 16 * s + 8 * h, Kc);
+                    for (int i = 0; i < 2; ++i) settle<VA>(ar[from][i], kc + 16 * i + 8 * h, Kc);
 #pragma unroll
-            for (int s = 0; s < 2; ++s) to_planes(ar[s], fa[s]);
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const bool first = KS == 16 || (s == 0 && cc == 0), last = KS == 16 || (s == 1 && cc == SUP / 32 - 1);
-                if (first) {
-                    stage_b(cur ^ 1, lk, ls);
-                    next_stage(lk, ls);
-                    load_b(lk, ls);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (s == 0) load_a(kc + 32);
+                for (int i = 0; i < 2; ++i) to_planes(ar[from][i], fa[i]);
+            }
+            if (16 * step % KS == 0) {
+                stage_b(cur ^ 1, lk);
+                lk += KS;
+                load_b(lk);
                 __builtin_amdgcn_sched_barrier(0);
-                const int slot = KS == 16 ? h : 4 * cc + 2 * s + h;
-                Planes<BF16> fb[2];
+            }
+            if (s == 0) load_a(from, kc + 32 * AHEAD);
+            __builtin_amdgcn_sched_barrier(0);
+            const int slot = 16 * step % KS / 8 + h;
+            Planes<BF16> fb[2];
 #pragma unroll
-                for (int p = 0; p < PL; ++p) fb[0].p[p] = lds[cur][p][slot][l32];
+            for (int p = 0; p < PL; ++p) fb[0].p[p] = lds[cur][p][slot][l32];
 #pragma unroll
-                for (int j = 0; j < NTILES; ++j) {            // the next tile is read while this one is multiplied
-                    if (j + 1 < NTILES)
+            for (int j = 0; j < NTILES; ++j) {                // the next tile is read while this one is multiplied
+                if (j + 1 < NTILES)
 #pragma unroll
-                        for (int p = 0; p < PL; ++p) fb[(j + 1) & 1].p[p] = lds[cur][p][slot][32 * (j + 1) + l32];
-                    mma<BF16>(fa[s], fb[j & 1], acc[j]);
-                }
-                __builtin_amdgcn_sched_group_barrier(0x100, PL, 0);
+                    for (int p = 0; p < PL; ++p) fb[(j + 1) & 1].p[p] = lds[cur][p][slot][32 * (j + 1) + l32];
+                mma<BF16>(fa[s], fb[j & 1], acc[j]);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x100, PL, 0);
 #pragma unroll
-                for (int j = 0; j < NTILES; ++j) {
-                    if (j + 1 < NTILES) __builtin_amdgcn_sched_group_barrier(0x100, PL, 0);    // LDS reads
-                    __builtin_amdgcn_sched_group_barrier(0x008, BF16 ? 1 : 6, 0);              // matrix instructions
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                if (last) {
-                    __syncthreads();
-                    cur ^= 1;
-                }
+            for (int j = 0; j < NTILES; ++j) {
+                if (j + 1 < NTILES) __builtin_amdgcn_sched_group_barrier(0x100, PL, 0);    // LDS reads
+                __builtin_amdgcn_sched_group_barrier(0x008, BF16 ? 1 : 6, 0);              // matrix instructions
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (16 * (step + 1) % KS == 0) {
+                __syncthreads();
+                cur ^= 1;
             }
         }
     }

@@ -111,3 +111,13 @@ def test_row_loads_stay_inside_their_rows():
 def test_offsets_inside_a_tile_fit_32_bits():
     """Rows of up to 2^21 elements: the last element that a tile of 256 rows may ask for lies below 2^31 bytes."""
     assert 255 * (1 << 21) * 4 + (1 << 21) * 4 - 1 < 1 << 31
+
+
+def test_look_ahead_past_the_last_index_wraps_around_nowhere():
+    """Chunks of A past the end start 2^31 bytes further on; a stage of B and the two after it ask for up to 190 rows past
+    the last one.  Both have to stay between every buffer's end (at most 2^31 - 1 bytes) and 2^32."""
+    far = 127 * (1 << 21) * 4 + (1 << 21) * 4 + 15
+    assert (1 << 31) + far < 1 << 32
+    for ldb in (1, 3, 256, 1 << 21):
+        Kc = ((1 << 29) - 1) // ldb - 64                      # the longest that the tall tiles take
+        assert (Kc + 64) * ldb < 1 << 29 and (Kc + 191) * ldb * 4 + ldb * 4 < 1 << 32
