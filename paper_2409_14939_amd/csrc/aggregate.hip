@@ -24,7 +24,7 @@
 //   backward 123 / 84;  of 5 313 nodes, 8 columns bf16, both directions: 391 / 20 (a group was a single lane)
 //   reddit-shaped layer, 602 columns (8-byte slices, five column tiles / 16-byte slices, three): 83 / 81, 100 / 92
 //   256 rows, 64 columns: 4.6 / 4.0, backward 8.2 / 5.4
-//   rows of 404 and 256 bytes, 2.56 M edges: 217 / 218, 105 / 108 - nothing to share out there
+//   rows of 400 and 256 bytes, 2.56 M edges: 217 / 218, 104 / 109 - nothing to share out there
 //
 // f32 rows accumulate in fp64, bf16 rows in fp32; one rounding at the store.
 //
@@ -45,7 +45,7 @@ constexpr int kReduceBlocks = 1024;   // workgroups for the long rows, whose num
 // that neighbouring rows (which share output cache lines and first-touch source
 // rows) share an L2, while every XCD still samples the whole row range: blocks
 // whose hubs all sit at low ids stay balanced.  The column tiles of a row set
-// (rows wider than 64 slices) sit in neighbouring wavefronts.
+// sit in neighbouring wavefronts, or (by_tile) as far apart as can be.
 struct WaveId {
     int64_t w;        // index of the wavefront's first fine row set / P.sets_per_wave
     int tile;         // column tile
@@ -57,8 +57,15 @@ __device__ __forceinline__ WaveId map_wave(const PullParams &P)
     const uint64_t lb = ((uint64_t)(q / kXcdRun) * kXcds + x) * kXcdRun + q % kXcdRun;
     const uint64_t v = lb * (kBlock / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     WaveId r;
-    r.w = P.ntiles > 1 ? (int64_t)__umul64hi(v, P.tile_inv) : (int64_t)v;     // v < 2^34, ntiles < 2^20: exact
-    r.tile = (int)(v - (uint64_t)r.w * (uint32_t)P.ntiles);
+    const uint64_t div = P.ntiles > 1 ? __umul64hi(v, P.tile_inv) : v;        // v < 2^34, ntiles < 2^20, nwaves < 2^28: exact
+    if (P.by_tile) {
+        const bool none = div >= (uint32_t)P.ntiles;                            // wavefronts that fill the last workgroups
+        r.tile = none ? 0 : (int)div;
+        r.w = none ? P.nwaves : (int64_t)(v - div * (uint64_t)P.nwaves);
+    } else {
+        r.w = (int64_t)div;
+        r.tile = (int)(v - div * (uint32_t)P.ntiles);
+    }
     return r;
 }
 
@@ -99,7 +106,7 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
     const int lane = threadIdx.x & (kWave - 1);
     Window<DT, VB> &win = windows[WAVE ? 0 : threadIdx.x / kWave];
     const WaveId id = map_wave(P);
-    const int64_t slice = WAVE ? (int64_t)id.tile * kWave + lane : lane & (P.G - 1);
+    const int64_t slice = WAVE ? (int64_t)id.tile * kWave + lane : (int64_t)id.tile * P.G + (lane & (P.G - 1));
     const int64_t lane_off = slice_offset<VB>(P, slice);
     const bool active = slice * VB < P.row_bytes;
     // all that the wavefront needs to know first, loaded together
@@ -227,7 +234,7 @@ static int slice_bytes(int64_t row_bytes)
 }
 
 // ceil(2^64 / n): the upper half of its product with x is x / n while x * n < 2^64.  0 for n = 1.
-static uint64_t tile_inverse(int n) { return n > 1 ? UINT64_MAX / (uint64_t)n + 1 : 0; }
+static uint64_t tile_inverse(int64_t n) { return n > 1 ? UINT64_MAX / (uint64_t)n + 1 : 0; }
 
 static void group_shape(int64_t row_bytes, int vb, int smallest, int *G, int *ntiles)
 {
@@ -236,6 +243,23 @@ static void group_shape(int64_t row_bytes, int vb, int smallest, int *G, int *nt
     while (g < kWave && g < slices) g <<= 1;
     *G = g;
     *ntiles = (int)ceil_div(slices, g);
+}
+
+// Are rows wider than 32 slices gathered in tiles of 32, all rows of one tile after the other?  The gathers of a pass then
+// come from a table that is so much smaller, and more of its often used rows stay in the caches.  Blocks over all
+// neighbours in power-law graphs, 256 columns, gcn f32, us, whole rows / tiles (table, times a row is read):
+//   656 MB, 9: 762 / 716;  154 MB, 39: 761 / 677;  203 MB, 19: 469 / 446;  298 MB, 9: 416 / 397;  391 MB, 11: 532 / 509;
+//   489 MB, 9: 625 / 620;  801 MB, 7: 817 / 767;  901 MB, 6: 778 / 750;  1.08 GB, 2.6: 487 / 492;  94 MB, 15: 152 / 163
+// Where all rows are read equally often there is less to keep (307 MB, 15: 721 / 721; 819 MB, 25: 3 238 / 3 437), but few
+// graphs are like that.  Not where the columns of long rows ascend (the first of these blocks backward: 416 / 500), nor
+// where tiles would share cache lines (602 columns: 83 / 93).  1 024 row sets keep the wavefronts of a tile many.
+constexpr int kTileLanes = 32;
+
+static bool column_by_column(const PullDesc &d, int64_t row_bytes, int G)
+{
+    return G == kWave && d.any_order && row_bytes % (kTileLanes * 16) == 0 && ((uintptr_t)d.in & 127) == 0 &&
+           d.num_cols * row_bytes >= (int64_t)128 << 20 && d.num_cols * (row_bytes / 16) <= (int64_t)UINT32_MAX &&
+           d.nnz >= 5 * d.num_cols && d.nsets >= 1024;
 }
 
 template <int DT, int VB, int W>
@@ -276,6 +300,7 @@ fastgl_status launch_pull(const PullDesc &d, hipStream_t s)
     P.row_bytes = d.feat * elem;
     P.feat = d.feat;
     P.row_mode = d.row_mode;
+    P.by_tile = 0;
     const int vb = slice_bytes(P.row_bytes);
     int G, ntiles;
     group_shape(P.row_bytes, vb, kUnrollNarrow, &G, &ntiles);   // a group loads as many column ids at a time as it has lanes
@@ -286,9 +311,13 @@ fastgl_status launch_pull(const PullDesc &d, hipStream_t s)
         G = kWave;
         ntiles = (int)ceil_div(ceil_div(P.row_bytes, (int64_t)vb), (int64_t)G);
     }
+    if (column_by_column(d, P.row_bytes, G)) {
+        G = kTileLanes;
+        ntiles = (int)(P.row_bytes / (kTileLanes * vb));
+        P.by_tile = 1;
+    }
     P.G = G; P.ntiles = ntiles;
     P.lg_G = __builtin_ctz((unsigned)G);
-    P.tile_inv = tile_inverse(ntiles);
     P.num_rows = d.num_rows;
     P.split = d.split;
     P.nsets = d.nsets;
@@ -304,13 +333,14 @@ fastgl_status launch_pull(const PullDesc &d, hipStream_t s)
     while (spw >= groups && spw < 8 * groups && d.nsets / (spw * 2) * ntiles >= 16384) spw *= 2;
     P.sets_per_wave = spw;
     P.nwaves = ceil_div(d.nsets, (int64_t)spw);
+    P.tile_inv = tile_inverse(P.by_tile ? P.nwaves : ntiles);
     const bool with_long = d.long_rows != nullptr && d.nnz > kLongThreshold;
     P.long_thr = with_long ? kLongThreshold : INT32_MAX;
     P.long_rows = with_long ? d.long_rows : nullptr;
     P.chunk_ptr = d.chunk_ptr; P.n_long = d.n_long; P.n_chunks = d.n_chunks;
     P.partials = (char *)d.partials;
     P.num_blocks = ceil_div(ceil_div(P.nwaves * ntiles, (int64_t)(kBlock / kWave)), (int64_t)kXcds * kXcdRun) * kXcdRun * kXcds;
-    P.chunk_waves = P.num_blocks * (kBlock / kWave) / ntiles;
+    P.chunk_waves = P.by_tile ? P.nwaves : P.num_blocks * (kBlock / kWave) / ntiles;
     if (P.num_blocks > 0x7FFFFFFFLL) {
         set_error("block too large for one launch (%lld workgroups)", (long long)P.num_blocks);
         return FASTGL_ERR_UNSUPPORTED;

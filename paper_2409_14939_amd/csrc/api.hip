@@ -152,6 +152,7 @@ fastgl_status aggregate_prepare(bool backward, const int32_t *indptr, const int3
     d.out = out;
     d.nnz = num_edges;
     d.partials = workspace;
+    d.any_order = !backward;
     if (!backward) {
         d.rowptr = indptr; d.col = indices; d.eid = nullptr;
         d.col_scale = mode == FASTGL_AGG_GCN ? pl->src_rsqrt : nullptr;

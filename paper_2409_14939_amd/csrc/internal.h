@@ -105,6 +105,7 @@ struct PullDesc {
     // long-row bucket (device-resident counts)
     const int32_t *long_rows, *chunk_ptr, *n_long, *n_chunks;
     void *partials;            // cap_chunks * feat accumulators
+    bool any_order;            // columns of a row in any order; false: a transposed block, where they ascend
     // equal-work row sets
     const int32_t *split;      // [nsets+1]
     int64_t nsets;

@@ -121,7 +121,8 @@ struct PullParams {
     const int32_t *split;     // [nsets+1] first row of every fine row set (equal work each)
     int64_t nsets;            // fine row sets
     int64_t nwaves;           // wavefronts per column tile = ceil(nsets / sets_per_wave)
-    int32_t ntiles;           // column tiles per row (1 unless a group is a whole wavefront)
+    int32_t ntiles;           // column tiles per row
+    int32_t by_tile;          // all rows of one column tile after the other; 0: the tiles of a row together
     int32_t G, lg_G;          // lanes per group (power of two), its logarithm
     int32_t unit_shift;       // rows start at multiples of 1 << unit_shift bytes (no more than a slice)
     int32_t sets_per_wave;    // consecutive fine row sets one wavefront takes
@@ -130,7 +131,7 @@ struct PullParams {
     int32_t long_thr;         // rows longer than this are left to the chunk kernels
     int64_t row_bytes;        // bytes of one feature row
     int64_t feat;
-    uint64_t tile_inv;        // ceil(2^64 / ntiles): division by multiplication (unused for one tile)
+    uint64_t tile_inv;        // ceil(2^64 / ntiles), by_tile: ceil(2^64 / nwaves): division by multiplication (unused for one tile)
     int64_t chunk_waves;      // wavefronts per column tile that take chunks of long rows
     int64_t num_blocks;       // launched blocks (multiple of kXcds)
     const int32_t *long_rows, *chunk_ptr, *n_long, *n_chunks;

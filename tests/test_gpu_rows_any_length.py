@@ -108,3 +108,23 @@ def test_edge_weight_grad(dtype, feat, edges_per_row):
     # fp64 sums rounded once; bf16: products exact, a chain of at most feat fp32 additions
     bound = 2.0 ** -24 * np.abs(want) + (feat + 2) * (2.0 ** -52 if dtype == "f32" else 2.0 ** -24) * terms
     assert (np.abs(got - want) <= bound).all()
+
+
+@pytest.mark.parametrize("dtype,feat,weighted", [("f32", 256, True), ("f32", 384, False), ("bf16", 1280, True)])
+def test_column_tiles_one_after_the_other(dtype, feat, weighted):
+    """Wide rows read five times each out of a table of 128 MB and more: by column tiles, against the oracle and the same
+    rows at an address that the tiles are not for; rows of none, of a few, of the longest unchunked and of chunked length."""
+    num_src = (128 << 20) // (feat * (4 if dtype == "f32" else 2)) + 1
+    rng = np.random.default_rng(feat)
+    lengths = np.concatenate([[0, 1, 256, 257, 3000], rng.integers(0, 60, 5 * num_src // 29)])
+    blk = block_of(rng.permutation(lengths), num_src, feat)
+    assert blk.num_edges >= 5 * num_src
+    X = make_inputs(rng, num_src, feat, dtype)
+    w = rng.standard_normal(blk.num_edges).astype(np.float32) if weighted else None
+    wd = None if w is None else torch.from_numpy(w).cuda()
+    ip, ix = dev_i32(blk.indptr), dev_i32(blk.indices)
+    aligned, moved = dev_feat(X, dtype), shifted(X, dtype, 2)
+    assert aligned.data_ptr() % 128 == 0
+    tiles, rows = (host_feat(B.fastgl_block_aggregate_fwd(ip, ix, wd, num_src, "gcn", x), dtype) for x in (aligned, moved))
+    assert_close(tiles, oracle.aggregate_fwd(blk.indptr, blk.indices, w, num_src, "gcn", dtype, X), dtype)
+    assert_close(tiles, rows, dtype)
