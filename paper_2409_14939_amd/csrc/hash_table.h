@@ -95,20 +95,20 @@ struct PositionTable {
 };
 
 // Slot whose key is gid after the call; `holder` = the position it was seen to hold (p: this call
-// put it there).  key_at(position) = the ID at an input position.  LOOK: the slot is first read by a load that
+// put it there).  key_at(position) = the ID at an input position.  `look`: the slot is first read by a load that
 // may come from this XCD's L2: the KEY of a slot never changes once it has one (a smaller position of the same
 // ID may replace the one it holds), so an old reading can only show the empty marker, and the compare-and-swap
-// settles that.  Without LOOK (IDs that are not expected in the table yet) the compare-and-swap comes first.
+// settles that.  Without (IDs that are not expected in the table yet) the compare-and-swap comes first.
 // Ends because the table always keeps empty slots.
-template <bool LOOK, class KeyAt>
+template <class KeyAt>
 __device__ __forceinline__ uint32_t claim_slot(const PositionTable &t, int64_t gid, int32_t p, const KeyAt &key_at,
-                                               int32_t &holder)
+                                               int32_t &holder, bool look)
 {
     uint32_t slot = hash_slot(gid, t.cap);
     const int32_t tag = t.tag(gid);
     for (;;) {
         int32_t w = kEmptySlot;
-        if (LOOK) w = __hip_atomic_load(&t.slot[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (look) w = __hip_atomic_load(&t.slot[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (w == kEmptySlot) {
             w = atomicCAS(&t.slot[slot], kEmptySlot, tag | p);
             if (w == kEmptySlot) {

@@ -36,6 +36,7 @@ struct IdmapArgs {
     int32_t *ref;             // ORDERED: [n] slot of every input position, bit 31 set on (candidates for) first
                               // occurrences; FUSED: [n_nbr] neighbour entry that claimed the ID;
                               // kNoSlot: nothing to translate
+    unsigned char *displaced; // ORDERED: [n] 1 where a smaller position of the same ID came after this one
     int32_t *block_cnt;       // [blocks + 1]
     int32_t *local_nbr;
     int64_t *unique_gid;
@@ -62,9 +63,13 @@ __global__ __launch_bounds__(256) void k_idmap_fill(IdmapArgs a)
         a.result[1] = 0;
     }
     fill_words(a.table, i);
+    if (!a.fused && i * 16 < a.n) reinterpret_cast<int4 *>(a.displaced)[i] = make_int4(0, 0, 0, 0);
 }
 
-// ORDERED pass 1: claim slots, keep the smallest position per slot.
+// ORDERED pass 1: claim slots, keep the smallest position per slot.  Destinations find their slots empty and do not look.
+// A position that was its ID's smallest when it came is marked by the smaller one that comes after it, so that nobody has to
+// read the slots a second time to see which are left.  (Counting them per block here, up when they come and down when they
+// are displaced, is slower than the pass below: the atomics meet in a few lines, 96 -> 105 us, with one small hop 14 -> 27.)
 __global__ __launch_bounds__(256) void k_idmap_insert_min(IdmapArgs a)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -76,8 +81,11 @@ __global__ __launch_bounds__(256) void k_idmap_insert_min(IdmapArgs a)
         atomicAdd(&a.result[1], 1);
     } else {
         int32_t q;
-        const uint32_t slot = claim_slot<true>(a.table, gid, (int32_t)p, IdAt{a}, q);
-        if (q > (int32_t)p) q = a.table.position(atomicMin(&a.table.slot[slot], a.table.tag(gid) | (int32_t)p));
+        const uint32_t slot = claim_slot(a.table, gid, (int32_t)p, IdAt{a}, q, p >= a.n_dst);
+        if (q > (int32_t)p) {
+            q = a.table.position(atomicMin(&a.table.slot[slot], a.table.tag(gid) | (int32_t)p));
+            if (q > (int32_t)p) a.displaced[q] = 1;
+        }
         if (q >= (int32_t)p)
             ref = (int32_t)slot | kFirstBit;
         else if (q < a.n_dst && p >= a.n_dst)
@@ -88,21 +96,35 @@ __global__ __launch_bounds__(256) void k_idmap_insert_min(IdmapArgs a)
     a.ref[p] = ref;
 }
 
-// ORDERED pass 2: which of the positions that were the smallest of their ID when they came are still, and how
-// many per block of kScanBlock positions.
-__global__ __launch_bounds__(kScanBlock) void k_idmap_count(IdmapArgs a)
+// ORDERED pass 2: how many positions of every block of kScanBlock are first occurrences, and which are not after all.
+// Four positions per thread; the arrays have room for whole fours.
+constexpr int kCountThreads = kScanBlock / 4;
+__global__ __launch_bounds__(kCountThreads) void k_idmap_count(IdmapArgs a)
 {
-    const int64_t p = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-    bool first = false;
+    __shared__ int wave_sum[kCountThreads / 64];
+    const int64_t p = ((int64_t)blockIdx.x * kCountThreads + threadIdx.x) * 4;
+    int c = 0;
     if (p < a.n) {
-        const int32_t ref = a.ref[p];
-        if (ref < 0) {                             // bit 31
-            first = a.table.position(a.table.slot[ref & kNoSlot]) == (int32_t)p;
-            if (!first) a.ref[p] = ref & kNoSlot;
+        const int4 r = *reinterpret_cast<const int4 *>(a.ref + p);
+        const uint32_t d = *reinterpret_cast<const uint32_t *>(a.displaced + p);
+        const int32_t ref[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (p + i >= a.n || ref[i] >= 0) continue;        // bit 31
+            if (d >> (8 * i) & 0xFF) a.ref[p + i] = ref[i] & kNoSlot;
+            else ++c;
         }
     }
-    const int c = __syncthreads_count(first);
-    if (threadIdx.x == 0) a.block_cnt[blockIdx.x] = c;
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) c += __shfl_xor(c, k);
+    if ((threadIdx.x & 63) == 0) wave_sum[threadIdx.x / 64] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int total = 0;
+#pragma unroll
+        for (int w = 0; w < kCountThreads / 64; ++w) total += wave_sum[w];
+        a.block_cnt[blockIdx.x] = total;
+    }
 }
 
 // More than kSumBlocks blocks only: block counts -> block offsets, in place, with the total behind them.
@@ -150,7 +172,7 @@ __global__ __launch_bounds__(256) void k_idmap_fused_dst(IdmapArgs a)
     if (p >= a.n_dst) return;
     const int64_t gid = a.dst_gid[p];
     int32_t q = kEmptySlot;
-    if (gid >= 0) claim_slot<false>(a.table, gid, (int32_t)p, IdAt{a}, q);
+    if (gid >= 0) claim_slot(a.table, gid, (int32_t)p, IdAt{a}, q, false);
     if (q == (int32_t)p)
         a.unique_gid[p] = gid;
     else
@@ -168,7 +190,7 @@ __global__ __launch_bounds__(kScanBlock) void k_idmap_fused_nbr(IdmapArgs a)
     const int64_t gid = active ? a.nbr_gid[e] : -1;
     const int32_t p = (int32_t)(a.n_dst + e);
     int32_t q = kEmptySlot;
-    if (gid >= 0) claim_slot<true>(a.table, gid, p, IdAt{a}, q);
+    if (gid >= 0) claim_slot(a.table, gid, p, IdAt{a}, q, true);
     const bool fresh = gid >= 0 && q == p;
     if (active) {
         a.ref[e] = q >= (int32_t)a.n_dst && !fresh ? q - (int32_t)a.n_dst : kNoSlot;
@@ -207,7 +229,7 @@ Layout layout(int64_t n)
     Layout L;
     size_t off = 0;
     L.table = off; off += align_up((size_t)(cap * kSlotRoom), 256);
-    L.ref = off; off += align_up((size_t)(n > 0 ? n : 1) * 4, 256);
+    L.ref = off; off += align_up((size_t)(n > 0 ? n : 1) * 4, 256);      // room for whole fours
     L.block_cnt = off; off += align_up((size_t)(ceil_div(n, kScanBlock) + 1) * 4, 256);
     L.total = off;
     return L;
@@ -273,6 +295,13 @@ fastgl_status fastgl_idmap(const int64_t *dst_gid, int64_t n_dst, const int64_t 
     a.n_dst = n_dst; a.n_nbr = n_nbr; a.n = n;
     const int64_t cap = position_slots(n, idmap_slots(n));
     a.table = PositionTable{(int32_t *)(ws + L.table), (uint32_t)cap, position_bits(n)};
+    // behind the slots, which leave a third of the table's room and more
+    const size_t displaced = align_up((size_t)ceil_div(cap, kFillVec) * kFillVec * sizeof(int32_t), 256);
+    if (L.table + displaced + align_up((size_t)n, 16) > L.ref) {
+        set_error("ID map: no room behind %lld slots", (long long)cap);      // not reached
+        return FASTGL_ERR_UNSUPPORTED;
+    }
+    a.displaced = (unsigned char *)(ws + L.table + displaced);
     a.ref = (int32_t *)(ws + L.ref);
     a.block_cnt = (int32_t *)(ws + L.block_cnt);
     a.local_nbr = local_nbr; a.unique_gid = unique_gid; a.result = result;
@@ -300,7 +329,7 @@ fastgl_status fastgl_idmap(const int64_t *dst_gid, int64_t n_dst, const int64_t 
         const dim3 blocks((unsigned)a.nblocks);
         hipLaunchKernelGGL(k_idmap_insert_min, grid(n, 256), dim3(256), 0, s, a);
         FASTGL_LAUNCH_CHECK("fastgl_idmap (insert)");
-        hipLaunchKernelGGL(k_idmap_count, blocks, dim3(kScanBlock), 0, s, a);
+        hipLaunchKernelGGL(k_idmap_count, blocks, dim3(kCountThreads), 0, s, a);
         FASTGL_LAUNCH_CHECK("fastgl_idmap (count)");
         if (a.nblocks <= kSumBlocks) {
             hipLaunchKernelGGL(k_idmap_rank<true>, blocks, dim3(kScanBlock), 0, s, a);

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void k_match_insert_prev(MatchArgs a)
     if (j >= a.n_prev) return;
     const int64_t gid = a.prev_gid[j];
     int32_t q = kEmptySlot;
-    if (gid >= 0) claim_slot<false>(a.table, gid, (int32_t)j, GidAt{a.prev_gid}, q);
+    if (gid >= 0) claim_slot(a.table, gid, (int32_t)j, GidAt{a.prev_gid}, q, false);
     if (q != (int32_t)j) atomicAdd(&a.result[1], 1);          // negative or repeated ID
 }
 
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void k_marks_fill(OverlapArgs a)
     }
 }
 
-// blockIdx.y = mini-batch, blockIdx.x walks its IDs.
+// blockIdx.y = mini-batch, blockIdx.x walks its IDs.  The first mini-batch's come first and find their slots empty.
 template <typename MARK>
 __global__ __launch_bounds__(256) void k_marks_insert(OverlapArgs a)
 {
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256) void k_marks_insert(OverlapArgs a)
     const int64_t gid = a.gid[p];
     if (gid < 0) return;
     int32_t q;
-    const uint32_t slot = claim_slot<true>(a.table, gid, (int32_t)p, GidAt{a.gid}, q);
+    const uint32_t slot = claim_slot(a.table, gid, (int32_t)p, GidAt{a.gid}, q, b > 0);
     if (q != (int32_t)p) a.marks[(size_t)slot * sizeof(MARK) + b] = 1;
 }
 
