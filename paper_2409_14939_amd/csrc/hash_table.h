@@ -198,13 +198,14 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int base, int &out_ex
 // scans them costs 5 us, more than the kernel that counted a small hop.  Beyond that, scan_block_counts.
 constexpr int kSumBlocks = 4096;
 
+template <int THREADS = kScanBlock>
 __device__ __forceinline__ int sum_before(const int32_t *block_cnt, int b)
 {
-    __shared__ int wave_sum_b[kScanBlock / 64];
+    __shared__ int wave_sum_b[THREADS / 64];
     int s = 0;
 #pragma unroll
-    for (int k = 0; k < kSumBlocks / kScanBlock; ++k) {
-        const int i = k * kScanBlock + threadIdx.x;
+    for (int k = 0; k < kSumBlocks / THREADS; ++k) {
+        const int i = k * THREADS + threadIdx.x;
         if (i < b) s += block_cnt[i];
     }
 #pragma unroll
@@ -213,7 +214,7 @@ __device__ __forceinline__ int sum_before(const int32_t *block_cnt, int b)
     __syncthreads();
     int total = 0;
 #pragma unroll
-    for (int w = 0; w < kScanBlock / 64; ++w) total += wave_sum_b[w];
+    for (int w = 0; w < THREADS / 64; ++w) total += wave_sum_b[w];
     return total;
 }
 

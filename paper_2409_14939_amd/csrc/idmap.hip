@@ -137,23 +137,42 @@ __global__ __launch_bounds__(kScanBlock) void k_idmap_scan(IdmapArgs a)
 
 // ORDERED pass 3: rank of every first occurrence = its local ID.  SUM: the block counts are not scanned yet.
 template <bool SUM>
-__global__ __launch_bounds__(kScanBlock) void k_idmap_rank(IdmapArgs a)
+__global__ __launch_bounds__(kCountThreads) void k_idmap_rank(IdmapArgs a)
 {
-    const int64_t p = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-    const int32_t ref = p < a.n ? a.ref[p] : kNoSlot;
-    const bool first = ref < 0;                    // bit 31
-    const int base = SUM ? sum_before(a.block_cnt, blockIdx.x) : a.block_cnt[blockIdx.x];
-    int rank;
-    const int mine = block_exclusive_scan(first ? 1 : 0, base, rank);
-    if (SUM && threadIdx.x == 0 && (int)blockIdx.x == a.nblocks - 1) a.result[0] = base + mine;
-    if (first) {
-        a.unique_gid[rank] = id_at(a, p);
-        if (p >= a.n_dst) {
-            a.table.slot[ref & kNoSlot] = rank;
-            a.local_nbr[p - a.n_dst] = rank;
+    const int64_t p0 = ((int64_t)blockIdx.x * kCountThreads + threadIdx.x) * 4;
+    int32_t ref[4] = {kNoSlot, kNoSlot, kNoSlot, kNoSlot};
+    int64_t gid[4];
+    if (p0 < a.n) {
+        const int4 r = *reinterpret_cast<const int4 *>(a.ref + p0);
+        ref[0] = r.x; ref[1] = r.y; ref[2] = r.z; ref[3] = r.w;
+    }
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (p0 + i >= a.n) ref[i] = kNoSlot;
+        if (ref[i] < 0) {                          // bit 31
+            gid[i] = id_at(a, p0 + i);
+            ++c;
         }
     }
-    if (p < a.n_dst && (!first || rank != (int)p)) atomicAdd(&a.result[1], 1);   // repeated destination
+    const int base = SUM ? sum_before<kCountThreads>(a.block_cnt, blockIdx.x) : a.block_cnt[blockIdx.x];
+    int rank;
+    const int mine = block_exclusive_scan(c, base, rank);
+    if (SUM && threadIdx.x == 0 && (int)blockIdx.x == a.nblocks - 1) a.result[0] = base + mine;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t p = p0 + i;
+        const bool first = ref[i] < 0;
+        if (first) {
+            a.unique_gid[rank] = gid[i];
+            if (p >= a.n_dst) {
+                a.table.slot[ref[i] & kNoSlot] = rank;
+                a.local_nbr[p - a.n_dst] = rank;
+            }
+        }
+        if (p < a.n_dst && (!first || rank != (int)p)) atomicAdd(&a.result[1], 1);   // repeated destination
+        rank += first;
+    }
 }
 
 // ORDERED pass 4: the entries that neither are first occurrences nor met a destination.
@@ -332,11 +351,11 @@ fastgl_status fastgl_idmap(const int64_t *dst_gid, int64_t n_dst, const int64_t 
         hipLaunchKernelGGL(k_idmap_count, blocks, dim3(kCountThreads), 0, s, a);
         FASTGL_LAUNCH_CHECK("fastgl_idmap (count)");
         if (a.nblocks <= kSumBlocks) {
-            hipLaunchKernelGGL(k_idmap_rank<true>, blocks, dim3(kScanBlock), 0, s, a);
+            hipLaunchKernelGGL(k_idmap_rank<true>, blocks, dim3(kCountThreads), 0, s, a);
         } else {
             hipLaunchKernelGGL(k_idmap_scan, dim3(1), dim3(kScanBlock), 0, s, a);
             FASTGL_LAUNCH_CHECK("fastgl_idmap (scan)");
-            hipLaunchKernelGGL(k_idmap_rank<false>, blocks, dim3(kScanBlock), 0, s, a);
+            hipLaunchKernelGGL(k_idmap_rank<false>, blocks, dim3(kCountThreads), 0, s, a);
         }
         FASTGL_LAUNCH_CHECK("fastgl_idmap (rank)");
         if (n_nbr > 0) {

@@ -119,3 +119,12 @@ def test_idmap_random_sweep():
         dst = pool[:n_dst]
         nbr = rng.integers(0, span, size=n_nbr)
         check(dst, nbr, f"sweep {case}")
+
+
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 7, 1021, 1023, 1024, 1025, 1027, 2047, 2049, 4097])
+def test_idmap_ends_inside_a_group_of_four_positions(n):
+    rng = np.random.default_rng(n)
+    for n_dst in (0, 1, n // 2, n - 1):
+        for span in (n, 3 * n):                    # many and few repeats, of destinations and of neighbours
+            dst = rng.permutation(span)[:n_dst]
+            check(dst, rng.integers(0, span, n - n_dst), "group of four")
