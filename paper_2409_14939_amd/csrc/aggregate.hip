@@ -262,12 +262,17 @@ static bool column_by_column(const PullDesc &d, int64_t row_bytes, int G)
            d.nnz >= 5 * d.num_cols && d.nsets >= 1024;
 }
 
+// 32 lanes have 8 gathers in flight where there are wavefronts enough to hide the longer way through the code: 2.56 M edges of
+// 100 floats 211 us with 6, 208 with 8 (gcn 218 and 217); a few hundred rows are better off with the shorter code.
+constexpr int64_t kManyWaves = 4096;
+
 template <int DT, int VB, int W>
 static void launch_rows(const PullParams &P, hipStream_t s)
 {
     const dim3 grid((unsigned)P.num_blocks);
     if (P.G == kWave) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollWave, true, false>), grid, dim3(kBlock), 0, s, P);
     else if (P.G <= kBatchLanes) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollNarrow, false, true>), grid, dim3(kBlock), 0, s, P);
+    else if (P.G == 32 && P.nwaves >= kManyWaves) hipLaunchKernelGGL((k_pull_rows<DT, 16, W, kUnrollWave, false, false>), grid, dim3(kBlock), 0, s, P);
     else hipLaunchKernelGGL((k_pull_rows<DT, 16, W, kUnroll, false, false>), grid, dim3(kBlock), 0, s, P);
 }
 
