@@ -263,8 +263,9 @@ static bool column_by_column(const PullDesc &d, int64_t row_bytes, int G)
 }
 
 // 32 lanes have 8 gathers in flight where there are wavefronts enough to hide the longer way through the code: 2.56 M edges of
-// 100 floats 211 us with 6, 208 with 8 (gcn 218 and 217); a few hundred rows are better off with the shorter code.
-constexpr int64_t kManyWaves = 4096;
+// 100 floats, 24 000 wavefronts 211 us with 6, 208 with 8 (gcn 218 and 217); 94 000 edges of 256 bf16, 6 144 wavefronts
+// 13.7 and 15.9.
+constexpr int64_t kManyWaves = 16384;
 
 template <int DT, int VB, int W>
 static void launch_rows(const PullParams &P, hipStream_t s)

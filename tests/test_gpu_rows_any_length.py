@@ -133,5 +133,5 @@ def test_column_tiles_one_after_the_other(dtype, feat, weighted):
 @pytest.mark.parametrize("dtype,feat,weighted", [("f32", 100, False), ("f32", 125, True), ("bf16", 200, False)])
 def test_many_wavefronts_of_two_groups(dtype, feat, weighted):
     """Enough rows for the variant with more gathers in flight: rows of none to a few edges and every remainder of a batch."""
-    blk = block_of(np.random.default_rng(feat).integers(0, 7, 60000), 5000, feat)
+    blk = block_of(np.random.default_rng(feat).integers(0, 7, 300000), 5000, feat)
     check_block(blk, "mean", dtype, feat, weighted, True, feat, "many wavefronts")
