@@ -12,9 +12,8 @@
 //     planes when it is written there, double buffered.  With NTILES = 8 a row is read and cut once for
 //     256 columns.
 //   k_update_small  bound by latency: too few rows to fill the chip with such tiles.  A workgroup owns
-//     32 x 64 results and its 4 wavefronts share the contracted range; every wavefront loads all its
-//     operands up front (no staging, no barrier before the end) and the four partial tiles are added in
-//     LDS.
+//     32 x 64 results and its 8 wavefronts share the contracted range; every wavefront loads the operands of two
+//     steps up front (no staging, no barrier before the end) and the partial tiles are added in LDS.
 //
 // us a call with cold caches, first version (128 x 128 tiles, both operands through LDS) -> whole turns of 32 or 64
 // indices, one chunk ahead -> now, fp32:
@@ -24,10 +23,12 @@
 // bf16: Y 300 K, 128 -> 256: 79 -> 78, gated dH 256 -> 128: 141 -> 128;  87 K, 128 -> 256: 26.8 -> 27.0 (1 % lost).
 // What is left of the 512 K product: 178 us without the matrix instructions, 190 without the stores, 143 to move its bytes
 // at 5.1 TB/s; priorities that let one of a unit's two workgroups run ahead of the other changed nothing.
-// k_update_small: 1 000, 256 -> 256: 34 -> 10 (bf16 29 -> 8);  16, 256 -> 47: 30 -> 9 (27 -> 7)
+// k_update_small, first version -> 4 wavefronts of 4 steps -> 8 of 2 (a launch that does nothing takes 6.4 so timed):
+//   1 000, 256 -> 256: 34 -> 10.1 -> 8.8 (bf16 29 -> 8.0 -> 6.9);  16, 256 -> 47: 30 -> 9.4 -> 8.1;  2 600, 100 -> 256: 10.8 -> 9.6;
+//   4 000, 256 -> 256: 14.3 -> 12.8 (16 wavefronts of 1 step: 13.6, 8.2 at 1 000 rows: their LDS leaves room for one workgroup)
 //
 // A step of 16 contracted indices goes into one matrix instruction per plane product (lane half h: indices 8 h .. + 7).
-// Tall tiles add the steps in ascending order, so results do not depend on a tile's width; small tiles add four
+// Tall tiles add the steps in ascending order, so results do not depend on a tile's width; small tiles add eight
 // partial sums of consecutive steps.  The tall loop ends with the last step that holds a term (K = 100: seven, which is
 // where most of 250 -> 220 came from: with whole turns eight were multiplied).
 #include <type_traits>
@@ -45,6 +46,7 @@ constexpr int kWaveRows = 32;
 constexpr int kTallRows = 128;                 // 4 wavefronts
 constexpr int kStageElems = 4096;              // elements of B per LDS stage
 constexpr int kSmallCols = 64;
+constexpr int kSmallWaves = 8;                 // share the contracted range of a small tile
 
 // Eight consecutive elements, as loaded.
 template <bool BF16>
@@ -538,19 +540,19 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES <= 4 && GATE && !BF16) 
 
 // ----------------------------------------------------------------------------------- small tiles
 template <bool BCOL, bool GATE, int VA, int VB, bool BF16>
-__global__ __launch_bounds__(256) void k_update_small(const RowsGemm g)
+__global__ __launch_bounds__(64 * kSmallWaves) void k_update_small(const RowsGemm g)
 {
-    constexpr int U = 4;                                       // steps of 16 contracted indices loaded together
+    constexpr int U = 2;                                       // steps of 16 contracted indices loaded together
     constexpr int kLd = kSmallCols + 4;                        // floats per row of a partial tile
-    __shared__ __attribute__((aligned(16))) float part[4][kWaveRows][kLd];
+    __shared__ __attribute__((aligned(16))) float part[kSmallWaves][kWaveRows][kLd];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, h = lane >> 5, l32 = lane & 31;
     const int64_t r0 = (int64_t)(blockIdx.x / g.tiles_c) * kWaveRows, c0 = (int64_t)(blockIdx.x % g.tiles_c) * kSmallCols;
     typedef typename QuadBits<BF16>::elem E;
     const int64_t row = r0 + l32 < g.M ? r0 + l32 : g.M - 1;
     const E *arow = static_cast<const E *>(g.a) + row * g.lda;
     const E *grow = GATE ? static_cast<const E *>(g.gate) + row * g.lda : nullptr;
-    // wavefront w: a contiguous quarter of the steps
-    const int Kc = (int)g.Kc, steps = (Kc + 15) / 16, per = (steps + 3) / 4;
+    // wavefront w: a contiguous part of the steps
+    const int Kc = (int)g.Kc, steps = (Kc + 15) / 16, per = (steps + kSmallWaves - 1) / kSmallWaves;
     const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
 
     f32x16 acc[2];
@@ -612,9 +614,16 @@ __global__ __launch_bounds__(256) void k_update_small(const RowsGemm g)
     const int64_t col = c0 + lane;
     const float bias = g.bias && col < g.N ? g.bias[col] : 0.f;
 #pragma unroll
-    for (int i = 0; i < kWaveRows / 4; ++i) {
-        const int r = 4 * i + wave;
-        float v = ((part[0][r][lane] + part[1][r][lane]) + (part[2][r][lane] + part[3][r][lane])) + bias;
+    for (int i = 0; i < kWaveRows / kSmallWaves; ++i) {
+        const int r = kSmallWaves * i + wave;
+        float p[kSmallWaves];
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) p[w] = part[w][r][lane];
+#pragma unroll
+        for (int n = kSmallWaves; n > 1; n /= 2)
+#pragma unroll
+            for (int w = 0; w < n / 2; ++w) p[w] = p[2 * w] + p[2 * w + 1];
+        float v = p[0] + bias;
         if (g.relu) v = v > 0.f ? v : 0.f;
         if (r0 + r < g.M && col < g.N) {
             if constexpr (BF16) c[(r0 + r) * g.N + col] = f32_to_bf16(v);
@@ -646,7 +655,7 @@ int row_vector(const void *p, const void *p2, int64_t K, bool bf16)
 template <int NTILES, bool BCOL, bool GATE, int VA, int VB, bool BF16>
 void launch_one(const RowsGemm &g, unsigned blocks, hipStream_t s)
 {
-    if constexpr (NTILES == 0) hipLaunchKernelGGL((k_update_small<BCOL, GATE, VA, VB, BF16>), dim3(blocks), dim3(256), 0, s, g);
+    if constexpr (NTILES == 0) hipLaunchKernelGGL((k_update_small<BCOL, GATE, VA, VB, BF16>), dim3(blocks), dim3(64 * kSmallWaves), 0, s, g);
     else hipLaunchKernelGGL((k_update_tall<NTILES, BCOL, GATE, VA, VB, BF16>), dim3(blocks), dim3(256), 0, s, g);
 }
 
