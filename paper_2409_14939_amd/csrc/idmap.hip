@@ -18,8 +18,8 @@
 // local ID).
 //
 // Bound by random accesses.  Products-shaped hop of 0.51 M destinations and 2.56 M neighbours, us, 16-byte
-// entries {key, smallest position, local ID} -> positions:  ordered 265 -> 166 (insert 134 -> 108, count 51 -> 20,
-// translate 43 -> 10);  fused 153 -> 124 (destinations 35 -> 23, translate 35 -> 11).
+// entries {key, smallest position, local ID} -> positions -> marks of the displaced:  ordered 265 -> 166 -> 139 (insert 134 -> 108
+// -> 96, count 51 -> 23 -> 5, rank 22 -> 18, translate 43 -> 11);  fused 153 -> 124 (destinations 35 -> 22, translate 35 -> 11).
 #include "fastgl_idmap.h"
 #include "hash_table.h"
 #include "internal.h"

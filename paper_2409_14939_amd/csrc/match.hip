@@ -11,8 +11,9 @@
 // that, entries carry a 64-bit mask, and every ID adds its mask to its mini-batch's row of the count matrix
 // (LDS histogram per workgroup, one atomic per workgroup and column).
 //
-// Four mini-batches of 1.15 M nodes, us, 16-byte entries with masks -> positions and marks: overlaps 481 -> 248
-// (insert 271 -> 212, count 188 -> 24, fill 23 -> 12); Match of two of them 130 -> 107 (insert 80 -> 54).
+// Four mini-batches of 1.15 M nodes, us, 16-byte entries with masks -> positions and marks: overlaps 481 -> 230
+// (insert 271 -> 211, 194 since the first mini-batch's IDs do not look, count 188 -> 24, fill 23 -> 12); Match of two
+// of them 130 -> 95 (insert 80 -> 46).
 #include <vector>
 
 #include "fastgl_match.h"
