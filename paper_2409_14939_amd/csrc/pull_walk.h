@@ -10,9 +10,9 @@
 
 namespace fastgl {
 
-// Row gathers in flight per lane: groups of 16 lanes (and of 32 in small launches), of at most kBatchLanes, and of a whole wavefront.  A group
-// loads as many column ids at a time (a chunk) as it has lanes, one of at most kBatchLanes lanes only those of the next
-// batch: all neighbours of 65 536 nodes, width 32, forward / backward 96 / 91 us so, 110 / 98 with chunks of two batches.
+// Row gathers in flight per lane: groups of 16 lanes (and of 32 in small launches), of at most kBatchLanes, and of a
+// whole wavefront (and of 32 lanes in large launches).  A group loads as many column ids at a time (a chunk) as it has
+// lanes, one of at most kBatchLanes lanes only those of the next batch: all neighbours of 65 536 nodes, width 32, forward / backward 96 / 91 us so, 110 / 98 with chunks of two batches.
 // 16 lanes, 2.56 M weighted edges of 64 floats: 108 us, 4 in flight 110, batches of 4 111.
 constexpr int kUnroll = 6;
 constexpr int kUnrollNarrow = 4;
