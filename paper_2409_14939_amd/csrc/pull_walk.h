@@ -169,15 +169,18 @@ enum { kNoWeight = 0, kColWeight = 1, kEdgeWeight = 2, kPermWeight = 3, kTwoWeig
 template <int W, typename acc_t> struct WeightT { using type = float; };
 template <typename acc_t> struct WeightT<kTwoWeights, acc_t> { using type = acc_t; };
 
-// Column ids, edge ids and weights of consecutive edges, one per lane of a group; past the end kend > 0 the last
-// edge's again.  No control flow around the loads: one behind a branch is waited for where the branch ends, and these are
-// to arrive while the rows of the edges before them are gathered.
-__device__ __forceinline__ int load_col(const PullParams &P, int k, int kend) { return P.col[k < kend ? k : kend - 1]; }
+// Column ids, edge ids and weights of consecutive edges, one per lane of a group; past the end kend > 0 those of the
+// block's first edge.  No control flow around the loads: one behind a branch is waited for where the branch ends, and
+// these are to arrive while the rows of the edges before them are gathered.  Past the end it is the first edge because
+// everybody's loads keep its cache line in L2; that of the last edge before the end has been displaced by then and came
+// once more from memory (2.56 M weighted edges of 64 floats: 628 -> 606 MB read, 110.9 -> 108.5 us; transposed, with edge
+// ids, 875 -> 840 MB, 165.2 -> 161.8).
+__device__ __forceinline__ int load_col(const PullParams &P, int k, int kend) { return P.col[k < kend ? k : 0]; }
 
 template <int W>
 __device__ __forceinline__ int load_eid(const PullParams &P, int k, int kend)
 {
-    const int at = k < kend ? k : kend - 1;
+    const int at = k < kend ? k : 0;
     if constexpr (W == kPermWeight) return P.eid[at];
     if constexpr (W == kTwoWeights) {
         const int id = (P.eid ? P.eid : P.col)[at];       // which one is a scalar
@@ -312,7 +315,7 @@ __device__ __forceinline__ void walk_flat(const PullParams &P, Window<DT, VB> &w
     // Edges j0 .. of the chunk at k0, which has n of them.  FULL: no masks.  Otherwise loads of edges that are not there
     // are masked out (a redundant load costs the address unit as much as any other: 222 -> 219 and 259 -> 256 us of the
     // headline mini-batch's input layer), except for groups that go batch by batch: past the end their lanes have the
-    // last edge again.
+    // block's first edge.
     auto batch = [&](auto full, int k0, int j0, int n) {
         constexpr bool FULL = decltype(full)::value;
         uint32_t raw[U][S::NW];
