@@ -1230,15 +1230,17 @@ static fastgl_status build_once(fastgl_plan *const *plans, const int *parts, con
     static_assert(sizeof(OnceArgs) <= 4096, "kernel arguments are passed by value");
     static bool raised = false;   // benign if two threads both do it
     if (!raised) {
-        FASTGL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_plan_once), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)sizeof(OnceShared)));
+        FASTGL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_plan_once<kOnceBits>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOnceLdsFullSmall));
+        FASTGL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_plan_once<kBucketBits>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOnceLdsFull));
         raised = true;
     }
     for (int at = 0; at < n; at += kOnceMaxJobs) {
         OnceArgs A;
         A.njobs = n - at < kOnceMaxJobs ? n - at : kOnceMaxJobs;
         int blocks = 0;
-        size_t lds = kOnceLdsDegrees;
+        bool any_full = false;
         for (int i = 0; i < A.njobs; ++i) {
             fastgl_plan *p = plans[at + i];
             const bool full = (parts[at + i] & FASTGL_PLAN_BWD) != 0, deg = !full && src_deg[at + i];
@@ -1253,14 +1255,29 @@ static fastgl_status build_once(fastgl_plan *const *plans, const int *parts, con
                               p->counters + 2, nullptr, full ? p->split_src : nullptr, p->num_edges);
             J.indptr_T = p->indptr_T; J.indices_T = p->indices_T;
             J.perm = full && (p->parts & FASTGL_PLAN_PERM) ? p->perm : nullptr;
-            J.buckets = full || deg ? (int)ceil_div(p->num_src > 0 ? p->num_src : (full ? 1 : 0), (int64_t)(full ? kOnceIds : kBucketIds)) : 0;
+            J.buckets = deg ? (int)ceil_div(p->num_src, (int64_t)kBucketIds) : 0;
+            J.further = full && p->num_edges > 0 ? (int)((p->num_edges - 1) / kOnceChunk) : 0;
             J.row_groups = (int)ceil_div(p->num_dst, (int64_t)kOnceThreads);
-            if (full) lds = sizeof(OnceShared);
-            A.first[i] = blocks;
-            blocks += J.buckets + (full ? 1 : 0) + 1 + J.row_groups;
+            any_full = any_full || full;
         }
-        A.first[A.njobs] = blocks;
-        hipLaunchKernelGGL(k_plan_once, dim3(blocks), dim3(kOnceThreads), lds, s, A);
+        auto deal = [&](int ids) {           // the workgroups of the launch; how many of them surely have work
+            int idle = 0;
+            blocks = 0;
+            for (int i = 0; i < A.njobs; ++i) {
+                OnceJob &J = A.job[i];
+                if (J.full) J.buckets = J.num_src > 0 ? (int)ceil_div(J.num_src, ids) : 1;
+                A.first[i] = blocks;
+                blocks += J.buckets + J.further + J.full + 1 + J.row_groups;
+                idle += J.further;
+            }
+            A.first[A.njobs] = blocks;
+            return blocks - idle;
+        };
+        const bool wide = deal(kOnceIds) > kOnceGroups && any_full;
+        if (wide) deal(kBucketIds);
+        const dim3 grid(blocks), threads(kOnceThreads);
+        if (wide) hipLaunchKernelGGL(k_plan_once<kBucketBits>, grid, threads, kOnceLdsFull, s, A);
+        else hipLaunchKernelGGL(k_plan_once<kOnceBits>, grid, threads, any_full ? kOnceLdsFullSmall : kOnceLdsDegrees, s, A);
         FASTGL_LAUNCH_CHECK("k_plan_once");
     }
     return FASTGL_OK;

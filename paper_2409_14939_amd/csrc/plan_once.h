@@ -4,16 +4,21 @@
 // before: for a block of a few thousand edges that is 20 us of launch latency around 2 us of work.  Here
 // nobody waits for anybody: every workgroup recomputes from the block's own arrays what it needs from the
 // others.  That costs reads (every bucket's workgroup scans all source ids, at most 256 KB out of L2) and chains of
-// steps in the workgroups that there is one of (the lists of long rows, a bucket's chunks): the limits below are where
+// steps in the workgroups that there is one of (the lists of long rows, a chunk): the limits below are where
 // those chains, growing with the block, take as long as the launches they save.
 //
 //   bucket      512 consecutive source ids: counts the edges per source of its bucket and the edges of the
 //               buckets before it, writes the bucket's rows of indptr_T, out-degrees, scale factors and row
-//               sets, collects the bucket's edges in order (8 192 at a time) and places them stably
+//               sets, collects the first chunk of the bucket's edges (4 096) in order and places them stably
 //               (counts per wavefront and source, column scan, lane match - as k_plan_buckets does); the
 //               destination row of an edge comes from a binary search in row pointers held in LDS.  Every workgroup
 //               looks at all source ids, so small buckets cost reads, but the chain from there on is as long as the
 //               edges of a bucket (15 369 edges over 6 597 sources, two layers: 25 us with 2 048 ids, 13 now)
+//   further chunks  one workgroup for each that there can be, (edges - 1) / 4 096 whatever the buckets are: finds from
+//               the buckets' counts which chunk of which bucket is its own.  With all chunks of a bucket in one workgroup a
+//               block whose hubs share a bucket was a chain: 49 152 edges over 12 288 sources, evenly spread / half / nearly
+//               all of them in one bucket: 27 / 92 / 145 us, now 27 / 34 / 35 (chunks of 8 192: 27 / 41 / 42; of 2 048: 30 /
+//               31 / 31, but they are more workgroups than the device holds where a call has many blocks)
 //   source degrees  the first half of that for 2 048 ids, for a forward-only plan of a GCN-normalised pass
 //   long sources    one workgroup: degrees of all sources, ordered list of the long ones
 //   destination rows  1 024 rows per workgroup: degrees, scale factors, row sets
@@ -33,10 +38,10 @@ constexpr int kOnceWaves = kOnceThreads / kWave;
 // Limits, us a plan in one launch / in stages (calls one after the other; a call that is waited for adds 3 to both).
 // Edges of a forward-only plan with source degrees: 16-bit row pointers and edge ids; 65 535 edges: 14 / 19.
 constexpr int kOnceEdges = 65535;
-// Edges of a full plan.  One bucket's workgroup places its edges chunk by chunk, so a block whose edges fall into few
-// buckets is a chain: 16 000 edges over 1 333 sources, 9 862 in one bucket, 27 / 40; 24 000 over 2 000, 16 932 in one,
-// 49 / 43.  With at most four edges per source on average the buckets stay small: 32 000 over 19 200 26 / 36 (5 199 in
-// one), 48 000 over 28 800 35 / 37 (6 356), evenly spread 24 / 32; 64 000 40 / 40.
+// Edges of a full plan: 20 000 over 2 000 sources 19 / 36 evenly spread, 22 / 41 with 95 % in one bucket.  With at most
+// four edges per source more of them: 48 000 over 28 800 24 / 36 and 34 / 50; 49 152 over 12 288 27 / 40 and 35 / 49, 8 000
+// of 40 000 of one source 35 / 50.  A source of most edges, which takes rows that repeat it, makes one counter the chain:
+// 46 000 of 49 152 edges 94 / 55, 20 000 of 30 000 52 / 50.
 constexpr int kOnceFullEdges = 20480;
 constexpr int kOnceSparseEdges = 49152;
 // Destination rows: one workgroup scans all of them for long ones, 1 024 a step.  Forward-only: 8 192 rows 6.7 / 8.4,
@@ -49,9 +54,12 @@ constexpr int kOnceRows = 24576;
 // need no list: 128 buckets, 262 144 sources, 14 / 19.
 constexpr int kOnceSourcesFull = 32768;
 constexpr int kOnceSources = 1 << 18;
-constexpr int kOnceChunk = 8192;           // edges of a bucket placed at a time
+constexpr int kOnceChunk = 4096;           // edges of a bucket that one workgroup places
 constexpr int kOnceMaxJobs = 8;
-constexpr int kOnceBits = 9;               // source ids of a bucket of a full plan
+// Workgroups that the device holds at once (one per compute unit).  A launch of more, several blocks of many sources,
+// has buckets of 2 048 ids: 8 blocks of 16 000 edges over 30 000 sources 30 us with 512 ids, 19 so; 4 blocks 18 and 18.
+constexpr int kOnceGroups = 256;
+constexpr int kOnceBits = 9;               // source ids of a bucket of a full plan, in launches of up to kOnceGroups workgroups
 constexpr int kOnceIds = 1 << kOnceBits;
 static_assert(kOnceIds <= kOnceThreads && kBucketIds == 2 * kOnceThreads, "one or two sources per thread");
 
@@ -60,7 +68,7 @@ struct OnceJob {
     RowsArgs dst, src;            // src.rowptr is not read; src.len_out / rsq / split NULL where not wanted
     int32_t *indptr_T, *indices_T, *perm;
     int32_t num_dst, num_src, num_edges;
-    int32_t buckets, row_groups;  // workgroups of those roles
+    int32_t buckets, further, row_groups;    // workgroups of those roles
     int32_t full;                 // with the transpose
 };
 
@@ -74,13 +82,16 @@ struct OnceShared {
     union {
         struct {
             int start[kBucketIds];                      // edges per source, then where its next edges go (within the bucket)
-            unsigned tab[kOnceWaves][kOnceIds / 2];     // per wavefront and source: count, then offset (16 bits each)
             uint32_t list[kOnceChunk];                  // collected edges: id | source within the bucket << 16
-            uint16_t rows[kOnceRows + 2];               // indptr
+            uint16_t rows[kOnceRows + 8];               // indptr
+            unsigned tab[kOnceWaves * kBucketIds / 2];  // per wavefront and source: count, then offset (16 bits each)
         };
         unsigned degree[kOnceSourcesFull / 2];          // 16-bit counters, two to a word
     };
 };
+constexpr size_t kOnceLdsFull = sizeof(OnceShared);
+constexpr size_t kOnceLdsFullSmall = sizeof(OnceShared) - sizeof(unsigned) * kOnceWaves * (kBucketIds - kOnceIds) / 2;
+static_assert(kOnceLdsFullSmall >= sizeof(unsigned) * kOnceSourcesFull / 2, "room for the degrees");
 constexpr size_t kOnceLdsDegrees = sizeof(int) * kBucketIds;   // a forward-only plan needs no more than this
 
 // The block's source ids, 64 per round; a wavefront owns the rounds r0 .. r1 - 1.
@@ -143,8 +154,9 @@ __device__ __forceinline__ void once_long_rows(const RowsArgs &A, int n, int *ld
 }
 
 // BITS: 1 << BITS source ids; FULL: with the transpose.
+// Bucket d; FULL: places the share-th chunk of its edges.
 template <int BITS, bool FULL>
-__device__ __forceinline__ void once_bucket(const OnceJob &J, int d, OnceShared &M, int *lds)
+__device__ __forceinline__ void once_bucket(const OnceJob &J, int d, int share, OnceShared &M, int *lds)
 {
     constexpr int kIds = 1 << BITS, kPer = kIds > kOnceThreads ? kIds / kOnceThreads : 1;   // sources per thread
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
@@ -189,41 +201,54 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, OnceShared 
         const int64_t r = (int64_t)d * kIds + kPer * t + k;
         const bool valid = holds && r < J.num_src;
         if (holds) M.start[kPer * t + k] = at;
-        if (FULL && valid) J.indptr_T[r] = B0 + at;
-        row_emit(J.src, r, valid, B0 + at, c[k], nl, nc);
+        if (share == 0) {
+            if (FULL && valid) J.indptr_T[r] = B0 + at;
+            row_emit(J.src, r, valid, B0 + at, c[k], nl, nc);
+        }
         at += c[k];
     }
     if constexpr (FULL) {
-        if (d == J.buckets - 1 && t == 0) J.indptr_T[J.num_src] = J.num_edges;
-        int span = 1;
-        while (span < J.num_dst) span <<= 1;
-        for (int f0 = 0; f0 < total; f0 += kOnceChunk) {
+        if (share == 0 && d == J.buckets - 1 && t == 0) J.indptr_T[J.num_src] = J.num_edges;
+        const int f0 = share * kOnceChunk;
+        if (f0 < total) {                    // the same for the workgroup
+            int span = 1;
+            while (span < J.num_dst) span <<= 1;
             const int n = total - f0 < kOnceChunk ? total - f0 : kOnceChunk;
-            uint4 *z = reinterpret_cast<uint4 *>(&M.tab[0][0]);
-            for (int k = t; k < (int)(sizeof(M.tab) / sizeof(uint4)); k += kOnceThreads) z[k] = make_uint4(0u, 0u, 0u, 0u);
+            uint4 *z = reinterpret_cast<uint4 *>(M.tab);
+            unsigned *tab = M.tab + w * (kIds / 2);
+            for (int k = t; k < kOnceWaves * kIds / 2 / 4; k += kOnceThreads) z[k] = make_uint4(0u, 0u, 0u, 0u);
             int to = listed - f0;            // place in this chunk's list of the next edge of this wavefront
-            run.each([&](int e, int32_t key, bool ok) {
-                const bool in = ok && (key >> BITS) == d;
-                const unsigned long long m = __ballot(in);
-                const int p = to + lanes_below((unsigned)m, (unsigned)(m >> 32));
-                if (in && p >= 0 && p < n) M.list[p] = (uint32_t)e | ((uint32_t)(key & (kIds - 1)) << 16);
-                to += __popcll(m);
-            });
+            auto collect = [&](auto first) {
+                run.each([&](int e, int32_t key, bool ok) {
+                    const bool in = ok && (key >> BITS) == d;
+                    const unsigned long long m = __ballot(in);
+                    const int p = to + lanes_below((unsigned)m, (unsigned)(m >> 32));
+                    if (!decltype(first)::value && in && p < 0) atomicAdd(&M.start[key & (kIds - 1)], 1);   // of an earlier chunk
+                    if (in && p >= 0 && p < n) M.list[p] = (uint32_t)e | ((uint32_t)(key & (kIds - 1)) << 16);
+                    to += __popcll(m);
+                });
+            };
+            if (share == 0) {
+                collect(std::true_type());
+            } else {
+                __syncthreads();             // M.start is written
+                collect(std::false_type());
+            }
             __syncthreads();
             // this wavefront's run of the list: seg entries, a multiple of 64
             const int seg = ((n + kOnceThreads - 1) / kOnceThreads) * kWave;
             const int s0 = w * seg < n ? w * seg : n, s1 = s0 + seg < n ? s0 + seg : n;
             for (int i = s0 + lane; i < s1; i += kWave) {
                 const int k = (int)(M.list[i] >> 16);
-                atomicAdd(&M.tab[w][k >> 1], 1u << ((k & 1) * 16));
+                atomicAdd(&tab[k >> 1], 1u << ((k & 1) * 16));
             }
             __syncthreads();
-            unsigned sum = 0;                // column scan over the wavefronts, two sources to a word
-            if (t < kIds / 2) {
+            if (t < kIds / 2) {              // column scan over the wavefronts, two sources to a word
+                unsigned sum = 0;
 #pragma unroll
                 for (int k = 0; k < kOnceWaves; ++k) {
-                    const unsigned v = M.tab[k][t];
-                    M.tab[k][t] = sum;
+                    const unsigned v = M.tab[k * (kIds / 2) + t];
+                    M.tab[k * (kIds / 2) + t] = sum;
                     sum += v;
                 }
             }
@@ -254,9 +279,9 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, OnceShared 
                     unsigned mlo, mhi;
                     match_lanes<BITS>(k, ok, mlo, mhi);
                     const int lower = lanes_below(mlo, mhi);
-                    const int prior = (int)((M.tab[w][k >> 1] >> sh) & 0xFFFFu);
+                    const int prior = (int)((tab[k >> 1] >> sh) & 0xFFFFu);
                     // the LDS read above is issued before this update by the same wavefront
-                    if (ok && lower == 0) atomicAdd(&M.tab[w][k >> 1], (unsigned)(__popc(mlo) + __popc(mhi)) << sh);
+                    if (ok && lower == 0) atomicAdd(&tab[k >> 1], (unsigned)(__popc(mlo) + __popc(mhi)) << sh);
                     const int pos = B0 + M.start[k] + prior + lower;
                     if (ok && pos < J.num_edges) {
                         J.indices_T[pos] = row[u];
@@ -264,13 +289,37 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, OnceShared 
                     }
                 }
             }
-            __syncthreads();
-            if (t < kIds / 2) {
-                M.start[2 * t] += (int)(sum & 0xFFFFu);
-                M.start[2 * t + 1] += (int)(sum >> 16);
-            }
         }
     }
+}
+
+// Which chunk behind the first of which bucket is the x-th?  There are at most (edges - 1) / kOnceChunk.
+template <int BITS>
+__device__ __forceinline__ bool once_further(const OnceJob &J, int x, OnceShared &M, int &bucket, int &share)
+{
+    constexpr int kSpread = 32;              // counters of a bucket: the edges of a wavefront mostly have the same one
+    static_assert(kOnceSourcesFull >> BITS <= kWave && kWave * kSpread <= kBucketIds, "a bucket per lane");
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int i = threadIdx.x; i < kWave * kSpread; i += kOnceThreads) M.start[i] = 0;
+    __syncthreads();
+    KeyRun(J.indices, J.num_edges).each([&](int, int32_t key, bool ok) {
+        if (ok && (uint32_t)key < (uint32_t)kOnceSourcesFull) atomicAdd(&M.start[(key >> BITS) * kSpread + (lane & (kSpread - 1))], 1);
+    });
+    __syncthreads();
+    int total = 0;
+    for (int i = 0; i < kSpread; ++i) total += M.start[lane * kSpread + ((lane + i) & (kSpread - 1))];
+    const int mine = total > kOnceChunk ? (total - 1) / kOnceChunk : 0;
+    int upto = mine;
+    for (int k = 1; k < kWave; k <<= 1) {
+        const int v = __shfl_up(upto, k);
+        upto += lane >= k ? v : 0;
+    }
+    __syncthreads();                         // the counters have been read
+    const unsigned long long has = __ballot(upto > x);
+    if (!has) return false;                  // the same for the workgroup
+    bucket = __ffsll((long long)has) - 1;
+    share = x - __shfl(upto - mine, bucket) + 1;
+    return true;
 }
 
 __device__ __forceinline__ void once_long_sources(const OnceJob &J, OnceShared &M, int *lds)
@@ -287,7 +336,9 @@ __device__ __forceinline__ void once_long_sources(const OnceJob &J, OnceShared &
     once_long_rows(J.src, n, lds, [&](int i) { return (int)((M.degree[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu); });
 }
 
-// Workgroups of a job, in this order: buckets, long sources (with the transpose), long destinations, row groups.
+// Workgroups of a job, in this order: buckets, their further chunks, long sources (with the transpose), long destinations,
+// row groups.  BITS: 1 << BITS sources to a bucket of a full plan.
+template <int BITS>
 __global__ __launch_bounds__(kOnceThreads) void k_plan_once(OnceArgs A)
 {
     extern __shared__ __align__(16) unsigned char dyn[];
@@ -297,12 +348,14 @@ __global__ __launch_bounds__(kOnceThreads) void k_plan_once(OnceArgs A)
     while (j + 1 < A.njobs && (int)blockIdx.x >= A.first[j + 1]) ++j;
     const OnceJob &J = A.job[j];
     int b = blockIdx.x - A.first[j];
-    if (b < J.buckets) {
-        if (J.full) once_bucket<kOnceBits, true>(J, b, M, lds);
-        else once_bucket<kBucketBits, false>(J, b, M, lds);
+    if (b < J.buckets + J.further) {
+        int share = 0;
+        if (b >= J.buckets && !once_further<BITS>(J, b - J.buckets, M, b, share)) return;
+        if (J.full) once_bucket<BITS, true>(J, b, share, M, lds);
+        else once_bucket<kBucketBits, false>(J, b, 0, M, lds);
         return;
     }
-    b -= J.buckets;
+    b -= J.buckets + J.further;
     if (J.full && b == 0) {
         once_long_sources(J, M, lds);
         return;

@@ -35,7 +35,10 @@ def test_plan_of_a_small_block(nd, ns, edges, hub):
 def test_small_blocks_next_to_a_large_one_and_alone():
     rng = np.random.default_rng(5)
     small = [exact_block(rng, 100, 3000, 2500, 400), exact_block(rng, 4000, 9000, 9000)]
-    for blocks in (small, small + [exact_block(rng, 30000, 50000, 90000, 700)]):
+    # more workgroups of 512 sources than the device has compute units: 2 048 to a workgroup
+    many = [exact_block(rng, 2000, 32768 - 2047 * i, 16000 + 97 * i, 300) for i in range(6)] + small
+    many[3].indices[:13000] = rng.integers(4096, 6144, 13000)
+    for blocks in (small, small + [exact_block(rng, 30000, 50000, 90000, 700)], many):
         dev = [(dev_i32(b.indptr), dev_i32(b.indices), b.num_src) for b in blocks]
         for blk, plan in zip(blocks, B.fastgl_block_plan_create_many(dev, B.PLAN_ALL | B.PLAN_PERM)):
             v = plan.export()
@@ -74,6 +77,22 @@ def test_full_plan_around_the_edge_limit(edges):
                                          (700, 512, 20000), (700, 513, 20000), (700, 1024, 8192), (700, 1025, 8193)])
 def test_full_plan_around_the_limit_of_sparse_blocks(nd, ns, edges):
     check_bookkeeping(exact_block(np.random.default_rng(ns + edges), nd, ns, edges, 500), "once")
+
+
+# nearly all edges in one bucket of 512 sources (over all of them, over 64, over one): its chunks go to different
+# workgroups; the other bucket gets just over a chunk where there is room.  Edges in the bucket: multiples of every power
+# of two up to 32 768, and one more
+@pytest.mark.parametrize("ns,bucket", [(12288, 0), (12288, 23), (32768, 63), (12800, 7)])
+@pytest.mark.parametrize("inside", [8192, 8193, 16385, 32768, 40961, 49152])
+def test_full_plan_of_a_block_with_one_full_bucket(ns, bucket, inside):
+    rng = np.random.default_rng(ns + bucket + inside)
+    blk = exact_block(rng, 5000, ns, 49152, 700)
+    for i, spread in enumerate((512, 64, 1)):
+        idx = 512 * ((bucket + 1) % (ns // 512)) + rng.integers(0, 512, 49152)
+        idx[rng.permutation(49152)[:inside]] = 512 * bucket + 3 * i + rng.integers(0, spread, inside) % (512 - 3 * i)
+        blk.indices[:] = idx
+        blk.check()
+        check_bookkeeping(blk, f"spread {spread}")
 
 
 @pytest.mark.parametrize("nd,ns,edges,hub", [(3000, 32768, 16384, 300), (3000, 32769, 16384, 300), (24576, 32768, 16384, 300),
