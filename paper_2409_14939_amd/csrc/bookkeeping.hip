@@ -1277,7 +1277,8 @@ static fastgl_status build_once(fastgl_plan *const *plans, const int *parts, con
         if (wide) deal(kBucketIds);
         const dim3 grid(blocks), threads(kOnceThreads);
         if (wide) hipLaunchKernelGGL(k_plan_once<kBucketBits>, grid, threads, kOnceLdsFull, s, A);
-        else hipLaunchKernelGGL(k_plan_once<kOnceBits>, grid, threads, any_full ? kOnceLdsFullSmall : kOnceLdsDegrees, s, A);
+        else if (any_full) hipLaunchKernelGGL(k_plan_once<kOnceBits>, grid, threads, kOnceLdsFullSmall, s, A);
+        else hipLaunchKernelGGL(k_plan_once<0>, grid, threads, kOnceLdsDegrees, s, A);
         FASTGL_LAUNCH_CHECK("k_plan_once");
     }
     return FASTGL_OK;

@@ -337,7 +337,7 @@ __device__ __forceinline__ void once_long_sources(const OnceJob &J, OnceShared &
 }
 
 // Workgroups of a job, in this order: buckets, their further chunks, long sources (with the transpose), long destinations,
-// row groups.  BITS: 1 << BITS sources to a bucket of a full plan.
+// row groups.  BITS: 1 << BITS sources to a bucket of a full plan; 0: there is none.
 template <int BITS>
 __global__ __launch_bounds__(kOnceThreads) void k_plan_once(OnceArgs A)
 {
@@ -349,16 +349,23 @@ __global__ __launch_bounds__(kOnceThreads) void k_plan_once(OnceArgs A)
     const OnceJob &J = A.job[j];
     int b = blockIdx.x - A.first[j];
     if (b < J.buckets + J.further) {
-        int share = 0;
-        if (b >= J.buckets && !once_further<BITS>(J, b - J.buckets, M, b, share)) return;
-        if (J.full) once_bucket<BITS, true>(J, b, share, M, lds);
-        else once_bucket<kBucketBits, false>(J, b, 0, M, lds);
+        if constexpr (BITS > 0) {
+            int share = 0;
+            if (b >= J.buckets && !once_further<BITS>(J, b - J.buckets, M, b, share)) return;
+            if (J.full) {
+                once_bucket<BITS, true>(J, b, share, M, lds);
+                return;
+            }
+        }
+        once_bucket<kBucketBits, false>(J, b, 0, M, lds);
         return;
     }
     b -= J.buckets + J.further;
-    if (J.full && b == 0) {
-        once_long_sources(J, M, lds);
-        return;
+    if constexpr (BITS > 0) {
+        if (J.full && b == 0) {
+            once_long_sources(J, M, lds);
+            return;
+        }
     }
     b -= J.full ? 1 : 0;
     if (b == 0) {
