@@ -40,8 +40,8 @@ constexpr int kOnceWaves = kOnceThreads / kWave;
 constexpr int kOnceEdges = 65535;
 // Edges of a full plan: 20 000 over 2 000 sources 19 / 36 evenly spread, 22 / 41 with 95 % in one bucket.  With at most
 // four edges per source more of them: 48 000 over 28 800 24 / 36 and 34 / 50; 49 152 over 12 288 27 / 40 and 35 / 49, 8 000
-// of 40 000 of one source 35 / 50.  A source of most edges, which takes rows that repeat it, makes one counter the chain:
-// 46 000 of 49 152 edges 94 / 55, 20 000 of 30 000 52 / 50.
+// of 40 000 of one source 35 / 50.  One source of many edges: 20 000 of 49 152 40 / 50, 46 000 49 / 53, 20 000 of 30 000
+// 34 / 52, 19 000 of 20 000 30 / 50.
 constexpr int kOnceFullEdges = 20480;
 constexpr int kOnceSparseEdges = 49152;
 // Destination rows: one workgroup scans all of them for long ones, 1 024 a step.  Forward-only: 8 192 rows 6.7 / 8.4,
@@ -160,8 +160,15 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, int share, 
 {
     constexpr int kIds = 1 << BITS, kPer = kIds > kOnceThreads ? kIds / kOnceThreads : 1;   // sources per thread
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    // kCopies counters of a source, by lane: many edges of one source are a chain of additions to one word
+    // (49 152 edges, 20 000 of one source, us a plan: 56 with one counter, 40 with four, 50 in stages; evenly spread 28.8
+    // and 29.3, 1 276 edges 8.2 and 8.4)
+    constexpr int kCopies = kBucketIds / kIds;
+    static_assert(kCopies == 1 || (kCopies == 4 && kPer == 1), "copies are added up by the thread that has the source");
+    int4 *const copies = reinterpret_cast<int4 *>(M.start);
+    const int copy = lane & (kCopies - 1);
     const KeyRun run(J.indices, J.num_edges);
-    for (int i = t; i < kIds; i += kOnceThreads) M.start[i] = 0;
+    for (int i = t; i < kIds * kCopies / 4; i += kOnceThreads) copies[i] = make_int4(0, 0, 0, 0);
     if (FULL)
         for (int i = t; i <= J.num_dst; i += kOnceThreads) M.rows[i] = (uint16_t)J.indptr[i];
     __syncthreads();
@@ -172,7 +179,7 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, int share, 
         const bool in = ok && b == d;
         mine += __popcll(__ballot(in));
         before += __popcll(__ballot(ok && b < d));
-        if (in) atomicAdd(&M.start[key & (kIds - 1)], 1);
+        if (in) atomicAdd(&M.start[(key & (kIds - 1)) * kCopies + copy], 1);
     });
     if (lane == 0) {
         lds[32 + w] = mine;
@@ -190,7 +197,12 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, int share, 
     int c[kPer], sum_c = 0;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-        c[k] = holds ? M.start[kPer * t + k] : 0;
+        if constexpr (kCopies == 4) {
+            const int4 v = copies[holds ? t : 0];
+            c[k] = holds ? v.x + v.y + v.z + v.w : 0;
+        } else {
+            c[k] = holds ? M.start[kPer * t + k] : 0;
+        }
         sum_c += c[k];
     }
     int all;
@@ -200,7 +212,10 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, int share, 
     for (int k = 0; k < kPer; ++k) {         // the bucket's rows
         const int64_t r = (int64_t)d * kIds + kPer * t + k;
         const bool valid = holds && r < J.num_src;
-        if (holds) M.start[kPer * t + k] = at;
+        if (holds) {
+            if constexpr (kCopies == 4) copies[t] = make_int4(at, 0, 0, 0);
+            else M.start[kPer * t + k] = at;
+        }
         if (share == 0) {
             if (FULL && valid) J.indptr_T[r] = B0 + at;
             row_emit(J.src, r, valid, B0 + at, c[k], nl, nc);
@@ -223,7 +238,8 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, int share, 
                     const bool in = ok && (key >> BITS) == d;
                     const unsigned long long m = __ballot(in);
                     const int p = to + lanes_below((unsigned)m, (unsigned)(m >> 32));
-                    if (!decltype(first)::value && in && p < 0) atomicAdd(&M.start[key & (kIds - 1)], 1);   // of an earlier chunk
+                    if (!decltype(first)::value && in && p < 0)   // of an earlier chunk
+                        atomicAdd(&M.start[(key & (kIds - 1)) * kCopies + copy], 1);
                     if (in && p >= 0 && p < n) M.list[p] = (uint32_t)e | ((uint32_t)(key & (kIds - 1)) << 16);
                     to += __popcll(m);
                 });
@@ -243,6 +259,10 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, int share, 
                 atomicAdd(&tab[k >> 1], 1u << ((k & 1) * 16));
             }
             __syncthreads();
+            if (kCopies > 1 && share > 0 && t < kIds) {
+                const int4 v = copies[t];
+                M.start[t * kCopies] = v.x + v.y + v.z + v.w;
+            }
             if (t < kIds / 2) {              // column scan over the wavefronts, two sources to a word
                 unsigned sum = 0;
 #pragma unroll
@@ -282,7 +302,7 @@ __device__ __forceinline__ void once_bucket(const OnceJob &J, int d, int share, 
                     const int prior = (int)((tab[k >> 1] >> sh) & 0xFFFFu);
                     // the LDS read above is issued before this update by the same wavefront
                     if (ok && lower == 0) atomicAdd(&tab[k >> 1], (unsigned)(__popc(mlo) + __popc(mhi)) << sh);
-                    const int pos = B0 + M.start[k] + prior + lower;
+                    const int pos = B0 + M.start[k * kCopies] + prior + lower;
                     if (ok && pos < J.num_edges) {
                         J.indices_T[pos] = row[u];
                         if (J.perm) J.perm[pos] = ee[u];
