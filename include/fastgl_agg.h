@@ -214,8 +214,9 @@ int32_t fastgl_long_row_threshold(void);
 int32_t fastgl_long_row_chunk(void);
 
 /* The plan cuts the rows into consecutive sets of this much work (edges + rows)
- * each; a lane group of the aggregation kernels takes 1-8 consecutive sets, so no
- * group is overloaded however skewed the degrees are. */
+ * each; a wavefront of the aggregation kernels takes a number of consecutive sets
+ * and its lane groups share their edges, so neither is overloaded however skewed
+ * the degrees are. */
 int32_t fastgl_work_per_group(void);
 
 /* Row gather from a device-resident feature table, the device-side tail of the
@@ -235,6 +236,13 @@ fastgl_status fastgl_block_validate(const int32_t *indptr, const int32_t *indice
 
 /* Text of the last error on the calling thread ("" if none). Host string. */
 const char *fastgl_last_error(void);
+
+/* Column tiles that a forward aggregation of a block of these sizes cuts its
+ * feature rows into (512 bytes each), 1: rows as a whole; 0 for bad sizes.  The
+ * order in which a row's terms are added depends on it, and on nothing but the
+ * sizes and the block. */
+int32_t fastgl_aggregate_column_tiles(int64_t num_dst, int64_t num_src, int64_t num_edges, int64_t feat,
+                                      fastgl_dtype dtype);
 
 #ifdef __cplusplus
 }

@@ -28,7 +28,7 @@ EXPORTS = [
     "fastgl_block_plan_bytes",
     "fastgl_block_plan_create", "fastgl_block_plan_create_many", "fastgl_block_plan_export", "fastgl_block_plan_destroy",
     "fastgl_block_workspace_bytes", "fastgl_long_row_threshold", "fastgl_long_row_chunk", "fastgl_work_per_group",
-    "fastgl_gather_rows", "fastgl_block_validate", "fastgl_last_error",
+    "fastgl_aggregate_column_tiles", "fastgl_gather_rows", "fastgl_block_validate", "fastgl_last_error",
     "fastgl_update_fwd", "fastgl_update_bwd", "fastgl_update_bwd_workspace_bytes", "fastgl_update_slab_rows",
     "fastgl_update_fwd_bf16", "fastgl_update_bwd_bf16", "fastgl_layer_fwd", "fastgl_layer_fwd_fuses",
     "fastgl_idmap", "fastgl_idmap_table_slots", "fastgl_idmap_workspace_bytes",
@@ -86,6 +86,8 @@ def lib() -> ctypes.CDLL:
         L.fastgl_long_row_threshold.restype = ctypes.c_int32
         L.fastgl_long_row_chunk.restype = ctypes.c_int32
         L.fastgl_work_per_group.restype = ctypes.c_int32
+        L.fastgl_aggregate_column_tiles.argtypes = [i64, i64, i64, i64, i32]
+        L.fastgl_aggregate_column_tiles.restype = ctypes.c_int32
         L.fastgl_gather_rows.argtypes = [p, i64, p, i64, i64, i32, p, p]
         L.fastgl_block_validate.argtypes = [p, p, i64, i64, i64, p, ctypes.POINTER(i64), p]
         L.fastgl_last_error.restype = ctypes.c_char_p

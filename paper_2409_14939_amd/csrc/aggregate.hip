@@ -8,8 +8,9 @@
 // of two, 4 to 64) covers G consecutive slices.  A wavefront owns a set of
 // consecutive rows (x one column tile) from start to end, so each output element
 // has a single writer and the summation order is fixed: results do not depend on
-// scheduling.  The row sets come from the plan and carry equal work (edges +
-// rows), and the groups of a wavefront share its edges equally (walk_flat), so
+// scheduling.  The order follows from the block (which rows a wavefront shares out)
+// and the sizes, not from where buffers lie.
+// The row sets come from the plan and carry equal work (edges + rows), and the groups of a wavefront share its edges equally (walk_flat), so
 // skewed degree distributions overload neither a wavefront nor a group.
 // The partial sum lives in registers (the paper keeps it in shared memory on its
 // GPU; with one lane per slice registers serve the same purpose at no traffic).
@@ -45,24 +46,28 @@ constexpr int kReduceBlocks = 1024;   // workgroups for the long rows, whose num
 // that neighbouring rows (which share output cache lines and first-touch source
 // rows) share an L2, while every XCD still samples the whole row range: blocks
 // whose hubs all sit at low ids stay balanced.  The column tiles of a row set
-// sit in neighbouring wavefronts, or (by_tile) as far apart as can be.
+// sit in neighbouring wavefronts, or (TILES: column_tiles) as far apart as can be.
 struct WaveId {
     int64_t w;        // index of the wavefront's first fine row set / P.sets_per_wave
     int tile;         // column tile
 };
 
+template <bool TILES>
 __device__ __forceinline__ WaveId map_wave(const PullParams &P)
 {
     const uint32_t x = blockIdx.x % kXcds, q = blockIdx.x / kXcds;
     const uint64_t lb = ((uint64_t)(q / kXcdRun) * kXcds + x) * kXcdRun + q % kXcdRun;
     const uint64_t v = lb * (kBlock / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     WaveId r;
-    const uint64_t div = P.ntiles > 1 ? __umul64hi(v, P.tile_inv) : v;        // v < 2^34, ntiles < 2^20, nwaves < 2^28: exact
-    if (P.by_tile) {
+    bool by_tile = TILES && P.by_tile;
+    if (TILES && P.hot) by_tile = *P.hot >= P.hot_min;
+    if (by_tile) {
+        const uint64_t div = P.nwaves > 1 ? __umul64hi(v, P.wave_inv) : v;    // v < 2^34, ntiles < 2^20, nwaves < 2^28: exact
         const bool none = div >= (uint32_t)P.ntiles;                            // wavefronts that fill the last workgroups
         r.tile = none ? 0 : (int)div;
         r.w = none ? P.nwaves : (int64_t)(v - div * (uint64_t)P.nwaves);
     } else {
+        const uint64_t div = P.ntiles > 1 ? __umul64hi(v, P.tile_inv) : v;
         r.w = (int64_t)div;
         r.tile = (int)(v - div * (uint32_t)P.ntiles);
     }
@@ -105,7 +110,7 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
     __shared__ Window<DT, VB> windows[WAVE ? 1 : kBlock / kWave];
     const int lane = threadIdx.x & (kWave - 1);
     Window<DT, VB> &win = windows[WAVE ? 0 : threadIdx.x / kWave];
-    const WaveId id = map_wave(P);
+    const WaveId id = map_wave<!WAVE && !BATCH && U == kUnrollWave>(P);
     const int64_t slice = WAVE ? (int64_t)id.tile * kWave + lane : (int64_t)id.tile * P.G + (lane & (P.G - 1));
     const int64_t lane_off = slice_offset<VB>(P, slice);
     const bool active = slice * VB < P.row_bytes;
@@ -245,21 +250,40 @@ static void group_shape(int64_t row_bytes, int vb, int smallest, int *G, int *nt
     *ntiles = (int)ceil_div(slices, g);
 }
 
-// Are rows wider than 32 slices gathered in tiles of 32, all rows of one tile after the other?  The gathers of a pass then
-// come from a table that is so much smaller, and more of its often used rows stay in the caches.  Blocks over all
-// neighbours in power-law graphs, 256 columns, gcn f32, us, whole rows / tiles (table, times a row is read):
-//   656 MB, 9: 762 / 716;  154 MB, 39: 761 / 677;  203 MB, 19: 469 / 446;  298 MB, 9: 416 / 397;  391 MB, 11: 532 / 509;
-//   489 MB, 9: 625 / 620;  801 MB, 7: 817 / 767;  901 MB, 6: 778 / 750;  1.08 GB, 2.6: 487 / 492;  94 MB, 15: 152 / 163
-// Where all rows are read equally often there is less to keep (307 MB, 15: 721 / 721; 819 MB, 25: 3 238 / 3 437), but few
-// graphs are like that.  Not where the columns of long rows ascend (the first of these blocks backward: 416 / 500), nor
-// where tiles would share cache lines (602 columns: 83 / 93).  1 024 row sets keep the wavefronts of a tile many.
+// Are rows wider than 32 slices gathered in column tiles of 32?  The choice decides in which order the edges of a row are
+// added, so it looks at sizes alone.  Not where the columns of long rows ascend, nor where tiles would share cache lines
+// (602 columns: 83 us whole, 93 in tiles).  1 024 row sets keep the wavefronts of a tile many.
 constexpr int kTileLanes = 32;
 
-static bool column_by_column(const PullDesc &d, int64_t row_bytes, int G)
+static bool column_tiles(int64_t num_rows, int64_t num_cols, int64_t nnz, int64_t row_bytes)
 {
-    return G == kWave && d.any_order && row_bytes % (kTileLanes * 16) == 0 && ((uintptr_t)d.in & 127) == 0 &&
-           d.num_cols * row_bytes >= (int64_t)128 << 20 && d.num_cols * (row_bytes / 16) <= (int64_t)UINT32_MAX &&
-           d.nnz >= 5 * d.num_cols && d.nsets >= 1024;
+    return row_bytes > kTileLanes * 16 && row_bytes % (kTileLanes * 16) == 0 &&
+           num_cols * row_bytes >= (int64_t)128 << 20 && num_cols * (row_bytes / 16) <= (int64_t)UINT32_MAX &&
+           nnz >= 5 * num_cols && num_row_sets(num_rows, nnz) >= 1024;
+}
+
+// All rows of one tile after the other: the gathers of a pass come from a table that is so much smaller, and more of its
+// often used rows stay in the caches.  But every pass reads the column ids and their scale factors again, and factors of
+// more than 2^18 columns fall out of L2 in between: then only where columns that are read more than kLongThreshold
+// times have a quarter of the edges, which a plan with the transpose knows (on the device; sums are the same either way).
+// us, whole rows / tiles of a row together / one tile after the other, columns drawn evenly, and in proportion to rank^-0.8
+// and ^-1.1 (12 % to 22 % and 44 % to 60 % of the edges are such columns'):
+//   256 f32 mean  200 MB read 12 times: 336 / 340 / 330, 292 / 290 / 272, 165 / 170 / 154;  600 MB: 979 / 978 / 990, 922 / 911 / 838,
+//                 528 / 529 / 470;  900 MB: 1 526 / 1 525 / 1 497, 1 322 / 1 327 / 1 298, 810 / 812 / 723
+//   256 f32 gcn   200 MB: 359 / 354 / 352, 310 / 301 / 292, 182 / 188 / 175;  600 MB: 1 075 / 1 072 / 1 145, 1 020 / 1 005 / 1 002,
+//                 597 / 598 / 572;  900 MB: 1 638 / 1 636 / 1 771, 1 470 / 1 471 / 1 535, 919 / 923 / 887
+//   512 bf16 gcn  600 MB: 1 073 / 1 097 / 1 146, 1 020 / 1 030 / 1 006, 595 / 608 / 574
+//   1 024 f32 gcn 600 MB: 1 002 / 989 / 1 000, 962 / 930 / 775, 658 / 657 / 523
+// all neighbours in a power-law graph (656 MB read 9 times, 36 %): 256 f32 gcn 820 / 790 / 753, mean 777 / 765 / 690; 512 bf16
+// gcn 880 / 840 / 795; another (557 MB, 6 times, 25 %) 469 / 446 / 436; (608 MB, 9 times, 4 %) 837 / 821 / 873
+constexpr int64_t kScaleInL2 = (int64_t)1 << 18;
+
+static void tile_order(const PullDesc &d, PullParams &P)
+{
+    if ((uintptr_t)d.in & 127) return;                         // tiles would share cache lines: together
+    P.by_tile = !d.col_scale || d.num_cols <= kScaleInL2;
+    P.hot = P.by_tile ? nullptr : d.hot_chunks;
+    P.hot_min = ceil_div(d.nnz, (int64_t)4 * kLongChunk);
 }
 
 // 32 lanes have 8 gathers in flight where there are wavefronts enough to hide the longer way through the code: 2.56 M edges of
@@ -273,7 +297,7 @@ static void launch_rows(const PullParams &P, hipStream_t s)
     const dim3 grid((unsigned)P.num_blocks);
     if (P.G == kWave) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollWave, true, false>), grid, dim3(kBlock), 0, s, P);
     else if (P.G <= kBatchLanes) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollNarrow, false, true>), grid, dim3(kBlock), 0, s, P);
-    else if (P.G == 32 && P.nwaves >= kManyWaves) hipLaunchKernelGGL((k_pull_rows<DT, 16, W, kUnrollWave, false, false>), grid, dim3(kBlock), 0, s, P);
+    else if (P.G == kTileLanes && (P.ntiles > 1 || P.nwaves >= kManyWaves)) hipLaunchKernelGGL((k_pull_rows<DT, 16, W, kUnrollWave, false, false>), grid, dim3(kBlock), 0, s, P);
     else hipLaunchKernelGGL((k_pull_rows<DT, 16, W, kUnroll, false, false>), grid, dim3(kBlock), 0, s, P);
 }
 
@@ -307,6 +331,7 @@ fastgl_status launch_pull(const PullDesc &d, hipStream_t s)
     P.feat = d.feat;
     P.row_mode = d.row_mode;
     P.by_tile = 0;
+    P.hot = nullptr; P.hot_min = 0;
     const int vb = slice_bytes(P.row_bytes);
     int G, ntiles;
     group_shape(P.row_bytes, vb, kUnrollNarrow, &G, &ntiles);   // a group loads as many column ids at a time as it has lanes
@@ -317,10 +342,11 @@ fastgl_status launch_pull(const PullDesc &d, hipStream_t s)
         G = kWave;
         ntiles = (int)ceil_div(ceil_div(P.row_bytes, (int64_t)vb), (int64_t)G);
     }
-    if (column_by_column(d, P.row_bytes, G)) {
+    const bool tiles = d.any_order && column_tiles(d.num_rows, d.num_cols, d.nnz, P.row_bytes);
+    if (tiles) {
         G = kTileLanes;
         ntiles = (int)(P.row_bytes / (kTileLanes * vb));
-        P.by_tile = 1;
+        tile_order(d, P);
     }
     P.G = G; P.ntiles = ntiles;
     P.lg_G = __builtin_ctz((unsigned)G);
@@ -339,14 +365,15 @@ fastgl_status launch_pull(const PullDesc &d, hipStream_t s)
     while (spw >= groups && spw < 8 * groups && d.nsets / (spw * 2) * ntiles >= 16384) spw *= 2;
     P.sets_per_wave = spw;
     P.nwaves = ceil_div(d.nsets, (int64_t)spw);
-    P.tile_inv = tile_inverse(P.by_tile ? P.nwaves : ntiles);
+    P.tile_inv = tile_inverse(ntiles);
+    P.wave_inv = tile_inverse(P.nwaves);
     const bool with_long = d.long_rows != nullptr && d.nnz > kLongThreshold;
     P.long_thr = with_long ? kLongThreshold : INT32_MAX;
     P.long_rows = with_long ? d.long_rows : nullptr;
     P.chunk_ptr = d.chunk_ptr; P.n_long = d.n_long; P.n_chunks = d.n_chunks;
     P.partials = (char *)d.partials;
     P.num_blocks = ceil_div(ceil_div(P.nwaves * ntiles, (int64_t)(kBlock / kWave)), (int64_t)kXcds * kXcdRun) * kXcdRun * kXcds;
-    P.chunk_waves = P.by_tile ? P.nwaves : P.num_blocks * (kBlock / kWave) / ntiles;
+    P.chunk_waves = tiles ? P.nwaves : P.num_blocks * (kBlock / kWave) / ntiles;
     if (P.num_blocks > 0x7FFFFFFFLL) {
         set_error("block too large for one launch (%lld workgroups)", (long long)P.num_blocks);
         return FASTGL_ERR_UNSUPPORTED;
@@ -411,3 +438,11 @@ fastgl_status launch_gather_rows(const void *table, const int64_t *ids, int64_t 
 }
 
 }  // namespace fastgl
+
+extern "C" int32_t fastgl_aggregate_column_tiles(int64_t num_dst, int64_t num_src, int64_t num_edges, int64_t feat, fastgl_dtype dtype)
+{
+    using namespace fastgl;
+    const int64_t row_bytes = feat * (dtype == FASTGL_F32 ? 4 : 2);
+    if (num_dst < 0 || num_src < 0 || num_edges < 0 || feat <= 0 || feat > (int64_t)1 << 24) return 0;
+    return column_tiles(num_dst, num_src, num_edges, row_bytes) ? (int32_t)(row_bytes / (kTileLanes * 16)) : 1;
+}

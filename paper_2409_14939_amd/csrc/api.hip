@@ -153,6 +153,7 @@ fastgl_status aggregate_prepare(bool backward, const int32_t *indptr, const int3
     d.nnz = num_edges;
     d.partials = workspace;
     d.any_order = !backward;
+    d.hot_chunks = !backward && (pl->parts & FASTGL_PLAN_BWD) ? pl->counters + 3 : nullptr;
     if (!backward) {
         d.rowptr = indptr; d.col = indices; d.eid = nullptr;
         d.col_scale = mode == FASTGL_AGG_GCN ? pl->src_rsqrt : nullptr;

@@ -106,6 +106,7 @@ struct PullDesc {
     const int32_t *long_rows, *chunk_ptr, *n_long, *n_chunks;
     void *partials;            // cap_chunks * feat accumulators
     bool any_order;            // columns of a row in any order; false: a transposed block, where they ascend
+    const int32_t *hot_chunks; // chunks of kLongChunk edges of the columns that are read more than kLongThreshold times, or NULL: unknown
     // equal-work row sets
     const int32_t *split;      // [nsets+1]
     int64_t nsets;

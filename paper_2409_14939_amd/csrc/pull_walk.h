@@ -10,8 +10,8 @@
 
 namespace fastgl {
 
-// Row gathers in flight per lane: groups of 16 lanes (and of 32 in small launches), of at most kBatchLanes, and of a
-// whole wavefront (and of 32 lanes in large launches).  A group loads as many column ids at a time (a chunk) as it has
+// Row gathers in flight per lane: groups of 16 lanes (and most of 32), of at most kBatchLanes, and of a whole wavefront (and of
+// 32 lanes in large f32 launches and with column tiles).  A group loads as many column ids at a time (a chunk) as it has
 // lanes, one of at most kBatchLanes lanes only those of the next batch: all neighbours of 65 536 nodes, width 32, forward / backward 96 / 91 us so, 110 / 98 with chunks of two batches.
 // 16 lanes, 2.56 M weighted edges of 64 floats: 108 us, 4 in flight 110, batches of 4 111.
 constexpr int kUnroll = 6;
@@ -122,7 +122,9 @@ struct PullParams {
     int64_t nsets;            // fine row sets
     int64_t nwaves;           // wavefronts per column tile = ceil(nsets / sets_per_wave)
     int32_t ntiles;           // column tiles per row
-    int32_t by_tile;          // all rows of one column tile after the other; 0: the tiles of a row together
+    int32_t by_tile;          // column tiles: all rows of one tile after the other; 0: the tiles of a row together
+    const int32_t *hot;       // not NULL: by tile if *hot >= hot_min
+    int64_t hot_min;
     int32_t G, lg_G;          // lanes per group (power of two), its logarithm
     int32_t unit_shift;       // rows start at multiples of 1 << unit_shift bytes (no more than a slice)
     int32_t sets_per_wave;    // consecutive fine row sets one wavefront takes
@@ -131,7 +133,8 @@ struct PullParams {
     int32_t long_thr;         // rows longer than this are left to the chunk kernels
     int64_t row_bytes;        // bytes of one feature row
     int64_t feat;
-    uint64_t tile_inv;        // ceil(2^64 / ntiles), by_tile: ceil(2^64 / nwaves): division by multiplication (unused for one tile)
+    uint64_t tile_inv;        // ceil(2^64 / ntiles): division by multiplication (unused for one tile)
+    uint64_t wave_inv;        // ceil(2^64 / nwaves)
     int64_t chunk_waves;      // wavefronts per column tile that take chunks of long rows
     int64_t num_blocks;       // launched blocks (multiple of kXcds)
     const int32_t *long_rows, *chunk_ptr, *n_long, *n_chunks;

@@ -8,7 +8,7 @@ import torch
 import blockgen as bg
 import oracle
 from paper_2409_14939_amd import binding as B
-from gpu_util import assert_close, dev_feat, dev_i32, host_feat, make_inputs
+from gpu_util import assert_close, dev_feat, dev_i32, host_feat, make_inputs, read_i32
 from test_gpu_parity import check_block
 
 pytestmark = pytest.mark.gpu
@@ -110,28 +110,69 @@ def test_edge_weight_grad(dtype, feat, edges_per_row):
     assert (np.abs(got - want) <= bound).all()
 
 
+def column_tiles(blk, feat, dtype):
+    return B.lib().fastgl_aggregate_column_tiles(blk.num_dst, blk.num_src, blk.num_edges, feat, B.DTYPES[dtype])
+
+
 @pytest.mark.parametrize("dtype,feat,weighted", [("f32", 256, True), ("f32", 384, False), ("bf16", 1280, True)])
 def test_column_tiles_one_after_the_other(dtype, feat, weighted):
-    """Wide rows read five times each out of a table of 128 MB and more: by column tiles, against the oracle and the same
-    rows at an address that the tiles are not for; rows of none, of a few, of the longest unchunked and of chunked length."""
+    """Wide rows read five times each out of a table of 128 MB and more: by column tiles, against the oracle; the same bits
+    from an address at which the tiles of a row go together; rows of none, of a few, of the longest unchunked and of
+    chunked length."""
     num_src = (128 << 20) // (feat * (4 if dtype == "f32" else 2)) + 1
     rng = np.random.default_rng(feat)
     lengths = np.concatenate([[0, 1, 256, 257, 3000], rng.integers(0, 60, 5 * num_src // 29)])
     blk = block_of(rng.permutation(lengths), num_src, feat)
-    assert blk.num_edges >= 5 * num_src
+    assert column_tiles(blk, feat, dtype) == feat * (4 if dtype == "f32" else 2) // 512
     X = make_inputs(rng, num_src, feat, dtype)
     w = rng.standard_normal(blk.num_edges).astype(np.float32) if weighted else None
     wd = None if w is None else torch.from_numpy(w).cuda()
     ip, ix = dev_i32(blk.indptr), dev_i32(blk.indices)
     aligned, moved = dev_feat(X, dtype), shifted(X, dtype, 2)
-    assert aligned.data_ptr() % 128 == 0
-    tiles, rows = (host_feat(B.fastgl_block_aggregate_fwd(ip, ix, wd, num_src, "gcn", x), dtype) for x in (aligned, moved))
-    assert_close(tiles, oracle.aggregate_fwd(blk.indptr, blk.indices, w, num_src, "gcn", dtype, X), dtype)
-    assert_close(tiles, rows, dtype)
+    assert aligned.data_ptr() % 128 == 0 and moved.data_ptr() % 128 != 0
+    one_by_one, together = (B.fastgl_block_aggregate_fwd(ip, ix, wd, num_src, "gcn", x) for x in (aligned, moved))
+    assert_close(host_feat(one_by_one, dtype), oracle.aggregate_fwd(blk.indptr, blk.indices, w, num_src, "gcn", dtype, X), dtype)
+    assert torch.equal(one_by_one, together)
+
+
+@pytest.mark.parametrize("dtype,feat", [("f32", 256), ("bf16", 512)])
+@pytest.mark.parametrize("hot", [False, True])
+def test_column_tiles_of_more_columns_than_have_their_scale_factors_in_l2(hot, dtype, feat):
+    """One tile after the other where often read columns have a quarter of the edges, which only a plan with the transpose
+    knows, else the tiles of a row together: the same bits, and a sample of rows against sums in fp64."""
+    num_src, num_dst = (1 << 18) + 1, 40000
+    rng = np.random.default_rng(feat + hot)
+    lengths = rng.integers(0, 68, num_dst)
+    lengths[:3] = 0, 256, 1000
+    blk = block_of(lengths, num_src, 3)
+    if hot:
+        blk.indices[::2] = 2500 * rng.integers(0, 100, blk.indices[::2].size)
+    assert column_tiles(blk, feat, dtype) == 2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(feat)
+    X = torch.randn((num_src, feat), generator=g, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    moved = torch.empty(X.numel() + 8, dtype=X.dtype, device="cuda")[8:].reshape(X.shape).copy_(X)
+    ip, ix = dev_i32(blk.indptr), dev_i32(blk.indices)
+    plan = B.fastgl_block_plan_create(ip, ix, num_src)
+    assert (4 * B.lib().fastgl_long_row_chunk() * int(read_i32(plan, plan.export().counters, 4)[3]) >= blk.num_edges) == hot
+    known = B.fastgl_block_aggregate_fwd(ip, ix, None, num_src, "gcn", X, plan=plan)
+    for other in (B.fastgl_block_aggregate_fwd(ip, ix, None, num_src, "gcn", X),
+                  B.fastgl_block_aggregate_fwd(ip, ix, None, num_src, "gcn", moved, plan=plan)):
+        assert torch.equal(known, other)
+    dout = np.bincount(blk.indices, minlength=num_src)
+    for r in [0, 1, 2, 3, 63, 64, 20000, num_dst - 1]:
+        cols = blk.indices[blk.indptr[r]:blk.indptr[r + 1]]
+        scale = 1 / np.sqrt(max(1, cols.size) * dout[cols].astype(np.float64))
+        terms = X[torch.from_numpy(cols.astype(np.int64)).cuda()].double() * torch.from_numpy(scale).cuda()[:, None]
+        want, size = terms.sum(0), terms.abs().sum(0)
+        # f32: weights rounded to fp32, fp64 sums, rounded once; bf16: fp32 products and sums, rounded to 8 bits
+        bound = size * (cols.size + 4) * 2.0 ** -24 + want.abs() * (2.0 ** -23 if dtype == "f32" else 2.0 ** -8)
+        assert ((known[r].double() - want).abs() <= bound).all(), r
 
 
 @pytest.mark.parametrize("dtype,feat,weighted", [("f32", 100, False), ("f32", 125, True), ("bf16", 200, False)])
 def test_many_wavefronts_of_two_groups(dtype, feat, weighted):
-    """Enough rows for the variant with more gathers in flight: rows of none to a few edges and every remainder of a batch."""
+    """Enough rows for the variant with more gathers in flight (f32) and wavefronts of several row sets: rows of none to a
+    few edges and every remainder of a batch."""
     blk = block_of(np.random.default_rng(feat).integers(0, 7, 300000), 5000, feat)
     check_block(blk, "mean", dtype, feat, weighted, True, feat, "many wavefronts")
