@@ -286,9 +286,12 @@ static void tile_order(const PullDesc &d, PullParams &P)
     P.hot_min = ceil_div(d.nnz, (int64_t)4 * kLongChunk);
 }
 
-// 32 lanes have 8 gathers in flight where there are wavefronts enough to hide the longer way through the code: 2.56 M edges of
-// 100 floats, 24 000 wavefronts 211 us with 6, 208 with 8 (gcn 218 and 217); 94 000 edges of 256 bf16, 6 144 wavefronts
-// 13.7 and 15.9.
+// 32 lanes have 8 gathers in flight where there are wavefronts enough to hide the longer way through the code, f32.  us, rows
+// of 2 to 8 edges (twice as many columns as rows), 6 in flight / 8, 100 columns sum, 100 gcn, 128 weighted:
+//   16 000 rows (6 000 wavefronts) 9.4 / 10.7, 11.1 / 11.6, 11.1 / 11.7;  64 000 (12 000) 29.4 / 29.9, 31.5 / 32.3, 31.7 / 32.0;
+//   128 000 (24 000, as the larger ones) 55.7 / 55.2, 59.9 / 59.9, 56.6 / 56.6;  256 000 110.4 / 109.8, 122.3 / 121.2, 113.9 / 112.6;
+//   512 000 216.2 / 215.7, 247.2 / 247.7, 221.7 / 221.0;  2.56 M edges of a products-shaped block 200.0 / 197.6, 218.0 / 216.4
+// bf16 gains nothing on average and loses up to 1.2 % with scale factors (256 columns, 512 000 rows: 252.8 / 255.7).
 constexpr int64_t kManyWaves = 16384;
 
 template <int DT, int VB, int W>
@@ -297,7 +300,7 @@ static void launch_rows(const PullParams &P, hipStream_t s)
     const dim3 grid((unsigned)P.num_blocks);
     if (P.G == kWave) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollWave, true, false>), grid, dim3(kBlock), 0, s, P);
     else if (P.G <= kBatchLanes) hipLaunchKernelGGL((k_pull_rows<DT, VB, W, kUnrollNarrow, false, true>), grid, dim3(kBlock), 0, s, P);
-    else if (P.G == kTileLanes && (P.ntiles > 1 || P.nwaves >= kManyWaves)) hipLaunchKernelGGL((k_pull_rows<DT, 16, W, kUnrollWave, false, false>), grid, dim3(kBlock), 0, s, P);
+    else if (P.G == kTileLanes && (P.ntiles > 1 || (DT == FASTGL_F32 && P.nwaves >= kManyWaves))) hipLaunchKernelGGL((k_pull_rows<DT, 16, W, kUnrollWave, false, false>), grid, dim3(kBlock), 0, s, P);
     else hipLaunchKernelGGL((k_pull_rows<DT, 16, W, kUnroll, false, false>), grid, dim3(kBlock), 0, s, P);
 }
 
