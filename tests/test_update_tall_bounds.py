@@ -4,12 +4,73 @@ Results: a tile's rows past the last one are not masked, only dropped that way; 
 survive, for any remainder of rows and columns and either element size.  Column operand (W of the forward pass): rows
 past the last one are not masked either; every one of their elements must come back as 0.  Rows loaded eight elements
 at a time (load_at, load_oct, buffer_oct; the small tiles have no buffer around them): every load lies inside its row,
-or, for rows of odd length in bf16, in the aligned dword that holds the row's last element.  The model mirrors the kernel's index arithmetic; it has to be changed with it."""
+or, for rows of odd length in bf16, in the aligned dword that holds the row's last element.  Look-ahead: which chunks of A
+and stages of B the loop asks for, and that it multiplies the right ones.  The model mirrors the kernel's index arithmetic
+and takes its constants from the source; it has to be changed with it."""
+import os
 import random
+import re
 
 import numpy as np
 
-TALL_ROWS, FULL = 128, 240
+SOURCE = open(os.path.join(os.path.dirname(__file__), "..", "paper_2409_14939_amd", "csrc", "update_rows.hip")).read()
+
+
+def constant(name):
+    text = re.search(rf"constexpr \w+ {name} = ([^;]+);", SOURCE).group(1)
+    return eval(re.sub(r"\(int64_t\)|u\b", "", re.sub(r"(0x[0-9A-Fa-f]+)u", r"\1", text)))
+
+
+TALL_ROWS, FULL = constant("kTallRows"), constant("kFull")
+NOWHERE, MAX_LD, STAGE_ELEMS = constant("kNowhere"), constant("kMaxTallLd"), constant("kStageElems")
+# the lines of the kernel that `fetches` repeats
+LOOP = ("KS = NT < 64 ? 64 : kStageElems / NT", "AHEAD = !BF16 && (NTILES == 4 || (GATE && NTILES == 8)) ? 1 : 2;",
+        "TURN = AHEAD == 1 && KS <= 32 ? 32 : 64;", "load_b(0);", "load_a(i, 32 * i);", "stage_b(0, 0);", "int lk = KS;",
+        "for (int k0 = 0; k0 < Kc; k0 += TURN) {", "for (int step = 0; step < TURN / 16; ++step) {",
+        "kc = k0 + 32 * cc, from = cc % AHEAD;", "if (step > 0 && k0 + 16 * step >= Kc) break;", "if (16 * step % KS == 0) {",
+        "stage_b(cur ^ 1, lk);", "lk += KS;", "if (s == 0) load_a(from, kc + 32 * AHEAD);", "slot = 16 * step % KS / 8 + h;",
+        "if (16 * (step + 1) % KS == 0) {", "row = arow + (k0 < Kc ? 0u : kNowhere);",
+        "buffer_cols<VB>(rb, (uint32_t)(k0 + 8 * bs) * ldb + bcol, ldb, bcols);")
+LIMIT = "(b_col && (g.Kc + 64) * g.ldb >= (int64_t)1 << 29)"
+
+
+def fetches(nt, bf16, gate, Kc):
+    """(first indices of the chunks of A, first indices of the stages of B, indices of a stage) that the loop asks for; asserts
+    that a step of 16 is multiplied out of the chunk and the stage that hold it."""
+    ks = 64 if 32 * nt < 64 else STAGE_ELEMS // (32 * nt)
+    ahead = 1 if not bf16 and (nt == 4 or (gate and nt == 8)) else 2
+    turn = 32 if ahead == 1 and ks <= 32 else 64
+    a, b = [32 * i for i in range(ahead)], [0, ks]
+    chunk, lds, loaded, cur, multiplied = list(a), [0, None], ks, 0, []
+    for k0 in range(0, Kc, turn):
+        for step in range(turn // 16):
+            kc = k0 + 32 * (step >> 1)
+            src = (step >> 1) % ahead
+            if step > 0 and k0 + 16 * step >= Kc:
+                break
+            if step & 1 == 0:
+                taken = chunk[src]
+            if 16 * step % ks == 0:
+                lds[cur ^ 1] = loaded
+                loaded += ks
+                b.append(loaded)
+            if step & 1 == 0:
+                chunk[src] = kc + 32 * ahead
+                a.append(chunk[src])
+            assert taken == kc and lds[cur] + 16 * step % ks == k0 + 16 * step
+            multiplied.append(k0 + 16 * step)
+            if 16 * (step + 1) % ks == 0:
+                cur ^= 1
+    assert multiplied == list(range(0, Kc, 16))
+    return a, b, ks
+
+
+FORMS = [(nt, bf16, gate) for nt in (1, 2, 4, 8) for bf16 in (False, True) for gate in (False, True)]
+
+
+def rows_ahead(Kc):
+    """Rows of a column operand past its last one that the loop asks for, at most."""
+    return max(max(b) + ks for b, ks in (fetches(*f, Kc)[1:] for f in FORMS)) - Kc
 
 
 def tall_tiles(M, N, b_col):
@@ -46,8 +107,8 @@ def stores_in_bounds(M, N, eb, b_col, size=exact):
 
 
 def column_operand_ends(K, N, eb, size=exact):
-    """Elements of the rows K, K + 1, ... that a stage of 64 contracted indices and the one ahead of it may ask for."""
-    row, col = np.meshgrid(np.arange(K, K + 128), np.arange(256), indexing="ij")
+    """Elements of the rows K, K + 1, ... that the loop asks for: all at or past the buffer's end."""
+    row, col = np.meshgrid(np.arange(K, K + rows_ahead(K)), np.arange(256), indexing="ij")
     return not ((row * N + col) * eb < size(K * N * eb)).any()
 
 
@@ -113,11 +174,30 @@ def test_offsets_inside_a_tile_fit_32_bits():
     assert 255 * (1 << 21) * 4 + (1 << 21) * 4 - 1 < 1 << 31
 
 
+def test_the_kernel_has_the_loop_that_the_model_repeats():
+    for line in LOOP + (LIMIT,):
+        assert line in SOURCE, line
+
+
+def test_the_loop_multiplies_every_step_out_of_what_it_loaded():
+    for form in FORMS:
+        for Kc in list(range(1, 200)) + [256, 601, 602, 1024]:
+            fetches(*form, Kc)
+
+
 def test_look_ahead_past_the_last_index_wraps_around_nowhere():
-    """Chunks of A past the end start 2^31 bytes further on; a stage of B and the two after it ask for up to 190 rows past
-    the last one.  Both have to stay between every buffer's end (at most 2^31 - 1 bytes) and 2^32."""
-    far = 127 * (1 << 21) * 4 + (1 << 21) * 4 + 15
-    assert (1 << 31) + far < 1 << 32
-    for ldb in (1, 3, 256, 1 << 21):
-        Kc = ((1 << 29) - 1) // ldb - 64                      # the longest that the tall tiles take
-        assert (Kc + 64) * ldb < 1 << 29 and (Kc + 191) * ldb * 4 + ldb * 4 < 1 << 32
+    """Chunks of A past the end start at kNowhere, stages of B past the end behind the last row: both have to stay between
+    every buffer's end (at most 2^31 - 1 bytes) and 2^32, for the longest rows and the largest column operands that the
+    tall tiles take."""
+    size = (1 << 31) - 1
+    for eb in (2, 4):
+        last = (TALL_ROWS - 1) * MAX_LD * eb + MAX_LD * eb + 15          # the row's last element, the load that holds it
+        assert NOWHERE > size and NOWHERE + last < 1 << 32
+    most = max(rows_ahead(Kc) for Kc in range(1, 300))
+    assert 64 < most <= 192                                              # the model sees more than one stage ahead
+    for ldb in (1, 3, 256, 257, MAX_LD):
+        Kc = ((1 << 29) - 1) // ldb - 64                                 # the most that LIMIT lets through
+        if Kc < 1:
+            continue
+        assert (Kc + 64) * ldb < 1 << 29 <= (Kc + 65) * ldb
+        assert Kc * ldb * 4 <= size and (Kc + most) * ldb * 4 + 8 < 1 << 32
