@@ -125,6 +125,26 @@ def test_idmap_random_sweep():
 def test_idmap_ends_inside_a_group_of_four_positions(n):
     rng = np.random.default_rng(n)
     for n_dst in (0, 1, n // 2, n - 1):
-        for span in (n, 3 * n):                    # many and few repeats, of destinations and of neighbours
+        for span in (n, 3 * n):                    # many and few repeats, of neighbours and of destinations among them
             dst = rng.permutation(span)[:n_dst]
             check(dst, rng.integers(0, span, n - n_dst), "group of four")
+
+
+@pytest.mark.parametrize("n", [2, 3, 5, 1023, 1024, 1025, 2049, 4097])
+@pytest.mark.parametrize("repeats", [1, 2, 1000])
+def test_idmap_counts_repeated_destinations_at_every_remainder(n, repeats):
+    """Destinations do not look whether their slot is taken, and the smallest position marks those it displaces: repeats in
+    the last group of four, over block edges and everywhere."""
+    rng = np.random.default_rng(n + repeats)
+    for n_dst in {n, n - 1, n // 2 + 1}:
+        dst = rng.permutation(3 * n)[:n_dst]
+        if n_dst < 2:
+            continue
+        at = rng.permutation(n_dst - 1)[:repeats] + 1
+        dst[at] = dst[0]
+        dst[-1] = dst[-2]
+        again = n_dst - np.unique(dst).size
+        for mode in ("ordered", "fused"):
+            print(f"case repeated destinations n={n} n_dst={n_dst} again={again} {mode}", flush=True)
+            _, _, _, bad = run(dst, rng.integers(0, 3 * n, n - n_dst), mode)
+            assert again <= bad <= n_dst
