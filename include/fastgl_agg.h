@@ -78,8 +78,8 @@ enum {
                                device memory, so without the hint every forward pass has to launch the
                                long-row reduction kernel just to find that it has nothing to do; with
                                it that launch is skipped.  Only speed depends on the hint: a row that
-                               is longer after all is still aggregated correctly, by one lane group
-                               alone.  The backward pass (rows = sources) is not affected. */
+                               is longer after all is still aggregated correctly, by one wavefront
+                               (two or more where rows are wider than 1 KB) alone.  The backward pass (rows = sources) is not affected. */
 };
 
 /* Opaque host-side handle; points into the caller's device buffer. */

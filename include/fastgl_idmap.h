@@ -49,7 +49,8 @@ typedef enum { FASTGL_IDMAP_ORDERED = 0, FASTGL_IDMAP_FUSED = 1 } fastgl_idmap_m
 
 /* Entries of 16 bytes that a workspace for n_ids = n_dst + n_nbr global IDs has
  * room for: 1.5 per input ID (at least 1024).  The table has at least as many
- * slots (32 bits each, four per input ID).  At most n_ids keys ever enter it, so
+ * slots (32 bits each): four per input ID for up to 2^28 IDs, beyond that as many
+ * as entries.  At most n_ids keys ever enter it, so
  * it keeps empty slots and linear probing always ends. 0 if n_ids is negative
  * or too large. */
 int64_t fastgl_idmap_table_slots(int64_t n_ids);

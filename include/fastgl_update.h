@@ -79,7 +79,7 @@ fastgl_status fastgl_update_bwd_bf16(const uint16_t *H, const uint16_t *W, const
                                      void *workspace, size_t workspace_bytes, void *stream);
 
 /* One layer in one call: aggregation (Eq. 1) followed by the update (Eq. 2),
- *   H = aggregate(X)        [num_dst, K]   exactly what fastgl_block_aggregate_fwd writes
+ *   H = aggregate(X)        [num_dst, K]   as fastgl_block_aggregate_fwd writes it
  *   Y = act(H W + bias)     [num_dst, N]
  * The graph arguments, edge_w, mode, plan and workspace are those of
  * fastgl_block_aggregate_fwd with feat = K (workspace >= fastgl_block_workspace_bytes);
@@ -88,8 +88,11 @@ fastgl_status fastgl_update_bwd_bf16(const uint16_t *H, const uint16_t *W, const
  * For a narrow layer - fastgl_layer_fwd_fuses(K, N, dtype) != 0: fp32, K a multiple of 4 and at
  * most 256, N at most 64, X and H 16-byte aligned; the class-score layer of a sampled GCN - both
  * steps run in ONE kernel and the aggregated rows do not travel through memory: each is rounded to
- * fp32 once, as the separate call would store it, and multiplied out of on-chip memory with fp32
- * multiply-adds in ascending k (a chain of K + 1 roundings per element of Y).  H may then be NULL
+ * fp32 once and multiplied out of on-chip memory with fp32 multiply-adds (four chains over a quarter of
+ * the k each, ascending, and their sum: at most K + 1 roundings per element of Y).  A row's terms are
+ * added in fp64 in the order of its edges; the separate call may add them in another order (narrow rows
+ * and column tiles in parts, long rows in chunks), so that H may differ from its result by the error
+ * of an fp64 sum, rounded to fp32.  H may then be NULL
  * (inference); when given it is written as a by-product for the backward pass.  Every row is
  * walked by one wavefront whatever its length: meant for sampled layers, whose rows are short.
  * Any other shape runs the two kernels of the separate calls back to back and needs H. */

@@ -99,3 +99,25 @@ def test_layer_fused_equals_separate_calls_in_H_and_full_size_output_layer():
     H2 = B.fastgl_block_aggregate_fwd(ip, ix, None, blk.num_src, "gcn", dev(X))
     torch.cuda.synchronize()
     assert torch.equal(Hd.view(torch.int32), H2.view(torch.int32))
+
+
+@pytest.mark.parametrize("K", [4, 32, 64, 100, 128])
+@pytest.mark.parametrize("mode,weighted", [("gcn", True), ("sum", False)])
+def test_fused_H_of_narrow_rows_against_the_aggregation_call(K, mode, weighted):
+    """Rows that several lane groups of the aggregation call share, and rows in chunks: it adds their terms in another order,
+    so both are one fp64 sum of the same fp32-weighted terms, rounded once."""
+    blk = small_block(K, nd=300, ns=900, hubs=5)
+    rng = np.random.default_rng(K)
+    X = bg.features_f32(rng, blk.num_src, K)
+    ew = rng.standard_normal(blk.num_edges).astype(np.float32) if weighted else None
+    W = rng.standard_normal((K, 16)).astype(np.float32)
+    ip, ix = dev_i32(blk.indptr), dev_i32(blk.indices)
+    H, _ = B.fastgl_layer_fwd(ip, ix, dev(ew), blk.num_src, mode, dev(X), dev(W), None, False)
+    H2 = B.fastgl_block_aggregate_fwd(ip, ix, dev(ew), blk.num_src, mode, dev(X)).cpu().numpy()
+    H = H.cpu().numpy()
+    terms = oracle.aggregate_fwd(blk.indptr, blk.indices, None if ew is None else np.abs(ew), blk.num_src, mode, "f32", np.abs(X))
+    longest = int(np.diff(blk.indptr).max())
+    assert longest > 256
+    # an fp64 sum of n terms in any order is off by at most n 2^-53 sum|t|, and is rounded to fp32 (half a unit, 2^-24)
+    bound = 2 * (2.0 ** -24 * np.maximum(np.abs(H), np.abs(H2)).astype(np.float64) + (longest + 4) * 2.0 ** -53 * terms) + 2.0 ** -148
+    assert (np.abs(H.astype(np.float64) - H2) <= bound).all()
