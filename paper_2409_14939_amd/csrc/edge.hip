@@ -7,6 +7,13 @@
 // per row, so the degree distribution does not matter: a group of 2^k lanes covers the row pieces of
 // one edge, several edges are in flight per group, and the lanes' partial dot products are added
 // with cross-lane reads.  The destination of every edge comes from a small expansion pass.
+// Pieces are of 16 bytes, of narrower rows the largest power of two that fits, of rows of any length and alignment; the groups
+// of a workgroup take neighbouring batches of edges, so that what they load of edge numbers and store lies together.
+// 2.56 M edges, us with the expansion pass; pieces of 16 bytes or one element and all edges of a group in a row -> pieces of
+// any size -> neighbouring batches (before that: element by element where a row is no whole number of pieces):
+//   f32   2 columns (98) 61 -> 50 -> 43;  3 (78) 78 -> 70 -> 50;  5 (76) 82 -> 82 -> 59;  9 (93) 110 -> 110 -> 67;
+//         13 (96) 122 -> 122 -> 75;  33 (299) 127 -> 127 -> 121;  64 (140) 140 -> 140 -> 130;  256 (582) 582 -> 582 -> 528
+//   bf16  4 (98) 72 -> 50 -> 43;  7 (66) 66 -> 73 -> 54;  9 (69) 78 -> 78 -> 58;  25 (105) 115 -> 115 -> 76;  100 (156) 152 -> 152 -> 140
 //
 // Softmax: a group of 8, 32 or 64 lanes (by the block's mean row length) walks one destination row
 // three times (maximum, sum of exponentials, write).  Rows longer than kLongRow are taken by whole workgroups of the
@@ -80,33 +87,41 @@ __device__ __forceinline__ ACC reduce4(const ACC (&v)[4], int l, int lanes, int 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// Dot product of one piece (PIECE bytes at byte offset `off` of both rows; 16 bytes or one element), which needs no more
-// alignment than an element.  RAGGED: without its first `skip` elements.
+// Dot product of one piece (PIECE bytes at byte offset `off` of both rows; a power of two, at least an element), which needs
+// no more alignment than an element.  RAGGED: without its first `skip` elements.
 template <bool BF16, int PIECE, bool RAGGED, typename ACC>
 __device__ __forceinline__ ACC piece_dot(const char *__restrict__ x, const char *__restrict__ g, int64_t off, int skip)
 {
     ACC s = 0;
-    if constexpr (PIECE == 16) {
-        using u32x4 = typename Words<BF16 ? 2 : 4>::x4;
-        const u32x4 a = *reinterpret_cast<const u32x4 *>(x + off), b = *reinterpret_cast<const u32x4 *>(g + off);
+    if constexpr (PIECE >= 4) {
+        using W = Words<BF16 ? 2 : 4>;
+        using Piece = typename std::conditional<PIECE == 16, typename W::x4,
+                                                typename std::conditional<PIECE == 8, typename W::x2, typename W::x1>::type>::type;
+        const Piece a = *reinterpret_cast<const Piece *>(x + off), b = *reinterpret_cast<const Piece *>(g + off);
         auto add = [&](int e, float u, float v) {
             const ACC t = (ACC)u * (ACC)v;
             s += !RAGGED || e >= skip ? t : (ACC)0;
         };
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if constexpr (BF16) {
-                add(2 * i, bf16_lo(a[i]), bf16_lo(b[i]));
-                add(2 * i + 1, bf16_hi(a[i]), bf16_hi(b[i]));
+        for (int i = 0; i < PIECE / 4; ++i) {
+            uint32_t p, q;
+            if constexpr (PIECE > 4) {
+                p = a[i];
+                q = b[i];
             } else {
-                add(i, __uint_as_float(a[i]), __uint_as_float(b[i]));
+                p = a;
+                q = b;
+            }
+            if constexpr (BF16) {
+                add(2 * i, bf16_lo(p), bf16_lo(q));
+                add(2 * i + 1, bf16_hi(p), bf16_hi(q));
+            } else {
+                add(i, __uint_as_float(p), __uint_as_float(q));
             }
         }
-    } else if constexpr (BF16) {
+    } else {
         const uint32_t a = *reinterpret_cast<const uint16_t *>(x + off), b = *reinterpret_cast<const uint16_t *>(g + off);
         s = (ACC)bf16_lo(a) * (ACC)bf16_lo(b);
-    } else {
-        s = (ACC)(*reinterpret_cast<const float *>(x + off)) * (ACC)(*reinterpret_cast<const float *>(g + off));
     }
     return s;
 }
@@ -153,28 +168,28 @@ __global__ __launch_bounds__(256) void k_edge_dot(const DotArgs a)
     const int lanes = a.lanes;
     const int groups_per_block = 256 / lanes;
     const int grp = threadIdx.x / lanes, l = threadIdx.x % lanes;
-    const int group_edges = kEdgeUnroll * a.steps;
-    const int64_t block_first = (int64_t)blockIdx.x * groups_per_block * group_edges;
+    const int step_edges = groups_per_block * kEdgeUnroll, block_edges = step_edges * a.steps;
+    const int64_t block_first = (int64_t)blockIdx.x * block_edges;
     if constexpr (STAGED) {
-        for (int i = threadIdx.x; i < groups_per_block * group_edges; i += 256) {
+        for (int i = threadIdx.x; i < block_edges; i += 256) {
             const int64_t e = block_first + i < a.E ? block_first + i : a.E - 1;   // a clamped edge is computed and dropped
             row_s[i] = a.edge_row[e];
             col_s[i] = a.indices[e];
         }
         __syncthreads();
     }
-    // a group takes a.steps batches of kEdgeUnroll consecutive edges; without staging the row and column of the
-    // next batch's edges are fetched while the current batch's rows are in flight
-    const int64_t first = block_first + grp * group_edges;
+    // a group takes a.steps batches of kEdgeUnroll consecutive edges, next to those of its neighbours; without staging the
+    // row and column of the next batch's edges are fetched while the current batch's rows are in flight
+    const int64_t first = block_first + grp * kEdgeUnroll;
     int32_t u[kEdgeUnroll], v[kEdgeUnroll], un[kEdgeUnroll], vn[kEdgeUnroll];
     auto numbers = [&](int step) {
 #pragma unroll
         for (int k = 0; k < kEdgeUnroll; ++k) {
             if constexpr (STAGED) {
-                un[k] = row_s[grp * group_edges + step * kEdgeUnroll + k];
-                vn[k] = col_s[grp * group_edges + step * kEdgeUnroll + k];
+                un[k] = row_s[step * step_edges + grp * kEdgeUnroll + k];
+                vn[k] = col_s[step * step_edges + grp * kEdgeUnroll + k];
             } else {
-                const int64_t at = first + step * kEdgeUnroll + k, e = at < a.E ? at : a.E - 1;
+                const int64_t at = first + step * step_edges + k, e = at < a.E ? at : a.E - 1;
                 un[k] = a.edge_row[e];
                 vn[k] = a.indices[e];
             }
@@ -182,7 +197,7 @@ __global__ __launch_bounds__(256) void k_edge_dot(const DotArgs a)
     };
     numbers(0);
     for (int step = 0; step < a.steps; ++step) {
-        const int64_t e0 = first + (int64_t)step * kEdgeUnroll;
+        const int64_t e0 = first + step * step_edges;
         if (e0 >= a.E) break;                                        // uniform over the group
 #pragma unroll
         for (int k = 0; k < kEdgeUnroll; ++k) {
@@ -556,7 +571,9 @@ fastgl_status fastgl_edge_weight_grad(const int32_t *indptr, const int32_t *indi
     a.src_scale = src_scale; a.grad_w = grad_w;
     a.E = num_edges; a.row_bytes = feat * elem;
     a.mode = mode == FASTGL_AGG_MEAN ? 1 : (mode == FASTGL_AGG_GCN ? 2 : 0);
-    const int piece = a.row_bytes >= 16 ? 16 : (int)elem;      // of rows of any length and alignment (piece_dot)
+    // of rows of any length and alignment (piece_dot): as much as a row has, up to 16 bytes
+    int piece = 16;
+    while (piece > a.row_bytes) piece /= 2;
     a.pieces = (int)ceil_div(a.row_bytes, (int64_t)piece);
     a.skip = (int)((a.pieces * (int64_t)piece - a.row_bytes) / elem);
     a.lanes = 1;
@@ -570,9 +587,18 @@ fastgl_status fastgl_edge_weight_grad(const int32_t *indptr, const int32_t *indi
                        num_edges, (int32_t *)a.edge_row);
     FASTGL_LAUNCH_CHECK("fastgl_edge_weight_grad (edge rows)");
     const bool bf = dtype == FASTGL_BF16;
-    if (piece == 16 && a.skip) bf ? launch_dot<true, 16, true>(a, s) : launch_dot<false, 16, true>(a, s);
-    else if (piece == 16) bf ? launch_dot<true, 16, false>(a, s) : launch_dot<false, 16, false>(a, s);
-    else bf ? launch_dot<true, 2, false>(a, s) : launch_dot<false, 4, false>(a, s);
+    auto go = [&](auto size) {
+        constexpr int P = decltype(size)::value;
+        if (bf) a.skip ? launch_dot<true, P, true>(a, s) : launch_dot<true, P, false>(a, s);
+        else if constexpr (P > 4) a.skip ? launch_dot<false, P, true>(a, s) : launch_dot<false, P, false>(a, s);
+        else if constexpr (P == 4) launch_dot<false, 4, false>(a, s);
+    };
+    switch (piece) {
+    case 16: go(std::integral_constant<int, 16>()); break;
+    case 8: go(std::integral_constant<int, 8>()); break;
+    case 4: go(std::integral_constant<int, 4>()); break;
+    default: launch_dot<true, 2, false>(a, s); break;
+    }
     FASTGL_LAUNCH_CHECK("fastgl_edge_weight_grad");
     return FASTGL_OK;
 }

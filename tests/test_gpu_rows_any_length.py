@@ -93,21 +93,32 @@ def test_copies(dtype, feat, by):
     assert (room[:64 + by] == 7).all() and (room[-64:] == 7).all()
 
 
-@pytest.mark.parametrize("dtype,feat", [(d, f) for d in FEATS for f in FEATS[d]])
-@pytest.mark.parametrize("edges_per_row", [2.0, 300.0])
-def test_edge_weight_grad(dtype, feat, edges_per_row):
+def check_edge_weight_grad(dtype, feat, edges_per_row, on_device):
     blk = bg.random_block(np.random.default_rng(feat), 140, 300, edges_per_row, empty_frac=0.2)
     rng = np.random.default_rng(feat)
     X, G = make_inputs(rng, blk.num_src, feat, dtype), make_inputs(rng, blk.num_dst, feat, dtype)
     x, g = (a.astype(np.float64) if dtype == "f32" else bg.bf16_bits_to_f32(a).astype(np.float64) for a in (X, G))
-    got = B.fastgl_edge_weight_grad(dev_i32(blk.indptr), dev_i32(blk.indices), blk.num_src, "sum", dev_feat(X, dtype),
-                                    dev_feat(G, dtype)).cpu().numpy()
+    got = B.fastgl_edge_weight_grad(dev_i32(blk.indptr), dev_i32(blk.indices), blk.num_src, "sum", on_device(X, dtype),
+                                    on_device(G, dtype)).cpu().numpy()
     rows = np.repeat(np.arange(blk.num_dst), np.diff(blk.indptr))
     terms = np.abs(g[rows] * x[blk.indices]).sum(1)
     want = (g[rows] * x[blk.indices]).sum(1)
     # fp64 sums rounded once; bf16: products exact, a chain of at most feat fp32 additions
     bound = 2.0 ** -24 * np.abs(want) + (feat + 2) * (2.0 ** -52 if dtype == "f32" else 2.0 ** -24) * terms
     assert (np.abs(got - want) <= bound).all()
+
+
+@pytest.mark.parametrize("dtype,feat", [(d, f) for d in FEATS for f in FEATS[d]])
+@pytest.mark.parametrize("edges_per_row", [2.0, 300.0])
+def test_edge_weight_grad(dtype, feat, edges_per_row):
+    check_edge_weight_grad(dtype, feat, edges_per_row, dev_feat)
+
+
+# rows of up to two pieces of every size, whole and ragged, at every address in a dword and just past aligned ones
+@pytest.mark.parametrize("dtype,feat", [("f32", f) for f in range(1, 9)] + [("bf16", f) for f in range(1, 17)])
+def test_edge_weight_grad_of_narrow_rows(dtype, feat):
+    for by in (0, 1, 3):
+        check_edge_weight_grad(dtype, feat, 7.0, lambda a, t: shifted(a, t, by))
 
 
 def column_tiles(blk, feat, dtype):
