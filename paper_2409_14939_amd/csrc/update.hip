@@ -514,13 +514,18 @@ __global__ __launch_bounds__(256) void k_update_reduce(const float *__restrict__
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) s += (double)v[u];
         }
-        if (k < hi) {
-            float v[kAhead];
+        // what is left, with as many loads as that takes and not 16 (few rows have a slab or two to a range)
+        auto rest = [&](auto count) {
+            constexpr int n = decltype(count)::value;
+            float v[n];
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) v[u] = q[(k + u < hi ? k + u : hi - 1) * stride];
+            for (int u = 0; u < n; ++u) v[u] = q[(k + u < hi ? k + u : hi - 1) * stride];
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) s += k + u < hi ? (double)v[u] : 0.0;
-        }
+            for (int u = 0; u < n; ++u) s += k + u < hi ? (double)v[u] : 0.0;
+        };
+        if (hi - k > 4) rest(std::integral_constant<int, kAhead>());
+        else if (hi - k > 1) rest(std::integral_constant<int, 4>());
+        else if (hi > k) rest(std::integral_constant<int, 1>());
     }
     partial[pt][el] = s;
     __syncthreads();
