@@ -393,6 +393,12 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES <= 4 && GATE && !BF16) 
     // Contracted indices per turn of the loop: no more than chunks and stages need (gated dH M = 512 K, 256 -> 100: 310 us
     // with 32, 323 with 64).
     constexpr int TURN = AHEAD == 1 && KS <= 32 ? 32 : 64;
+    // The turns before the last one are a loop of their own, without the questions where the range ends, and the last one stands
+    // behind it.  us, the questions in every turn / so, fp32:  Y 30 000 rows, 602 -> 256: 59.3 / 53.5, 200 000, 33 -> 57: 22.4 / 20.0;
+    // dH 45 000, 32 -> 300: 23.4 / 19.1, gated 26.7 / 24.6;  bf16:  Y 400 000, 99 -> 131: 125 / 101, 256 -> 47: 70 / 62, gated dH 87 000
+    // rows of 256: 44.6 / 39.7 (worst: 400 000, 100 <- 256 71.6 / 75.4).  Not for the fp32 forms that hold most registers:
+    // Y 400 000, 256 -> 256: 305 / 339, gated dH 131 -> 99: 176 / 199.
+    constexpr bool PLAIN = BF16 || !((NTILES == 8 && BCOL && !GATE) || (NTILES == 4 && GATE));
     Oct<BF16> ar[AHEAD][2], gr[AHEAD][GATE ? 2 : 1];
     auto load_a = [&](int to, int k0) {                       // this lane's octets of the chunk: indices k0 + 16 s + 8 h .. + 7
         const uint32_t row = arow + (k0 < Kc ? 0u : kNowhere);        // chunks past the end touch no memory
@@ -468,51 +474,18 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES <= 4 && GATE && !BF16) 
     // loads of the one after it are issued; then this one is multiplied.  Loads of B and A are issued in the
     // order in which they are waited for.
     Planes<BF16> fa[2];
-    for (int k0 = 0; k0 < Kc; k0 += TURN) {
-#pragma unroll
-        for (int step = 0; step < TURN / 16; ++step) {        // 16 contracted indices
-            const int cc = step >> 1, s = step & 1, kc = k0 + 32 * cc, from = cc % AHEAD;
-            if (step > 0 && k0 + 16 * step >= Kc) break;
-            if (s == 0) {
-                if constexpr (GATE)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) gate_oct(ar[from][i], gr[from][i]);
-                if (kc + 32 > Kc)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) settle<VA>(ar[from][i], kc + 16 * i + 8 * h, Kc);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) to_planes(ar[from][i], fa[i]);
-            }
-            if (16 * step % KS == 0) {
-                stage_b(cur ^ 1, lk);
-                lk += KS;
-                load_b(lk);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (s == 0) load_a(from, kc + 32 * AHEAD);
-            __builtin_amdgcn_sched_barrier(0);
-            const int slot = 16 * step % KS / 8 + h;
-            Planes<BF16> fb[2];
-#pragma unroll
-            for (int p = 0; p < PL; ++p) fb[0].p[p] = lds[cur][p][slot][l32];
-#pragma unroll
-            for (int j = 0; j < NTILES; ++j) {                // the next tile is read while this one is multiplied
-                if (j + 1 < NTILES)
-#pragma unroll
-                    for (int p = 0; p < PL; ++p) fb[(j + 1) & 1].p[p] = lds[cur][p][slot][32 * (j + 1) + l32];
-                mma<BF16>(fa[s], fb[j & 1], acc[j]);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x100, PL, 0);
-#pragma unroll
-            for (int j = 0; j < NTILES; ++j) {
-                if (j + 1 < NTILES) __builtin_amdgcn_sched_group_barrier(0x100, PL, 0);    // LDS reads
-                __builtin_amdgcn_sched_group_barrier(0x008, BF16 ? 1 : 6, 0);              // matrix instructions
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if (16 * (step + 1) % KS == 0) {
-                __syncthreads();
-                cur ^= 1;
-            }
+    if constexpr (PLAIN) {
+        auto turn = [&](auto last, int k0) {
+            constexpr bool LAST = decltype(last)::value;
+#include "update_tall_turn.inc"
+        };
+        int k0 = 0;
+        for (; k0 + TURN < Kc; k0 += TURN) turn(std::false_type(), k0);
+        turn(std::true_type(), k0);
+    } else {
+        constexpr bool LAST = true;
+        for (int k0 = 0; k0 < Kc; k0 += TURN) {
+#include "update_tall_turn.inc"
         }
     }
 

@@ -13,7 +13,8 @@ import re
 
 import numpy as np
 
-SOURCE = open(os.path.join(os.path.dirname(__file__), "..", "paper_2409_14939_amd", "csrc", "update_rows.hip")).read()
+CSRC = os.path.join(os.path.dirname(__file__), "..", "paper_2409_14939_amd", "csrc")
+SOURCE = "".join(open(os.path.join(CSRC, name)).read() for name in ("update_rows.hip", "update_tall_turn.inc"))
 
 
 def constant(name):
@@ -26,8 +27,9 @@ NOWHERE, MAX_LD, STAGE_ELEMS = constant("kNowhere"), constant("kMaxTallLd"), con
 # the lines of the kernel that `fetches` repeats
 LOOP = ("KS = NT < 64 ? 64 : kStageElems / NT", "AHEAD = !BF16 && (NTILES == 4 || (GATE && NTILES == 8)) ? 1 : 2;",
         "TURN = AHEAD == 1 && KS <= 32 ? 32 : 64;", "load_b(0);", "load_a(i, 32 * i);", "stage_b(0, 0);", "int lk = KS;",
-        "for (int k0 = 0; k0 < Kc; k0 += TURN) {", "for (int step = 0; step < TURN / 16; ++step) {",
-        "kc = k0 + 32 * cc, from = cc % AHEAD;", "if (step > 0 && k0 + 16 * step >= Kc) break;", "if (16 * step % KS == 0) {",
+        "for (; k0 + TURN < Kc; k0 += TURN) turn(std::false_type(), k0);",
+        "turn(std::true_type(), k0);", "for (int k0 = 0; k0 < Kc; k0 += TURN) {", "for (int step = 0; step < TURN / 16; ++step) {",
+        "kc = k0 + 32 * cc, from = cc % AHEAD;", "if (LAST && step > 0 && k0 + 16 * step >= Kc) break;", "if (16 * step % KS == 0) {",
         "stage_b(cur ^ 1, lk);", "lk += KS;", "if (s == 0) load_a(from, kc + 32 * AHEAD);", "slot = 16 * step % KS / 8 + h;",
         "if (16 * (step + 1) % KS == 0) {", "row = arow + (k0 < Kc ? 0u : kNowhere);",
         "buffer_cols<VB>(rb, (uint32_t)(k0 + 8 * bs) * ldb + bcol, ldb, bcols);")
