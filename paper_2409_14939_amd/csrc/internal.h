@@ -12,7 +12,7 @@ constexpr int kWave = 64;
 constexpr int kBlock = 256;            // threads per workgroup (4 wavefronts)
 constexpr int kLongThreshold = 256;    // rows longer than this go through the chunked path
 constexpr int kLongChunk = 128;        // edges per partial-sum chunk
-constexpr int kWorkPerGroup = 16;      // edges + rows per fine row set (a lane group takes 1-8 sets)
+constexpr int kWorkPerGroup = 16;      // edges + rows per fine row set (a wavefront takes one to 8 for each of its lane groups)
 constexpr int kMaxScanBlocks = 1024;   // blocks of a two-kernel scan / compaction
 constexpr int kRadixBits = 8;
 constexpr int kRadixBins = 1 << kRadixBits;

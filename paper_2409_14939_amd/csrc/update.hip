@@ -605,9 +605,10 @@ bool narrow(int64_t K, int64_t N) { return N >= 1 && N <= kNarrowCols && K > 0 &
 //   dH  N = 1: 6.4 / 9.7, 29 / 51, 59 / 104;   N = 3: 6.9 / 10.5, 42 / 71, 91 / 145;   N = 4: 9.1 / 8.9, 68 / 47,
 //       143 / 101;   N = 8: 13 / 9, 127 / 47, 274 / 98
 // So beyond the line Y is faster on tall tiles from two columns on, dH from four (the rule sends it there from five).
-// Y with one column is not (in the step of an attention head, part of H still in the Infinity Cache, 1.15 M rows took
-// 53 / 82): it stays with them because another order of terms would turn a few of millions of LeakyReLU signs from
-// what earlier versions of the library gave.  Below the line the order is the multiply-adds'.
+// Y with one column is NOT faster on them: the multiply-adds took 53 us in the step of an attention head, 1.15 M rows with part
+// of H still in the Infinity Cache, the tall tiles 82.  It goes to the tall tiles all the same, not for speed but to keep the
+// order of its terms: another one would turn a few of millions of LeakyReLU signs from what earlier versions of the library
+// gave.  Below the line the order is the multiply-adds'.
 constexpr int64_t kNarrowRows = 16384;
 
 // Rows per slab: a function of the shape alone, so results do not depend on the device or the run.

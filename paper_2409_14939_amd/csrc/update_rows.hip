@@ -20,7 +20,8 @@
 //   Y   M = 1.15 M, 100 -> 64: 381 -> 225 -> 218;  512 K, 100 -> 256: 257 -> 250 -> 220, 730 MB at 3.3 TB/s;
 //       91 K, 256 -> 256: 97 -> 87 -> 84, 855 TFLOP/s of plane products where a large bf16 product reaches 1 135
 //   dH, gated  M = 1.15 M, 64 -> 100: 347 -> 284 -> 272;  512 K, 256 -> 100: 316 -> 310;  91 K, 256 -> 256: 109 -> 121 -> 110
-// (the first two with their buffers allocated otherwise 202 -> 193 and 279 -> 236: where they lie is worth 10 %);
+// (where buffers lie is worth 10 to 15 %: allocated otherwise, Y of 1.15 M rows took 202 -> 193 in the last step and Y of 512 K
+// rows 279 -> 236, so that 250 -> 220 is a gain only as both sides had the same buffers);
 // bf16: Y 300 K, 128 -> 256: 79 -> 78, gated dH 256 -> 128: 141 -> 128;  87 K, 128 -> 256: 26.8 -> 27.0 (1 % lost).
 // What is left of the 512 K product: 178 us without the matrix instructions, 190 without the stores, 143 to move its bytes
 // at 5.1 TB/s; priorities that let one of a unit's two workgroups run ahead of the other changed nothing.
