@@ -606,7 +606,7 @@ bool narrow(int64_t K, int64_t N) { return N >= 1 && N <= kNarrowCols && K > 0 &
 //       143 / 101;   N = 8: 13 / 9, 127 / 47, 274 / 98
 // So beyond the line Y is faster on tall tiles from two columns on, dH from four (the rule sends it there from five).
 // Y with one column is NOT faster on them: the multiply-adds took 53 us in the step of an attention head, 1.15 M rows with part
-// of H still in the Infinity Cache, the tall tiles 82.  It goes to the tall tiles all the same, not for speed but to keep the
+// of H still in the Infinity Cache, the tall tiles 82 then and 66 now.  It goes to the tall tiles all the same, not for speed but to keep the
 // order of its terms: another one would turn a few of millions of LeakyReLU signs from what earlier versions of the library
 // gave.  Below the line the order is the multiply-adds'.
 constexpr int64_t kNarrowRows = 16384;
