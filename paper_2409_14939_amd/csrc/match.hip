@@ -101,8 +101,14 @@ __global__ __launch_bounds__(kScanBlock) void k_match_rank(MatchArgs a)
 }
 
 // Row copy: one thread moves one VEC-byte piece; consecutive threads take consecutive pieces of a row.  The last piece of a
-// row ends with it, so that rows of any length and alignment move 16 bytes per thread.
-template <int ELEM, int VEC>
+// row ends with it, so that rows of any length and alignment move 16 bytes per thread.  Bound by HBM.  STREAM: loads past the
+// caches, as the stores go anyway: a row is read once, and what the loads leave behind pushes out what is still to be written.
+// us, 400-byte rows, 60 % from the last matrix, cached loads / past the caches: 80 MB 41 / 41, 132 MB 68 / 69, 192 MB 91 / 74,
+// 260 MB 122 / 99, 460 MB 195 / 173 (4.7 -> 5.3 TB/s);  460 MB right after the gather of its loaded rows 179 / 170.  The
+// table gather gains nothing by it: alone behind a fill 119 / 127 at 192 MB, 235 / 238 at 460.
+constexpr int64_t kStreamBytes = (int64_t)160 << 20;
+
+template <int ELEM, int VEC, bool STREAM>
 __global__ __launch_bounds__(256) void k_assemble_rows(const char *__restrict__ X_prev, const char *__restrict__ X_load,
                                                        const int32_t *__restrict__ src_row, int64_t n_new,
                                                        int64_t row_bytes, int pieces, uint64_t pieces_inv, char *__restrict__ X_new)
@@ -115,9 +121,10 @@ __global__ __launch_bounds__(256) void k_assemble_rows(const char *__restrict__ 
     const char *src = r >= 0 ? X_prev + (int64_t)r * row_bytes : X_load + (int64_t)(-1 - r) * row_bytes;
     char *dst = X_new + i * row_bytes + off;
     using u32x4 = typename Words<ELEM>::x4;
-    if (VEC == 16)
-        __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(src + off), reinterpret_cast<u32x4 *>(dst));
-    else if (VEC == 4)
+    if constexpr (VEC == 16) {
+        const u32x4 *from = reinterpret_cast<const u32x4 *>(src + off);
+        __builtin_nontemporal_store(STREAM ? __builtin_nontemporal_load(from) : *from, reinterpret_cast<u32x4 *>(dst));
+    } else if (VEC == 4)
         *reinterpret_cast<uint32_t *>(dst) = *reinterpret_cast<const uint32_t *>(src + off);
     else
         *reinterpret_cast<uint16_t *>(dst) = *reinterpret_cast<const uint16_t *>(src + off);
@@ -430,8 +437,14 @@ fastgl_status fastgl_assemble_rows(const void *X_prev, int64_t n_prev, const voi
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, g, dim3(256), 0, s, xp, xl, src_row, n_new, row_bytes, (int)pieces, inv, (char *)X_new);
     };
-    if (dtype == FASTGL_F32) vec == 16 ? go(k_assemble_rows<4, 16>) : go(k_assemble_rows<4, 4>);
-    else vec == 16 ? go(k_assemble_rows<2, 16>) : go(k_assemble_rows<2, 2>);
+    const bool past = n_new * row_bytes >= kStreamBytes;
+    if (dtype == FASTGL_F32) {
+        if (vec == 16) past ? go(k_assemble_rows<4, 16, true>) : go(k_assemble_rows<4, 16, false>);
+        else go(k_assemble_rows<4, 4, false>);
+    } else {
+        if (vec == 16) past ? go(k_assemble_rows<2, 16, true>) : go(k_assemble_rows<2, 16, false>);
+        else go(k_assemble_rows<2, 2, false>);
+    }
     FASTGL_LAUNCH_CHECK("fastgl_assemble_rows");
     return FASTGL_OK;
 }
