@@ -75,14 +75,18 @@ struct Quad {
 };
 
 // Four elements from p on, which need no more alignment than an element has.
+template <bool ONCE>
 __device__ __forceinline__ float4 load_four(const float *p)
 {
-    const Words<4>::x4 w = *reinterpret_cast<const Words<4>::x4 *>(p);
+    const Words<4>::x4 *q = reinterpret_cast<const Words<4>::x4 *>(p);
+    const Words<4>::x4 w = ONCE ? __builtin_nontemporal_load(q) : *q;
     return make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3]));
 }
+template <bool ONCE>
 __device__ __forceinline__ uint2 load_four(const uint16_t *p)
 {
-    const Words<2>::x2 w = *reinterpret_cast<const Words<2>::x2 *>(p);
+    const Words<2>::x2 *q = reinterpret_cast<const Words<2>::x2 *>(p);
+    const Words<2>::x2 w = ONCE ? __builtin_nontemporal_load(q) : *q;
     return make_uint2(w[0], w[1]);
 }
 // The same one by one, where a row has fewer: element i < n, the others the first one again.
@@ -146,7 +150,7 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t (&w)[PLA
 // (stage).  Lane t has out indices 4(t%32)..+3 of contracted 2(t/32) and 2(t/32) + 1.  SUM keeps a running sum per held
 // out index of everything staged.  MASK = false is for steps that lie inside the contracted range.
 // QUADS: rows of at least four elements; else element by element.
-template <bool QUADS, bool GATE, bool BF16, int PLANES, bool SUM>
+template <bool QUADS, bool GATE, bool BF16, int PLANES, bool SUM, bool ONCE>
 struct PlaneMover {
     typedef typename QuadBits<BF16>::elem E;
     Quad<GATE, BF16> r[2];      // [slot]
@@ -189,8 +193,8 @@ struct PlaneMover {
             const bool ok = !MASK || in_range(s, k0, kend);
             if constexpr (QUADS) {
                 const uint32_t o = ok ? off[s] : first;
-                r[s].v = load_four(p + origin + o);
-                if constexpr (GATE) r[s].g[0] = load_four(gate + origin + o);
+                r[s].v = load_four<ONCE>(p + origin + o);
+                if constexpr (GATE) r[s].g[0] = load_four<ONCE>(gate + origin + o);
             } else {
                 r[s].v = load_few(p + origin, off[s], ok ? n_out : 0);
                 if constexpr (GATE) r[s].g[0] = load_few(gate + origin, off[s], ok ? n_out : 0);
@@ -240,7 +244,7 @@ struct PlaneMover {
 
 // A tile of 64 out indices: lane t has out indices 2(t%32), +1 of contracted 2(t/32) and 2(t/32) + 1, so that all lanes
 // have the same share; LDS as above, the first 64 dwords of every pair.
-template <bool QUADS, bool GATE, bool BF16, int PLANES, bool SUM>
+template <bool QUADS, bool GATE, bool BF16, int PLANES, bool SUM, bool ONCE>
 struct HalfMover {
     typedef typename QuadBits<BF16>::elem E;
     typedef typename std::conditional<BF16, uint32_t, float2>::type Duo;
@@ -277,9 +281,11 @@ struct HalfMover {
         if constexpr (QUADS) {
             const E *q = base + (ok ? off[s] : first);
             if constexpr (BF16) {
-                return *reinterpret_cast<const Words<2>::x1 *>(q);
+                const Words<2>::x1 *at = reinterpret_cast<const Words<2>::x1 *>(q);
+                return ONCE ? __builtin_nontemporal_load(at) : *at;
             } else {
-                const Words<4>::x2 w = *reinterpret_cast<const Words<4>::x2 *>(q);
+                const Words<4>::x2 *at = reinterpret_cast<const Words<4>::x2 *>(q);
+                const Words<4>::x2 w = ONCE ? __builtin_nontemporal_load(at) : *at;
                 return make_float2(__uint_as_float(w[0]), __uint_as_float(w[1]));
             }
         } else {
@@ -428,7 +434,7 @@ __device__ __forceinline__ void run_steps(MoverA &ma, MoverB &mb, char *la, char
 }
 
 // FA: a wavefront's 32-row fragments.  2: the tile is 128 x 128.  1: it is 128 x 64, a wavefront has 32 rows of it.
-template <bool QUADS, bool GATE, bool BF16, int FA>
+template <bool QUADS, bool GATE, bool BF16, int FA, bool ONCE_A, bool ONCE_B>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_update_gemm(const GemmArgs g)
 {
     constexpr int PLANES = BF16 ? 1 : 3;
@@ -460,9 +466,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    PlaneMover<QUADS, false, BF16, PLANES, false> ma;
-    typename std::conditional<FA == 2, PlaneMover<QUADS, GATE, BF16, PLANES, true>,
-                              HalfMover<QUADS, GATE, BF16, PLANES, true>>::type mb;
+    PlaneMover<QUADS, false, BF16, PLANES, false, ONCE_A> ma;
+    typename std::conditional<FA == 2, PlaneMover<QUADS, GATE, BF16, PLANES, true, ONCE_B>,
+                              HalfMover<QUADS, GATE, BF16, PLANES, true, ONCE_B>>::type mb;
     ma.init(g.a, r0, g.R);
     mb.init(g.b, c0, g.C);
     run_steps<PLANES, FA>(ma, mb, lds_a[0], lds_b[0], kbeg, kend, QUADS, wr, wc, l32, h, acc);
@@ -563,8 +569,23 @@ fastgl_status launch_gemm(GemmArgs &g, bool bf16, hipStream_t s, const char *wha
     auto gated = [&](auto q, auto type, auto fa) {
         constexpr bool Q = decltype(q)::value, T = decltype(type)::value;
         constexpr int FA = decltype(fa)::value;
-        if (g.b.gate) go(k_update_gemm<Q, true, T, FA>);
-        else go(k_update_gemm<Q, false, T, FA>);
+        auto pick = [&](auto oa, auto ob) {
+            constexpr bool A = decltype(oa)::value, B = decltype(ob)::value;
+            if (g.b.gate) go(k_update_gemm<Q, true, T, FA, A, B>);
+            else go(k_update_gemm<Q, false, T, FA, A, B>);
+        };
+        // fp32 operands that one workgroup reads, because there is one tile in the other dimension, are loaded past the caches.  us,
+        // cached / past the caches: 1.15 M rows, 100 x 64: 183 / 163;  512 K rows, gated, 100 x 256: 241 / 233 (the operand of
+        // 256 columns alone; with the other one too, which two tiles read, 241);  91 K rows, gated, 256 x 256, each read by two tiles:
+        // 91 / 95.  bf16 gains nothing: 85 K rows, 128 x 256: 29.3 / 30.4.
+        constexpr bool may = Q && !T;
+        const bool oa = may && g.tiles_c == 1, ob = may && g.tiles_r == 1;
+        if constexpr (may) {
+            if (oa && ob) return pick(std::true_type(), std::true_type());
+            if (oa) return pick(std::true_type(), std::false_type());
+            if (ob) return pick(std::false_type(), std::true_type());
+        }
+        pick(std::false_type(), std::false_type());
     };
     auto typed = [&](auto q, auto fa) {
         if (bf16) gated(q, std::true_type(), fa);
