@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libfastgl_agg.so")
 HOST = os.path.join(HERE, "_host.so")
-SOURCES = ["api.hip", "bookkeeping.hip", "aggregate.hip", "update.hip", "update_narrow.hip", "update_rows.hip", "idmap.hip", "match.hip", "edge.hip",
+SOURCES = ["api.hip", "bookkeeping.hip", "aggregate.hip", "update.hip", "update_narrow.hip", "update_rows.hip", "idmap.hip", "match.hip", "overlap.hip", "edge.hip",
            "static_scratch.hip", "layer.hip"]
 
 

@@ -133,6 +133,9 @@ fastgl_status aggregate_run(bool backward, const int32_t *indptr, const int32_t 
                             const fastgl_plan *plan, void *workspace, void *stream);
 fastgl_status launch_gather_rows(const void *table, const int64_t *ids, int64_t n, int64_t feat,
                                  fastgl_dtype dtype, void *out, hipStream_t s);
+// Overlap counts of 1 to 8 mini-batches of many IDs (overlap.hip).  offsets: host, n + 1.
+fastgl_status launch_overlap_buckets(const int64_t *gid, const int64_t *offsets, int n, int64_t *counts, int32_t *violations,
+                                     char *ws, size_t ws_bytes, hipStream_t s);
 fastgl_status validate_block(const int32_t *indptr, const int32_t *indices, int64_t num_dst,
                              int64_t num_src, int64_t num_edges, void *scratch, int64_t *n_violations,
                              hipStream_t s);

@@ -5,15 +5,13 @@
 // the row of the last feature matrix): the last mini-batch's IDs are inserted, the new mini-batch's IDs probe
 // it; the misses are compacted in position order (count per block, rank) into the load lists.
 //
-// The pairwise overlaps of n mini-batches come from ONE table over all their IDs.  Up to kMarkBatches
-// mini-batches a slot has a byte per mini-batch beside it that every holder of the ID sets with a plain store
-// (twice the rate of an atomic or), and the pairs are counted by reading those marks once, in order; beyond
-// that, entries carry a 64-bit mask, and every ID adds its mask to its mini-batch's row of the count matrix
-// (LDS histogram per workgroup, one atomic per workgroup and column).
+// The pairwise overlaps of n mini-batches: many IDs of up to kMarkBatches mini-batches go through buckets that fit LDS
+// (overlap.hip); otherwise ONE table over all their IDs.  Up to kMarkBatches mini-batches a slot has a byte per mini-batch
+// beside it that every holder of the ID sets with a plain store (twice the rate of an atomic or), and the pairs are counted
+// by reading those marks once, in order; beyond that, entries carry a 64-bit mask, and every ID adds its mask to its
+// mini-batch's row of the count matrix (LDS histogram per workgroup, one atomic per workgroup and column).
 //
-// Four mini-batches of 1.15 M nodes, us, 16-byte entries with masks -> positions and marks: overlaps 481 -> 230
-// (insert 271 -> 211, 194 since the first mini-batch's IDs do not look, count 188 -> 24, fill 23 -> 12); Match of two
-// of them 130 -> 95 (insert 80 -> 46).
+// Match of two mini-batches of 1.15 M nodes, us, 16-byte entries -> positions: 130 -> 95 (insert 80 -> 46).
 #include <vector>
 
 #include "fastgl_match.h"
@@ -132,6 +130,11 @@ __global__ __launch_bounds__(256) void k_assemble_rows(const char *__restrict__ 
 
 static_assert(sizeof(MaskSlot) <= kSlotRoom, "an entry fits its slot's room");
 constexpr int kMarkBatches = 8;
+// Windows of this many IDs go through buckets.  us, one table / buckets, IDs below 2.4 M and of 40 bits: 4 mini-batches of 20 000
+// 36 / 28 and 29 / 29, 66 000 44 / 32 and 40 / 32, 200 000 66 / 38 and 66 / 41, 400 000 97 / 44 and 103 / 51, 1.15 M 235 / 84
+// and 226 / 112, 2.4 M 493 / 147 and 433 / 204;  8 of 66 000 71 / 47, of 1.15 M 519 / 192;  2 of 140 000 44 / 31.  Beyond the
+// upper line buckets of IDs that do not repeat outgrow their tables.
+constexpr int64_t kBucketIds = (int64_t)1 << 16, kMostBucketIds = (int64_t)12 << 20;
 constexpr int kCountBlocks = 256;            // workgroups that read the marks: one per compute unit
 
 struct OverlapArgs {
@@ -499,6 +502,8 @@ fastgl_status fastgl_overlap_counts(const int64_t *gid, const int64_t *offsets_h
     hipStream_t s = (hipStream_t)stream;
     const dim3 g((unsigned)ceil_div(longest, 256), (unsigned)n);
     char *ws = (char *)workspace;
+    if (n <= kMarkBatches && total >= kBucketIds && total <= kMostBucketIds)
+        return launch_overlap_buckets(gid, offsets_host, n, counts, violations, ws, workspace_bytes, s);
     if (n > kMarkBatches) {
         a.masks = (MaskSlot *)(ws + L.table);
         a.slot_of = (int32_t *)(ws + L.slot_of);
