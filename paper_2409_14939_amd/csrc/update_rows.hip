@@ -11,6 +11,7 @@
 //     and cuts them into planes in registers.  B goes through LDS (all wavefronts of the workgroup read it), cut into
 //     planes when it is written there, double buffered.  With NTILES = 8 a row is read and cut once for
 //     256 columns.
+//   k_update_held   k_update_tall's tiles for many rows of whole fp32 tiles: B stays in LDS, wavefronts go on alone.
 //   k_update_small  bound by latency: too few rows to fill the chip with such tiles.  A workgroup owns
 //     32 x 64 results and its 8 wavefronts share the contracted range; every wavefront loads the operands of two
 //     steps up front (no staging, no barrier before the end) and the partial tiles are added in LDS.
@@ -513,6 +514,158 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES <= 4 && GATE && !BF16) 
     else write(std::integral_constant<int, 0>());
 }
 
+// ---------------------------------------------------------------------- tall tiles, B in LDS for good
+// Y of fp32 rows of four and more elements, many of them, N = 32 NTILES: one workgroup per compute unit keeps all of B in LDS,
+// cut into planes once, and its wavefronts take tiles of 32 rows one after the other, each for itself: no barrier and no conversion of B in the
+// loop, so that one wavefront's loads and stores run under the other's matrix instructions.  The steps of a tile are those of
+// k_update_tall in the same order: the same results.  Y of 512 K rows, 100 -> 256, in a training step: 227 us with k_update_tall, 183;
+// 730 MB, 143 to move them, and 156 for the matrix instructions at the 1 135 TFLOP/s of a large product.  Loads of A in whole lines that
+// reach their lanes through LDS, past the caches or not, gained nothing.
+constexpr int kHeldBlocks = 256;               // one per compute unit
+constexpr int64_t kHeldLds = 160 * 1024;       // of a workgroup
+constexpr int kHeldThreads = 512;              // two wavefronts per SIMD
+
+// B in LDS, [plane][octet slot][column] x 16 bytes, and 16 bytes of zeros: the octet behind the last one of an odd number.
+inline int64_t held_lds(int ntiles, int64_t Kc) { return ceil_div(Kc, 8) * ntiles * 32 * 3 * 16 + 16; }
+
+// LAST: steps of the last turn, 1 to 4 (a constant: accumulators that reach the end by several paths take a second set of
+// registers).
+template <int NTILES, int LAST>
+__global__ __launch_bounds__(kHeldThreads, 2) void k_update_held(const RowsGemm g)
+{
+    constexpr int NT = NTILES * 32, THREADS = kHeldThreads, WAVES = THREADS / kWave, PL = 3;
+    extern __shared__ uint4 planes[];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), h = lane >> 5, l32 = lane & 31;
+    const int Kc = (int)g.Kc, slots = (Kc + 7) >> 3;
+    const uint32_t ldb = (uint32_t)g.ldb * 4;
+    {
+        const Rsrc rb = buffer_from(g.b, g.Kc * g.ldb * 4);
+        for (int u = t; u < slots * (NT / 2); u += THREADS) {
+            const int bc = 2 * (u % (NT / 2)), slot = u / (NT / 2);
+            ColPair<false> c;                                  // rows of B past the end read as 0
+            buffer_cols<4>(rb, (uint32_t)(8 * slot) * ldb + (uint32_t)bc * 4, ldb, c);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                Planes<false> f;
+                to_planes(column(c, i), f);
+#pragma unroll
+                for (int p = 0; p < PL; ++p) planes[(p * slots + slot) * NT + bc + i] = f.p[p];
+            }
+        }
+        if (t == 0) planes[PL * slots * NT] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+    }
+    float bias[NTILES];
+#pragma unroll
+    for (int j = 0; j < NTILES; ++j) bias[j] = g.bias ? g.bias[32 * j + l32] : 0.f;
+
+    const int64_t tiles = (g.M + kWaveRows - 1) / kWaveRows, stride = (int64_t)gridDim.x * WAVES;
+    // Two chunks of 32 contracted indices under way: octets s of row l32, indices k0 + 16 s + 8 h .. + 7.  Chunks past the end
+    // touch no memory.
+    Oct<false> ar[2][2];
+    auto load_a = [&](int to, int64_t tile, int k0) {
+        const int64_t r0 = tile * kWaveRows;
+        const bool there = tile < tiles && k0 < Kc;
+        const Rsrc ra = buffer_from((const char *)g.a + (there ? r0 * g.lda * 4 : 0), there ? (g.M - r0) * g.lda * 4 : 0);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) buffer_oct<4>(ra, (uint32_t)l32 * (uint32_t)g.lda * 4, k0 + 16 * s + 8 * h, Kc, ar[to][s]);
+    };
+    Planes<false> fa[2];
+    const bool relu = g.relu != 0;
+    int64_t tile = (int64_t)blockIdx.x * WAVES + wave;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) load_a(i, tile, 32 * i);
+    for (; tile < tiles; tile += stride) {
+        f32x16 acc[NTILES];
+#pragma unroll
+        for (int j = 0; j < NTILES; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+        // STEPS steps from k0 on; then = tile and index of what the chunks' registers are loaded with
+        auto turn = [&](auto steps, int k0, int64_t then, int then_k0) {
+            constexpr int STEPS = decltype(steps)::value;
+            if (STEPS <= 2) load_a(1, then, then_k0 + 32);      // there is no second chunk
+#pragma unroll
+            for (int step = 0; step < STEPS; ++step) {
+                const int cc = step >> 1, s = step & 1;
+                if (s == 0) {
+                    const int kc = k0 + 32 * cc;
+                    if (kc + 32 > Kc)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) settle<4>(ar[cc][i], kc + 16 * i + 8 * h, Kc);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) to_planes(ar[cc][i], fa[i]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_a(cc, then, then_k0 + 32 * cc);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const int slot = (k0 + 16 * step) / 8 + h;
+                const bool there = slot < slots;
+                const uint4 *at = planes + (there ? slot * NT + l32 : PL * slots * NT);
+                const int plane = there ? slots * NT : 0, next = there ? 32 : 0;
+                Planes<false> fb[2];
+#pragma unroll
+                for (int p = 0; p < PL; ++p) fb[0].p[p] = at[p * plane];
+#pragma unroll
+                for (int j = 0; j < NTILES; ++j) {             // the next tile is read while this one is multiplied
+                    if (j + 1 < NTILES)
+#pragma unroll
+                        for (int p = 0; p < PL; ++p) fb[(j + 1) & 1].p[p] = at[p * plane + (j + 1) * next];
+                    mma<false>(fa[s], fb[j & 1], acc[j]);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x100, PL, 0);
+#pragma unroll
+                for (int j = 0; j < NTILES; ++j) {
+                    if (j + 1 < NTILES) __builtin_amdgcn_sched_group_barrier(0x100, PL, 0);    // LDS reads
+                    __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);                         // matrix instructions
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        int k0 = 0;
+        for (; k0 + 64 < Kc; k0 += 64) turn(std::integral_constant<int, 4>(), k0, tile, k0 + 64);
+        turn(std::integral_constant<int, LAST>(), k0, tile + stride, 0);
+
+        const int64_t r0 = tile * kWaveRows;
+        const Rsrc rc = buffer_from((const char *)g.c + r0 * g.N * 4, (g.M - r0) * g.N * 4);
+        // made anew for every tile: kept over the loop, the offsets of a lane's results would take more registers than there are
+        uint32_t ldc = (uint32_t)g.N * 4;
+        asm volatile("" : "+s"(ldc));
+        const uint32_t coff = (uint32_t)(4 * h) * ldc + (uint32_t)l32 * 4;
+        // not past the caches: 512 K rows, 100 -> 256: 183 us so, 189 with streaming stores
+#pragma unroll
+        for (int j = 0; j < NTILES; ++j) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                float v = acc[j][e] + bias[j];
+                if (relu) v = v > 0.f ? v : 0.f;
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rc, coff + 32 * j * 4 + (uint32_t)(8 * (e >> 2) + (e & 3)) * ldc, 0, 0);
+            }
+        }
+    }
+}
+
+template <int NTILES, int LAST>
+fastgl_status launch_held(const RowsGemm &g, hipStream_t s)
+{
+    FASTGL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_update_held<NTILES, LAST>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kHeldLds));
+    hipLaunchKernelGGL((k_update_held<NTILES, LAST>), dim3(kHeldBlocks), dim3(kHeldThreads),
+                       held_lds(NTILES, g.Kc), s, g);
+    return FASTGL_OK;
+}
+
+template <int NTILES>
+fastgl_status launch_held_steps(const RowsGemm &g, hipStream_t s)
+{
+    switch (ceil_div((g.Kc - 1) % 64 + 1, 16)) {
+        case 1: return launch_held<NTILES, 1>(g, s);
+        case 2: return launch_held<NTILES, 2>(g, s);
+        case 3: return launch_held<NTILES, 3>(g, s);
+        default: return launch_held<NTILES, 4>(g, s);
+    }
+}
+
 // ----------------------------------------------------------------------------------- small tiles
 template <bool BCOL, bool GATE, int VA, int VB, bool BF16>
 __global__ __launch_bounds__(64 * kSmallWaves) void k_update_small(const RowsGemm g)
@@ -690,6 +843,27 @@ int tall_tiles(int64_t M, int64_t N, bool b_col)
     return best;
 }
 
+// Does k_update_held take these tiles?  B fits LDS, a tile has no columns that do not exist, and the rounds in which its wavefronts
+// take their tiles are nearly full.  us with cold caches, k_update_tall / k_update_held, by K -> N:
+//   rows (rounds)   32 -> 256    64 -> 256    100 -> 256     |  32 -> 128    100 -> 128   128 -> 128   200 -> 128
+//   66 K  (1.0)     30.0 / 26.4  37.4 / 34.7  50.0 / 50.7    |  14.2 / 16.8  29.2 / 33.9  28.7 / 36.2  46.2 / 50.8
+//   98 K  (1.5)     33.1 / 28.8  40.6 / 35.6  54.2 / 53.2    |  16.9 / 18.4  35.9 / 36.6  33.8 / 37.6  50.8 / 55.0
+//   131 K (2.0)     38.6 / 34.4  47.3 / 42.0  63.0 / 57.0    |  24.3 / 20.8  47.3 / 42.8  46.1 / 47.3  68.6 / 62.7
+//   140 K (2.1)     44.8 / 42.4  55.7 / 55.9  74.3 / 75.4    |  26.0 / 26.8  48.4 / 52.3  46.8 / 54.0  72.2 / 79.0
+//   215 K (3.3)     61.5 / 60.4  75.2 / 78.0  99.5 / 102     |  36.1 / 37.6  66.0 / 69.6  66.8 / 75.0  101 / 106
+//   262 K (4.0)     73.8 / 65.7  83.7 / 83.7  114 / 109      |  44.4 / 42.6  77.9 / 76.0  80.8 / 86.5  120 / 110
+//   420 K (6.4)     116 / 104    132 / 129    174 / 162      |  69.0 / 68.0  114 / 113    121 / 122    175 / 162
+//   700 K (10.7)    184 / 168    208 / 205    274 / 242      |  116 / 102    178 / 163    180 / 173    262 / 241
+// With columns that do not exist, or rows that are no whole lines, it loses (512 K rows: 64 -> 200 141 / 160, 37 -> 100 78 / 87), and so
+// do narrower tiles (100 -> 64 104 / 113, 256 -> 47 172 / 189).
+bool held_fits(int ntiles, int64_t M, int64_t Kc, int64_t N)
+{
+    if ((ntiles != 8 && ntiles != 4) || N != 32 * ntiles || held_lds(ntiles, Kc) > kHeldLds) return false;
+    const int64_t waves = kHeldBlocks * kHeldThreads / kWave, tiles = ceil_div(M, kWaveRows), rounds = ceil_div(tiles, waves);
+    if (ntiles == 4) return rounds >= 9;
+    return rounds >= 2 && (rounds == 2 || 20 * tiles >= 17 * rounds * waves);
+}
+
 }  // namespace
 
 fastgl_status launch_rows_gemm(RowsGemm g, bool b_col, bool bf16, hipStream_t s, const char *what)
@@ -705,6 +879,12 @@ fastgl_status launch_rows_gemm(RowsGemm g, bool b_col, bool bf16, hipStream_t s,
     if (blocks >= INT32_MAX) {
         set_error("%s: too many tiles (%lld)", what, (long long)blocks);
         return FASTGL_ERR_UNSUPPORTED;
+    }
+    if (b_col && !bf16 && va == 4 && held_fits(ntiles, g.M, g.Kc, g.N)) {
+        const fastgl_status st = ntiles == 8 ? launch_held_steps<8>(g, s) : launch_held_steps<4>(g, s);
+        if (st != FASTGL_OK) return st;
+        FASTGL_LAUNCH_CHECK(what);
+        return FASTGL_OK;
     }
     switch (ntiles) {
         case 0: launch_tiles<0>(g, b_col, bf16, va, vb, (unsigned)blocks, s); break;
