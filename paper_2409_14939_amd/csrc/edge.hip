@@ -15,8 +15,8 @@
 //         13 (96) 122 -> 122 -> 75;  33 (299) 127 -> 127 -> 121;  64 (140) 140 -> 140 -> 130;  256 (582) 582 -> 582 -> 528
 //   bf16  4 (98) 72 -> 50 -> 43;  7 (66) 66 -> 73 -> 54;  9 (69) 78 -> 78 -> 58;  25 (105) 115 -> 115 -> 76;  100 (156) 152 -> 152 -> 140
 //
-// Softmax: a group of 8, 32 or 64 lanes (by the block's mean row length) walks one destination row
-// three times (maximum, sum of exponentials, write).  Rows longer than kLongRow are taken by whole workgroups of the
+// Softmax: rows of up to 24 edges on average are walked many to a wavefront (walk_short_rows); of others a group of 32 or 64 lanes
+// walks one destination row three times (maximum, sum of exponentials, write).  Rows longer than kLongRow are taken by whole workgroups of the
 // same launch that look for them (softmax_long_rows).  exp and the sums are fp64, so the result is the correctly
 // rounded quotient up to one unit in the last place.  Forward, us: 2.56 M edges in rows of 5, none long: 34 (a queue
 // of long rows with launches of its own: 40; no workgroups that look: 32); 32 neighbouring rows of 20 000 among short
@@ -231,6 +231,88 @@ __global__ __launch_bounds__(256) void k_edge_dot(const DotArgs a)
     }
 }
 
+// ---------------------------------------------------------------- short rows, up to 64 to a wavefront
+// What the kernels on rows of a few edges are bound by is latency and instructions: with 8 lanes per row most lanes are idle, and every
+// 8 edges of a long row are a chain of dependent loads.  Here a wavefront takes 8 to 64 neighbouring rows.  Their edges lie one after the
+// other: all lanes load them, in order, into LDS; then 1 to 8 lanes put their row together there, and per-edge results go out in
+// order again.  Rows of more than kLaneRow edges per such lane are put together by the wavefront, one after the other.  Rows that do not
+// fit LDS together are taken in several goes; one that does not fit alone is left to op.whole().
+// us, 8 lanes per row / this: 2.56 M edges, 513 K rows of 5: softmax 24 / 16, its gradient 16.3 / 12.8, scores 18.0 / 15.5,
+// their gradient by destination 19.6 / 15.3;  819 K edges, rows of 20: 6.5 / 6.6, 5.0 / 5.2, 5.9 / 6.2, 5.4 / 5.8;  479 K edges, 30 K
+// rows, the longest of 13 405: 58 / 33, 31 / 17, 372 / 44, 320 / 33.
+constexpr int kLaneRow = 64;
+constexpr int64_t kShortMean = 24;   // mean length of rows that are walked so
+constexpr int kWalkLoads = 4;        // edges in flight per lane
+constexpr int kWalkWaves = 4;        // of a workgroup
+
+// Rows whose lengths are a power of two start at different banks.
+__device__ __forceinline__ int stage_slot(int k) { return k + (k >> 4); }
+constexpr int stage_slots(int edges) { return edges + edges / 16; }
+
+__device__ __forceinline__ void stage_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");       // a wavefront's own LDS accesses are in order
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Rows of a wavefront, 64 / rows lanes each: fewer where rows are longer, and where there were too few wavefronts.
+inline int walk_rows_per_wave(int64_t num_rows, int64_t mean, int most, int64_t waves)
+{
+    int rows = most;
+    while (rows > 8 && (rows * mean > 448 || num_rows < rows * waves)) rows >>= 1;
+    return rows;
+}
+inline unsigned walk_blocks(int64_t num_rows, int rows) { return (unsigned)ceil_div(num_rows, (int64_t)rows * kWalkWaves); }
+
+// Op: STAGE, edges of a go;  Word, what LDS holds of an edge;  load(k0, end, w): edges k0 + 64 i's;  own(r): what a row brings along;  row(st, lo, hi, r,
+// own, l, lanes): row r, edges lo .. hi - 1 of the stage, by a group of lanes, this one lane l of it;  whole(b, e, r, own): by all, from memory;
+// EDGES: result(word) goes to op.out[k] afterwards.
+template <class Op>
+__device__ __forceinline__ void walk_short_rows(const int32_t *__restrict__ rowptr, int64_t num_rows, int64_t first, int rows,
+                                                typename Op::Word *st, const Op &op)
+{
+    typedef typename Op::Word Word;
+    const int lane = threadIdx.x & (kWave - 1), lanes = kWave / rows, q = lane / lanes;
+    const int64_t limit = first + rows < num_rows ? first + rows : num_rows;
+    auto begin = [&](int64_t r) { return rowptr[r < limit ? r : limit]; };                // rows that there are not are empty
+    const int b = begin(first + lane), e = begin(first + lane + 1);                       // of row `lane`
+    const int qb = begin(first + q), qe = begin(first + q + 1);                           // of the row that the lane works on
+    const int64_t r = first + q;
+    const float own = op.own(r < limit ? r : limit - 1);
+    int s = 0;
+    while (s < rows) {
+        const int base = __builtin_amdgcn_readlane(b, s);
+        const unsigned long long beyond = __ballot(lane >= s && lane < rows && e - base > Op::STAGE);
+        const int n = beyond ? (int)__ffsll((long long)beyond) - 1 : rows;
+        if (n == s) {
+            op.whole(base, __builtin_amdgcn_readlane(e, s), first + s, __shfl(own, s * lanes));
+            ++s;
+            continue;
+        }
+        const int end = __builtin_amdgcn_readlane(e, n - 1);
+        for (int k0 = base + lane; k0 - lane < end; k0 += kWave * kWalkLoads) {
+            Word w[kWalkLoads];
+            op.load(k0, end, w);             // no branch around the loads: they go out together
+#pragma unroll
+            for (int i = 0; i < kWalkLoads; ++i)
+                if (k0 + i * kWave < end) st[stage_slot(k0 + i * kWave - base)] = w[i];
+        }
+        stage_fence();
+        const bool mine = q >= s && q < n && r < limit, wide = qe - qb > kLaneRow * lanes;
+        if (mine && !wide) op.row(st, qb - base, qe - base, r, own, lane % lanes, lanes);
+        for (unsigned long long todo = __ballot(mine && wide && lane % lanes == 0); todo; todo &= todo - 1) {
+            const int w = (int)__ffsll((long long)todo) - 1;
+            op.row(st, __builtin_amdgcn_readlane(qb, w) - base, __builtin_amdgcn_readlane(qe, w) - base, first + w / lanes,
+                   __shfl(own, w), lane, kWave);
+        }
+        stage_fence();
+        if (Op::EDGES)
+            for (int k = base + lane; k < end; k += kWave) op.out[k] = op.result(st[stage_slot(k - base)]);
+        stage_fence();
+        s = n;
+    }
+}
+
 // ---------------------------------------------------------------- softmax
 struct SoftmaxArgs {
     const int32_t *indptr;
@@ -341,6 +423,87 @@ __global__ __launch_bounds__(256) void k_edge_softmax_rows(const SoftmaxArgs a)
         softmax_row_fwd(a.in0, a.out, b, e, l, lanes);
 }
 
+// Rows of a wavefront's walk.  The exponentials stay in LDS from the sum to the quotient.
+struct SoftmaxFwd {
+    static constexpr int STAGE = kLongRow;   // what whole workgroups do not take fits
+    typedef double Word;
+    static constexpr bool EDGES = true;
+    const float *score;
+    float *out;
+    __device__ __forceinline__ void load(int k0, int end, Word (&w)[kWalkLoads]) const
+    {
+#pragma unroll
+        for (int i = 0; i < kWalkLoads; ++i) {
+            const int k = k0 + i * kWave;
+            w[i] = (double)score[k < end ? k : end - 1];
+        }
+    }
+    __device__ __forceinline__ float own(int64_t) const { return 0.f; }
+    __device__ __forceinline__ float result(Word w) const { return (float)w; }
+    __device__ __forceinline__ void row(Word *st, int lo, int hi, int64_t, float, int l, int lanes) const
+    {
+        double m = -INFINITY, z = 0.0;
+        for (int k = lo + l; k < hi; k += lanes) m = fmax(m, st[stage_slot(k)]);
+        m = lanes_max(m, lanes);
+        for (int k = lo + l; k < hi; k += lanes) {
+            const double x = exp(st[stage_slot(k)] - m);
+            st[stage_slot(k)] = x;
+            z += x;
+        }
+        z = group_sum<double>(z, lanes);
+        for (int k = lo + l; k < hi; k += lanes) st[stage_slot(k)] /= z;
+    }
+    __device__ __forceinline__ void whole(int, int, int64_t, float) const {}        // softmax_long_rows has it
+};
+
+struct SoftmaxBwd {
+    static constexpr int STAGE = kLongRow;   // what whole workgroups do not take fits
+    typedef float2 Word;                     // alpha and its gradient; then the score's gradient
+    static constexpr bool EDGES = true;
+    const float *alpha, *da;
+    float *out;
+    __device__ __forceinline__ void load(int k0, int end, Word (&w)[kWalkLoads]) const
+    {
+#pragma unroll
+        for (int i = 0; i < kWalkLoads; ++i) {
+            const int k = k0 + i * kWave, at = k < end ? k : end - 1;
+            w[i] = make_float2(alpha[at], da[at]);
+        }
+    }
+    __device__ __forceinline__ float own(int64_t) const { return 0.f; }
+    __device__ __forceinline__ float result(Word w) const { return w.x; }
+    static __device__ __forceinline__ double term(Word w) { return (double)w.x * (double)w.y; }
+    static __device__ __forceinline__ void put(Word *st, int k, double s)
+    {
+        const Word w = st[stage_slot(k)];
+        st[stage_slot(k)].x = (float)((double)w.x * ((double)w.y - s));
+    }
+    __device__ __forceinline__ void row(Word *st, int lo, int hi, int64_t, float, int l, int lanes) const
+    {
+        double s = 0.0;
+        for (int k = lo + l; k < hi; k += lanes) s += term(st[stage_slot(k)]);
+        s = group_sum<double>(s, lanes);
+        for (int k = lo + l; k < hi; k += lanes) put(st, k, s);
+    }
+    __device__ __forceinline__ void whole(int, int, int64_t, float) const {}
+};
+
+__global__ __launch_bounds__(256) void k_edge_softmax_short(const SoftmaxArgs a, int rows)
+{
+    __shared__ __align__(16) char stage[kWalkWaves][stage_slots(kLongRow) * 8];
+    if ((int)blockIdx.x < a.seekers) {
+        softmax_long_rows(a);
+        return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t first = ((int64_t)(blockIdx.x - a.seekers) * kWalkWaves + wave) * rows;
+    if (first >= a.num_dst) return;
+    if (a.backward)
+        walk_short_rows(a.indptr, a.num_dst, first, rows, reinterpret_cast<float2 *>(stage[wave]), SoftmaxBwd{a.in0, a.in1, a.out});
+    else
+        walk_short_rows(a.indptr, a.num_dst, first, rows, reinterpret_cast<double *>(stage[wave]), SoftmaxFwd{a.in0, a.out});
+}
+
 template <int lanes>
 void launch_softmax(const SoftmaxArgs &a, hipStream_t s)
 {
@@ -424,9 +587,11 @@ fastgl_status softmax(bool backward, const int32_t *indptr, int64_t num_dst, int
     a.backward = backward;
     a.seekers = (int)(E / kLongRow < kMostSeekers ? E / kLongRow : kMostSeekers);   // no more than there can be long rows
     hipStream_t s = (hipStream_t)stream;
-    // lanes per destination row by the block's mean row length (rows of sampled blocks are short)
+    // by the block's mean row length (rows of sampled blocks are short)
     const int64_t mean = E / (num_dst > 0 ? num_dst : 1);
-    if (mean < 24) launch_softmax<8>(a, s);
+    const int rows = walk_rows_per_wave(num_dst, mean, kWave, 2048);
+    if (mean < kShortMean)
+        hipLaunchKernelGGL(k_edge_softmax_short, dim3(a.seekers + walk_blocks(num_dst, rows)), dim3(256), 0, s, a, rows);
     else if (mean < 96) launch_softmax<32>(a, s);
     else launch_softmax<64>(a, s);
     FASTGL_LAUNCH_CHECK("edge softmax");
@@ -473,12 +638,95 @@ __global__ __launch_bounds__(256) void k_edge_score(const ScoreArgs a)
     }
 }
 
+// Rows of a wavefront's walk: what the edge's other end has, and the edge's gradient or its score.
+template <bool BACKWARD>
+struct ScoreRows {
+    static constexpr int STAGE = 512;
+    typedef float2 Word;
+    static constexpr bool EDGES = !BACKWARD;
+    const ScoreArgs &a;
+    float *out;
+    __device__ __forceinline__ void load(int k0, int end, Word (&w)[kWalkLoads]) const
+    {
+        int at[kWalkLoads], col[kWalkLoads], id[kWalkLoads];
+#pragma unroll
+        for (int i = 0; i < kWalkLoads; ++i) {
+            const int k = k0 + i * kWave;
+            at[i] = k < end ? k : end - 1;
+            col[i] = a.col[at[i]];
+            id[i] = BACKWARD && a.eid ? a.eid[at[i]] : at[i];
+        }
+#pragma unroll
+        for (int i = 0; i < kWalkLoads; ++i) w[i] = make_float2(a.col_val[col[i]], BACKWARD ? a.grad_score[id[i]] : 0.f);
+    }
+    __device__ __forceinline__ float own(int64_t r) const { return a.row_val[r]; }
+    __device__ __forceinline__ float result(Word w) const { return w.y; }
+    __device__ __forceinline__ double term(double mine, Word w) const
+    {
+        return (double)w.y * (mine + (double)w.x > 0.0 ? 1.0 : a.slope);          // the sum is exact: both are fp32
+    }
+    __device__ __forceinline__ float score(double mine, Word w) const
+    {
+        const double x = mine + (double)w.x;
+        return (float)(x > 0.0 ? x : a.slope * x);
+    }
+    __device__ __forceinline__ void row(Word *st, int lo, int hi, int64_t r, float own, int l, int lanes) const
+    {
+        const double mine = (double)own;
+        double acc = 0.0;
+        for (int k = lo + l; k < hi; k += lanes) {
+            const Word w = st[stage_slot(k)];
+            if (BACKWARD) acc += term(mine, w);
+            else st[stage_slot(k)].y = score(mine, w);
+        }
+        if (BACKWARD) {
+            acc = group_sum<double>(acc, lanes);
+            if (l == 0) out[r] = (float)acc;
+        }
+    }
+    __device__ __forceinline__ void whole(int b, int e, int64_t r, float own) const
+    {
+        const int l = threadIdx.x & (kWave - 1);
+        const double mine = (double)own;
+        double acc = 0.0;
+        for (int k0 = b + l; k0 - l < e; k0 += kWave * kWalkLoads) {
+            Word w[kWalkLoads];
+            load(k0, e, w);
+#pragma unroll
+            for (int i = 0; i < kWalkLoads; ++i) {
+                const int k = k0 + i * kWave;
+                if (k >= e) continue;
+                if (BACKWARD) acc += term(mine, w[i]);
+                else out[k] = score(mine, w[i]);
+            }
+        }
+        if (BACKWARD) {
+            acc = group_sum<double>(acc, kWave);
+            if (l == 0) out[r] = (float)acc;
+        }
+    }
+};
+
+template <bool BACKWARD>
+__global__ __launch_bounds__(256) void k_edge_score_short(const ScoreArgs a, int rows)
+{
+    __shared__ float2 stage[kWalkWaves][stage_slots(ScoreRows<BACKWARD>::STAGE)];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t first = ((int64_t)blockIdx.x * kWalkWaves + wave) * rows;
+    if (first < a.num_rows) walk_short_rows(a.rowptr, a.num_rows, first, rows, stage[wave], ScoreRows<BACKWARD>{a, a.out});
+}
+
 template <bool BACKWARD>
 void launch_score(const ScoreArgs &a, int64_t nnz, hipStream_t s)
 {
     const int64_t mean = nnz / (a.num_rows > 0 ? a.num_rows : 1);
-    if (mean < 24)
-        hipLaunchKernelGGL((k_edge_score<8, BACKWARD>), dim3((unsigned)ceil_div(a.num_rows * 8, 256)), dim3(256), 0, s, a);
+    // Destinations: 64 rows to a wavefront, if that leaves 2 048 of them.  Sources come in order of their first appearance, the much
+    // used ones next to each other, and their rows are shorter: 16, or 8.  us with 64 / 32 / 16 / 8 rows, 8 lanes per row as above:
+    // 1.15 M sources 67 / 51 / 49 / 66 (60);  299 K 31 / 20 / 13 / 17 (17);  191 K 15 / 6.9 / 7.3 / 10 (6.3);  107 K, up to 616 edges,
+    // 46 / 46 / 28 / 20 (23)
+    const int rows = a.eid ? walk_rows_per_wave(a.num_rows, mean, 16, 8192) : walk_rows_per_wave(a.num_rows, mean, kWave, 2048);
+    if (mean < kShortMean)
+        hipLaunchKernelGGL(k_edge_score_short<BACKWARD>, dim3(walk_blocks(a.num_rows, rows)), dim3(256), 0, s, a, rows);
     else if (mean < 96)
         hipLaunchKernelGGL((k_edge_score<32, BACKWARD>), dim3((unsigned)ceil_div(a.num_rows * 32, 256)), dim3(256), 0, s, a);
     else
