@@ -37,7 +37,7 @@
 namespace fastgl {
 
 constexpr int kXcdRun = 16;
-constexpr int kReduceBlocks = 1024;   // workgroups for the long rows, whose number the host does not know
+constexpr int kReduceBlocks = 2048;   // workgroups for the long rows, whose number the host does not know
 
 // Which (row sets, column tile) a wavefront works on.
 //
@@ -151,56 +151,83 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
     }
 }
 
-// Long rows: the partial sums of a row's chunks, scaled and stored.  A workgroup takes a (row, column tile); its
-// 256 / G groups sum consecutive ranges of the chunks, each in chunk order with 8 loads in flight, and the ranges
-// are added in order.  Bound by latency: a row of 25 000 edges has 200 chunks, a chain of 25 loads for one group.
-// Both directions of the all-neighbours block (65 536 and 1 M rows, up to 25 000 edges), us, one group per row -> now:
-// 32 -> 21 with 32 columns, 52 -> 43 with 256.
+// Long rows: the partial sums of a row's chunks, scaled and stored.  A unit is a (row, column tile).  One of no more chunks than a
+// workgroup has groups (256 / G) is added up by one group, others by a workgroup: its groups sum consecutive ranges of the
+// chunks, each in chunk order with 8 loads in flight, and the ranges are added in order.  Bound by latency: most rows have few chunks, a row
+// of 25 000 edges has 200, a chain of 25 loads for one group.  All-neighbours block (65 536 rows, 2 570 of them long, up to 26 000
+// edges, and 640 K, 3 642 long, up to 1 800), forward and backward, us, a workgroup to every unit -> now: 32 columns
+// 11.0 + 10.8 -> 10.9 + 5.2;  256 columns, where most units need a workgroup or all loads are under way, 29.9 + 13.6 -> 30.0 + 13.3
+// (1 024 workgroups: 32.0 + 15.1).
 template <int DT, int VB>
 __global__ __launch_bounds__(kBlock) void k_reduce_chunks(PullParams P)
 {
     using S = Slice<DT, VB>;
     using acc_t = typename S::acc_t;
     __shared__ acc_t range_sum[S::NE][kBlock];
+    __shared__ int many[kBlock], n_many;
     const int tid = threadIdx.x, sub = tid & (P.G - 1), part = tid / P.G, parts = kBlock / P.G;
     const int64_t total = (int64_t)(*P.n_long) * P.ntiles;
-    for (int64_t unit = blockIdx.x; unit < total; unit += gridDim.x) {
-        const int li = (int)(unit / P.ntiles);
-        const int tile = (int)(unit - (int64_t)li * P.ntiles);
+    auto add_chunks = [&](int lo, int hi, int64_t lane_off, acc_t (&acc)[S::NE]) {
+        const acc_t *src = reinterpret_cast<const acc_t *>(P.partials) + lane_off / S::ES;
+        for (int c0 = lo; c0 < hi; c0 += 8) {
+            acc_t load[8][S::NE];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int i = 0; i < S::NE; ++i)
+                    load[k][i] = c0 + k < hi ? src[(int64_t)(c0 + k) * P.feat + i] : (acc_t)0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int i = 0; i < S::NE; ++i) acc[i] += load[k][i];
+        }
+    };
+    for (int64_t unit = (int64_t)blockIdx.x * parts + part; unit < total; unit += (int64_t)gridDim.x * parts) {
+        const int li = (int)(unit / P.ntiles), tile = (int)(unit - (int64_t)li * P.ntiles);
         const int64_t slice = (int64_t)tile * P.G + sub, lane_off = slice_offset<VB>(P, slice);
-        const bool active = slice * VB < P.row_bytes;
-        const int row = P.long_rows[li];
-        const int first = P.chunk_ptr[li], last = P.chunk_ptr[li + 1];
-        const int per = (last - first + parts - 1) / parts;
-        const int lo = first + part * per, hi = lo + per < last ? lo + per : last;
+        const int row = P.long_rows[li], first = P.chunk_ptr[li], last = P.chunk_ptr[li + 1];
+        if (last - first > parts || slice * VB >= P.row_bytes) continue;
+        const int len = P.rowptr[row + 1] - P.rowptr[row];
         acc_t acc[S::NE];
 #pragma unroll
         for (int i = 0; i < S::NE; ++i) acc[i] = (acc_t)0;
-        const acc_t *src = reinterpret_cast<const acc_t *>(P.partials) + lane_off / S::ES;
-        if (active) {
-            for (int c0 = lo; c0 < hi; c0 += 8) {
-                acc_t load[8][S::NE];
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-#pragma unroll
-                    for (int i = 0; i < S::NE; ++i)
-                        load[k][i] = c0 + k < hi ? src[(int64_t)(c0 + k) * P.feat + i] : (acc_t)0;
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-#pragma unroll
-                    for (int i = 0; i < S::NE; ++i) acc[i] += load[k][i];
-            }
-        }
-        __syncthreads();                       // the previous unit's sums have been read
-#pragma unroll
-        for (int i = 0; i < S::NE; ++i) range_sum[i][tid] = acc[i];
-        __syncthreads();
-        if (part != 0 || !active) continue;    // the barriers of the next unit are reached by all
-        for (int q = 1; q < parts && q * per < last - first; ++q)
-#pragma unroll
-            for (int i = 0; i < S::NE; ++i) acc[i] += range_sum[i][q * P.G + sub];
-        const int len = P.rowptr[row + 1] - P.rowptr[row];
+        add_chunks(first, last, lane_off, acc);
         S::store(P.out + (int64_t)row * P.row_bytes + lane_off, acc, row_scale<acc_t>(P.row_mode, len));
+    }
+    for (int64_t base = blockIdx.x; base < total; base += (int64_t)gridDim.x * kBlock) {
+        if (tid == 0) n_many = 0;
+        __syncthreads();
+        const int64_t at = base + (int64_t)tid * gridDim.x;
+        if (at < total) {
+            const int li = (int)(at / P.ntiles);
+            if (P.chunk_ptr[li + 1] - P.chunk_ptr[li] > parts) many[atomicAdd(&n_many, 1)] = tid;      // in any order: units are independent
+        }
+        __syncthreads();
+        const int n = n_many;
+        for (int m = 0; m < n; ++m) {
+            const int64_t unit = base + (int64_t)many[m] * gridDim.x;
+            const int li = (int)(unit / P.ntiles), tile = (int)(unit - (int64_t)li * P.ntiles);
+            const int64_t slice = (int64_t)tile * P.G + sub, lane_off = slice_offset<VB>(P, slice);
+            const bool active = slice * VB < P.row_bytes;
+            const int row = P.long_rows[li], first = P.chunk_ptr[li], last = P.chunk_ptr[li + 1];
+            const int per = (last - first + parts - 1) / parts;
+            const int lo = first + part * per, hi = lo + per < last ? lo + per : last;
+            acc_t acc[S::NE];
+#pragma unroll
+            for (int i = 0; i < S::NE; ++i) acc[i] = (acc_t)0;
+            if (active) add_chunks(lo, hi, lane_off, acc);
+            __syncthreads();                       // the previous unit's sums have been read
+#pragma unroll
+            for (int i = 0; i < S::NE; ++i) range_sum[i][tid] = acc[i];
+            __syncthreads();
+            if (part != 0 || !active) continue;    // the barriers of the next unit are reached by all
+            for (int q = 1; q < parts && q * per < last - first; ++q)
+#pragma unroll
+                for (int i = 0; i < S::NE; ++i) acc[i] += range_sum[i][q * P.G + sub];
+            const int len = P.rowptr[row + 1] - P.rowptr[row];
+            S::store(P.out + (int64_t)row * P.row_bytes + lane_off, acc, row_scale<acc_t>(P.row_mode, len));
+        }
+        __syncthreads();                           // the list is the next units'
     }
 }
 

@@ -22,6 +22,29 @@ def test_widths(feat, dtype, mode, weighted):
         check_block(blk, mode, dtype, feat, weighted, True, feat + hub, f"hub {hub}")
 
 
+@pytest.mark.parametrize("feat,dtype,parts", [(256, "f32", 4), (128, "f32", 8), (602, "f32", 4), (40, "f32", 16), (5, "bf16", 64)])
+def test_rows_of_few_and_of_many_chunks(feat, dtype, parts):
+    """Long rows of one chunk less than a workgroup has groups to one more, some with a short last chunk, side by side, in
+    both directions (every source that is used is used as often)."""
+    lengths = [257, 384, 385] + [128 * c + d for c in (parts - 1, parts, parts + 1, 2 * parts, 3 * parts + 1) for d in (-127, -1, 0) if 128 * c + d > 0]
+    rng = np.random.default_rng(feat)
+    deg = rng.permutation(np.concatenate([lengths, rng.integers(0, 4, 50)]))
+    ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    src = rng.permutation(deg.size)[:deg.size // 2]
+    ix = np.concatenate([np.repeat(src, deg[src]), rng.integers(0, deg.size, ip[-1])])[:ip[-1]]
+    blk = bg.Block(ip, rng.permutation(ix).astype(np.int32), deg.size, deg.size)
+    check_block(blk, "mean", dtype, feat, True, True, feat, "chunks")
+
+
+def test_more_long_rows_than_one_pass_takes():
+    """More (row, column tile) pairs than the groups of all workgroups together."""
+    rng = np.random.default_rng(3)
+    deg = np.where(np.arange(2900) % 700 == 5, 257 + 128 * 5, 257)
+    ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    blk = bg.Block(ip, rng.integers(0, 3000, ip[-1]).astype(np.int32), deg.size, 3000)
+    check_block(blk, "sum", "f32", 602, False, False, 3, "many long rows")
+
+
 @pytest.mark.parametrize("rows", [1, 3, 4, 5, 2047, 2048, 2049, 2065])
 @pytest.mark.parametrize("mode,K,N,weighted", [("gcn", 256, 47, False), ("gcn", 60, 64, True), ("sum", 4, 1, False)])
 def test_layer_rows(rows, mode, K, N, weighted):
