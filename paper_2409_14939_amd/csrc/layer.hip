@@ -20,7 +20,7 @@
 //      y[r][n] = ((s0 + s1) + (s2 + s3)) + b[n]
 // Bound by latency where there are few rows: the rows' gathers and W come in together, and the chain of
 // multiply-adds is a quarter of K long.  K = 256, N = 47, us,
-// W through LDS and K terms per wavefront -> now: 16 rows of 15 edges 21.6 -> 8.5, 8 000 rows 42 -> 37.
+// W through LDS and K terms per wavefront -> now: 16 rows of 15 edges 21.6 -> 8.5, 8 000 rows 42 -> 37 (four rows to a wavefront; with two 35).
 //
 // Every other shape takes the two kernels of the separate calls, back to back on the stream.
 #include "fastgl_update.h"
@@ -33,9 +33,17 @@ constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxFusedK = 256;     // 64 lanes x 4 floats
 constexpr int kFusedCols = 64;      // one lane per output column
 constexpr int kQuarter = kMaxFusedK / kWavesPerBlock;   // most terms of a wavefront
-// Rows of a wavefront: one while that gives at most two workgroups per compute unit, else four (every workgroup
-// reads W once).
-constexpr int64_t kFewRows = 2048;
+// Rows of a wavefront: one while that gives at most three workgroups per compute unit, else two (every workgroup reads W
+// once); four where rows are short and many.  us, GCN, 1 / 2 / 4 rows, by K -> N and edges of a row:
+//   rows      256 -> 47, 15       256 -> 47, 5        100 -> 47, 15       64 -> 16, 10
+//   2 048     9.1 / 11.2 / 20.0   7.9 / 9.9 / 16.1    7.3 / 8.0 / 13.0    6.6 / 7.3 / 9.4
+//   3 000     12.8 / 14.7 / 20.8  9.0 / 11.4 / 15.5   8.5 / 9.9 / 13.8    7.2 / 8.1 / 9.8
+//   4 000     17.6 / 16.9 / 22.8  12.8 / 10.4 / 15.8  11.6 / 10.0 / 14.3  9.1 / 7.5 / 9.8
+//   6 000     21.8 / 22.0 / 27.8  15.6 / 12.6 / 18.0  15.4 / 12.8 / 16.6  11.2 / 10.1 / 10.8
+//   8 000     28.5 / 30.4 / 32.3  20.9 / 20.7 / 20.7  19.2 / 18.9 / 18.2  14.9 / 12.5 / 11.7
+//   16 000    49.5 / 49.6 / 59.4  36.8 / 32.4 / 39.0  34.7 / 30.4 / 34.4  27.9 / 20.7 / 20.5
+//   64 000    202 / 179 / 185     139 / 107 / 109     126 / 105 / 104     99 / 70 / 60
+constexpr int64_t kFewRows = 3072, kManyShortRows = 6144, kShortK = 64;
 
 struct LayerParams {
     PullParams pull;                // rowptr, col, eid, edge_w, col_scale, in, G = 64, row_mode, row_bytes, feat
@@ -149,6 +157,8 @@ void launch_layer(const LayerParams &L, hipStream_t s)
 {
     if (L.rows <= kFewRows)
         hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 1>), dim3((unsigned)ceil_div(L.rows, kWavesPerBlock)), dim3(kBlock), 0, s, L);
+    else if (L.K > kShortK || L.rows <= kManyShortRows)
+        hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 2>), dim3((unsigned)ceil_div(L.rows, 2 * kWavesPerBlock)), dim3(kBlock), 0, s, L);
     else
         hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 4>), dim3((unsigned)ceil_div(L.rows, 4 * kWavesPerBlock)), dim3(kBlock), 0, s, L);
 }
