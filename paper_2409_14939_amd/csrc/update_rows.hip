@@ -518,7 +518,7 @@ __global__ __launch_bounds__(256, NTILES == 8 || (NTILES <= 4 && GATE && !BF16) 
 // Y of fp32 rows of four and more elements, many of them, N = 32 NTILES: one workgroup per compute unit keeps all of B in LDS,
 // cut into planes once, and its wavefronts take tiles of 32 rows one after the other, each for itself: no barrier and no conversion of B in the
 // loop, so that one wavefront's loads and stores run under the other's matrix instructions.  The steps of a tile are those of
-// k_update_tall in the same order: the same results.  Y of 512 K rows, 100 -> 256, in a training step: 227 us with k_update_tall, 183;
+// k_update_tall in the same order: the same results.  Y of 512 K rows, 100 -> 256, in a training step: 231 us with k_update_tall, 192;
 // 730 MB, 143 to move them, and 156 for the matrix instructions at the 1 135 TFLOP/s of a large product.  Loads of A in whole lines that
 // reach their lanes through LDS, past the caches or not, gained nothing.
 constexpr int kHeldBlocks = 256;               // one per compute unit
@@ -632,14 +632,14 @@ __global__ __launch_bounds__(kHeldThreads, 2) void k_update_held(const RowsGemm 
         uint32_t ldc = (uint32_t)g.N * 4;
         asm volatile("" : "+s"(ldc));
         const uint32_t coff = (uint32_t)(4 * h) * ldc + (uint32_t)l32 * 4;
-        // not past the caches: 512 K rows, 100 -> 256: 183 us so, 189 with streaming stores
+        // past the caches: 512 K rows, 100 -> 256: 183 us alone without, 189 so, but the aggregation that reads Y next takes 172 and 150 us
 #pragma unroll
         for (int j = 0; j < NTILES; ++j) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 float v = acc[j][e] + bias[j];
                 if (relu) v = v > 0.f ? v : 0.f;
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rc, coff + 32 * j * 4 + (uint32_t)(8 * (e >> 2) + (e & 3)) * ldc, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rc, coff + 32 * j * 4 + (uint32_t)(8 * (e >> 2) + (e & 3)) * ldc, 0, kStream);
             }
         }
     }
