@@ -151,8 +151,8 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
     }
 }
 
-// Long rows: the partial sums of a row's chunks, scaled and stored.  A unit is a (row, column tile).  One of no more chunks than a
-// workgroup has groups (256 / G) is added up by one group, others by a workgroup: its groups sum consecutive ranges of the
+// Long rows: the partial sums of a row's chunks, scaled and stored.  A unit is a (row, column tile).  Where there are more units than
+// workgroups, one of no more chunks than a workgroup has groups (256 / G) is added up by one group; others by a workgroup: its groups sum consecutive ranges of the
 // chunks, each in chunk order with 8 loads in flight, and the ranges are added in order.  Bound by latency: most rows have few chunks, a row
 // of 25 000 edges has 200, a chain of 25 loads for one group.  All-neighbours block (65 536 rows, 2 570 of them long, up to 26 000
 // edges, and 640 K, 3 642 long, up to 1 800), forward and backward, us, a workgroup to every unit -> now: 32 columns
@@ -182,7 +182,8 @@ __global__ __launch_bounds__(kBlock) void k_reduce_chunks(PullParams P)
                 for (int i = 0; i < S::NE; ++i) acc[i] += load[k][i];
         }
     };
-    for (int64_t unit = (int64_t)blockIdx.x * parts + part; unit < total; unit += (int64_t)gridDim.x * parts) {
+    const bool spread = total > gridDim.x;         // else every unit has a workgroup, and nobody looks for them
+    for (int64_t unit = (int64_t)blockIdx.x * parts + part; spread && unit < total; unit += (int64_t)gridDim.x * parts) {
         const int li = (int)(unit / P.ntiles), tile = (int)(unit - (int64_t)li * P.ntiles);
         const int64_t slice = (int64_t)tile * P.G + sub, lane_off = slice_offset<VB>(P, slice);
         const int row = P.long_rows[li], first = P.chunk_ptr[li], last = P.chunk_ptr[li + 1];
@@ -195,17 +196,20 @@ __global__ __launch_bounds__(kBlock) void k_reduce_chunks(PullParams P)
         S::store(P.out + (int64_t)row * P.row_bytes + lane_off, acc, row_scale<acc_t>(P.row_mode, len));
     }
     for (int64_t base = blockIdx.x; base < total; base += (int64_t)gridDim.x * kBlock) {
-        if (tid == 0) n_many = 0;
-        __syncthreads();
-        const int64_t at = base + (int64_t)tid * gridDim.x;
-        if (at < total) {
-            const int li = (int)(at / P.ntiles);
-            if (P.chunk_ptr[li + 1] - P.chunk_ptr[li] > parts) many[atomicAdd(&n_many, 1)] = tid;      // in any order: units are independent
+        int n = 1;
+        if (spread) {
+            if (tid == 0) n_many = 0;
+            __syncthreads();
+            const int64_t at = base + (int64_t)tid * gridDim.x;
+            if (at < total) {
+                const int li = (int)(at / P.ntiles);
+                if (P.chunk_ptr[li + 1] - P.chunk_ptr[li] > parts) many[atomicAdd(&n_many, 1)] = tid;      // in any order: units are independent
+            }
+            __syncthreads();
+            n = n_many;
         }
-        __syncthreads();
-        const int n = n_many;
         for (int m = 0; m < n; ++m) {
-            const int64_t unit = base + (int64_t)many[m] * gridDim.x;
+            const int64_t unit = spread ? base + (int64_t)many[m] * gridDim.x : base;
             const int li = (int)(unit / P.ntiles), tile = (int)(unit - (int64_t)li * P.ntiles);
             const int64_t slice = (int64_t)tile * P.G + sub, lane_off = slice_offset<VB>(P, slice);
             const bool active = slice * VB < P.row_bytes;
