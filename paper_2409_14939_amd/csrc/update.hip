@@ -434,7 +434,7 @@ __device__ __forceinline__ void run_steps(MoverA &ma, MoverB &mb, char *la, char
 }
 
 // FA: a wavefront's 32-row fragments.  2: the tile is 128 x 128.  1: it is 128 x 64, a wavefront has 32 rows of it.
-template <bool QUADS, bool GATE, bool BF16, int FA, bool ONCE_A, bool ONCE_B>
+template <bool QUADS, bool GATE, bool BF16, int FA, bool ONCE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_update_gemm(const GemmArgs g)
 {
     constexpr int PLANES = BF16 ? 1 : 3;
@@ -466,9 +466,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    PlaneMover<QUADS, false, BF16, PLANES, false, ONCE_A> ma;
-    typename std::conditional<FA == 2, PlaneMover<QUADS, GATE, BF16, PLANES, true, ONCE_B>,
-                              HalfMover<QUADS, GATE, BF16, PLANES, true, ONCE_B>>::type mb;
+    PlaneMover<QUADS, false, BF16, PLANES, false, ONCE> ma;
+    typename std::conditional<FA == 2, PlaneMover<QUADS, GATE, BF16, PLANES, true, ONCE>,
+                              HalfMover<QUADS, GATE, BF16, PLANES, true, ONCE>>::type mb;
     ma.init(g.a, r0, g.R);
     mb.init(g.b, c0, g.C);
     run_steps<PLANES, FA>(ma, mb, lds_a[0], lds_b[0], kbeg, kend, QUADS, wr, wc, l32, h, acc);
@@ -569,23 +569,18 @@ fastgl_status launch_gemm(GemmArgs &g, bool bf16, hipStream_t s, const char *wha
     auto gated = [&](auto q, auto type, auto fa) {
         constexpr bool Q = decltype(q)::value, T = decltype(type)::value;
         constexpr int FA = decltype(fa)::value;
-        auto pick = [&](auto oa, auto ob) {
-            constexpr bool A = decltype(oa)::value, B = decltype(ob)::value;
-            if (g.b.gate) go(k_update_gemm<Q, true, T, FA, A, B>);
-            else go(k_update_gemm<Q, false, T, FA, A, B>);
+        auto pick = [&](auto once) {
+            constexpr bool ONCE = decltype(once)::value;
+            if (g.b.gate) go(k_update_gemm<Q, true, T, FA, ONCE>);
+            else go(k_update_gemm<Q, false, T, FA, ONCE>);
         };
-        // fp32 operands that one workgroup reads, because there is one tile in the other dimension, are loaded past the caches.  us,
-        // cached / past the caches: 1.15 M rows, 100 x 64: 183 / 163;  512 K rows, gated, 100 x 256: 241 / 233 (the operand of
-        // 256 columns alone; with the other one too, which two tiles read, 241);  91 K rows, gated, 256 x 256, each read by two tiles:
-        // 91 / 95.  bf16 gains nothing: 85 K rows, 128 x 256: 29.3 / 30.4.
-        constexpr bool may = Q && !T;
-        const bool oa = may && g.tiles_c == 1, ob = may && g.tiles_r == 1;
-        if constexpr (may) {
-            if (oa && ob) return pick(std::true_type(), std::true_type());
-            if (oa) return pick(std::true_type(), std::false_type());
-            if (ob) return pick(std::false_type(), std::true_type());
-        }
-        pick(std::false_type(), std::false_type());
+        // One tile: fp32 operands that one workgroup reads are loaded past the caches.  us, cached / past the caches: 1.15 M rows,
+        // 100 x 64: 183 / 163.  An operand of several is not, nor one beside it: 512 K rows, gated, 100 x 256, whose 256 columns
+        // one tile reads, alone 241 / 233, in a training step 251 / 256;  91 K rows, gated, 256 x 256, each read by two tiles: 91 / 95.
+        // bf16 gains nothing: 85 K rows, 128 x 256: 29.3 / 30.4.
+        if constexpr (Q && !T)
+            if (g.tiles_r == 1 && g.tiles_c == 1) return pick(std::true_type());
+        pick(std::false_type());
     };
     auto typed = [&](auto q, auto fa) {
         if (bf16) gated(q, std::true_type(), fa);
