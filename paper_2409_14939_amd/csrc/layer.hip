@@ -20,7 +20,7 @@
 //      y[r][n] = ((s0 + s1) + (s2 + s3)) + b[n]
 // Bound by latency where there are few rows: the rows' gathers and W come in together, and the chain of
 // multiply-adds is a quarter of K long.  K = 256, N = 47, us,
-// W through LDS and K terms per wavefront -> now: 16 rows of 15 edges 21.6 -> 8.5, 8 000 rows 42 -> 37 (four rows to a wavefront; with two 35).
+// W through LDS and K terms per wavefront -> now: 16 rows of 15 edges 21.6 -> 8.5, 8 000 rows 42 -> 37.
 //
 // Every other shape takes the two kernels of the separate calls, back to back on the stream.
 #include "fastgl_update.h"
@@ -33,17 +33,19 @@ constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxFusedK = 256;     // 64 lanes x 4 floats
 constexpr int kFusedCols = 64;      // one lane per output column
 constexpr int kQuarter = kMaxFusedK / kWavesPerBlock;   // most terms of a wavefront
-// Rows of a wavefront: one while that gives at most three workgroups per compute unit, else two (every workgroup reads W
-// once); four where rows are short and many.  us, GCN, 1 / 2 / 4 rows, by K -> N and edges of a row:
+// Rows of a wavefront: one, two or four while that gives at most three workgroups per compute unit (every workgroup reads W
+// once); beyond that two, which leave the unit more wavefronts, and four where rows are short.  us right after X was written, GCN,
+// 1 / 2 / 4 rows, by K -> N and edges of a row:
 //   rows      256 -> 47, 15       256 -> 47, 5        100 -> 47, 15       64 -> 16, 10
-//   2 048     9.1 / 11.2 / 20.0   7.9 / 9.9 / 16.1    7.3 / 8.0 / 13.0    6.6 / 7.3 / 9.4
-//   3 000     12.8 / 14.7 / 20.8  9.0 / 11.4 / 15.5   8.5 / 9.9 / 13.8    7.2 / 8.1 / 9.8
-//   4 000     17.6 / 16.9 / 22.8  12.8 / 10.4 / 15.8  11.6 / 10.0 / 14.3  9.1 / 7.5 / 9.8
-//   6 000     21.8 / 22.0 / 27.8  15.6 / 12.6 / 18.0  15.4 / 12.8 / 16.6  11.2 / 10.1 / 10.8
-//   8 000     28.5 / 30.4 / 32.3  20.9 / 20.7 / 20.7  19.2 / 18.9 / 18.2  14.9 / 12.5 / 11.7
-//   16 000    49.5 / 49.6 / 59.4  36.8 / 32.4 / 39.0  34.7 / 30.4 / 34.4  27.9 / 20.7 / 20.5
-//   64 000    202 / 179 / 185     139 / 107 / 109     126 / 105 / 104     99 / 70 / 60
-constexpr int64_t kFewRows = 3072, kManyShortRows = 6144, kShortK = 64;
+//   2 048     13.8 / 15.4 / 24.0  11.2 / 12.8 / 19.0  10.7 / 12.1 / 17.2  8.9 / 9.9 / 13.1
+//   3 000     16.3 / 17.8 / 23.4  12.9 / 14.0 / 19.6  12.0 / 13.2 / 17.7  9.9 / 10.8 / 13.5
+//   4 000     21.5 / 20.0 / 25.4  17.3 / 14.9 / 20.3  16.4 / 13.8 / 18.0  13.6 / 10.9 / 13.6
+//   6 000     26.5 / 25.5 / 30.4  20.2 / 18.0 / 22.3  19.2 / 16.4 / 20.2  15.4 / 12.3 / 14.7
+//   8 000     32.5 / 35.0 / 35.2  25.0 / 25.1 / 24.2  23.9 / 23.0 / 21.5  19.4 / 16.5 / 14.8
+//   12 000    43.4 / 43.9 / 46.2  32.9 / 30.4 / 29.6  31.9 / 27.5 / 26.4  25.6 / 19.9 / 17.2
+//   16 000    53.9 / 54.2 / 64.5  40.8 / 37.5 / 44.1  40.6 / 35.1 / 38.4  32.7 / 24.8 / 24.8
+//   64 000    228 / 207 / 217     156 / 132 / 131     157 / 132 / 127     109 / 79 / 67
+constexpr int64_t kOneRow = 3 * 256 * kWavesPerBlock, kShortK = 64;
 
 struct LayerParams {
     PullParams pull;                // rowptr, col, eid, edge_w, col_scale, in, G = 64, row_mode, row_bytes, feat
@@ -155,9 +157,9 @@ bool fuses(int64_t K, int64_t N, fastgl_dtype dtype, const void *X, const void *
 template <int WEIGHTS>
 void launch_layer(const LayerParams &L, hipStream_t s)
 {
-    if (L.rows <= kFewRows)
+    if (L.rows <= kOneRow)
         hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 1>), dim3((unsigned)ceil_div(L.rows, kWavesPerBlock)), dim3(kBlock), 0, s, L);
-    else if (L.K > kShortK || L.rows <= kManyShortRows)
+    else if (L.rows <= 2 * kOneRow || (L.rows > 4 * kOneRow && L.K > kShortK))
         hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 2>), dim3((unsigned)ceil_div(L.rows, 2 * kWavesPerBlock)), dim3(kBlock), 0, s, L);
     else
         hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 4>), dim3((unsigned)ceil_div(L.rows, 4 * kWavesPerBlock)), dim3(kBlock), 0, s, L);
