@@ -165,8 +165,9 @@ __global__ __launch_bounds__(kBlock) void k_reduce_chunks(PullParams P)
     using acc_t = typename S::acc_t;
     __shared__ acc_t range_sum[S::NE][kBlock];
     __shared__ int many[kBlock], n_many;
-    const int tid = threadIdx.x, sub = tid & (P.G - 1), part = tid / P.G, parts = kBlock / P.G;
     const int64_t total = (int64_t)(*P.n_long) * P.ntiles;
+    if (blockIdx.x >= total) return;
+    const int tid = threadIdx.x, sub = tid & (P.G - 1), part = tid >> P.lg_G, parts = kBlock >> P.lg_G;
     auto add_chunks = [&](int lo, int hi, int64_t lane_off, acc_t (&acc)[S::NE]) {
         const acc_t *src = reinterpret_cast<const acc_t *>(P.partials) + lane_off / S::ES;
         for (int c0 = lo; c0 < hi; c0 += 8) {
