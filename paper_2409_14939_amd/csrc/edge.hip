@@ -15,7 +15,7 @@
 //         13 (96) 122 -> 122 -> 75;  33 (299) 127 -> 127 -> 121;  64 (140) 140 -> 140 -> 130;  256 (582) 582 -> 582 -> 528
 //   bf16  4 (98) 72 -> 50 -> 43;  7 (66) 66 -> 73 -> 54;  9 (69) 78 -> 78 -> 58;  25 (105) 115 -> 115 -> 76;  100 (156) 152 -> 152 -> 140
 //
-// Softmax: rows of up to 24 edges on average are walked many to a wavefront (walk_short_rows); of others a group of 32 or 64 lanes
+// Softmax: rows of up to 24 edges on average are walked many to a wavefront (walk_short_rows); of others, and of few, a group of 8, 32 or 64 lanes
 // walks one destination row three times (maximum, sum of exponentials, write).  Rows longer than kLongRow are taken by whole workgroups of the
 // same launch that look for them (softmax_long_rows).  exp and the sums are fp64, so the result is the correctly
 // rounded quotient up to one unit in the last place.  Forward, us: 2.56 M edges in rows of 5, none long: 34 (a queue
@@ -233,14 +233,14 @@ __global__ __launch_bounds__(256) void k_edge_dot(const DotArgs a)
 
 // ---------------------------------------------------------------- short rows, up to 64 to a wavefront
 // What the kernels on rows of a few edges are bound by is latency and instructions: with 8 lanes per row most lanes are idle, and every
-// 8 edges of a long row are a chain of dependent loads.  Here a wavefront takes 8 to 64 neighbouring rows.  Their edges lie one after the
-// other: all lanes load them, in order, into LDS; then 1 to 8 lanes put their row together there, and per-edge results go out in
+// 8 edges of a long row are a chain of dependent loads.  Here a wavefront takes 16 to 64 neighbouring rows.  Their edges lie one after the
+// other: all lanes load them, in order, into LDS; then 1 to 4 lanes put their row together there, and per-edge results go out in
 // order again.  Rows of more than kLaneRow edges per such lane are put together by the wavefront, one after the other.  Rows that do not
 // fit LDS together are taken in several goes; one that does not fit alone is left to op.whole().
 // us, 8 lanes per row / this: 2.56 M edges, 513 K rows of 5: softmax 24 / 16, its gradient 16.3 / 12.8, scores 18.0 / 15.5,
-// their gradient by destination 19.6 / 15.3;  819 K edges, rows of 20: 6.5 / 6.6, 5.0 / 5.2, 5.9 / 6.2, 5.4 / 5.8;  479 K edges, 30 K
-// rows, the longest of 13 405: 58 / 33, 31 / 17, 372 / 44, 320 / 33.
+// their gradient by destination 19.6 / 15.3;  819 K edges, rows of 20: 6.5 / 6.6, 5.0 / 5.2, 5.9 / 6.2, 5.4 / 5.8.
 constexpr int kLaneRow = 64;
+constexpr int kFewLanes = 32;        // groups of fewer lanes leave rows beyond kLaneRow to the wavefront
 constexpr int64_t kShortMean = 24;   // mean length of rows that are walked so
 constexpr int kWalkLoads = 4;        // edges in flight per lane
 constexpr int kWalkWaves = 4;        // of a workgroup
@@ -262,6 +262,10 @@ inline int walk_rows_per_wave(int64_t num_rows, int64_t mean, int most, int64_t 
     while (rows > 8 && (rows * mean > 448 || num_rows < rows * waves)) rows >>= 1;
     return rows;
 }
+// Blocks of so few rows that a wavefront would take 8 of them are left to groups of 8 lanes, whose kernels are shorter: 8 090 rows of
+// 10, softmax 3.9 us, 4.5 walked, its gradient 3.3 and 3.8, scores 3.6 and 4.0, their gradient 3.4 and 4.2.  Their rows beyond kLaneRow are the wavefront's, too: 30 000
+// rows, the longest of 13 405 edges, all rows by 8 lanes / so: softmax 58 / 35, its gradient 31 / 17, scores 372 / 43, their gradient 320 / 28.
+constexpr int kGroupRows = 8;
 inline unsigned walk_blocks(int64_t num_rows, int rows) { return (unsigned)ceil_div(num_rows, (int64_t)rows * kWalkWaves); }
 
 // Op: STAGE, edges of a go;  Word, what LDS holds of an edge;  load(k0, end, w): edges k0 + 64 i's;  own(r): what a row brings along;  row(st, lo, hi, r,
@@ -417,10 +421,19 @@ __global__ __launch_bounds__(256) void k_edge_softmax_rows(const SoftmaxArgs a)
         if (e - b > kLongRow) e = b;
     }
     // all lanes of a group hold the same (b, e): the cross-lane sums below see whole groups
-    if (a.backward)
-        softmax_row_bwd(a.in0, a.in1, a.out, b, e, l, lanes);
-    else
-        softmax_row_fwd(a.in0, a.out, b, e, l, lanes);
+    auto walk = [&](int beg, int end, int lane, int n) {
+        if (a.backward)
+            softmax_row_bwd(a.in0, a.in1, a.out, beg, end, lane, n);
+        else
+            softmax_row_fwd(a.in0, a.out, beg, end, lane, n);
+    };
+    const bool wide = lanes < kFewLanes && e - b > kLaneRow;
+    if (!wide) walk(b, e, l, lanes);
+    if (lanes < kFewLanes)
+        for (unsigned long long todo = __ballot(wide && l == 0); todo; todo &= todo - 1) {
+            const int w = (int)__ffsll((long long)todo) - 1;
+            walk(__builtin_amdgcn_readlane(b, w), __builtin_amdgcn_readlane(e, w), threadIdx.x & (kWave - 1), kWave);
+        }
 }
 
 // Rows of a wavefront's walk.  The exponentials stay in LDS from the sum to the quotient.
@@ -590,7 +603,8 @@ fastgl_status softmax(bool backward, const int32_t *indptr, int64_t num_dst, int
     // by the block's mean row length (rows of sampled blocks are short)
     const int64_t mean = E / (num_dst > 0 ? num_dst : 1);
     const int rows = walk_rows_per_wave(num_dst, mean, kWave, 2048);
-    if (mean < kShortMean)
+    if (mean < kShortMean && rows <= kGroupRows) launch_softmax<8>(a, s);
+    else if (mean < kShortMean)
         hipLaunchKernelGGL(k_edge_softmax_short, dim3(a.seekers + walk_blocks(num_dst, rows)), dim3(256), 0, s, a, rows);
     else if (mean < 96) launch_softmax<32>(a, s);
     else launch_softmax<64>(a, s);
@@ -611,32 +625,6 @@ struct ScoreArgs {
     float *out;                            // forward: [E] scores; backward: [num_rows] sums
     double slope;
 };
-
-template <int lanes, bool BACKWARD>
-__global__ __launch_bounds__(256) void k_edge_score(const ScoreArgs a)
-{
-    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / lanes;
-    const int l = threadIdx.x % lanes;
-    int b = 0, e = 0;
-    double mine = 0.0;
-    if (r < a.num_rows) {
-        b = a.rowptr[r];
-        e = a.rowptr[r + 1];
-        mine = (double)a.row_val[r];
-    }
-    double acc = 0.0;
-    for (int k = b + l; k < e; k += lanes) {
-        const double x = mine + (double)a.col_val[a.col[k]];      // exact: both are fp32
-        if (!BACKWARD)
-            a.out[k] = (float)(x > 0.0 ? x : a.slope * x);
-        else
-            acc += (double)a.grad_score[a.eid ? a.eid[k] : k] * (x > 0.0 ? 1.0 : a.slope);
-    }
-    if (BACKWARD) {
-        acc = group_sum<double>(acc, lanes);       // every lane of the group takes part
-        if (l == 0 && r < a.num_rows) a.out[r] = (float)acc;
-    }
-}
 
 // Rows of a wavefront's walk: what the edge's other end has, and the edge's gradient or its score.
 template <bool BACKWARD>
@@ -707,6 +695,39 @@ struct ScoreRows {
     }
 };
 
+template <int lanes, bool BACKWARD>
+__global__ __launch_bounds__(256) void k_edge_score(const ScoreArgs a)
+{
+    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / lanes;
+    const int l = threadIdx.x % lanes;
+    int b = 0, e = 0;
+    double mine = 0.0;
+    if (r < a.num_rows) {
+        b = a.rowptr[r];
+        e = a.rowptr[r + 1];
+        mine = (double)a.row_val[r];
+    }
+    const bool wide = lanes < kFewLanes && e - b > kLaneRow;
+    double acc = 0.0;
+    for (int k = b + l; k < e && !wide; k += lanes) {
+        const double x = mine + (double)a.col_val[a.col[k]];      // exact: both are fp32
+        if (!BACKWARD)
+            a.out[k] = (float)(x > 0.0 ? x : a.slope * x);
+        else
+            acc += (double)a.grad_score[a.eid ? a.eid[k] : k] * (x > 0.0 ? 1.0 : a.slope);
+    }
+    if (BACKWARD) {
+        acc = group_sum<double>(acc, lanes);       // every lane of the group takes part
+        if (l == 0 && r < a.num_rows && !wide) a.out[r] = (float)acc;
+    }
+    if (lanes < kFewLanes)
+        for (unsigned long long todo = __ballot(wide && l == 0); todo; todo &= todo - 1) {
+            const int w = (int)__ffsll((long long)todo) - 1;
+            ScoreRows<BACKWARD>{a, a.out}.whole(__builtin_amdgcn_readlane(b, w), __builtin_amdgcn_readlane(e, w), r - (threadIdx.x & (kWave - 1)) / lanes + w / lanes,
+                                                __shfl((float)mine, w));
+        }
+}
+
 template <bool BACKWARD>
 __global__ __launch_bounds__(256) void k_edge_score_short(const ScoreArgs a, int rows)
 {
@@ -721,11 +742,14 @@ void launch_score(const ScoreArgs &a, int64_t nnz, hipStream_t s)
 {
     const int64_t mean = nnz / (a.num_rows > 0 ? a.num_rows : 1);
     // Destinations: 64 rows to a wavefront, if that leaves 2 048 of them.  Sources come in order of their first appearance, the much
-    // used ones next to each other, and their rows are shorter: 16, or 8.  us with 64 / 32 / 16 / 8 rows, 8 lanes per row as above:
+    // used ones next to each other, and their rows are shorter: 16, or groups of 8 lanes.  us with 64 / 32 / 16 / 8 rows, 8 lanes per row as above:
     // 1.15 M sources 67 / 51 / 49 / 66 (60);  299 K 31 / 20 / 13 / 17 (17);  191 K 15 / 6.9 / 7.3 / 10 (6.3);  107 K, up to 616 edges,
-    // 46 / 46 / 28 / 20 (23)
+    // 46 / 46 / 28 / 20 (23; 11 with its
+    // long rows left to wavefronts)
     const int rows = a.eid ? walk_rows_per_wave(a.num_rows, mean, 16, 8192) : walk_rows_per_wave(a.num_rows, mean, kWave, 2048);
-    if (mean < kShortMean)
+    if (mean < kShortMean && rows <= kGroupRows)
+        hipLaunchKernelGGL((k_edge_score<8, BACKWARD>), dim3((unsigned)ceil_div(a.num_rows * 8, 256)), dim3(256), 0, s, a);
+    else if (mean < kShortMean)
         hipLaunchKernelGGL(k_edge_score_short<BACKWARD>, dim3(walk_blocks(a.num_rows, rows)), dim3(256), 0, s, a, rows);
     else if (mean < 96)
         hipLaunchKernelGGL((k_edge_score<32, BACKWARD>), dim3((unsigned)ceil_div(a.num_rows * 32, 256)), dim3(256), 0, s, a);
