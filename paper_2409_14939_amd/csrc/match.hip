@@ -81,20 +81,38 @@ __global__ __launch_bounds__(kScanBlock) void k_match_scan(MatchArgs a)
     if (threadIdx.x == 0) a.result[0] = total;
 }
 
-// SUM: the block counts are not scanned yet.
+// SUM: the block counts are not scanned yet.  Four positions per thread, loaded before the counts: bound by latency, 1.15 M
+// positions, 40 % misses, one position per thread 11.6 us, so 9.8.
+constexpr int kRankThreads = kScanBlock / 4;
 template <bool SUM>
-__global__ __launch_bounds__(kScanBlock) void k_match_rank(MatchArgs a)
+__global__ __launch_bounds__(kRankThreads) void k_match_rank(MatchArgs a)
 {
-    const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-    const bool miss = i < a.n_new && a.src_row[i] < 0;
-    const int base = SUM ? sum_before(a.block_cnt, blockIdx.x) : a.block_cnt[blockIdx.x];
+    const int64_t i0 = ((int64_t)blockIdx.x * kRankThreads + threadIdx.x) * 4;
+    bool miss[4];
+    int64_t gid[4];
+    int c = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t i = i0 + u < a.n_new ? i0 + u : a.n_new - 1;          // past the end: the last one again
+        miss[u] = a.src_row[i] < 0;
+        gid[u] = a.new_gid[i];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        miss[u] = miss[u] && i0 + u < a.n_new;
+        c += miss[u];
+    }
+    const int base = SUM ? sum_before<kRankThreads>(a.block_cnt, blockIdx.x) : a.block_cnt[blockIdx.x];
     int k;
-    const int mine = block_exclusive_scan(miss ? 1 : 0, base, k);
+    const int mine = block_exclusive_scan(c, base, k);
     if (SUM && threadIdx.x == 0 && (int)blockIdx.x == a.nblocks - 1) a.result[0] = base + mine;
-    if (miss) {
-        a.src_row[i] = -1 - k;
-        a.load_pos[k] = (int32_t)i;
-        a.load_gid[k] = a.new_gid[i];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if (!miss[u]) continue;
+        a.src_row[i0 + u] = -1 - k;
+        a.load_pos[k] = (int32_t)(i0 + u);
+        a.load_gid[k] = gid[u];
+        ++k;
     }
 }
 
@@ -387,11 +405,11 @@ fastgl_status fastgl_match(const int64_t *prev_gid, int64_t n_prev, const int64_
         hipLaunchKernelGGL(k_match_probe, dim3((unsigned)a.nblocks), dim3(kScanBlock), 0, s, a);
         FASTGL_LAUNCH_CHECK("fastgl_match (probe)");
         if (a.nblocks <= kSumBlocks) {
-            hipLaunchKernelGGL(k_match_rank<true>, dim3((unsigned)a.nblocks), dim3(kScanBlock), 0, s, a);
+            hipLaunchKernelGGL(k_match_rank<true>, dim3((unsigned)a.nblocks), dim3(kRankThreads), 0, s, a);
         } else {
             hipLaunchKernelGGL(k_match_scan, dim3(1), dim3(kScanBlock), 0, s, a);
             FASTGL_LAUNCH_CHECK("fastgl_match (scan)");
-            hipLaunchKernelGGL(k_match_rank<false>, dim3((unsigned)a.nblocks), dim3(kScanBlock), 0, s, a);
+            hipLaunchKernelGGL(k_match_rank<false>, dim3((unsigned)a.nblocks), dim3(kRankThreads), 0, s, a);
         }
         FASTGL_LAUNCH_CHECK("fastgl_match (rank)");
     }
