@@ -116,3 +116,14 @@ def test_match_full_size_minibatches():
     benchmark times."""
     a, b = bg.minibatch_node_sets(2, 2000)
     check_match(a, b, "config2 mini-batches")
+
+
+@pytest.mark.parametrize("n_new", [1, 2, 3, 4, 6, 1023, 1024, 1025, 1026, 2047, 4096 * 1024 + 1])
+def test_match_ranks_at_every_remainder(n_new):
+    """Misses are ranked four positions to a thread, 1 024 to a workgroup; beyond 4 096 workgroups their counts are scanned
+    by a launch of their own."""
+    rng = np.random.default_rng(n_new)
+    new = 5 + 3 * rng.permutation(n_new).astype(np.int64)
+    prev = rng.choice(new, n_new // 3, replace=False)
+    check_match(prev, new, "remainders")
+    check_match(prev + 1, new, "all missed")
