@@ -81,9 +81,9 @@ __global__ __launch_bounds__(256) void k_idmap_insert_min(IdmapArgs a)
         atomicAdd(&a.result[1], 1);
     } else {
         int32_t q;
-        const uint32_t slot = claim_slot(a.table, gid, (int32_t)p, IdAt{a}, q, p >= a.n_dst);
+        const uint32_t slot = claim_slot(a.table, gid, id_hash(gid), (int32_t)p, IdAt{a}, q, p >= a.n_dst);
         if (q > (int32_t)p) {
-            q = a.table.position(atomicMin(&a.table.slot[slot], a.table.tag(gid) | (int32_t)p));
+            q = a.table.position(atomicMin(&a.table.slot[slot], a.table.tag(id_hash(gid)) | (int32_t)p));
             if (q > (int32_t)p) a.displaced[q] = 1;
         }
         if (q >= (int32_t)p)
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void k_idmap_fused_dst(IdmapArgs a)
     if (p >= a.n_dst) return;
     const int64_t gid = a.dst_gid[p];
     int32_t q = kEmptySlot;
-    if (gid >= 0) claim_slot(a.table, gid, (int32_t)p, IdAt{a}, q, false);
+    if (gid >= 0) claim_slot(a.table, gid, id_hash(gid), (int32_t)p, IdAt{a}, q, false);
     if (q == (int32_t)p)
         a.unique_gid[p] = gid;
     else
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kScanBlock) void k_idmap_fused_nbr(IdmapArgs a)
     const int64_t gid = active ? a.nbr_gid[e] : -1;
     const int32_t p = (int32_t)(a.n_dst + e);
     int32_t q = kEmptySlot;
-    if (gid >= 0) claim_slot(a.table, gid, p, IdAt{a}, q, true);
+    if (gid >= 0) claim_slot(a.table, gid, id_hash(gid), p, IdAt{a}, q, true);
     const bool fresh = gid >= 0 && q == p;
     if (active) {
         a.ref[e] = q >= (int32_t)a.n_dst && !fresh ? q - (int32_t)a.n_dst : kNoSlot;

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void k_match_insert_prev(MatchArgs a)
     if (j >= a.n_prev) return;
     const int64_t gid = a.prev_gid[j];
     int32_t q = kEmptySlot;
-    if (gid >= 0) claim_slot(a.table, gid, (int32_t)j, GidAt{a.prev_gid}, q, false);
+    if (gid >= 0) claim_slot(a.table, gid, id_hash(gid), (int32_t)j, GidAt{a.prev_gid}, q, false);
     if (q != (int32_t)j) atomicAdd(&a.result[1], 1);          // negative or repeated ID
 }
 
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void k_marks_insert(OverlapArgs a)
     const int64_t gid = a.gid[p];
     if (gid < 0) return;
     int32_t q;
-    const uint32_t slot = claim_slot(a.table, gid, (int32_t)p, GidAt{a.gid}, q, b > 0);
+    const uint32_t slot = claim_slot(a.table, gid, near_hash(gid), (int32_t)p, GidAt{a.gid}, q, b > 0);
     if (q != (int32_t)p) a.marks[(size_t)slot * sizeof(MARK) + b] = 1;
 }
 

@@ -11,7 +11,7 @@
 //   k_overlap_bucket  a bucket's distinct IDs with a bit per mini-batch that holds them; the pairs they add up to
 //   k_overlap_sum     adds up the buckets
 //
-// The hash is a multiplication by an odd number, one to one on 64 bits.  Its upper bits are the bucket; the others, shifted up,
+// The hash (near_hash) is one to one on 64 bits.  Its upper bits are the bucket; the others, shifted up,
 // leave as many low bits free: an item is the rest of the hash and the mini-batch in 8 bytes, a slot of the table the rest of
 // the hash and the mask of the mini-batches.  An empty slot is 0 (a mask never is).
 //
@@ -58,8 +58,6 @@ struct BucketArgs {
     int32_t *violations;
 };
 
-__device__ __forceinline__ uint64_t hash_of(int64_t gid) { return (uint64_t)gid * 0x9E3779B97F4A7C15ull; }
-
 // Negative IDs are in no bucket.
 __global__ __launch_bounds__(kHistThreads) void k_overlap_hist(BucketArgs a)
 {
@@ -78,7 +76,7 @@ __global__ __launch_bounds__(kHistThreads) void k_overlap_hist(BucketArgs a)
         }
 #pragma unroll
         for (int u = 0; u < kBatch; ++u)
-            if (i0 + (int64_t)u * kHistThreads < end && gid[u] >= 0) atomicAdd(&h[hash_of(gid[u]) >> (64 - a.bits)], 1);
+            if (i0 + (int64_t)u * kHistThreads < end && gid[u] >= 0) atomicAdd(&h[near_hash(gid[u]) >> (64 - a.bits)], 1);
     }
     __syncthreads();
     for (int d = t; d < buckets; d += kHistThreads) a.cnt[(int64_t)blockIdx.x * buckets + d] = h[d];
@@ -159,7 +157,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_overlap_split(BucketArgs a)
             int b = 0;
 #pragma unroll
             for (int x = 1; x < kMostBatches; ++x) b += x < a.n && p >= a.offsets[x];
-            const uint64_t h = hash_of(gid[i]);
+            const uint64_t h = near_hash(gid[i]);
             d[i] = p < end && gid[i] >= 0 ? (int)(h >> (64 - a.bits)) : -1;
             item[i] = h << a.bits | (unsigned)b;
             rank[i] = d[i] >= 0 ? atomicAdd(&cnt[d[i]], 1) : 0;
@@ -194,87 +192,89 @@ __global__ __launch_bounds__(kSplitThreads) void k_overlap_split(BucketArgs a)
     }
 }
 
-// A finaliser of 64 bits, one to one: which of the passes an ID belongs to.
-__device__ __forceinline__ uint64_t mixed(uint64_t x)
-{
-    x ^= x >> 32;
-    x *= 0xD6E8FEB86659FD93ull;
-    x ^= x >> 32;
-    x *= 0xD6E8FEB86659FD93ull;
-    return x ^ x >> 32;
-}
-
-// A bucket of more distinct IDs than a table may hold is put together again in passes, each of which takes the IDs of one class
-// of a second hash, two classes and then twice as many while one of them is still too large (both hashes are one to one, so that
-// distinct IDs do come apart).
+// A bucket of more distinct IDs than a table may hold (IDs that were chosen for their hashes) is put together in passes: what finds no
+// room and is not in the table either moves to the front of the bucket's items, which are the next pass's.  A pass takes more than
+// kMostHeld distinct IDs off, whatever their hashes: n of them in one bucket cost this workgroup n / kMostHeld passes over half of
+// them on average.
 template <int NB, int BITS>
 __global__ __launch_bounds__(kBucketThreads) void k_overlap_bucket(BucketArgs a)
 {
-    constexpr int PAIRS = NB * (NB + 1) / 2, kSlots = 1 << BITS, kMostHeld = most_held(BITS);
+    constexpr int PAIRS = NB * (NB + 1) / 2, kSlots = 1 << BITS, kMostHeld = most_held(BITS), kBatch = 8;
     __shared__ __align__(16) unsigned long long table[kSlots];
-    __shared__ int held, sum[PAIRS];
-    const int t = threadIdx.x, items = a.tot[blockIdx.x];
-    const unsigned long long *in = a.items + a.first[blockIdx.x];
-    int lg = 0;
-    const bool may_fill = items > kMostHeld;
+    __shared__ int held, left, sum[PAIRS];
+    const int t = threadIdx.x;
+    unsigned long long *in = a.items + a.first[blockIdx.x];
+    int items = a.tot[blockIdx.x];
     int c[PAIRS];
-    bool again = true;
-    while (again) {
 #pragma unroll
-        for (int k = 0; k < PAIRS; ++k) c[k] = 0;
-        again = false;
-        for (uint64_t pass = 0; pass < (uint64_t)1 << lg && !again; ++pass) {
-            for (int s = t; s < kSlots / 2; s += kBucketThreads) reinterpret_cast<uint4 *>(table)[s] = make_uint4(0, 0, 0, 0);
-            if (t == 0) held = 0;
-            __syncthreads();
-            constexpr int kBatch = 8;
-            bool full = false;
-            for (int i0 = t; i0 < items && !full; i0 += kBatch * kBucketThreads) {
-                unsigned long long w[kBatch];
+    for (int k = 0; k < PAIRS; ++k) c[k] = 0;
+    while (items > 0) {
+        for (int s = t; s < kSlots / 2; s += kBucketThreads) reinterpret_cast<uint4 *>(table)[s] = make_uint4(0, 0, 0, 0);
+        if (t == 0) held = left = 0;
+        __syncthreads();
+        const bool may_fill = items > kMostHeld;
+        bool full = false;
+        for (int i0 = t; i0 < items && !full; i0 += kBatch * kBucketThreads) {
+            unsigned long long w[kBatch];
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const int i = i0 + u * kBucketThreads;
-                    w[u] = in[i < items ? i : items - 1];
-                }
+            for (int u = 0; u < kBatch; ++u) {
+                const int i = i0 + u * kBucketThreads;
+                w[u] = in[i < items ? i : items - 1];
+            }
 #pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const unsigned long long key = w[u] & ~(unsigned long long)0xFF, bit = 1ull << (w[u] & 7);
-                    bool todo = i0 + u * kBucketThreads < items && !full;
-                    if (may_fill) todo = todo && (mixed(key) & (((uint64_t)1 << lg) - 1)) == pass;
-                    uint32_t slot = (uint32_t)(w[u] >> (64 - BITS));
-                    while (todo) {
-                        unsigned long long v = *(volatile unsigned long long *)&table[slot];
+            for (int u = 0; u < kBatch; ++u) {
+                const unsigned long long key = w[u] & ~(unsigned long long)0xFF, bit = 1ull << (w[u] & 7);
+                const bool todo = i0 + u * kBucketThreads < items && !full;
+                uint32_t slot = (uint32_t)(w[u] >> (64 - BITS));
+                while (todo) {
+                    unsigned long long v = *(volatile unsigned long long *)&table[slot];
+                    if (v == 0) {
+                        v = atomicCAS(&table[slot], 0ull, key | bit);
                         if (v == 0) {
-                            v = atomicCAS(&table[slot], 0ull, key | bit);
-                            if (v == 0) {
-                                if (may_fill) full = atomicAdd(&held, 1) >= kMostHeld;
-                                break;
-                            }
-                        }
-                        if ((v ^ key) <= 0xFF) {
-                            if (!(v & bit)) atomicOr(&table[slot], bit);
+                            if (may_fill) full = atomicAdd(&held, 1) >= kMostHeld;
                             break;
                         }
-                        slot = (slot + 1) & (kSlots - 1);
                     }
+                    if ((v ^ key) <= 0xFF) {
+                        if (!(v & bit)) atomicOr(&table[slot], bit);
+                        break;
+                    }
+                    slot = (slot + 1) & (kSlots - 1);
                 }
             }
-            __syncthreads();
-            if (may_fill && held > kMostHeld) {          // the same for the workgroup
-                again = true;
-                ++lg;
-            } else {
-                for (int s = t; s < kSlots; s += kBucketThreads) {
-                    const unsigned m = (unsigned)table[s];
-                    int k = 0;
-#pragma unroll
-                    for (int x = 0; x < NB; ++x)
-#pragma unroll
-                        for (int y = x; y < NB; ++y, ++k) c[k] += (m >> x) & (m >> y) & 1;
-                }
-            }
-            __syncthreads();                 // the table and `held` are the next pass's
         }
+        __syncthreads();
+        const bool over = may_fill && held > kMostHeld;       // the same for the workgroup; no thread adds to the table any more
+        for (int base = 0; over && base < items; base += kBatch * kBucketThreads) {
+            unsigned long long w[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int i = base + u * kBucketThreads + t;
+                w[u] = in[i < items ? i : items - 1];
+            }
+            __syncthreads();                 // up to here the items have been read: there is room for as many
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                if (base + u * kBucketThreads + t >= items) continue;
+                const unsigned long long key = w[u] & ~(unsigned long long)0xFF, bit = 1ull << (w[u] & 7);
+                uint32_t slot = (uint32_t)(w[u] >> (64 - BITS));
+                unsigned long long v;
+                while ((v = *(volatile unsigned long long *)&table[slot]) != 0 && (v ^ key) > 0xFF) slot = (slot + 1) & (kSlots - 1);
+                if (v == 0) in[atomicAdd(&left, 1)] = w[u];
+                else if (!(v & bit)) atomicOr(&table[slot], bit);
+            }
+        }
+        __syncthreads();
+        for (int s = t; s < kSlots; s += kBucketThreads) {
+            const unsigned m = (unsigned)table[s];
+            int k = 0;
+#pragma unroll
+            for (int x = 0; x < NB; ++x)
+#pragma unroll
+                for (int y = x; y < NB; ++y, ++k) c[k] += (m >> x) & (m >> y) & 1;
+        }
+        items = left;                        // 0 but after an overflow
+        __syncthreads();                     // the table, `held` and `left` are the next pass's
     }
     if (t < PAIRS) sum[t] = 0;
     __syncthreads();

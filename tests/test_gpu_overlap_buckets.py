@@ -10,7 +10,7 @@ from paper_2409_14939_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 LINE = 1 << 16                   # IDs from which the buckets are used
-ODD = 0x9E3779B97F4A7C15         # of the hash
+ODD = np.uint64(0x9E3779B97F4A7C15)     # of near_hash
 
 
 def counted(sets):
@@ -31,8 +31,22 @@ def window(rng, sizes, span):
     return sets
 
 
+def ids_of(hashes):
+    """The IDs with these hashes (uint64): near_hash backwards."""
+    x = hashes * np.uint64(pow(int(ODD), -1, 2 ** 64))
+    far = (x >> np.uint64(22)) * ODD
+    return (x ^ (far ^ far >> np.uint64(32)) * ODD >> np.uint64(42)).astype(np.int64)
+
+
+def crowd(rng, count, bits):
+    """Distinct IDs whose hashes agree in the upper `bits` bits, in random order."""
+    h = rng.integers(0, 2 ** (64 - bits), size=3 * count).astype(np.uint64) | np.uint64(0xA5 << (64 - bits))
+    ids = np.unique(ids_of(h))
+    return rng.permutation(ids[ids >= 0])[:count]
+
+
 @pytest.mark.parametrize("total,n", [(LINE - 1, 4), (LINE, 4), (LINE + 1, 1), (2400 * 256, 2), (2400 * 256 + 1, 8), (2400 * 512 + 1, 5),
-                                     (2400 * 1024 + 1, 3), (2560 * 2048, 4), (2560 * 2048 + 1, 8)])
+                                     (2400 * 1024 + 1, 3), (2560 * 2048, 4), (2560 * 2048 + 1, 8), (2560 * 2048 + 1, 3), (12 << 20, 4), ((12 << 20) + 1, 4)])
 def test_sizes(total, n):
     rng = np.random.default_rng(total + n)
     cuts = np.sort(rng.integers(total // (2 * n), total, size=n - 1)) if n > 1 else np.array([], np.int64)
@@ -43,16 +57,34 @@ def test_sizes(total, n):
     assert violations == 0 and np.array_equal(counts, oracle.overlap_matrix(sets))
 
 
-@pytest.mark.parametrize("in_one", [3000, 3100, 30_000])
+@pytest.mark.parametrize("in_one", [3000, 3072, 3073, 3100, 30_000])
 def test_a_bucket_that_overflows(in_one):
     """Distinct IDs whose hashes agree in the upper 8 bits, all in one bucket: within a table's room, just beyond, far beyond."""
     rng = np.random.default_rng(in_one)
-    back = pow(ODD, -1, 2 ** 64)
-    same = np.unique([x for x in ((0xA5 << 56 | int(v)) * back % 2 ** 64 for v in rng.integers(0, 2 ** 56, size=3 * in_one)) if x < 2 ** 63])
-    same = rng.permutation(same.astype(np.int64))[:in_one]
+    same = crowd(rng, in_one, 8)
     others = rng.permutation(np.unique(rng.integers(0, 2 ** 40, size=LINE)))
     sets = [np.concatenate([same, others[:100_000]]), np.concatenate([others[50_000:250_000], same[: in_one // 2]])]
     sets[1] = np.concatenate([sets[1], 2 ** 50 + np.arange(max(0, LINE - sum(map(len, sets))))])
+    counts, violations = counted(sets)
+    assert violations == 0 and np.array_equal(counts, oracle.overlap_matrix(sets))
+
+
+@pytest.mark.parametrize("in_one,bits,total,n", [(10_000, 8, LINE, 8), (7000, 11, 2560 * 2048 + 1, 3), (20_000, 11, 2560 * 2048 + 1, 8)])
+def test_overflow_with_more_mini_batches_and_large_tables(in_one, bits, total, n):
+    """Every mini-batch holds its own half of the crowded IDs; a table holds 3 072 of them, a large one 7 168."""
+    rng = np.random.default_rng(in_one + n)
+    same = crowd(rng, in_one, bits)
+    pool = rng.permutation(total)[: 2 * total // n] + 2 ** 50
+    sets = [np.concatenate([rng.permutation(same)[: in_one // 2], rng.permutation(pool)[: total // n - in_one // 2 + 1]]) for _ in range(n)]
+    assert sum(map(len, sets)) >= total
+    counts, violations = counted(sets)
+    assert violations == 0 and np.array_equal(counts, oracle.overlap_matrix(sets))
+
+
+@pytest.mark.parametrize("stride", [832_040, 14_930_352, 267_914_296, 2 ** 20, 2 ** 40 + 1])
+def test_multiples_of_a_number(stride):
+    rng = np.random.default_rng(7)
+    sets = [rng.permutation(32_770)[:16_385].astype(np.int64) * stride for _ in range(4)]
     counts, violations = counted(sets)
     assert violations == 0 and np.array_equal(counts, oracle.overlap_matrix(sets))
 
