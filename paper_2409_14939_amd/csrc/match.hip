@@ -148,11 +148,15 @@ __global__ __launch_bounds__(256) void k_assemble_rows(const char *__restrict__ 
 
 static_assert(sizeof(MaskSlot) <= kSlotRoom, "an entry fits its slot's room");
 constexpr int kMarkBatches = 8;
-// Windows of this many IDs go through buckets.  us, one table / buckets, IDs below 2.4 M and of 40 bits: 4 mini-batches of 20 000
-// 36 / 28 and 29 / 29, 66 000 44 / 32 and 40 / 32, 200 000 66 / 38 and 66 / 41, 400 000 97 / 44 and 103 / 51, 1.15 M 235 / 84
-// and 226 / 112, 2.4 M 493 / 147 and 433 / 204;  8 of 66 000 71 / 47, of 1.15 M 519 / 192;  2 of 140 000 44 / 31.  Beyond the
-// upper line buckets of IDs that do not repeat outgrow their tables.
-constexpr int64_t kBucketIds = (int64_t)1 << 16, kMostBucketIds = (int64_t)12 << 20;
+// Windows of this many IDs go through buckets: five launches, against two and a fill that all the random accesses of few IDs
+// hide behind.  us, one table / buckets, IDs that lie close together, IDs below 4 times a mini-batch's number, and of 40 bits:
+//   2 mini-batches   66 000 15 / 25, 19 / 25, 23 / 25;  260 000 25 / 28, 29 / 29, 36 / 29;  400 000 31 / 32, 36 / 36, 42 / 33;  800 000 48 / 37, 56 / 40, 62 / 38
+//   4                66 000 16 / 25, 16 / 25, 21 / 25;  260 000 27 / 28, 28 / 29, 34 / 28;  400 000 32 / 31, 35 / 32, 39 / 32;  800 000 51 / 36, 55 / 38, 57 / 36
+//   8                66 000 26 / 33, 26 / 34, 29 / 34;  190 000 36 / 36, 36 / 36, 40 / 35;  400 000 46 / 39, 51 / 39, 52 / 39
+// A program's window of two mini-batches, matches and assembly with it: 67 000 IDs 80 / 87, 264 000 102 / 105, 439 000 122 / 123,
+// 502 000 150 / 146;  of three 503 000 166 / 160, 752 000 234 / 218.  1.15 M IDs a mini-batch: 4 of them 235 / 84 and, of 40 bits, 226 / 101,
+// 8 519 / 192.  Beyond the upper line buckets of IDs that do not repeat outgrow their tables.
+constexpr int64_t kBucketIds = (int64_t)7 << 16, kBucketIdsMany = (int64_t)3 << 16, kMostBucketIds = (int64_t)12 << 20;
 constexpr int kCountBlocks = 256;            // workgroups that read the marks: one per compute unit
 
 struct OverlapArgs {
@@ -520,7 +524,7 @@ fastgl_status fastgl_overlap_counts(const int64_t *gid, const int64_t *offsets_h
     hipStream_t s = (hipStream_t)stream;
     const dim3 g((unsigned)ceil_div(longest, 256), (unsigned)n);
     char *ws = (char *)workspace;
-    if (n <= kMarkBatches && total >= kBucketIds && total <= kMostBucketIds)
+    if (n <= kMarkBatches && total >= (n <= 4 ? kBucketIds : kBucketIdsMany) && total <= kMostBucketIds)
         return launch_overlap_buckets(gid, offsets_host, n, counts, violations, ws, workspace_bytes, s);
     if (n > kMarkBatches) {
         a.masks = (MaskSlot *)(ws + L.table);

@@ -9,7 +9,7 @@ import oracle
 from paper_2409_14939_amd import binding as B
 
 pytestmark = pytest.mark.gpu
-LINE = 1 << 16                   # IDs from which the buckets are used
+LINE, LINE_MANY = 7 << 16, 3 << 16   # IDs from which the buckets are used: up to four mini-batches, more
 ODD = np.uint64(0x9E3779B97F4A7C15)     # of near_hash
 
 
@@ -45,7 +45,7 @@ def crowd(rng, count, bits):
     return rng.permutation(ids[ids >= 0])[:count]
 
 
-@pytest.mark.parametrize("total,n", [(LINE - 1, 4), (LINE, 4), (LINE + 1, 1), (2400 * 256, 2), (2400 * 256 + 1, 8), (2400 * 512 + 1, 5),
+@pytest.mark.parametrize("total,n", [(LINE - 1, 4), (LINE, 4), (LINE + 1, 1), (LINE_MANY - 1, 5), (LINE_MANY, 8), (LINE_MANY, 5), (2400 * 256, 2), (2400 * 256 + 1, 8), (2400 * 512 + 1, 5),
                                      (2400 * 1024 + 1, 3), (2560 * 2048, 4), (2560 * 2048 + 1, 8), (2560 * 2048 + 1, 3), (12 << 20, 4), ((12 << 20) + 1, 4)])
 def test_sizes(total, n):
     rng = np.random.default_rng(total + n)
@@ -69,7 +69,7 @@ def test_a_bucket_that_overflows(in_one):
     assert violations == 0 and np.array_equal(counts, oracle.overlap_matrix(sets))
 
 
-@pytest.mark.parametrize("in_one,bits,total,n", [(10_000, 8, LINE, 8), (7000, 11, 2560 * 2048 + 1, 3), (20_000, 11, 2560 * 2048 + 1, 8)])
+@pytest.mark.parametrize("in_one,bits,total,n", [(10_000, 8, LINE_MANY, 8), (7000, 11, 2560 * 2048 + 1, 3), (20_000, 11, 2560 * 2048 + 1, 8)])
 def test_overflow_with_more_mini_batches_and_large_tables(in_one, bits, total, n):
     """Every mini-batch holds its own half of the crowded IDs; a table holds 3 072 of them, a large one 7 168."""
     rng = np.random.default_rng(in_one + n)
@@ -81,10 +81,11 @@ def test_overflow_with_more_mini_batches_and_large_tables(in_one, bits, total, n
     assert violations == 0 and np.array_equal(counts, oracle.overlap_matrix(sets))
 
 
+@pytest.mark.parametrize("count", [16_385, LINE // 4])
 @pytest.mark.parametrize("stride", [832_040, 14_930_352, 267_914_296, 2 ** 20, 2 ** 40 + 1])
-def test_multiples_of_a_number(stride):
+def test_multiples_of_a_number(stride, count):
     rng = np.random.default_rng(7)
-    sets = [rng.permutation(32_770)[:16_385].astype(np.int64) * stride for _ in range(4)]
+    sets = [rng.permutation(2 * count)[:count].astype(np.int64) * stride for _ in range(4)]
     counts, violations = counted(sets)
     assert violations == 0 and np.array_equal(counts, oracle.overlap_matrix(sets))
 
