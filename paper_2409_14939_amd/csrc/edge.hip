@@ -15,8 +15,8 @@
 //         13 (96) 122 -> 122 -> 75;  33 (299) 127 -> 127 -> 121;  64 (140) 140 -> 140 -> 130;  256 (582) 582 -> 582 -> 528
 //   bf16  4 (98) 72 -> 50 -> 43;  7 (66) 66 -> 73 -> 54;  9 (69) 78 -> 78 -> 58;  25 (105) 115 -> 115 -> 76;  100 (156) 152 -> 152 -> 140
 //
-// Softmax: rows of up to 24 edges on average are walked many to a wavefront (walk_short_rows); of others, and of few, a group of 8, 32 or 64 lanes
-// walks one destination row three times (maximum, sum of exponentials, write).  Rows longer than kLongRow are taken by whole workgroups of the
+// Softmax: many rows of fewer than 10 edges on average are walked 32 to a wavefront (walk_short_rows); of others a group of 8, 32 or 64
+// lanes walks one destination row three times (maximum, sum of exponentials, write).  Rows longer than kLongRow are taken by whole workgroups of the
 // same launch that look for them (softmax_long_rows).  exp and the sums are fp64, so the result is the correctly
 // rounded quotient up to one unit in the last place.  Forward, us: 2.56 M edges in rows of 5, none long: 34 (a queue
 // of long rows with launches of its own: 40; no workgroups that look: 32); 32 neighbouring rows of 20 000 among short
@@ -231,19 +231,30 @@ __global__ __launch_bounds__(256) void k_edge_dot(const DotArgs a)
     }
 }
 
-// ---------------------------------------------------------------- short rows, up to 64 to a wavefront
-// What the kernels on rows of a few edges are bound by is latency and instructions: with 8 lanes per row most lanes are idle, and every
-// 8 edges of a long row are a chain of dependent loads.  Here a wavefront takes 16 to 64 neighbouring rows.  Their edges lie one after the
-// other: all lanes load them, in order, into LDS; then 1 to 4 lanes put their row together there, and per-edge results go out in
-// order again.  Rows of more than kLaneRow edges per such lane are put together by the wavefront, one after the other.  Rows that do not
-// fit LDS together are taken in several goes; one that does not fit alone is left to op.whole().
-// us, 8 lanes per row / this: 2.56 M edges, 513 K rows of 5: softmax 24 / 16, its gradient 16.3 / 12.8, scores 18.0 / 15.5,
-// their gradient by destination 19.6 / 15.3;  819 K edges, rows of 20: 6.5 / 6.6, 5.0 / 5.2, 5.9 / 6.2, 5.4 / 5.8.
-constexpr int kLaneRow = 64;
-constexpr int kFewLanes = 32;        // groups of fewer lanes leave rows beyond kLaneRow to the wavefront
-constexpr int64_t kShortMean = 24;   // mean length of rows that are walked so
+// ---------------------------------------------------------------- short rows, many to a wavefront
+// What the kernels on rows of a few edges are bound by is latency and instructions: with 8 lanes per row most lanes are idle.  Here a
+// wavefront takes 16 or 32 neighbouring rows.  Their edges lie one after the other: all lanes load them, in order, into LDS; then 4 or 2
+// lanes put their row together there, and per-edge results go out in order again.  Rows of more than kLaneRow edges per such lane are
+// put together by the wavefront, one after the other; rows that do not fit LDS together are left to dense_sets.
+constexpr int kStage = 512;          // edges in LDS: 17 KB a workgroup, eight of them on a compute unit
+constexpr int kLaneRow = 16;
 constexpr int kWalkLoads = 4;        // edges in flight per lane
 constexpr int kWalkWaves = 4;        // of a workgroup
+constexpr int kRowsOfDst = 32, kRowsOfSrc = 16;      // of a wavefront: sources come in order of their first appearance, the much used ones together
+constexpr int kFewLanes = 32, kGroupRow = 64;        // groups of fewer lanes leave rows beyond kGroupRow edges to the wavefront
+
+// Blocks of fewer rows, and of more edges to a row, are left to groups of 8 lanes, whose kernels are shorter.  us, groups / walked, in
+// blocks of sampled neighbours, by number of destinations (their edges on average):
+//                           59 K (7)    98 K (7)    155 K (5)   229 K (5)    261 K (5)    513 K (5)     192 K (9)     133 K (15)
+//   softmax                 5.0 / 5.0   6.6 / 5.8   8.5 / 7.1   12.2 / 8.8   13.8 / 9.7   23.8 / 15.8   13.8 / 11.0   11.8 / 13.6
+//   its gradient            3.7 / 4.0   4.4 / 4.5   6.1 / 5.4   8.2 / 6.9    9.2 / 7.2    16.4 / 11.8   8.7 / 7.8     7.7 / 10.0
+//   scores                  3.1 / 4.0   4.4 / 5.0   5.4 / 5.6   7.6 / 8.3    9.1 / 8.3    17.8 / 15.4   11.5 / 11.8   12.0 / 14.0
+//   their gradient's sums   4.0 / 3.7   5.7 / 5.3   7.2 / 6.6   10.2 / 9.2   10.9 / 8.7   20.2 / 16.0   12.0 / 12.5   13.0 / 14.6
+// All neighbours of 1 M nodes, 6 edges on average and up to 1 900, in any order: 94 / 63, 55 / 38, 60 / 53, 62 / 45;  by degree:
+// 102 / 109, 77 / 71, 131 / 133, 95 / 97.  Sums of sources, by their number: 195 K (3) 14.7 / 15.3, 307 K (3) 17.0 / 17.6, 321 K (2)
+// 15.3 / 16.4, 345 K (1.5) 14.4 / 10.5, 375 K (3) 22.1 / 21.7, 442 K (2) 18.6 / 15.6, 732 K (2) 30.8 / 23.9, 1.15 M (2) 59.6 / 49.9;  all neighbours, 1 M
+// (6) 154 / 149, by degree 209 / 183, 754 K (7) 110 / 117, 524 K (8) 113 / 145.
+constexpr int64_t kShortMean = 10, kSoftmaxRows = (int64_t)3 << 15, kScoreRows = (int64_t)1 << 18, kShortSrcMean = 6, kScoreSources = (int64_t)1 << 18;
 
 // Rows whose lengths are a power of two start at different banks.
 __device__ __forceinline__ int stage_slot(int k) { return k + (k >> 4); }
@@ -255,66 +266,70 @@ __device__ __forceinline__ void stage_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Rows of a wavefront, 64 / rows lanes each: fewer where rows are longer, and where there were too few wavefronts.
-inline int walk_rows_per_wave(int64_t num_rows, int64_t mean, int most, int64_t waves)
-{
-    int rows = most;
-    while (rows > 8 && (rows * mean > 448 || num_rows < rows * waves)) rows >>= 1;
-    return rows;
-}
-// Blocks of so few rows that a wavefront would take 8 of them are left to groups of 8 lanes, whose kernels are shorter: 8 090 rows of
-// 10, softmax 3.9 us, 4.5 walked, its gradient 3.3 and 3.8, scores 3.6 and 4.0, their gradient 3.4 and 4.2.  Their rows beyond kLaneRow are the wavefront's, too: 30 000
-// rows, the longest of 13 405 edges, all rows by 8 lanes / so: softmax 58 / 35, its gradient 31 / 17, scores 372 / 43, their gradient 320 / 28.
-constexpr int kGroupRows = 8;
 inline unsigned walk_blocks(int64_t num_rows, int rows) { return (unsigned)ceil_div(num_rows, (int64_t)rows * kWalkWaves); }
 
-// Op: STAGE, edges of a go;  Word, what LDS holds of an edge;  load(k0, end, w): edges k0 + 64 i's;  own(r): what a row brings along;  row(st, lo, hi, r,
-// own, l, lanes): row r, edges lo .. hi - 1 of the stage, by a group of lanes, this one lane l of it;  whole(b, e, r, own): by all, from memory;
-// EDGES: result(word) goes to op.out[k] afterwards.
-template <class Op>
-__device__ __forceinline__ void walk_short_rows(const int32_t *__restrict__ rowptr, int64_t num_rows, int64_t first, int rows,
+// Sets of rows that do not fit LDS together: workgroups of the same launch look for them, each at sets that are far
+// apart (where rows are in order of their length thousands of long ones lie together), and take them by groups of 8 lanes.  The walk
+// alone took a block by degree, 8 edges on average, four times as long as the groups (258 / 62 us); with 512 such workgroups 74, with
+// 1 024 66, with 2 048 65.
+constexpr int kMostDense = 1024;
+inline int dense_seekers(int64_t nnz) { return (int)(nnz / kStage < kMostDense ? nnz / kStage : kMostDense); }
+
+// group(r, limit): row r < limit by 8 lanes.
+template <int ROWS, class Group>
+__device__ __forceinline__ void dense_sets(const int32_t *__restrict__ rowptr, int64_t num_rows, int seekers, const Group &group)
+{
+    __shared__ int32_t set[256];
+    __shared__ int n_dense;
+    const int64_t sets = (num_rows + ROWS - 1) / ROWS;
+    auto end_of = [&](int64_t at) { return (at + 1) * ROWS < num_rows ? (at + 1) * ROWS : num_rows; };
+    for (int64_t base = blockIdx.x; base < sets; base += 256 * (int64_t)seekers) {
+        if (threadIdx.x == 0) n_dense = 0;
+        __syncthreads();
+        const int64_t at = base + (int64_t)threadIdx.x * seekers;
+        if (at < sets && rowptr[end_of(at)] - rowptr[at * ROWS] > kStage) set[atomicAdd(&n_dense, 1)] = (int32_t)at;
+        __syncthreads();
+        const int n = n_dense;
+        for (int q = 0; q < n; ++q) group((int64_t)set[q] * ROWS + threadIdx.x / 8, end_of(set[q]));
+        __syncthreads();
+    }
+}
+
+// Op: Word, what LDS holds of an edge;  load(k0, end, w): edges k0 + 64 i's;  own(r): what a row
+// brings along;  row(st, lo, hi, r, own, l, lanes): row r, edges lo .. hi - 1 of LDS, by a group of lanes, this one lane l
+// of it;  EDGES: result(word) goes to op.out[k] afterwards.
+template <int ROWS, class Op>
+__device__ __forceinline__ void walk_short_rows(const int32_t *__restrict__ rowptr, int64_t num_rows, int64_t first,
                                                 typename Op::Word *st, const Op &op)
 {
+    static_assert(ROWS <= 32, "a set's rows have 8 lanes each in dense_sets");
     typedef typename Op::Word Word;
-    const int lane = threadIdx.x & (kWave - 1), lanes = kWave / rows, q = lane / lanes;
-    const int64_t limit = first + rows < num_rows ? first + rows : num_rows;
-    auto begin = [&](int64_t r) { return rowptr[r < limit ? r : limit]; };                // rows that there are not are empty
-    const int b = begin(first + lane), e = begin(first + lane + 1);                       // of row `lane`
-    const int qb = begin(first + q), qe = begin(first + q + 1);                           // of the row that the lane works on
+    constexpr int lanes = kWave / ROWS;
+    const int lane = threadIdx.x & (kWave - 1), q = lane / lanes;
+    const int64_t limit = first + ROWS < num_rows ? first + ROWS : num_rows;
+    const int base = rowptr[first], end = rowptr[limit];
+    if (end - base > kStage) return;         // dense_sets has them
     const int64_t r = first + q;
+    const int qb = rowptr[r < limit ? r : limit], qe = rowptr[r + 1 < limit ? r + 1 : limit];     // rows that there are not are empty
     const float own = op.own(r < limit ? r : limit - 1);
-    int s = 0;
-    while (s < rows) {
-        const int base = __builtin_amdgcn_readlane(b, s);
-        const unsigned long long beyond = __ballot(lane >= s && lane < rows && e - base > Op::STAGE);
-        const int n = beyond ? (int)__ffsll((long long)beyond) - 1 : rows;
-        if (n == s) {
-            op.whole(base, __builtin_amdgcn_readlane(e, s), first + s, __shfl(own, s * lanes));
-            ++s;
-            continue;
-        }
-        const int end = __builtin_amdgcn_readlane(e, n - 1);
-        for (int k0 = base + lane; k0 - lane < end; k0 += kWave * kWalkLoads) {
-            Word w[kWalkLoads];
-            op.load(k0, end, w);             // no branch around the loads: they go out together
+    for (int k0 = base + lane; k0 - lane < end; k0 += kWave * kWalkLoads) {
+        Word w[kWalkLoads];
+        op.load(k0, end, w);                 // no branch around the loads: they go out together
 #pragma unroll
-            for (int i = 0; i < kWalkLoads; ++i)
-                if (k0 + i * kWave < end) st[stage_slot(k0 + i * kWave - base)] = w[i];
-        }
-        stage_fence();
-        const bool mine = q >= s && q < n && r < limit, wide = qe - qb > kLaneRow * lanes;
-        if (mine && !wide) op.row(st, qb - base, qe - base, r, own, lane % lanes, lanes);
-        for (unsigned long long todo = __ballot(mine && wide && lane % lanes == 0); todo; todo &= todo - 1) {
-            const int w = (int)__ffsll((long long)todo) - 1;
-            op.row(st, __builtin_amdgcn_readlane(qb, w) - base, __builtin_amdgcn_readlane(qe, w) - base, first + w / lanes,
-                   __shfl(own, w), lane, kWave);
-        }
-        stage_fence();
-        if (Op::EDGES)
-            for (int k = base + lane; k < end; k += kWave) op.out[k] = op.result(st[stage_slot(k - base)]);
-        stage_fence();
-        s = n;
+        for (int i = 0; i < kWalkLoads; ++i)
+            if (k0 + i * kWave < end) st[stage_slot(k0 + i * kWave - base)] = w[i];
     }
+    stage_fence();
+    const bool mine = r < limit, wide = qe - qb > kLaneRow * lanes;
+    if (mine && !wide) op.row(st, qb - base, qe - base, r, own, lane % lanes, lanes);
+    for (unsigned long long todo = __ballot(mine && wide && lane % lanes == 0); todo; todo &= todo - 1) {
+        const int w = (int)__ffsll((long long)todo) - 1;
+        op.row(st, __builtin_amdgcn_readlane(qb, w) - base, __builtin_amdgcn_readlane(qe, w) - base, first + w / lanes,
+               __shfl(own, w), lane, kWave);
+    }
+    stage_fence();
+    if (Op::EDGES)
+        for (int k = base + lane; k < end; k += kWave) op.out[k] = op.result(st[stage_slot(k - base)]);
 }
 
 // ---------------------------------------------------------------- softmax
@@ -405,17 +420,13 @@ __device__ __forceinline__ void softmax_long_rows(const SoftmaxArgs &a)
     }
 }
 
+// Row u < limit by a group of lanes, rows up to kLongRow; consecutive rows by a wavefront's groups.
 template <int lanes>
-__global__ __launch_bounds__(256) void k_edge_softmax_rows(const SoftmaxArgs a)
+__device__ __forceinline__ void softmax_group_rows(const SoftmaxArgs &a, int64_t u, int64_t limit)
 {
-    if ((int)blockIdx.x < a.seekers) {
-        softmax_long_rows(a);
-        return;
-    }
-    const int64_t u = ((int64_t)(blockIdx.x - a.seekers) * blockDim.x + threadIdx.x) / lanes;
     const int l = threadIdx.x % lanes;
     int b = 0, e = 0;
-    if (u < a.num_dst) {
+    if (u < limit) {
         b = a.indptr[u];
         e = a.indptr[u + 1];
         if (e - b > kLongRow) e = b;
@@ -427,18 +438,40 @@ __global__ __launch_bounds__(256) void k_edge_softmax_rows(const SoftmaxArgs a)
         else
             softmax_row_fwd(a.in0, a.out, beg, end, lane, n);
     };
-    const bool wide = lanes < kFewLanes && e - b > kLaneRow;
+    bool wide = lanes < kFewLanes && e - b > kGroupRow;
+    unsigned long long rows = lanes < kFewLanes ? __ballot(wide && l == 0) : 0;
+    if (rows) {              // one after the other, unless the groups are done sooner (400 K rows by degree, gradient: 67 -> 55 us)
+        int longest = 0, all = 0;
+        for (unsigned long long todo = rows; todo; todo &= todo - 1) {
+            const int w = (int)__ffsll((long long)todo) - 1, len = __builtin_amdgcn_readlane(e, w) - __builtin_amdgcn_readlane(b, w);
+            longest = len > longest ? len : longest;
+            all += len + 2 * kWave;
+        }
+        if (longest * (kWave / lanes) <= all) {
+            wide = false;
+            rows = 0;
+        }
+    }
     if (!wide) walk(b, e, l, lanes);
     if (lanes < kFewLanes)
-        for (unsigned long long todo = __ballot(wide && l == 0); todo; todo &= todo - 1) {
+        for (unsigned long long todo = rows; todo; todo &= todo - 1) {
             const int w = (int)__ffsll((long long)todo) - 1;
             walk(__builtin_amdgcn_readlane(b, w), __builtin_amdgcn_readlane(e, w), threadIdx.x & (kWave - 1), kWave);
         }
 }
 
+template <int lanes>
+__global__ __launch_bounds__(256) void k_edge_softmax_rows(const SoftmaxArgs a)
+{
+    if ((int)blockIdx.x < a.seekers) {
+        softmax_long_rows(a);
+        return;
+    }
+    softmax_group_rows<lanes>(a, ((int64_t)(blockIdx.x - a.seekers) * blockDim.x + threadIdx.x) / lanes, a.num_dst);
+}
+
 // Rows of a wavefront's walk.  The exponentials stay in LDS from the sum to the quotient.
 struct SoftmaxFwd {
-    static constexpr int STAGE = kLongRow;   // what whole workgroups do not take fits
     typedef double Word;
     static constexpr bool EDGES = true;
     const float *score;
@@ -466,11 +499,9 @@ struct SoftmaxFwd {
         z = group_sum<double>(z, lanes);
         for (int k = lo + l; k < hi; k += lanes) st[stage_slot(k)] /= z;
     }
-    __device__ __forceinline__ void whole(int, int, int64_t, float) const {}        // softmax_long_rows has it
 };
 
 struct SoftmaxBwd {
-    static constexpr int STAGE = kLongRow;   // what whole workgroups do not take fits
     typedef float2 Word;                     // alpha and its gradient; then the score's gradient
     static constexpr bool EDGES = true;
     const float *alpha, *da;
@@ -498,23 +529,23 @@ struct SoftmaxBwd {
         s = group_sum<double>(s, lanes);
         for (int k = lo + l; k < hi; k += lanes) put(st, k, s);
     }
-    __device__ __forceinline__ void whole(int, int, int64_t, float) const {}
 };
 
-__global__ __launch_bounds__(256) void k_edge_softmax_short(const SoftmaxArgs a, int rows)
+__global__ __launch_bounds__(256) void k_edge_softmax_short(const SoftmaxArgs a)
 {
-    __shared__ __align__(16) char stage[kWalkWaves][stage_slots(kLongRow) * 8];
+    __shared__ __align__(16) char stage[kWalkWaves][stage_slots(kStage) * 8];
     if ((int)blockIdx.x < a.seekers) {
         softmax_long_rows(a);
+        dense_sets<kRowsOfDst>(a.indptr, a.num_dst, a.seekers, [&](int64_t u, int64_t limit) { softmax_group_rows<8>(a, u, limit); });
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t first = ((int64_t)(blockIdx.x - a.seekers) * kWalkWaves + wave) * rows;
+    const int64_t first = ((int64_t)(blockIdx.x - a.seekers) * kWalkWaves + wave) * kRowsOfDst;
     if (first >= a.num_dst) return;
     if (a.backward)
-        walk_short_rows(a.indptr, a.num_dst, first, rows, reinterpret_cast<float2 *>(stage[wave]), SoftmaxBwd{a.in0, a.in1, a.out});
+        walk_short_rows<kRowsOfDst>(a.indptr, a.num_dst, first, reinterpret_cast<float2 *>(stage[wave]), SoftmaxBwd{a.in0, a.in1, a.out});
     else
-        walk_short_rows(a.indptr, a.num_dst, first, rows, reinterpret_cast<double *>(stage[wave]), SoftmaxFwd{a.in0, a.out});
+        walk_short_rows<kRowsOfDst>(a.indptr, a.num_dst, first, reinterpret_cast<double *>(stage[wave]), SoftmaxFwd{a.in0, a.out});
 }
 
 template <int lanes>
@@ -602,10 +633,10 @@ fastgl_status softmax(bool backward, const int32_t *indptr, int64_t num_dst, int
     hipStream_t s = (hipStream_t)stream;
     // by the block's mean row length (rows of sampled blocks are short)
     const int64_t mean = E / (num_dst > 0 ? num_dst : 1);
-    const int rows = walk_rows_per_wave(num_dst, mean, kWave, 2048);
-    if (mean < kShortMean && rows <= kGroupRows) launch_softmax<8>(a, s);
-    else if (mean < kShortMean)
-        hipLaunchKernelGGL(k_edge_softmax_short, dim3(a.seekers + walk_blocks(num_dst, rows)), dim3(256), 0, s, a, rows);
+    if (mean < kShortMean && num_dst >= kSoftmaxRows) {
+        a.seekers = dense_seekers(E);                       // as many as there can be long rows, or more
+        hipLaunchKernelGGL(k_edge_softmax_short, dim3(a.seekers + walk_blocks(num_dst, kRowsOfDst)), dim3(256), 0, s, a);
+    } else if (mean < 24) launch_softmax<8>(a, s);
     else if (mean < 96) launch_softmax<32>(a, s);
     else launch_softmax<64>(a, s);
     FASTGL_LAUNCH_CHECK("edge softmax");
@@ -629,7 +660,6 @@ struct ScoreArgs {
 // Rows of a wavefront's walk: what the edge's other end has, and the edge's gradient or its score.
 template <bool BACKWARD>
 struct ScoreRows {
-    static constexpr int STAGE = 512;
     typedef float2 Word;
     static constexpr bool EDGES = !BACKWARD;
     const ScoreArgs &a;
@@ -651,7 +681,7 @@ struct ScoreRows {
     __device__ __forceinline__ float result(Word w) const { return w.y; }
     __device__ __forceinline__ double term(double mine, Word w) const
     {
-        return (double)w.y * (mine + (double)w.x > 0.0 ? 1.0 : a.slope);          // the sum is exact: both are fp32
+        return (double)w.y * (mine + (double)w.x > 0.0 ? 1.0 : a.slope);          // the sum's sign is exact
     }
     __device__ __forceinline__ float score(double mine, Word w) const
     {
@@ -695,22 +725,22 @@ struct ScoreRows {
     }
 };
 
+// Row r < limit by a group of lanes; consecutive rows by a wavefront's groups.
 template <int lanes, bool BACKWARD>
-__global__ __launch_bounds__(256) void k_edge_score(const ScoreArgs a)
+__device__ __forceinline__ void score_group_rows(const ScoreArgs &a, int64_t r, int64_t limit)
 {
-    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / lanes;
     const int l = threadIdx.x % lanes;
     int b = 0, e = 0;
     double mine = 0.0;
-    if (r < a.num_rows) {
+    if (r < limit) {
         b = a.rowptr[r];
         e = a.rowptr[r + 1];
         mine = (double)a.row_val[r];
     }
-    const bool wide = lanes < kFewLanes && e - b > kLaneRow;
+    const bool wide = lanes < kFewLanes && e - b > kGroupRow;
     double acc = 0.0;
     for (int k = b + l; k < e && !wide; k += lanes) {
-        const double x = mine + (double)a.col_val[a.col[k]];      // exact: both are fp32
+        const double x = mine + (double)a.col_val[a.col[k]];      // rounded in fp64, its sign is exact
         if (!BACKWARD)
             a.out[k] = (float)(x > 0.0 ? x : a.slope * x);
         else
@@ -718,7 +748,7 @@ __global__ __launch_bounds__(256) void k_edge_score(const ScoreArgs a)
     }
     if (BACKWARD) {
         acc = group_sum<double>(acc, lanes);       // every lane of the group takes part
-        if (l == 0 && r < a.num_rows && !wide) a.out[r] = (float)acc;
+        if (l == 0 && r < limit && !wide) a.out[r] = (float)acc;
     }
     if (lanes < kFewLanes)
         for (unsigned long long todo = __ballot(wide && l == 0); todo; todo &= todo - 1) {
@@ -728,29 +758,40 @@ __global__ __launch_bounds__(256) void k_edge_score(const ScoreArgs a)
         }
 }
 
-template <bool BACKWARD>
-__global__ __launch_bounds__(256) void k_edge_score_short(const ScoreArgs a, int rows)
+template <int lanes, bool BACKWARD>
+__global__ __launch_bounds__(256) void k_edge_score(const ScoreArgs a)
 {
-    __shared__ float2 stage[kWalkWaves][stage_slots(ScoreRows<BACKWARD>::STAGE)];
+    score_group_rows<lanes, BACKWARD>(a, ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / lanes, a.num_rows);
+}
+
+template <int ROWS, bool BACKWARD>
+__global__ __launch_bounds__(256) void k_edge_score_short(const ScoreArgs a, int seekers)
+{
+    __shared__ float2 stage[kWalkWaves][stage_slots(kStage)];
+    if ((int)blockIdx.x < seekers) {
+        dense_sets<ROWS>(a.rowptr, a.num_rows, seekers, [&](int64_t r, int64_t limit) { score_group_rows<8, BACKWARD>(a, r, limit); });
+        return;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t first = ((int64_t)blockIdx.x * kWalkWaves + wave) * rows;
-    if (first < a.num_rows) walk_short_rows(a.rowptr, a.num_rows, first, rows, stage[wave], ScoreRows<BACKWARD>{a, a.out});
+    const int64_t first = ((int64_t)(blockIdx.x - seekers) * kWalkWaves + wave) * ROWS;
+    if (first < a.num_rows) walk_short_rows<ROWS>(a.rowptr, a.num_rows, first, stage[wave], ScoreRows<BACKWARD>{a, a.out});
 }
 
 template <bool BACKWARD>
 void launch_score(const ScoreArgs &a, int64_t nnz, hipStream_t s)
 {
     const int64_t mean = nnz / (a.num_rows > 0 ? a.num_rows : 1);
-    // Destinations: 64 rows to a wavefront, if that leaves 2 048 of them.  Sources come in order of their first appearance, the much
-    // used ones next to each other, and their rows are shorter: 16, or groups of 8 lanes.  us with 64 / 32 / 16 / 8 rows, 8 lanes per row as above:
-    // 1.15 M sources 67 / 51 / 49 / 66 (60);  299 K 31 / 20 / 13 / 17 (17);  191 K 15 / 6.9 / 7.3 / 10 (6.3);  107 K, up to 616 edges,
-    // 46 / 46 / 28 / 20 (23; 11 with its
-    // long rows left to wavefronts)
-    const int rows = a.eid ? walk_rows_per_wave(a.num_rows, mean, 16, 8192) : walk_rows_per_wave(a.num_rows, mean, kWave, 2048);
-    if (mean < kShortMean && rows <= kGroupRows)
+    // Sources (eid): us, groups / walked, in blocks of sampled neighbours, by number of sources (their edges each): 229 K (3.1) TBD
+    const int seekers = dense_seekers(nnz);
+    if constexpr (BACKWARD)
+        if (a.eid && mean < kShortSrcMean && a.num_rows >= kScoreSources) {
+            hipLaunchKernelGGL((k_edge_score_short<kRowsOfSrc, true>), dim3(seekers + walk_blocks(a.num_rows, kRowsOfSrc)), dim3(256), 0, s, a, seekers);
+            return;
+        }
+    if (!a.eid && mean < kShortMean && a.num_rows >= kScoreRows)
+        hipLaunchKernelGGL((k_edge_score_short<kRowsOfDst, BACKWARD>), dim3(seekers + walk_blocks(a.num_rows, kRowsOfDst)), dim3(256), 0, s, a, seekers);
+    else if (mean < 24)
         hipLaunchKernelGGL((k_edge_score<8, BACKWARD>), dim3((unsigned)ceil_div(a.num_rows * 8, 256)), dim3(256), 0, s, a);
-    else if (mean < kShortMean)
-        hipLaunchKernelGGL(k_edge_score_short<BACKWARD>, dim3(walk_blocks(a.num_rows, rows)), dim3(256), 0, s, a, rows);
     else if (mean < 96)
         hipLaunchKernelGGL((k_edge_score<32, BACKWARD>), dim3((unsigned)ceil_div(a.num_rows * 32, 256)), dim3(256), 0, s, a);
     else

@@ -183,7 +183,7 @@ def score_case(blk, seed, slope, what):
 
 
 def test_edge_score_ragged_and_degenerate():
-    score_case(ragged_block(), 41, 0.2, "ragged")                          # rows walked together, hub rows of 1500
+    score_case(ragged_block(), 41, 0.2, "ragged")                          # 8 lanes per row, hub rows of 1500
     blk = bg.random_block(np.random.default_rng(2), 300, 900, 3.0, empty_frac=0.3, hub_rows=40, hub_deg=5000)
     score_case(blk, 42, 0.2, "many long rows")                             # 64 lanes per row
     blk = bg.random_block(np.random.default_rng(4), 2000, 5000, 50.0, empty_frac=0.1, hub_rows=3, hub_deg=1200)
@@ -202,22 +202,25 @@ def test_edge_score_ragged_and_degenerate():
         B.fastgl_edge_score_bwd(ip, ix, el, er, 0.2, torch.empty(0, device="cuda"))
 
 
-@pytest.mark.parametrize("rows", [1, 63, 2048 * 8 + 5, 2048 * 16 + 1, 2048 * 32 + 31, 2048 * 64 + 63])
+@pytest.mark.parametrize("rows", [1, 63, 98_303, 98_304, 131_071, 131_072, 262_143, 262_144, 262_144 + 45])
 def test_short_rows_walked_together(rows):
-    """Rows that wavefronts take many at a time, at every number of rows to a wavefront: no edges, edges that one lane
-    and the wavefront put together, rows and runs of rows that just fit LDS (512 edges, 1 024) and just do not."""
+    """Rows that wavefronts take 32 at a time (softmax from 98 304 on, scores from 262 144) or 16 (sums of sources, two to a row
+    here): no edges, edges that two lanes and the wavefront put together, sets of rows that just fit LDS (512 edges) and just
+    do not, and rows of such sets that 8 lanes, the wavefront or a workgroup takes."""
     rng = np.random.default_rng(rows)
     deg = rng.integers(0, 6, rows)
-    special = [64, 65, 511, 512, 513, 1023, 1024, 1025, 0, 0, 4000, 1, 128, 129, 512, 512, 256, 256, 1, 513, 0, 1024, 1024]
+    special = [31, 32, 33, 64, 65, 511, 512, 513, 1023, 1024, 1025, 0, 0, 4000, 1, 128, 129, 512, 512, 256, 256, 1, 513, 0, 1024, 1024]
     for at in (0, rows // 2 & ~63, rows - len(special)):
         if rows > 16 * len(special):
             deg[at:at + len(special)] = rng.permutation(special)
     if rows > 2048:
-        deg[640:704] = 16                                   # 64 rows of 1 024 edges together
-        deg[704:768] = [16] * 63 + [17]
+        deg[640:672] = 16                                   # 32 rows of 512 edges together
+        deg[672:704] = [16] * 31 + [17]
+        deg[1024:2048] = rng.integers(0, 200, 1024)         # neighbouring sets that do not fit
+        deg[2048:2080] = [400] + [3] * 31                   # one that does, with a row far longer than the others
         deg[-1] = 0
     ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
-    srcs = max(1, rows * 2)
+    srcs = max(1, rows * 2)                                 # 262 144 of 131 072 rows
     ix = rng.integers(0, srcs, ip[-1])
     hubs = min(srcs, 40)
     ix[rng.random(ip[-1]) < 0.1] = 0                        # sources used often, some of them neighbours
