@@ -543,6 +543,8 @@ __global__ __launch_bounds__(256) void k_update_reduce(const float *__restrict__
     if (dst) *dst = (float)t;
 }
 
+constexpr int64_t kOnceBytes = (int64_t)128 << 20;
+
 fastgl_status launch_gemm(GemmArgs &g, bool bf16, hipStream_t s, const char *what)
 {
     // Up to 64 result columns: no matrix instructions and no conversions for columns that do not exist.
@@ -574,12 +576,17 @@ fastgl_status launch_gemm(GemmArgs &g, bool bf16, hipStream_t s, const char *wha
             if (g.b.gate) go(k_update_gemm<Q, true, T, FA, ONCE>);
             else go(k_update_gemm<Q, false, T, FA, ONCE>);
         };
-        // One tile: fp32 operands that one workgroup reads are loaded past the caches.  us, cached / past the caches: 1.15 M rows,
-        // 100 x 64: 183 / 163.  An operand of several is not, nor one beside it: 512 K rows, gated, 100 x 256, whose 256 columns
+        // One tile: fp32 operands that one workgroup reads are loaded past the caches, from a size on that the caches no longer hold
+        // together with what else a step has written.  us, cached / past the caches, operands just written, 512 MB written after them, and
+        // gated with two more results written between them and the call:
+        //   100 x 64    39 MB 16 / 17, 21 / 16, 17 / 19;  112 MB 26 / 31, 47 / 28, 29 / 30;  164 MB 36 / 40, 69 / 39, 48 / 41;  754 MB 199 / 158, 206 / 148, 206 / 160
+        //   96 x 18     46 MB 19 / 22, 24 / 20, 20 / 23;  114 MB 33 / 38, 47 / 35, 35 / 44;  182 MB 49 / 54, 73 / 52, 54 / 54;  524 MB 146 / 136, 170 / 134, 165 / 145
+        //   64 x 128    77 MB 29 / 30, 38 / 31, 31 / 31;  131 MB 40 / 40, 60 / 41, 56 / 50;  192 MB 55 / 56, 83 / 57, 83 / 62;  883 MB 246 / 222, 260 / 224, 281 / 247
+        // An operand of several tiles is not, nor one beside it: 512 K rows, gated, 100 x 256, whose 256 columns
         // one tile reads, alone 241 / 233, in a training step 251 / 256;  91 K rows, gated, 256 x 256, each read by two tiles: 91 / 95.
         // bf16 gains nothing: 85 K rows, 128 x 256: 29.3 / 30.4.
         if constexpr (Q && !T)
-            if (g.tiles_r == 1 && g.tiles_c == 1) return pick(std::true_type());
+            if (g.tiles_r == 1 && g.tiles_c == 1 && g.Kc * (g.R + g.C) * 4 >= kOnceBytes) return pick(std::true_type());
         pick(std::false_type());
     };
     auto typed = [&](auto q, auto fa) {

@@ -29,3 +29,8 @@ def test_assembly_around_the_size(feat, dtype, more):
 @pytest.mark.parametrize("relu", [False, True])
 def test_weight_gradient_by_number_of_tiles(M, K, N, relu):
     run_case(M, K, N, relu, bias=True, seed=M + K + N, what="tiles")
+
+
+@pytest.mark.parametrize("M", [204_600, 204_601])          # 100 + 64 columns: below 128 MB, from where one tile's operands go past the caches
+def test_weight_gradient_around_the_size(M):
+    run_case(M, 100, 64, M % 2 == 0, bias=True, seed=M, what="size")
