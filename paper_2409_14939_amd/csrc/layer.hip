@@ -34,18 +34,22 @@ constexpr int kMaxFusedK = 256;     // 64 lanes x 4 floats
 constexpr int kFusedCols = 64;      // one lane per output column
 constexpr int kQuarter = kMaxFusedK / kWavesPerBlock;   // most terms of a wavefront
 // Rows of a wavefront: one, two or four while that gives at most three workgroups per compute unit (every workgroup reads W
-// once); beyond that two, which leave the unit more wavefronts, and four where rows are short.  us right after X was written, GCN,
-// 1 / 2 / 4 rows, by K -> N and edges of a row:
-//   rows      256 -> 47, 15       256 -> 47, 5        100 -> 47, 15       64 -> 16, 10
-//   2 048     13.8 / 15.4 / 24.0  11.2 / 12.8 / 19.0  10.7 / 12.1 / 17.2  8.9 / 9.9 / 13.1
-//   3 000     16.3 / 17.8 / 23.4  12.9 / 14.0 / 19.6  12.0 / 13.2 / 17.7  9.9 / 10.8 / 13.5
-//   4 000     21.5 / 20.0 / 25.4  17.3 / 14.9 / 20.3  16.4 / 13.8 / 18.0  13.6 / 10.9 / 13.6
-//   6 000     26.5 / 25.5 / 30.4  20.2 / 18.0 / 22.3  19.2 / 16.4 / 20.2  15.4 / 12.3 / 14.7
-//   8 000     32.5 / 35.0 / 35.2  25.0 / 25.1 / 24.2  23.9 / 23.0 / 21.5  19.4 / 16.5 / 14.8
-//   12 000    43.4 / 43.9 / 46.2  32.9 / 30.4 / 29.6  31.9 / 27.5 / 26.4  25.6 / 19.9 / 17.2
-//   16 000    53.9 / 54.2 / 64.5  40.8 / 37.5 / 44.1  40.6 / 35.1 / 38.4  32.7 / 24.8 / 24.8
-//   64 000    228 / 207 / 217     156 / 132 / 131     157 / 132 / 127     109 / 79 / 67
-constexpr int64_t kOneRow = 3 * 256 * kWavesPerBlock, kShortK = 64;
+// once); beyond that two again, which leave the unit more wavefronts, for half as many rows more, and up to 65 536 rows where a row gathers
+// much (kMuch: columns times edges).  us right after X was written, GCN, 1 / 2 / 4 rows, by K -> N and edges of a row:
+//   rows      256 -> 47, 15       256 -> 47, 5        100 -> 47, 15       100 -> 47, 5        64 -> 16, 10
+//   2 048     13.8 / 15.4 / 24.0  11.2 / 12.8 / 19.0  10.7 / 12.1 / 17.2                      8.9 / 9.9 / 13.1
+//   3 000     16.3 / 17.8 / 23.4  12.9 / 14.0 / 19.6  12.0 / 13.2 / 17.7                      9.9 / 10.8 / 13.5
+//   4 000     21.5 / 20.0 / 25.4  17.3 / 14.9 / 20.3  16.4 / 13.8 / 18.0                      13.6 / 10.9 / 13.6
+//   6 000     26.5 / 25.5 / 30.4  20.2 / 18.0 / 22.3  19.2 / 16.4 / 20.2                      15.4 / 12.3 / 14.7
+//   8 000     29.7 / 31.9 / 32.2  19.4 / 19.9 / 19.8  20.3 / 20.1 / 18.6  14.6 / 12.9 / 12.4  15.8 / 14.6 / 12.7
+//   12 000    40.0 / 40.8 / 43.4  26.6 / 23.6 / 24.6  27.8 / 24.0 / 23.2  20.4 / 15.7 / 14.3  21.8 / 16.9 / 14.8
+//   13 000    42.6 / 44.6 / 56.4  28.9 / 27.6 / 35.6  30.4 / 28.2 / 32.2  22.3 / 18.8 / 20.7  23.8 / 20.1 / 21.2
+//   16 000    49.5 / 50.0 / 62.4  34.2 / 30.8 / 37.8  36.0 / 31.7 / 35.3  27.2 / 20.9 / 22.6  28.6 / 22.4 / 22.5
+//   20 000    59.1 / 59.8 / 71.6  41.6 / 36.5 / 42.7  43.1 / 38.4 / 39.2  32.2 / 25.2 / 24.5  34.7 / 27.0 / 25.0
+//   32 000    109 / 99 / 109      62.8 / 53.0 / 60.6  66.6 / 55.8 / 57.5  49.2 / 36.6 / 34.6  53.0 / 39.7 / 35.1
+//   64 000    225 / 201 / 210     123 / 99 / 109      133 / 106 / 106     95.9 / 67.5 / 61.1  102 / 74 / 63
+//   100 000   351 / 318 / 324     217 / 176 / 169     245 / 198 / 181     146 / 103 / 90      157 / 113 / 96
+constexpr int64_t kOneRow = 3 * 256 * kWavesPerBlock, kManyRows = (int64_t)1 << 16, kMuch = 1024;
 
 struct LayerParams {
     PullParams pull;                // rowptr, col, eid, edge_w, col_scale, in, G = 64, row_mode, row_bytes, feat
@@ -155,11 +159,12 @@ bool fuses(int64_t K, int64_t N, fastgl_dtype dtype, const void *X, const void *
 }
 
 template <int WEIGHTS>
-void launch_layer(const LayerParams &L, hipStream_t s)
+void launch_layer(const LayerParams &L, int64_t edges, hipStream_t s)
 {
+    const bool much = L.rows <= kManyRows && L.K * edges >= kMuch * L.rows;
     if (L.rows <= kOneRow)
         hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 1>), dim3((unsigned)ceil_div(L.rows, kWavesPerBlock)), dim3(kBlock), 0, s, L);
-    else if (L.rows <= 2 * kOneRow || (L.rows > 4 * kOneRow && L.K > kShortK))
+    else if (L.rows <= 2 * kOneRow || (L.rows > 4 * kOneRow && (L.rows <= 6 * kOneRow || much)))
         hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 2>), dim3((unsigned)ceil_div(L.rows, 2 * kWavesPerBlock)), dim3(kBlock), 0, s, L);
     else
         hipLaunchKernelGGL((k_layer_rows<WEIGHTS, 4>), dim3((unsigned)ceil_div(L.rows, 4 * kWavesPerBlock)), dim3(kBlock), 0, s, L);
@@ -248,10 +253,10 @@ fastgl_status fastgl_layer_fwd(const int32_t *indptr, const int32_t *indices, co
     L.H = (float *)H; L.Y = (float *)Y;
     L.rows = num_dst; L.K = (int32_t)K; L.N = (int32_t)N; L.relu = relu != 0;
     hipStream_t s = (hipStream_t)stream;
-    if (d.edge_w && d.col_scale) launch_layer<kTwoWeights>(L, s);
-    else if (d.edge_w) launch_layer<kEdgeWeight>(L, s);
-    else if (d.col_scale) launch_layer<kColWeight>(L, s);
-    else launch_layer<kNoWeight>(L, s);
+    if (d.edge_w && d.col_scale) launch_layer<kTwoWeights>(L, num_edges, s);
+    else if (d.edge_w) launch_layer<kEdgeWeight>(L, num_edges, s);
+    else if (d.col_scale) launch_layer<kColWeight>(L, num_edges, s);
+    else launch_layer<kNoWeight>(L, num_edges, s);
     FASTGL_LAUNCH_CHECK("fastgl_layer_fwd");
     return FASTGL_OK;
 }

@@ -1,7 +1,7 @@
 """Row walks at the widths where their kind changes (32 and 33 slices: lane groups or whole wavefronts; 64 and 65: one or
 two column tiles), with no, one and two weights per edge, long rows whose chunks fill one or several ranges of the
-reduction; and the one-kernel layer around the numbers of rows where a wavefront takes two or four of them (3 072, 6 144, 12 288).
-Against the oracle, with the tolerances of the parity tests and of the layer's tests."""
+reduction; and the one-kernel layer around the numbers of rows where a wavefront takes two or four of them (3 072, 6 144,
+12 288, 18 432, 65 536).  Against the oracle, with the tolerances of the parity tests and of the layer's tests."""
 import numpy as np
 import pytest
 
@@ -45,7 +45,7 @@ def test_more_long_rows_than_one_pass_takes():
     check_block(blk, "sum", "f32", 602, False, False, 3, "many long rows")
 
 
-@pytest.mark.parametrize("rows", [1, 3, 4, 5, 2047, 2048, 2049, 2065, 3072, 3073, 3079, 6144, 6145, 6161, 12288, 12289])
+@pytest.mark.parametrize("rows", [1, 3, 4, 5, 2047, 2048, 2049, 2065, 3072, 3073, 3079, 6144, 6145, 6161, 12288, 12289, 18432, 18433, 65536, 65537])
 @pytest.mark.parametrize("mode,K,N,weighted", [("gcn", 256, 47, False), ("gcn", 60, 64, True), ("sum", 4, 1, False)])
 def test_layer_rows(rows, mode, K, N, weighted):
     rng = np.random.default_rng(rows + K)
