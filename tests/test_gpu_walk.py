@@ -2,6 +2,9 @@
 two column tiles), with no, one and two weights per edge, long rows whose chunks fill one or several ranges of the
 reduction; and the one-kernel layer around the numbers of rows where a wavefront takes two or four of them (3 072, 6 144,
 12 288, 18 432, 65 536).  Against the oracle, with the tolerances of the parity tests and of the layer's tests."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -10,6 +13,7 @@ from test_gpu_layer import check_layer
 from test_gpu_parity import check_block
 
 pytestmark = pytest.mark.gpu
+SOURCE = open(os.path.join(os.path.dirname(__file__), "..", "paper_2409_14939_amd", "csrc", "aggregate.hip")).read()
 
 
 @pytest.mark.parametrize("mode,weighted", [("sum", False), ("mean", True), ("gcn", False), ("gcn", True)])
@@ -25,7 +29,7 @@ def test_widths(feat, dtype, mode, weighted):
 @pytest.mark.parametrize("feat,dtype,parts", [(256, "f32", 4), (128, "f32", 8), (602, "f32", 4), (40, "f32", 16), (5, "bf16", 64)])
 def test_rows_of_few_and_of_many_chunks(feat, dtype, parts):
     """Long rows of one chunk less than a workgroup has groups to one more, some with a short last chunk, side by side, in
-    both directions (every source that is used is used as often)."""
+    both directions (every source that is used is used as often).  So few that each has a workgroup."""
     lengths = [257, 384, 385] + [128 * c + d for c in (parts - 1, parts, parts + 1, 2 * parts, 3 * parts + 1) for d in (-127, -1, 0) if 128 * c + d > 0]
     rng = np.random.default_rng(feat)
     deg = rng.permutation(np.concatenate([lengths, rng.integers(0, 4, 50)]))
@@ -43,6 +47,28 @@ def test_more_long_rows_than_one_pass_takes():
     ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
     blk = bg.Block(ip, rng.integers(0, 3000, ip[-1]).astype(np.int32), deg.size, 3000)
     check_block(blk, "sum", "f32", 602, False, False, 3, "many long rows")
+
+
+@pytest.mark.parametrize("feat,dtype,parts,tiles", [(256, "f32", 4, 1), (128, "f32", 8, 1), (602, "f32", 4, 3), (40, "f32", 16, 1), (5, "bf16", 64, 1)])
+def test_more_units_than_workgroups(feat, dtype, parts, tiles):
+    """More than twice as many (row, column tile) units as workgroups, in both directions (a source is used as often as the row of its
+    number has edges): rows of up to as many chunks as a workgroup has groups are added up by one group, several groups to a
+    wavefront where rows are narrow; of those with more a workgroup has several on its list."""
+    blocks = int(re.search(r"kReduceBlocks = (\d+);", SOURCE).group(1))
+    rows, apart = 2 * blocks // tiles + 60, blocks // tiles
+    deg = np.full(rows, 257)
+    at = 10
+    for c in (parts - 1, parts, parts + 1, 2 * parts, 3 * parts + 1):
+        for d in (-127, -1, 0):
+            # the same workgroup's units: `blocks` of them apart
+            deg[[at, at + apart - 1, at + apart, at + apart + 1]] = max(257, 128 * c + d)
+            at += 3
+    lists = np.repeat((deg + 127) // 128, tiles)[: 2 * blocks].reshape(2, blocks) > parts
+    assert deg.min() > 256 and rows * tiles > 2 * blocks and (lists.sum(axis=0) == 2).sum() >= 9
+    rng = np.random.default_rng(feat)
+    ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    ix = rng.permutation(np.repeat(np.arange(rows), deg)).astype(np.int32)
+    check_block(bg.Block(ip, ix, rows, rows), "mean", dtype, feat, True, True, feat, "units")
 
 
 @pytest.mark.parametrize("rows", [1, 3, 4, 5, 2047, 2048, 2049, 2065, 3072, 3073, 3079, 6144, 6145, 6161, 12288, 12289, 18432, 18433, 65536, 65537])
