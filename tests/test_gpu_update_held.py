@@ -4,6 +4,7 @@ with the oracle; and one product against float64."""
 import pytest
 import torch
 
+from test_gpu_guard_bands import Guarded
 from paper_2409_14939_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -20,12 +21,25 @@ def in_parts(H, W, bias, relu):
     return torch.cat([B.fastgl_update_fwd(h, W, bias, relu) for h in H.chunk((H.shape[0] - 1) // 60_000 + 1)])
 
 
-# K: each number of steps of the last turn and its edges, the smallest and the largest that LDS holds; M: remainders of a tile of
-# 32 rows, one tile more than one and than two rounds of 2 048 wavefronts have, rounds that are just full enough
-@pytest.mark.parametrize("M,K,N", [(65_537, K, 256) for K in (4, 8, 16, 17, 32, 33, 47, 49, 64, 65, 80, 81, 100, 101, 104)] +
-                         [(65_568, 100, 256), (131_072, 60, 256), (196_607, 100, 256), (300_001, 37, 256),
-                          (524_289, 100, 128), (524_320, 212, 128), (530_001, 5, 128)])
-def test_same_bits(M, K, N):
+def held(M, K, N):
+    """Does the kernel take it?  The rule of held_fits: weights that fit LDS, rounds of 2 048 tiles of 32 rows nearly full."""
+    lds = -(-K // 8) * N * 3 * 16 + 16 <= 160 * 1024
+    tiles = -(-M // 32)
+    rounds = -(-tiles // 2048)
+    return lds and (rounds >= 9 if N == 128 else rounds == 2 or (rounds > 2 and 20 * tiles >= 17 * rounds * 2048))
+
+
+# K: each number of steps of the last turn and its edges, the smallest and the largest that LDS holds and the first beyond; M:
+# remainders of a tile of 32 rows, one tile more than one round, two rounds that are full, rounds that are just full enough
+CASES = ([(65_537, K, 256, True) for K in (4, 8, 16, 17, 32, 33, 47, 49, 64, 65, 80, 81, 100, 101, 104)] + [(65_537, 105, 256, False)] +
+         [(65_568, 100, 256, True), (131_072, 60, 256, True), (131_073, 60, 256, False), (196_607, 100, 256, True), (300_001, 37, 256, True)] +
+         [(524_289, K, 128, True) for K in (16, 32, 96, 100, 128, 192)] + [(524_288, 100, 128, False)] +
+         [(524_320, 208, 128, True), (524_320, 209, 128, False), (530_001, 5, 128, True)])
+
+
+@pytest.mark.parametrize("M,K,N,takes", CASES)
+def test_same_bits(M, K, N, takes):
+    assert held(M, K, N) == takes
     print(f"case held M={M} K={K} N={N}", flush=True)
     H, W, bias = data(M, K, N, M + K)
     relu = K % 2 == 0
@@ -50,3 +64,17 @@ def test_elements_that_are_not_finite():
     got, ref = B.fastgl_update_fwd(H, W, bias, False), in_parts(H, W, bias, False)
     assert torch.equal(got.isfinite(), ref.isfinite()) and torch.equal(got.nan_to_num(), ref.nan_to_num())
     assert bool(got[5, :7].isfinite().all()) and not bool(got[:, 7].isfinite().any())
+
+
+@pytest.mark.parametrize("M,K,N", [(65_537, 101, 256), (524_319, 33, 128)])
+def test_between_guard_bands(M, K, N):
+    """The result's neighbours stay as they are; what lies around the operands is NaN and reaches no result."""
+    assert held(M, K, N)
+    around = []
+    for t in data(M, K, N, 7)[:2]:
+        around.append(Guarded(*t.shape, torch.float32))
+        around[-1].t.copy_(t)
+    Y = Guarded(M, N, torch.float32)
+    B.fastgl_update_fwd(around[0].t, around[1].t, None, False, Y=Y.t)
+    Y.check("held")
+    assert torch.equal(Y.t, in_parts(around[0].t.clone(), around[1].t.clone(), None, False))
