@@ -843,25 +843,32 @@ int tall_tiles(int64_t M, int64_t N, bool b_col)
     return best;
 }
 
-// Does k_update_held take these tiles?  B fits LDS, a tile has no columns that do not exist, and the rounds in which its wavefronts
-// take their tiles are nearly full.  us with cold caches, k_update_tall / k_update_held, by K -> N:
-//   rows (rounds)   32 -> 256    64 -> 256    100 -> 256     |  32 -> 128    100 -> 128   128 -> 128   200 -> 128
-//   66 K  (1.0)     30.0 / 26.4  37.4 / 34.7  50.0 / 50.7    |  14.2 / 16.8  29.2 / 33.9  28.7 / 36.2  46.2 / 50.8
-//   98 K  (1.5)     33.1 / 28.8  40.6 / 35.6  54.2 / 53.2    |  16.9 / 18.4  35.9 / 36.6  33.8 / 37.6  50.8 / 55.0
-//   131 K (2.0)     38.6 / 34.4  47.3 / 42.0  63.0 / 57.0    |  24.3 / 20.8  47.3 / 42.8  46.1 / 47.3  68.6 / 62.7
-//   140 K (2.1)     44.8 / 42.4  55.7 / 55.9  74.3 / 75.4    |  26.0 / 26.8  48.4 / 52.3  46.8 / 54.0  72.2 / 79.0
-//   215 K (3.3)     61.5 / 60.4  75.2 / 78.0  99.5 / 102     |  36.1 / 37.6  66.0 / 69.6  66.8 / 75.0  101 / 106
-//   262 K (4.0)     73.8 / 65.7  83.7 / 83.7  114 / 109      |  44.4 / 42.6  77.9 / 76.0  80.8 / 86.5  120 / 110
-//   420 K (6.4)     116 / 104    132 / 129    174 / 162      |  69.0 / 68.0  114 / 113    121 / 122    175 / 162
-//   700 K (10.7)    184 / 168    208 / 205    274 / 242      |  116 / 102    178 / 163    180 / 173    262 / 241
-// With columns that do not exist, or rows that are no whole lines, it loses (512 K rows: 64 -> 200 141 / 160, 37 -> 100 78 / 87), and so
-// do narrower tiles (100 -> 64 104 / 113, 256 -> 47 172 / 189).
+// Does k_update_held take these tiles?  B fits LDS, a tile has no columns that do not exist, and what is saved, cutting B anew in every
+// workgroup, is more than what the tiles' end costs: the rounds in which its wavefronts take their tiles are nearly full and a tile has
+// many steps, or there are hardly more tiles than wavefronts (256 columns).  us with the aggregation that reads the result, right after
+// the operand was written, k_update_tall / k_update_held, by K -> N:
+//   rows (rounds)    32 -> 256   64 -> 256   72 -> 256   88 -> 256   96 -> 256   100 -> 256
+//   72 K  (1.1)      46 / 43     53 / 49                                         63 / 59
+//   131 K (2.0)      70 / 67     78 / 81     83 / 85     87 / 83     86 / 90     91 / 82
+//   196 K (3.0)      99 / 102    111 / 114   118 / 118   125 / 118   125 / 125   130 / 122
+//   300 K (4.6)      149 / 152   167 / 172   178 / 173   191 / 181   186 / 177   198 / 185
+//   420 K (6.4)      204 / 214   225 / 232   235 / 234   250 / 243   251 / 239   273 / 258
+//   512 K (7.8)      245 / 247   271 / 265   287 / 279   300 / 291   312 / 293   324 / 306
+//   rows (rounds)    32 -> 128   112 -> 128  128 -> 128  144 -> 128  160 -> 128  176 -> 128  200 -> 128
+//   540 K (8.2)      134 / 135   206 / 212   238 / 224   236 / 228   238 / 231   251 / 246   291 / 276
+//   655 K (10.0)     161 / 167   247 / 238   254 / 244   271 / 262   281 / 275   302 / 287   342 / 321
+//   800 K (12.2)     196 / 200   300 / 302   306 / 313   331 / 334   342 / 342   365 / 359   412 / 389
+//   1 M   (15.3)     246 / 250   378 / 378   382 / 380   412 / 412   430 / 427   451 / 441   516 / 487
+// At 140 K and 215 K rows, rounds that are not full, it loses (100 -> 256 alone, cold: 74 / 75, 100 / 102), at 8 rounds and fewer with
+// 128 columns as well; with columns that do not exist, or rows that are no whole lines (512 K rows: 64 -> 200 141 / 160, 37 -> 100 78 / 87),
+// and in narrower tiles (100 -> 64 104 / 113, 256 -> 47 172 / 189).
 bool held_fits(int ntiles, int64_t M, int64_t Kc, int64_t N)
 {
     if ((ntiles != 8 && ntiles != 4) || N != 32 * ntiles || held_lds(ntiles, Kc) > kHeldLds) return false;
     const int64_t waves = kHeldBlocks * kHeldThreads / kWave, tiles = ceil_div(M, kWaveRows), rounds = ceil_div(tiles, waves);
-    if (ntiles == 4) return rounds >= 9;
-    return rounds >= 2 && (rounds == 2 || 20 * tiles >= 17 * rounds * waves);
+    if (ntiles == 4) return rounds >= 9 && Kc > 144;
+    if (rounds == 2) return 2 * tiles <= 3 * waves || Kc > 96;
+    return rounds > 2 && Kc > 64 && 20 * tiles >= 17 * rounds * waves;
 }
 
 }  // namespace
