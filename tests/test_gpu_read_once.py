@@ -31,6 +31,16 @@ def test_weight_gradient_by_number_of_tiles(M, K, N, relu):
     run_case(M, K, N, relu, bias=True, seed=M + K + N, what="tiles")
 
 
+@pytest.mark.parametrize("relu", [False, True])
 @pytest.mark.parametrize("M", [204_600, 204_601])          # 100 + 64 columns: below 128 MB, from where one tile's operands go past the caches
-def test_weight_gradient_around_the_size(M):
-    run_case(M, 100, 64, M % 2 == 0, bias=True, seed=M, what="size")
+def test_weight_gradient_around_the_size(M, relu):
+    """Against float64; the bound of the parity tests: a chain as long as a slab, and the rounding of the result."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    H, dY, Y = (torch.empty((M, n), device="cuda").normal_(generator=g) for n in (100, 64, 64))
+    _, dW, db = B.fastgl_update_bwd(H, torch.ones((100, 64), device="cuda"), Y if relu else None, dY, relu, want=("dW", "db"))
+    dZ = (dY * (Y > 0) if relu else dY).double()
+    ref, size = H.double().T @ dZ, H.double().abs().T @ dZ.abs()
+    u = (min(M, B.fastgl_update_slab_rows(M, 100, 64)) + 4) * 2.0 ** -24
+    assert bool(((dW.double() - ref).abs() <= u * size + 2.0 ** -24 * ref.abs()).all())
+    assert bool(((db.double() - dZ.sum(0)).abs() <= u * dZ.abs().sum(0)).all())

@@ -49,7 +49,8 @@ def test_more_long_rows_than_one_pass_takes():
     check_block(blk, "sum", "f32", 602, False, False, 3, "many long rows")
 
 
-@pytest.mark.parametrize("feat,dtype,parts,tiles", [(256, "f32", 4, 1), (128, "f32", 8, 1), (602, "f32", 4, 3), (40, "f32", 16, 1), (5, "bf16", 64, 1)])
+@pytest.mark.parametrize("feat,dtype,parts,tiles", [(256, "f32", 4, 1), (128, "f32", 8, 1), (602, "f32", 4, 3), (40, "f32", 16, 1),
+                                                    (5, "bf16", 64, 1)])
 def test_more_units_than_workgroups(feat, dtype, parts, tiles):
     """More than twice as many (row, column tile) units as workgroups, in both directions (a source is used as often as the row of its
     number has edges): rows of up to as many chunks as a workgroup has groups are added up by one group, several groups to a
