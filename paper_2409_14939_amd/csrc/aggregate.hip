@@ -152,12 +152,13 @@ __global__ __launch_bounds__(kBlock) void k_pull_rows(PullParams P)
 }
 
 // Long rows: the partial sums of a row's chunks, scaled and stored.  A unit is a (row, column tile).  Where there are more units than
-// workgroups, one of no more chunks than a workgroup has groups (256 / G) is added up by one group; others by a workgroup: its groups sum consecutive ranges of the
-// chunks, each in chunk order with 8 loads in flight, and the ranges are added in order.  Bound by latency: most rows have few chunks, a row
-// of 25 000 edges has 200, a chain of 25 loads for one group.  All-neighbours block (65 536 rows, 2 570 of them long, up to 26 000
-// edges, and 640 K, 3 642 long, up to 1 800), forward and backward, us, a workgroup to every unit -> now: 32 columns
-// 11.0 + 10.8 -> 10.9 + 5.2;  256 columns, where most units need a workgroup or all loads are under way, 29.9 + 13.6 -> 30.0 + 13.3
-// (1 024 workgroups: 32.0 + 15.1).
+// workgroups, one of no more chunks than a workgroup has groups (256 / G) is added up by one group; others by a workgroup: its
+// groups sum consecutive ranges of the chunks, each in chunk order with 8 loads in flight, and the ranges are added in order.  Bound by
+// latency: most rows have few chunks, a row of 25 000 edges has 200, a chain of 25 loads for one group.  All-neighbours block (65 536
+// rows, 2 570 of them long, up to 26 000 edges, and 640 K, 3 642 long, up to 1 800), forward + backward in a program, us, 1 024 workgroups
+// and one to every unit in turn -> now: 32 columns 10.8 + 10.5 -> 11.1 + 5.6;  256 columns 28.7 + 12.5 -> 26.4 + 12.4.  One loop for both
+// ways takes 96 registers instead of 107 (five workgroups to a compute unit instead of four): 12.1 + 6.0, 27.2 + 11.6;  blocks of a few
+// hundred rows with some long ones the same in all three.
 template <int DT, int VB>
 __global__ __launch_bounds__(kBlock) void k_reduce_chunks(PullParams P)
 {

@@ -252,9 +252,10 @@ constexpr int kFewLanes = 32, kGroupRow = 64;        // groups of fewer lanes le
 //   their gradient's sums   4.0 / 3.7   5.7 / 5.3   7.2 / 6.6   10.2 / 9.2   10.9 / 8.7   20.2 / 16.0   12.0 / 12.5   13.0 / 14.6
 // All neighbours of 1 M nodes, 6 edges on average and up to 1 900, in any order: 94 / 63, 55 / 38, 60 / 53, 62 / 45;  by degree:
 // 102 / 109, 77 / 71, 131 / 133, 95 / 97.  Sums of sources, by their number: 195 K (3) 14.7 / 15.3, 307 K (3) 17.0 / 17.6, 321 K (2)
-// 15.3 / 16.4, 345 K (1.5) 14.4 / 10.5, 375 K (3) 22.1 / 21.7, 442 K (2) 18.6 / 15.6, 732 K (2) 30.8 / 23.9, 1.15 M (2) 59.6 / 49.9;  all neighbours, 1 M
-// (6) 154 / 149, by degree 209 / 183, 754 K (7) 110 / 117, 524 K (8) 113 / 145.
-constexpr int64_t kShortMean = 10, kSoftmaxRows = (int64_t)3 << 15, kScoreRows = (int64_t)1 << 18, kShortSrcMean = 6, kScoreSources = (int64_t)1 << 18;
+// 15.3 / 16.4, 345 K (1.5) 14.4 / 10.5, 375 K (3) 22.1 / 21.7, 442 K (2) 18.6 / 15.6, 732 K (2) 30.8 / 23.9, 1.15 M (2) 59.6 / 49.9;
+// all neighbours, 1 M (6) 154 / 149, by degree 209 / 183, 754 K (7) 110 / 117, 524 K (8) 113 / 145.
+constexpr int64_t kShortMean = 10, kSoftmaxRows = (int64_t)3 << 15, kScoreRows = (int64_t)1 << 18;
+constexpr int64_t kShortSrcMean = 6, kScoreSources = (int64_t)1 << 18;
 
 // Rows whose lengths are a power of two start at different banks.
 __device__ __forceinline__ int stage_slot(int k) { return k + (k >> 4); }
@@ -781,15 +782,16 @@ template <bool BACKWARD>
 void launch_score(const ScoreArgs &a, int64_t nnz, hipStream_t s)
 {
     const int64_t mean = nnz / (a.num_rows > 0 ? a.num_rows : 1);
-    // Sources (eid): us, groups / walked, in blocks of sampled neighbours, by number of sources (their edges each): 229 K (3.1) TBD
     const int seekers = dense_seekers(nnz);
     if constexpr (BACKWARD)
         if (a.eid && mean < kShortSrcMean && a.num_rows >= kScoreSources) {
-            hipLaunchKernelGGL((k_edge_score_short<kRowsOfSrc, true>), dim3(seekers + walk_blocks(a.num_rows, kRowsOfSrc)), dim3(256), 0, s, a, seekers);
+            hipLaunchKernelGGL((k_edge_score_short<kRowsOfSrc, true>), dim3(seekers + walk_blocks(a.num_rows, kRowsOfSrc)),
+                               dim3(256), 0, s, a, seekers);
             return;
         }
     if (!a.eid && mean < kShortMean && a.num_rows >= kScoreRows)
-        hipLaunchKernelGGL((k_edge_score_short<kRowsOfDst, BACKWARD>), dim3(seekers + walk_blocks(a.num_rows, kRowsOfDst)), dim3(256), 0, s, a, seekers);
+        hipLaunchKernelGGL((k_edge_score_short<kRowsOfDst, BACKWARD>), dim3(seekers + walk_blocks(a.num_rows, kRowsOfDst)),
+                           dim3(256), 0, s, a, seekers);
     else if (mean < 24)
         hipLaunchKernelGGL((k_edge_score<8, BACKWARD>), dim3((unsigned)ceil_div(a.num_rows * 8, 256)), dim3(256), 0, s, a);
     else if (mean < 96)

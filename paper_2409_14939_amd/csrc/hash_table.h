@@ -107,8 +107,8 @@ struct PositionTable {
 };
 
 // Slot whose key is gid after the call; `holder` = the position it was seen to hold (p: this call
-// put it there).  key_at(position) = the ID at an input position; hash: of gid, the same function for a whole table.  `look`: the slot is first read by a load that
-// may come from this XCD's L2: the KEY of a slot never changes once it has one (a smaller position of the same
+// put it there).  key_at(position) = the ID at an input position; hash: of gid, the same function for a whole
+// table.  `look`: the slot is first read by a load that may come from this XCD's L2: the KEY of a slot never changes once it has one (a smaller position of the same
 // ID may replace the one it holds), so an old reading can only show the empty marker, and the compare-and-swap
 // settles that.  Without (IDs that are not expected in the table yet) the compare-and-swap comes first.
 // Ends because the table always keeps empty slots.

@@ -15,10 +15,10 @@
 // leave as many low bits free: an item is the rest of the hash and the mini-batch in 8 bytes, a slot of the table the rest of
 // the hash and the mask of the mini-batches.  An empty slot is 0 (a mask never is).
 //
-// Four mini-batches of 1.15 M nodes, us: 233 in one table (fill 13, insert 197, count 24), 91 here (IDs per bucket 10, columns
-// 5, split 45, buckets 25, sum 6).  What is left is the split: 37 MB in and out at 1.7 TB/s, chains of LDS steps between barriers
-// (1 024 threads of four IDs instead of 512 of eight: 47).  Buckets: tables of 8 192 slots with 4 500 IDs 39, of 4 096 with 2 250 25
-// (four workgroups to a compute unit instead of two; 256 threads 28).
+// Four mini-batches of 1.15 M nodes, us, kernels of a traced window: 233 in one table (fill 13, insert 197, count 24), 89 here (IDs
+// per bucket 10, columns 5, split 44, buckets 25, sum 6).  What is left is the split: 37 MB in and out at 1.7 TB/s, chains of LDS
+// steps between barriers (1 024 threads of four IDs instead of 512 of eight: 47).  Buckets: tables of 8 192 slots with 4 500 IDs 39,
+// of 4 096 with 2 250 25 (four workgroups to a compute unit instead of two; 256 threads 28).
 #include "hash_table.h"
 #include "internal.h"
 

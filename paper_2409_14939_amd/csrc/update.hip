@@ -543,6 +543,7 @@ __global__ __launch_bounds__(256) void k_update_reduce(const float *__restrict__
     if (dst) *dst = (float)t;
 }
 
+// Operands of so many bytes are loaded past the caches, where one tile reads them (launch_gemm has both sides).
 constexpr int64_t kOnceBytes = (int64_t)128 << 20;
 
 fastgl_status launch_gemm(GemmArgs &g, bool bf16, hipStream_t s, const char *what)
