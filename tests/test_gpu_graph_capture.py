@@ -87,3 +87,56 @@ def test_update_idmap_match_edge_capture_and_replay():
         for k in outs:
             assert torch.equal(O[k], ref[k]), (rep, k)
         assert torch.equal(O["uniq"][:U], ref_uniq) and torch.equal(O["load_gid"][:nl], ref_lgid), rep
+
+
+def test_kernels_of_large_calls_capture_and_replay():
+    """The same for kernels that only large calls reach: weights held in LDS, rows of edges walked together in both directions,
+    a layer of two rows to a wavefront, operands past the caches, overlaps through buckets."""
+    rng = np.random.default_rng(6)
+    deg = rng.integers(0, 6, 262_200)
+    deg[1000:1064] = 90
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    nd, ns, E = deg.size, 300_000, int(indptr[-1])
+    ip, ix = dev_i32(indptr), dev_i32(rng.integers(0, ns, E).astype(np.int32))
+    plan = B.fastgl_block_plan_create(ip, ix, ns, B.PLAN_ALL | B.PLAN_PERM)
+    fp = np.arange(0, 13_001 * 6, 6, dtype=np.int32)             # 13 000 rows of 6 edges
+    fip, fix = dev_i32(fp), dev_i32(rng.integers(0, 20_000, fp[-1]).astype(np.int32))
+    fplan = B.fastgl_block_plan_create(fip, fix, 20_000)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    f32 = lambda *s: torch.empty(s, device="cuda").normal_(generator=g)
+    el, er, H, W, X, Wx, big, dY = f32(nd), f32(ns), f32(65_600, 100), f32(100, 256), f32(20_000, 64), f32(64, 16), f32(204_700, 100), f32(204_700, 64)
+    ids = rng.permutation(700_000)
+    gid = torch.from_numpy(np.concatenate([ids[:250_000], ids[100_000:350_000]])).cuda()
+    ws = torch.empty(B.fastgl_overlap_workspace_bytes(500_000), dtype=torch.uint8, device="cuda")
+    print("case graph capture of large calls", flush=True)
+
+    def step():
+        sc = B.fastgl_edge_score_fwd(ip, ix, el, er, 0.2)
+        alpha = B.fastgl_edge_softmax_fwd(ip, sc)
+        ds = B.fastgl_edge_softmax_bwd(ip, alpha, sc)
+        out = [sc, alpha, ds, *B.fastgl_edge_score_bwd(ip, ix, el, er, 0.2, ds, plan=plan)]
+        out += [B.fastgl_update_fwd(H, W, None, True), *B.fastgl_layer_fwd(fip, fix, None, 20_000, "gcn", X, Wx, None, True, plan=fplan)]
+        out += [B.fastgl_update_bwd(big, Wx.new_ones(100, 64), None, dY, False, want=("dW",))[1]]
+        return out + list(B.fastgl_overlap_counts(gid, [0, 250_000, 500_000], ws))
+
+    ref = [t.clone() for t in step()]
+    assert ref[-2].tolist() == [[250_000, 150_000], [150_000, 250_000]] and ref[-1].tolist() == [0]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        step()
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            got = step()
+    torch.cuda.current_stream().wait_stream(side)
+    for rep in range(3):
+        for t in got:                                    # eager work between replays: wipe every output
+            t.zero_()
+        ws.random_(0, 255)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for i, (a, b) in enumerate(zip(got, ref)):
+            assert torch.equal(a, b), (rep, i)
