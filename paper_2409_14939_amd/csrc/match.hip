@@ -121,7 +121,9 @@ __global__ __launch_bounds__(kRankThreads) void k_match_rank(MatchArgs a)
 // caches, as the stores go anyway: a row is read once, and what the loads leave behind pushes out what is still to be written.
 // us, 400-byte rows, 60 % from the last matrix, cached loads / past the caches: 80 MB 41 / 41, 132 MB 68 / 69, 192 MB 91 / 74,
 // 260 MB 122 / 99, 460 MB 195 / 173 (4.7 -> 5.3 TB/s);  460 MB right after the gather of its loaded rows 179 / 170.  The
-// table gather gains nothing by it: alone behind a fill 119 / 127 at 192 MB, 235 / 238 at 460.
+// table gather gains nothing by it: alone behind a fill 119 / 127 at 192 MB, 235 / 238 at 460.  Windows of two mini-batches over and over,
+// assembly and the two gathers, which find more of the table: 183 MB 71 + 128 / 75 + 121, 208 MB 79 + 143 / 84 + 136, 250 MB 97 + 164 / 98
+// + 160, 294 MB 119 + 187 / 115 + 186.
 constexpr int64_t kStreamBytes = (int64_t)160 << 20;
 
 template <int ELEM, int VEC, bool STREAM>
