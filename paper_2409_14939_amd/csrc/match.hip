@@ -156,8 +156,8 @@ constexpr int kMarkBatches = 8;
 //   4                66 000 16 / 25, 16 / 25, 21 / 25;  260 000 27 / 28, 28 / 29, 34 / 28;  400 000 32 / 31, 35 / 32, 39 / 32;  800 000 51 / 36, 55 / 38, 57 / 36
 //   8                66 000 26 / 33, 26 / 34, 29 / 34;  190 000 36 / 36, 36 / 36, 40 / 35;  400 000 46 / 39, 51 / 39, 52 / 39
 // A program's window of two mini-batches, matches and assembly with it: 67 000 IDs 80 / 87, 264 000 102 / 105, 439 000 122 / 123,
-// 502 000 150 / 146;  of three 503 000 166 / 160, 752 000 234 / 218.  1.15 M IDs a mini-batch: 4 of them 235 / 84 and, of 40 bits, 226 / 101,
-// 8 519 / 192.  Beyond the upper line buckets of IDs that do not repeat outgrow their tables.
+// 502 000 150 / 146;  of three 503 000 166 / 160, 752 000 234 / 218.  Called alone with 1.15 M IDs a mini-batch: 4 of them 235 / 87 and, of
+// 40 bits, 226 / 102, 8 519 / 199.  Beyond the upper line buckets of IDs that do not repeat outgrow their tables.
 constexpr int64_t kBucketIds = (int64_t)7 << 16, kBucketIdsMany = (int64_t)3 << 16, kMostBucketIds = (int64_t)12 << 20;
 constexpr int kCountBlocks = 256;            // workgroups that read the marks: one per compute unit
 
